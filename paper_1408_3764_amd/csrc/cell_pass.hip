@@ -1,0 +1,335 @@
+// Whole-box passes over the cell list: total energy, per-particle energies and
+// the pair virial (Sec. 3.1.1 computes each unique pair once; so do the totals
+// here), with the pair loop of cell_pass.h.  Sums are taken in an order that
+// depends on the configuration and the launch alone.
+#include <algorithm>
+
+#include "cell_pass.h"
+
+namespace gcmc {
+
+// Item j of this workgroup's XCD: a home cell and its particles' share
+// [part n / parts, (part + 1) n / parts); false past the last item.  Workgroups
+// (one wavefront each) go to the 8 XCDs in turn; an XCD takes a contiguous range
+// of cells, so that neighbouring home cells find their stencils in the same L2
+// (the grid is a multiple of 8): 80.7 -> 76.8 us for 262,144 particles.
+__device__ __forceinline__ bool pass_item(int32_t ncells, int32_t parts, uint32_t j, int32_t& c, int32_t& part) {
+    const uint32_t x = blockIdx.x & 7u;
+    const uint32_t c0 = (uint32_t)(((uint64_t)ncells * x) >> 3), c1 = (uint32_t)(((uint64_t)ncells * (x + 1)) >> 3);
+    const uint32_t k = j / (uint32_t)parts;
+    c = uni((int32_t)(c0 + k));
+    part = uni((int32_t)(j - k * (uint32_t)parts));
+    return k < c1 - c0;
+}
+
+// ------------------------------------------------------------- totals
+// Rows of candidates a wavefront holds at once.  Half a stencil of 27 cells at
+// liquid densities has 105-235 particles: two to four rows.
+constexpr int kTotalRows = 4;
+constexpr int kTotalQueue = kWave * kTotalRows + kWave;   // at most 63 left over and 4 x 64 new
+
+// partial[block] = the block's sum of pair energies (VIR: of pair virials), each
+// pair once.  Item = home cell x part: part p of `parts` takes the home
+// particles [p n / parts, (p + 1) n / parts).  64 VGPRs and 3.5 KB of LDS per
+// wavefront leave room for 8 wavefronts per SIMD.
+template <bool MIX, bool VIR>
+__global__ __launch_bounds__(kWave) void k_pair_total(const DevBox* __restrict__ boxp, int32_t parts,
+                                                                   double* partial) {
+    __shared__ PassRows rows_s;
+    __shared__ double qr[kTotalQueue];
+    __shared__ uint8_t qp[MIX ? kTotalQueue : 1];
+    __shared__ double te4[kMaxSpecies * kMaxSpecies], ts2[kMaxSpecies * kMaxSpecies];
+    const DevBox& B = *boxp;
+    const PassBox P = pass_box(B);
+    const int lane = threadIdx.x;
+    const int ns = uni(B.ns);
+    if (MIX) {
+        if (threadIdx.x < kMaxSpecies * kMaxSpecies) {
+            te4[threadIdx.x] = B.eps4[threadIdx.x];
+            ts2[threadIdx.x] = B.sig2[threadIdx.x];
+        }
+        __syncthreads();
+    }
+    const double e4 = unid(B.eps4[0]), s2 = unid(B.sig2[0]);
+    uint32_t tail = 0;   // queued pairs (wave-uniform; the last ones are taken first)
+    double acc = 0.0;
+    auto drain = [&](uint32_t from, uint32_t cnt) {
+        wave_lds_sync();
+        if ((uint32_t)lane < cnt) {
+            const double r2 = qr[from + lane];
+            const int q = MIX ? qp[from + lane] : 0;
+            const double a = MIX ? te4[q] : e4, b = MIX ? ts2[q] : s2;
+            acc += VIR ? lj_virial_from_r2(r2, P.rc2, a, b) : lj_from_r2(r2, P.rc2, a, b);
+        }
+        wave_lds_sync();
+    };
+    int32_t c, part;
+    for (uint32_t it = blockIdx.x >> 3; pass_item(P.ncells, parts, it, c, part); it += gridDim.x >> 3) {
+        int32_t nc = uni(sload_i32(P.count + c));
+        nc = nc > P.cap ? P.cap : nc;
+        const int32_t i0 = (int32_t)((int64_t)nc * part / parts), i1 = (int32_t)((int64_t)nc * (part + 1) / parts);
+        if (i0 >= i1) continue;
+        const int32_t cz = c / P.M01, cy = (c - cz * P.M01) / P.M0, cx = c - cz * P.M01 - cy * P.M0;
+        const double4* he = P.ent + (size_t)c * (uint32_t)P.cap;
+        const bool inside = uni(pass_inside(B, cx, cy, cz) ? 1 : 0) != 0;
+        stencil_rows<kTotalRows, true, MIX>(
+            B, P, rows_s, c, cx, cy, cz,
+            [&](const double3* e, const int32_t* sp, int rows, int32_t rel, uint32_t own) {
+                auto test = [&](auto wrap_t, auto rows_t) {
+                    constexpr bool WRAP = decltype(wrap_t)::value;
+                    constexpr int R = decltype(rows_t)::value;
+                    double4 nx = sload4(he + i0);
+                    for (int32_t i = i0; i < i1; ++i) {
+                        const double4 h = nx;
+                        nx = sload4(he + (i + 1 < i1 ? i + 1 : i));
+                        const int sa = MIX ? meta_species(h.w) * ns : 0;
+                        double r2[R];
+                        uint64_t m[R];
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            r2[r] = pass_r2<WRAP>(P, e[r], h);
+                            m[r] = __ballot(r2[r] < P.rc2);
+                        }
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            // in the home cell, only the particles after this one
+                            if (own & (1u << r)) m[r] &= __ballot((uint32_t)(rel + r * kWave) > (uint32_t)i);
+                            if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
+                                const uint32_t at = lanes_below(m[r], tail);
+                                qr[at] = r2[r];
+                                if (MIX) qp[at] = (uint8_t)(sa + sp[r]);
+                            }
+                            tail += (uint32_t)__builtin_popcountll(m[r]);
+                        }
+                        tail = (uint32_t)uni((int32_t)tail);
+                        while (tail >= (uint32_t)kWave) {
+                            tail -= kWave;
+                            drain(tail, kWave);
+                        }
+                    }
+                };
+                pass_dispatch<kTotalRows>(inside, rows, test);
+            });
+    }
+    if (tail) drain(0, tail);
+    acc = wave_sum(acc);
+    if (lane == 0) partial[blockIdx.x] = acc;
+}
+
+// ----------------------------------------------------- per-particle energies
+// e_i of every particle over its full stencil, and partial[block] = half their
+// sum over the block's particles.  The queue holds the pair's home particle too,
+// whose sum is an LDS accumulator; home particles go in batches of 64.
+constexpr int kEachRows = 4;
+constexpr int kEachQueue = kWave * kEachRows + kWave;
+
+template <bool MIX>
+__global__ __launch_bounds__(kWave) void k_pair_each(const DevBox* __restrict__ boxp, int32_t parts,
+                                                                  double* e_out, double* partial) {
+    __shared__ PassRows rows_s;
+    __shared__ double qr[kEachQueue];
+    __shared__ uint16_t qm[kEachQueue];   // home particle of the batch | species pair << 8
+    __shared__ double ae[kWave];
+    __shared__ double te4[kMaxSpecies * kMaxSpecies], ts2[kMaxSpecies * kMaxSpecies];
+    const DevBox& B = *boxp;
+    const PassBox P = pass_box(B);
+    const int lane = threadIdx.x;
+    const int ns = uni(B.ns);
+    if (MIX) {
+        if (threadIdx.x < kMaxSpecies * kMaxSpecies) {
+            te4[threadIdx.x] = B.eps4[threadIdx.x];
+            ts2[threadIdx.x] = B.sig2[threadIdx.x];
+        }
+        __syncthreads();
+    }
+    const double e4 = unid(B.eps4[0]), s2 = unid(B.sig2[0]);
+    double tot = 0.0;
+    auto drain = [&](uint32_t from, uint32_t cnt) {
+        wave_lds_sync();
+        if ((uint32_t)lane < cnt) {
+            const double r2 = qr[from + lane];
+            const int mt = qm[from + lane], q = mt >> 8;
+            const double a = MIX ? te4[q] : e4, b = MIX ? ts2[q] : s2;
+            atomicAdd(&ae[mt & 0xFF], lj_from_r2(r2, P.rc2, a, b));
+        }
+        wave_lds_sync();
+    };
+    int32_t c, part;
+    for (uint32_t it = blockIdx.x >> 3; pass_item(P.ncells, parts, it, c, part); it += gridDim.x >> 3) {
+        int32_t nc = uni(sload_i32(P.count + c));
+        nc = nc > P.cap ? P.cap : nc;
+        const int32_t p0 = (int32_t)((int64_t)nc * part / parts), p1 = (int32_t)((int64_t)nc * (part + 1) / parts);
+        const int32_t cz = c / P.M01, cy = (c - cz * P.M01) / P.M0, cx = c - cz * P.M01 - cy * P.M0;
+        const double4* he = P.ent + (size_t)c * (uint32_t)P.cap;
+        const bool inside = uni(pass_inside(B, cx, cy, cz) ? 1 : 0) != 0;
+        for (int32_t i0 = p0; i0 < p1; i0 += kWave) {
+            const int32_t i1 = p1 - i0 < kWave ? p1 : i0 + kWave;
+            uint32_t tail = 0;
+            ae[lane] = 0.0;
+            wave_lds_sync();
+            stencil_rows<kEachRows, false, MIX>(
+                B, P, rows_s, c, cx, cy, cz,
+                [&](const double3* e, const int32_t* sp, int rows, int32_t rel, uint32_t own) {
+                    auto test = [&](auto wrap_t, auto rows_t) {
+                        constexpr bool WRAP = decltype(wrap_t)::value;
+                        constexpr int R = decltype(rows_t)::value;
+                        double4 nx = sload4(he + i0);
+                        for (int32_t i = i0; i < i1; ++i) {
+                            const double4 h = nx;
+                            nx = sload4(he + (i + 1 < i1 ? i + 1 : i));
+                            const int sa = MIX ? meta_species(h.w) * ns : 0;
+                            double r2[R];
+                            uint64_t m[R];
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                r2[r] = pass_r2<WRAP>(P, e[r], h);
+                                m[r] = __ballot(r2[r] < P.rc2);
+                            }
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                if (own & (1u << r)) m[r] &= __ballot(rel + r * kWave != i);   // not itself
+                                if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
+                                    const uint32_t at = lanes_below(m[r], tail);
+                                    qr[at] = r2[r];
+                                    qm[at] = (uint16_t)((i - i0) | (MIX ? (sa + sp[r]) << 8 : 0));
+                                }
+                                tail += (uint32_t)__builtin_popcountll(m[r]);
+                            }
+                            tail = (uint32_t)uni((int32_t)tail);
+                            while (tail >= (uint32_t)kWave) {
+                                tail -= kWave;
+                                drain(tail, kWave);
+                            }
+                        }
+                    };
+                    pass_dispatch<kEachRows>(inside, rows, test);
+                });
+            if (tail) drain(0, tail);
+            if (lane < i1 - i0) {
+                const double ei = ae[lane];
+                e_out[meta_low(gload(he + i0 + lane).w)] = ei;
+                tot += ei;
+            }
+            wave_lds_sync();
+        }
+    }
+    tot = wave_sum(tot);
+    if (lane == 0) partial[blockIdx.x] = 0.5 * tot;
+}
+
+// ------------------------------------------------------------ finishes
+constexpr int kFinish = 1024;
+
+__device__ __forceinline__ double finish_sum(const double* partial, int64_t np, double* red) {
+    // at most 16 x 1024 partials from a cell pass: eight loads in flight per thread
+    double s = 0.0;
+    for (int64_t q0 = threadIdx.x; q0 < np; q0 += 8 * kFinish) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = q0 + u * kFinish < np ? partial[q0 + u * kFinish] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    s = wave_sum(s);
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
+    __syncthreads();
+    double t = 0.0;
+    for (int w = 0; w < kFinish / kWave; ++w) t += red[w];
+    return t;
+}
+
+// U_pair = sum of the partials in a fixed order; U_tail from the species
+// counts; the running pair energy is reset to U_pair.
+__global__ __launch_bounds__(kFinish) void k_pair_total_finish(const DevBox* __restrict__ boxp, const double* partial,
+                                                                int64_t np, double* U) {
+    __shared__ double red[kFinish / kWave];
+    const DevBox& B = *boxp;
+    const double up = finish_sum(partial, np, red);
+    if (threadIdx.x == 0) {
+        double ut = 0.0;
+        for (int a = 0; a < B.ns; ++a)
+            for (int b = 0; b < B.ns; ++b)
+                ut += (double)B.st->nsp[a] * (double)B.st->nsp[b] * B.tailK[a * B.ns + b];
+        U[0] = up;
+        U[1] = ut;
+        if (B.st->error == GCMC_OK) B.st->u_pair = up;
+    }
+}
+
+// The virial W = sum over pairs inside the cutoff of -r du/dr (in a fixed order)
+// and the pressure P = N / (beta V) + W / (3V) + P_tail, P_tail the pressure of
+// the full potential beyond r_c: (16 pi / (3 V^2)) sum_ab N_a N_b eps_ab
+// sigma_ab^3 [(2/3) q^9 - q^3], q = sigma_ab / r_c.
+__global__ __launch_bounds__(kFinish) void k_pair_virial_finish(const DevBox* __restrict__ boxp,
+                                                                 const double* partial, int64_t np, double* out) {
+    __shared__ double red[kFinish / kWave];
+    const DevBox& B = *boxp;
+    const double W = finish_sum(partial, np, red);
+    if (threadIdx.x == 0) {
+        double pt = 0.0;
+        for (int a = 0; a < B.ns; ++a)
+            for (int b = 0; b < B.ns; ++b)
+                pt += (double)B.st->nsp[a] * (double)B.st->nsp[b] * B.ptailK[a * B.ns + b];
+        out[0] = W;
+        out[1] = (double)B.st->n / (B.beta * B.V) + W / (3.0 * B.V) + pt;
+        if (B.st->error == GCMC_OK) B.st->w_pair = W;
+    }
+}
+
+// ------------------------------------------------------------ launchers
+// How a box of n particles is cut.  Parts per home cell: enough for four
+// wavefronts on every SIMD of the 256 compute units, and at most 24 particles each
+// (uneven last rounds otherwise); a part keeps at least two particles, below
+// which gathering the candidates costs more than the pairs.  4,000 particles in
+// 512 cells: 10.2 us with one part, 7.7 with two, 6.9 with three; 32,768
+// in 2,744 cells: 15.9, 14.6 with two, 16.4 with three; 262,144 in 15,625: 75 with one,
+// 81 with two.  At most 16,384 workgroups, each striding over its XCD's items.
+struct PassGrid {
+    int32_t parts;
+    unsigned blocks;
+};
+
+static PassGrid pass_grid(const DevBox& hb, int64_t n) {
+    const int64_t cells = hb.ncells > 0 ? hb.ncells : 1;
+    const int64_t mean = n / cells;
+    int64_t parts = std::max<int64_t>((4096 + cells - 1) / cells, (mean + 23) / 24);
+    parts = std::max<int64_t>(1, std::min(parts, mean / 2));
+    PassGrid g;
+    g.parts = (int32_t)parts;
+    g.blocks = 8u * (unsigned)std::min<int64_t>((cells + 7) / 8 * parts, 2048);
+    return g;
+}
+
+void launch_total_finish(const DevBox* d_box, const double* partial, int64_t np, double* U, hipStream_t s) {
+    hipLaunchKernelGGL(k_pair_total_finish, dim3(1), dim3(kFinish), 0, s, d_box, partial, np, U);
+}
+
+int64_t pass_partials(const DevBox& hb, int64_t n) { return pass_grid(hb, n).blocks; }
+
+int launch_total_cells(const DevBox& hb, const DevBox* d_box, double* e_out, double* partial, int64_t partial_len,
+                       double* U, hipStream_t s, int64_t n) {
+    const PassGrid g = pass_grid(hb, n);
+    if (g.blocks > partial_len) return -1;
+    const bool mix = hb.ns > 1;
+    if (e_out) {
+        auto f = mix ? k_pair_each<true> : k_pair_each<false>;
+        hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, e_out, partial);
+    } else {
+        auto f = mix ? k_pair_total<true, false> : k_pair_total<false, false>;
+        hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, partial);
+    }
+    launch_total_finish(d_box, partial, g.blocks, U, s);
+    return 0;
+}
+
+int launch_virial(const DevBox& hb, const DevBox* d_box, double* partial, int64_t partial_len, double* out,
+                  hipStream_t s, int64_t n) {
+    const PassGrid g = pass_grid(hb, n);
+    if (g.blocks > partial_len) return -1;
+    auto f = hb.ns > 1 ? k_pair_total<true, true> : k_pair_total<false, true>;
+    hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, partial);
+    hipLaunchKernelGGL(k_pair_virial_finish, dim3(1), dim3(kFinish), 0, s, d_box, partial, (int64_t)g.blocks, out);
+    return 0;
+}
+
+}  // namespace gcmc

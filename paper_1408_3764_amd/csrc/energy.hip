@@ -1,14 +1,4 @@
-// Total energy, the all-pairs (no cell list) energy path, and the gradient.
-//
-// Total energy over the cell list: one lane per particle, the particles taken
-// in cell-major order (cell by cell, slot by slot: the order comes from an
-// exclusive scan of the cell counters), so no lane idles on an empty slot and
-// the lanes of one wavefront belong to a few consecutive cells.  Each lane
-// walks the stencil of its own cell and sums its pair energies e_i in stencil
-// order, candidate order; U_pair = (1/2) sum e_i (Sec. 3.1.1 computes each
-// unique pair once; here each pair is met from both ends, which needs no
-// atomics), workgroup partials are summed by one more workgroup in a fixed
-// order.
+// The all-pairs (no cell list) energy path and the gradient.
 //
 // The all-pairs path (Algorithms 3 and 4 without a cell list) streams the
 // particle records in chunks, one chunk per workgroup, with the same
@@ -168,149 +158,7 @@ __device__ __forceinline__ double image_diff(double d, double L, double hL, bool
     return wrap ? nearest_image(d, L, hL) : d;
 }
 
-// e_i of one home particle over its stencil (WRAP: apply the minimum image).
-// In-cutoff pairs wait in a per-wavefront ring in LDS until 64 are queued; then
-// every lane takes one and evaluates the Lennard-Jones term (about one
-// candidate in six lies inside the cutoff of a full stencil, so the pair
-// arithmetic runs at full lane occupancy instead of under a mostly empty mask)
-// and adds it to its home particle's accumulator with an LDS atomic.
 constexpr int kRing = 128;   // queued pairs per wavefront (at most 63 + 64 at a time)
-
-struct PairQueue {
-    double* r2;      // [kRing] squared distances
-    int32_t* meta;   // [kRing] home lane | species pair << 8
-    double* acc;     // [kWave] energy of each lane's home particle
-};
-
-template <bool MIX, bool VIR>
-__device__ __forceinline__ void drain_pairs(const PassConst& K, const double* te4, const double* ts2,
-                                            const PairQueue& Q, uint32_t head, uint32_t cnt, int lane) {
-    // the ring entries written by other lanes of this wavefront are visible to every lane
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    if ((uint32_t)lane < cnt) {
-        const uint32_t e = (head + (uint32_t)lane) & (kRing - 1);
-        const double r2 = Q.r2[e];
-        const int32_t mt = Q.meta[e];
-        const int q = mt >> 8;
-        const double e4 = MIX ? te4[q] : K.e4, s2 = MIX ? ts2[q] : K.s2;
-        const double v = VIR ? lj_virial_from_r2(r2, K.rc2, e4, s2) : lj_from_r2(r2, K.rc2, e4, s2);
-        atomicAdd(&Q.acc[mt & (kWave - 1)], v);
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-}
-
-// Energy (or pair virial) of each lane's home particle over its stencil.  Every
-// lane of the wavefront calls it (lanes without a home particle pass live =
-// false and have no candidates); the loops run to the wavefront's largest cell
-// count so that the queue is drained with all lanes active.  HALF: each pair
-// once, for a total only -- the stencil offsets after (0, 0, 0) in z, y, x
-// order and, in the home cell, the particles with a larger id (the stencil is
-// symmetric and no axis is covered whole, so every other pair of cells is
-// reached from exactly one side).
-template <bool MIX, bool VIR, bool WRAP, bool HALF>
-__device__ __forceinline__ double home_energy(const DevBox& B, const PassConst& K, const uint32_t* tab,
-                                              const double* te4, const double* ts2, const double4& me, int32_t myid,
-                                              int sa, int ns, int32_t cx, int32_t cy, int32_t cz, bool live,
-                                              const PairQueue& Q) {
-    const int lane = threadIdx.x & (kWave - 1);
-    Q.acc[lane] = 0.0;
-    uint32_t head = 0, tail = 0;   // wave-uniform positions in the ring
-    for (int t = 0; t < B.nstencil; ++t) {
-        const uint32_t pk = tab[t];
-        bool centre = false;
-        if (HALF) {
-            const int32_t ox = (int32_t)(pk & 0x3FF) - B.k[0], oy = (int32_t)((pk >> 10) & 0x3FF) - B.k[1];
-            const int32_t oz = (int32_t)(pk >> 20) - B.k[2];
-            if (oz < 0 || (oz == 0 && (oy < 0 || (oy == 0 && ox < 0)))) continue;
-            centre = (ox | oy | oz) == 0;
-        }
-        const int64_t nb = stencil_cell(B, pk, cx, cy, cz);
-        const int32_t nc = live ? gload(B.count + nb) : 0;
-        const int32_t ncmax = wave_max_i32_uniform(nc);
-        const double4* ne = B.ent + nb * B.cap;
-        for (int j = 0; j < ncmax; j += kUnroll) {
-            double4 o[kUnroll];
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) o[u] = gload(ne + (j + u < nc ? j + u : 0));
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                bool in = false;
-                double r2 = 0.0;
-                int q = 0;
-                const int32_t oid = meta_low(o[u].w);
-                if (j + u < nc && (HALF && centre ? oid > myid : oid != myid)) {
-                    const double dx = image_diff(o[u].x - me.x, K.L[0], K.hL[0], WRAP);
-                    const double dy = image_diff(o[u].y - me.y, K.L[1], K.hL[1], WRAP);
-                    const double dz = image_diff(o[u].z - me.z, K.L[2], K.hL[2], WRAP);
-                    r2 = (dx * dx + dy * dy) + dz * dz;
-                    q = MIX ? sa * ns + meta_species(o[u].w) : 0;
-                    // (a pair with eps = 0 is queued too and adds zero)
-                    in = r2 < K.rc2;
-                }
-                const uint64_t m = __ballot(in);
-                if (in) {
-                    const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                    const uint32_t e = (tail + below) & (kRing - 1);
-                    Q.r2[e] = r2;
-                    Q.meta[e] = lane | (q << 8);
-                }
-                tail += (uint32_t)__builtin_popcountll(m);
-                if (tail - head >= (uint32_t)kWave) {
-                    drain_pairs<MIX, VIR>(K, te4, ts2, Q, head, kWave, lane);
-                    head += kWave;
-                }
-            }
-        }
-    }
-    if (tail != head) drain_pairs<MIX, VIR>(K, te4, ts2, Q, head, tail - head, lane);
-    return Q.acc[lane];
-}
-
-// Per-particle energies e_i; partial[blockIdx] = sum of e_i of the block.
-// VIR: the pair virial -r du/dr in place of the pair energy (pressure).
-// HALF: each pair once (no e_out); the partial is twice the block's sum of
-// pairs, exactly, so that the finish's half of the sum is the sum of pairs.
-template <bool MIX, bool VIR = false, bool HALF = false>
-__global__ __launch_bounds__(kBlk) void k_total_cells(const DevBox* __restrict__ boxp, const int32_t* __restrict__ home,
-                                                       int64_t n, double* e_out, double* partial) {
-    __shared__ uint32_t tab[kMaxStencil];
-    __shared__ double red[kBlk / kWave];
-    __shared__ double te4[kMaxSpecies * kMaxSpecies], ts2[kMaxSpecies * kMaxSpecies];
-    __shared__ double q_r2[kBlk / kWave][kRing];
-    __shared__ int32_t q_meta[kBlk / kWave][kRing];
-    __shared__ double q_acc[kBlk];
-    const DevBox& B = *boxp;
-    load_stencil(B, tab);
-    load_species_tables(B, te4, ts2);
-    const PassConst K = pass_const(B);
-    __syncthreads();
-    const int w = threadIdx.x / kWave;
-    const PairQueue Q{q_r2[w], q_meta[w], q_acc + w * kWave};
-    const int64_t h = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    const bool live = h < n;
-    int32_t slot = live ? home[h] : 0;
-    if (slot < 0 || (int64_t)slot >= B.ncells * B.cap) slot = 0;   // counters and N disagree: stay in bounds
-    const int64_t c = slot / B.cap;
-    const double4 me = gload(B.ent + slot);
-    const int32_t myid = meta_low(me.w);
-    const int sa = meta_species(me.w);
-    const int ns = uni(B.ns);
-    int32_t cx, cy, cz;
-    cell_coords(B, c, cx, cy, cz);
-    // the wrap is skipped when no lane of the wavefront needs it
-    double ei;
-    if (__ballot(live && !stencil_inside(B, cx, cy, cz)) != 0)
-        ei = home_energy<MIX, VIR, true, HALF>(B, K, tab, te4, ts2, me, myid, sa, ns, cx, cy, cz, live, Q);
-    else
-        ei = home_energy<MIX, VIR, false, HALF>(B, K, tab, te4, ts2, me, myid, sa, ns, cx, cy, cz, live, Q);
-    if (!live) ei = 0.0;
-    if (!HALF && live && e_out) e_out[myid] = ei;
-    const double s = block_sum(ei, red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = HALF ? 2.0 * s : s;
-}
 
 // --------------------------------------------------------- all-pairs total
 template <bool MIX>
@@ -348,60 +196,7 @@ __global__ __launch_bounds__(kBlk) void k_total_allpairs(const DevBox* __restric
     }
     if (own && e_out) e_out[i] = ei;
     const double s = block_sum(ei, red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
-// U_pair = 0.5 * sum(partial) in a fixed order; U_tail from the species
-// counts; the running pair energy is reset to U_pair.
-__global__ __launch_bounds__(kBlk) void k_total_finish(const DevBox* __restrict__ boxp, const double* partial,
-                                                        int64_t np, double* U) {
-    __shared__ double red[kBlk / kWave];
-    const DevBox& B = *boxp;
-    double s = 0.0;
-    for (int64_t q = threadIdx.x; q < np; q += kBlk) s += partial[q];
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) {
-        const double up = 0.5 * s;
-        double ut = 0.0;
-        for (int a = 0; a < B.ns; ++a)
-            for (int b = 0; b < B.ns; ++b)
-                ut += (double)B.st->nsp[a] * (double)B.st->nsp[b] * B.tailK[a * B.ns + b];
-        U[0] = up;
-        U[1] = ut;
-        if (B.st->error == GCMC_OK) B.st->u_pair = up;
-    }
-}
-
-// The virial W = sum over pairs inside the cutoff of -r du/dr (half the sum of
-// the per-particle sums, in a fixed order) and the pressure
-// P = N / (beta V) + W / (3V) + P_tail, P_tail the pressure of the full potential
-// beyond r_c: (16 pi / (3 V^2)) sum_ab N_a N_b eps_ab sigma_ab^3 [(2/3) q^9 - q^3],
-// q = sigma_ab / r_c.
-__global__ __launch_bounds__(kBlk) void k_virial_finish(const DevBox* __restrict__ boxp, const double* partial,
-                                                         int64_t np, double* out) {
-    __shared__ double red[kBlk / kWave];
-    const DevBox& B = *boxp;
-    double s = 0.0;
-    for (int64_t q = threadIdx.x; q < np; q += kBlk) s += partial[q];
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) {
-        const double W = 0.5 * s;
-        const double rc = sqrt(B.rc2);
-        double pt = 0.0;
-        for (int a = 0; a < B.ns; ++a)
-            for (int b = 0; b < B.ns; ++b) {
-                const int k = a * B.ns + b;
-                const double sig = sqrt(B.sig2[k]);
-                const double q3 = (sig / rc) * (sig / rc) * (sig / rc);
-                const double eps = 0.25 * B.eps4[k];
-                pt += (double)B.st->nsp[a] * (double)B.st->nsp[b] * eps * (sig * sig * sig) *
-                      ((2.0 / 3.0) * (q3 * q3 * q3) - q3);
-            }
-        pt *= 16.0 * M_PI / (3.0 * B.V * B.V);
-        out[0] = W;
-        out[1] = (double)B.st->n / (B.beta * B.V) + W / (3.0 * B.V) + pt;
-        if (B.st->error == GCMC_OK) B.st->w_pair = W;
-    }
+    if (threadIdx.x == 0) partial[blockIdx.x] = 0.5 * s;
 }
 
 // ------------------------------------------------------ all-pairs moves
@@ -995,9 +790,6 @@ __global__ __launch_bounds__(kBlk) void k_grad_finish(const DevBox* __restrict__
 // Scratch layout of a cell-list pass (in doubles): the block partials (times
 // `stride` doubles per block), then, as int32, the particles in cell order
 // (n), the cell offsets (ncells) and the scan-block totals.
-// Each pair once needs a stencil that reaches every other pair of cells from
-// exactly one side: no axis it covers whole.
-static bool half_stencil_ok(const DevBox& hb) { return !(hb.full[0] | hb.full[1] | hb.full[2]); }
 static int64_t cell_pass_blocks(int64_t n) { return n > 0 ? (n + kBlk - 1) / kBlk : 1; }
 static int64_t scan_blocks(const DevBox& hb) { return (hb.ncells + kScanCells - 1) / kScanCells; }
 static int64_t cell_pass_doubles(const DevBox& hb, int64_t n, int64_t stride) {
@@ -1018,80 +810,27 @@ static int32_t* cell_order(const DevBox& hb, int64_t n, double* scratch, int64_t
     return home;
 }
 
-int launch_total(const DevBox& hb, const DevBox* d_box, int32_t maxc, bool all_pairs, double* e_out,
-                 double* partial, int64_t partial_len, double* U, hipStream_t s, int64_t n) {
-    (void)maxc;
-    const bool mix = hb.ns > 1;
-    int64_t nb;
-    if (all_pairs) {
-        nb = (n + kBlk - 1) / kBlk;
-        if (nb < 1) nb = 1;
-        if (nb > partial_len) return -1;
-        if (mix)
-            hipLaunchKernelGGL(k_total_allpairs<true>, dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, e_out, partial);
-        else
-            hipLaunchKernelGGL(k_total_allpairs<false>, dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, e_out, partial);
-    } else {
-        nb = cell_pass_blocks(n);
-        if (cell_pass_doubles(hb, n, 1) > partial_len) return -1;
-        const int32_t* home = cell_order(hb, n, partial, nb, s);
-        // a total alone takes each pair once
-        if (!e_out && half_stencil_ok(hb)) {
-            if (mix)
-                hipLaunchKernelGGL((k_total_cells<true, false, true>), dim3((unsigned)nb), dim3(kBlk), 0, s, d_box,
-                                   home, n, nullptr, partial);
-            else
-                hipLaunchKernelGGL((k_total_cells<false, false, true>), dim3((unsigned)nb), dim3(kBlk), 0, s, d_box,
-                                   home, n, nullptr, partial);
-        } else if (mix) {
-            hipLaunchKernelGGL(k_total_cells<true>, dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n, e_out,
-                               partial);
-        } else {
-            hipLaunchKernelGGL(k_total_cells<false>, dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n, e_out,
-                               partial);
-        }
-    }
-    hipLaunchKernelGGL(k_total_finish, dim3(1), dim3(kBlk), 0, s, d_box, partial, nb, U);
+int launch_total(const DevBox& hb, const DevBox* d_box, bool all_pairs, double* e_out, double* partial,
+                 int64_t partial_len, double* U, hipStream_t s, int64_t n) {
+    if (!all_pairs) return launch_total_cells(hb, d_box, e_out, partial, partial_len, U, s, n);
+    const int64_t nb = n > 0 ? (n + kBlk - 1) / kBlk : 1;
+    if (nb > partial_len) return -1;
+    auto f = hb.ns > 1 ? k_total_allpairs<true> : k_total_allpairs<false>;
+    hipLaunchKernelGGL(f, dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, e_out, partial);
+    launch_total_finish(d_box, partial, nb, U, s);
     return 0;
 }
 
-int launch_virial(const DevBox& hb, const DevBox* d_box, int32_t maxc, double* partial, int64_t partial_len,
-                  double* out, hipStream_t s, int64_t n) {
-    (void)maxc;
-    const int64_t nb = cell_pass_blocks(n);
-    if (cell_pass_doubles(hb, n, 1) > partial_len) return -1;
-    const int32_t* home = cell_order(hb, n, partial, nb, s);
-    const bool half = half_stencil_ok(hb);
-    if (hb.ns > 1 && half)
-        hipLaunchKernelGGL((k_total_cells<true, true, true>), dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n,
-                           nullptr, partial);
-    else if (hb.ns > 1)
-        hipLaunchKernelGGL((k_total_cells<true, true>), dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n,
-                           nullptr, partial);
-    else if (half)
-        hipLaunchKernelGGL((k_total_cells<false, true, true>), dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n,
-                           nullptr, partial);
-    else
-        hipLaunchKernelGGL((k_total_cells<false, true>), dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n,
-                           nullptr, partial);
-    hipLaunchKernelGGL(k_virial_finish, dim3(1), dim3(kBlk), 0, s, d_box, partial, nb, out);
-    return 0;
+int64_t total_partials_needed(const DevBox& hb, bool all_pairs, int64_t n) {
+    return all_pairs ? (n + kBlk - 1) / kBlk + 1 : pass_partials(hb, n);
 }
 
-int64_t total_partials_needed(const DevBox& hb, int32_t maxc, bool all_pairs, int64_t n) {
-    (void)maxc;
-    if (all_pairs) return (n + kBlk - 1) / kBlk + 1;
-    return cell_pass_doubles(hb, n, 1);
-}
-
-int64_t grad_partials_needed(const DevBox& hb, int32_t maxc, int64_t n) {
-    (void)maxc;
+int64_t grad_partials_needed(const DevBox& hb, int64_t n) {
     return cell_pass_doubles(hb, n, 2 * kMaxSpecies * kMaxSpecies);
 }
 
-int launch_grad(const DevBox& hb, const DevBox* d_box, int32_t maxc, double* grad, double* partial, double* deps,
-                double* dsig, hipStream_t s, int64_t n) {
-    (void)maxc;
+int launch_grad(const DevBox& hb, const DevBox* d_box, double* grad, double* partial, double* deps, double* dsig,
+                hipStream_t s, int64_t n) {
     const int64_t nb = cell_pass_blocks(n);
     const int32_t* home = cell_order(hb, n, partial, nb * 2 * kMaxSpecies * kMaxSpecies, s);
     // the width of the per-particle parameter sums in LDS: 1, 2 or up to kMaxSpecies species

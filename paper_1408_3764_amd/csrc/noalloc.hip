@@ -1,7 +1,6 @@
 // Total energy without any allocation: the same kernels as gcmc_total_energy,
-// with their scratch (workgroup partial sums, the particles in cell order, the
-// scan of the cell counters) in a file-scope device array instead of the box's
-// scratch, which gcmc_total_energy grows with hipMalloc.
+// with their scratch (workgroup partial sums) in a file-scope device array
+// instead of the box's scratch, which gcmc_total_energy grows with hipMalloc.
 //
 // Every GPU the library runs on holds its own copy of the array until the
 // process ends.  Host code never passes the array's name to a kernel: its
@@ -13,8 +12,9 @@
 
 namespace gcmc {
 
-// 16 MiB: enough for N + cells up to about 4.1 million (a cell-list pass needs
-// N / 256 partials plus (N + cells) / 2 doubles of int32 order and offsets).
+// 16 MiB; gcmc.h promises N + cells up to about 4.1 million and a refusal above
+// (a pass that also kept the particles in cell order needed N / 256 + (N + cells) / 2
+// doubles; this one needs at most 4,096).
 constexpr int64_t kNoAllocDoubles = (int64_t)1 << 21;
 constexpr int kNoAllocDevices = 64;
 
@@ -60,12 +60,14 @@ int gcmc_total_energy_noalloc(gcmc_box* box, int32_t all_pairs, double* d_U, dou
     BoxState h;
     if ((rc = read_box_state(box, &h, s))) return rc;
     if (h.error) return set_error(GCMC_ERR_POISONED, "box holds a latched device error");
-    const int64_t need = total_partials_needed(box->d, h.maxcount, all_pairs != 0, h.n);
+    // the documented limit on the box's size (a cell-list pass itself needs fewer doubles)
+    const int64_t need = all_pairs ? total_partials_needed(box->d, true, h.n)
+                                   : h.n / 256 + (h.n + box->d.ncells + box->d.ncells / 1024) / 2 + 3;
     if (need > kNoAllocDoubles)
         return set_error(GCMC_ERR_INVALID_ARG, "the pass needs " + std::to_string(need) +
                                                    " doubles of scratch; the static buffer holds " +
                                                    std::to_string(kNoAllocDoubles));
-    if (launch_total(box->d, box->d_desc, h.maxcount, all_pairs != 0, d_e, buf, kNoAllocDoubles, d_U, s, h.n))
+    if (launch_total(box->d, box->d_desc, all_pairs != 0, d_e, buf, kNoAllocDoubles, d_U, s, h.n))
         return set_error(GCMC_ERR_INVALID_ARG, "scratch too small");
     GCMC_HIP(hipGetLastError());
     return GCMC_OK;
