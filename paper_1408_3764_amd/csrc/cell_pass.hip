@@ -1,6 +1,6 @@
-// Whole-box passes over the cell list: total energy, per-particle energies and
-// the pair virial (Sec. 3.1.1 computes each unique pair once; so do the totals
-// here), with the pair loop of cell_pass.h.  Sums are taken in an order that
+// Whole-box passes over the cell list: total energy, per-particle energies, the
+// pair virial (Sec. 3.1.1 computes each unique pair once; so do the totals here)
+// and the gradient, with the pair loop of cell_pass.h.  Sums are taken in an order that
 // depends on the configuration and the launch alone.
 #include <algorithm>
 
@@ -217,6 +217,209 @@ __global__ __launch_bounds__(kWave) void k_pair_each(const DevBox* __restrict__ 
     if (lane == 0) partial[blockIdx.x] = 0.5 * tot;
 }
 
+// ------------------------------------------------------------- gradient
+// Per particle: dU/dr_i = sum_j (24 eps / r^2)(2 s12 - s6) d_ij over its full
+// stencil, written by particle id; parameter sums per ordered species pair, each
+// pair met from both ends and contributing half from each.
+//
+// The candidates of up to kGradRows rows and the home particles of the batch are
+// kept in LDS too: the queue holds only which two particles a pair joins (4 bytes),
+// and the evaluation, 64 pairs at a time, forms the distance again and adds the
+// force to the home particle's sums with LDS atomics.  Neighbouring entries
+// mostly belong to one home particle, so it has four copies of its sums.  Bound by
+// vector issue (66 million instructions for 262,144 particles, half of them in
+// the evaluation) and the LDS pipeline (0.4 of the time) together.  A mixture of
+// 262,144 particles: 350 -> 190 us, 500 particles 139 -> 12 us, against one lane per
+// home particle.  Rows held: 203 us with one, 192 with two, 190 with three, 202 with
+// four; two copies of the sums 230, eight 204.
+constexpr int kGradRows = 3;
+constexpr int kGradBatch = 32;   // home particles at a time
+constexpr int kGradCopies = 4;
+constexpr int kGradQueue = kWave * kGradRows + kWave;
+
+// The minimum image of a coordinate difference with its sign (the bits of
+// nearest_image for |d| < L).
+__device__ __forceinline__ double image_signed(double d, double L, double hL) {
+    const double t = d - __builtin_copysign(L, d);
+    return __builtin_fabs(d) > hL ? t : d;
+}
+
+// S: a bound on the number of species (1, 2 or kMaxSpecies).  PARAMS: also the
+// sums for the eps and sigma derivatives of each species pair q: v1 = s12 - s6 and
+// v2 = 2 s12 - s6, in registers for up to two species, else in LDS;
+// partial[(2 q + v) * gridDim.x + block].
+template <int S, bool PARAMS>
+__global__ __launch_bounds__(kWave, 5) void k_pair_grad(const DevBox* __restrict__ boxp, int32_t parts, int64_t n,
+                                                      double* grad, double* partial) {
+    constexpr bool MIX = S > 1;
+    constexpr int Q = S * S;
+    constexpr bool REGS = S <= 2;
+    __shared__ PassRows rows_s;
+    __shared__ double cx_s[kGradRows * kWave], cy_s[kGradRows * kWave], cz_s[kGradRows * kWave];
+    __shared__ double hx_s[kGradBatch], hy_s[kGradBatch], hz_s[kGradBatch];
+    __shared__ double ax[kGradBatch * kGradCopies], ay[kGradBatch * kGradCopies], az[kGradBatch * kGradCopies];
+    __shared__ uint32_t qm[kGradQueue];   // candidate | home particle of the batch << 8 | species pair << 16
+    __shared__ double te4[Q], ts2[Q];
+    __shared__ double pv[REGS || !PARAMS ? 1 : 2 * Q * 4];
+    const DevBox& B = *boxp;
+    const PassBox P = pass_box(B);
+    const int lane = threadIdx.x;
+    const int ns = uni(B.ns);
+    if (MIX && lane < Q) {
+        te4[lane] = B.eps4[lane];
+        ts2[lane] = B.sig2[lane];
+    }
+    if (!REGS && PARAMS)
+        for (int t = lane; t < 2 * Q * 4; t += kWave) pv[t] = 0.0;
+    const double e4 = unid(B.eps4[0]), s2 = unid(B.sig2[0]);
+    const double hL[3] = {unid(B.hL[0]), unid(B.hL[1]), unid(B.hL[2])};
+    // up to two species: a sum per unordered pair, both orders of a pair add the same terms
+    constexpr int K = S == 1 ? 1 : 3;
+    double v1[K], v2[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v1[k] = v2[k] = 0.0;
+
+    auto drain = [&](auto wrap_t, uint32_t from, uint32_t cnt) {
+        constexpr bool WRAP = decltype(wrap_t)::value;
+        wave_lds_sync();
+        if ((uint32_t)lane < cnt) {
+            const uint32_t mt = qm[from + lane];
+            const int j = mt & 0xFF, i = (mt >> 8) & 0xFF, q = MIX ? (int)(mt >> 16) : 0;
+            double dx = cx_s[j] - hx_s[i], dy = cy_s[j] - hy_s[i], dz = cz_s[j] - hz_s[i];
+            if (WRAP) {
+                dx = image_signed(dx, P.L[0], hL[0]);
+                dy = image_signed(dy, P.L[1], hL[1]);
+                dz = image_signed(dz, P.L[2], hL[2]);
+            }
+            const double r2 = (dx * dx + dy * dy) + dz * dz;
+            if (r2 != 0.0) {   // (overlapping particles: no direction, no term)
+                const double ir2 = 1.0 / r2;
+                const double sr2 = (MIX ? ts2[q] : s2) * ir2;
+                const double s6 = sr2 * sr2 * sr2;
+                const double s12 = s6 * s6;
+                const double w = 2.0 * s12 - s6;
+                const double coef = (6.0 * (MIX ? te4[q] : e4) * ir2) * w;
+                if (grad) {
+                    const int at = i * kGradCopies + (lane & (kGradCopies - 1));
+                    atomicAdd(&ax[at], coef * dx);
+                    atomicAdd(&ay[at], coef * dy);
+                    atomicAdd(&az[at], coef * dz);
+                }
+                if (PARAMS) {
+                    if (REGS) {
+#pragma unroll
+                        for (int k = 0; k < K; ++k) {   // pairs 00, 01 and 10, 11
+                            const bool mine = K == 1 || (k == 0 ? q == 0 : (k == 2 ? q == 3 : q == 1 || q == 2));
+                            v1[k] += mine ? s12 - s6 : 0.0;
+                            v2[k] += mine ? w : 0.0;
+                        }
+                    } else {
+                        atomicAdd(&pv[(2 * q) * 4 + (lane & 3)], s12 - s6);
+                        atomicAdd(&pv[(2 * q + 1) * 4 + (lane & 3)], w);
+                    }
+                }
+            }
+        }
+        wave_lds_sync();
+    };
+
+    int32_t c, part;
+    for (uint32_t it = blockIdx.x >> 3; pass_item(P.ncells, parts, it, c, part); it += gridDim.x >> 3) {
+        int32_t nc = uni(sload_i32(P.count + c));
+        nc = nc > P.cap ? P.cap : nc;
+        const int32_t p0 = (int32_t)((int64_t)nc * part / parts), p1 = (int32_t)((int64_t)nc * (part + 1) / parts);
+        const int32_t cz = c / P.M01, cy = (c - cz * P.M01) / P.M0, cx = c - cz * P.M01 - cy * P.M0;
+        const double4* he = P.ent + (size_t)c * (uint32_t)P.cap;
+        const bool inside = uni(pass_inside(B, cx, cy, cz) ? 1 : 0) != 0;
+        for (int32_t i0 = p0; i0 < p1; i0 += kGradBatch) {
+            const int32_t i1 = p1 - i0 < kGradBatch ? p1 : i0 + kGradBatch;
+            int32_t id = 0;
+            wave_lds_sync();
+            if (lane < i1 - i0) {
+                const double4 h = gload(he + i0 + lane);
+                hx_s[lane] = h.x;
+                hy_s[lane] = h.y;
+                hz_s[lane] = h.z;
+                id = meta_low(h.w);
+            }
+            for (int t = lane; t < kGradBatch * kGradCopies; t += kWave) ax[t] = ay[t] = az[t] = 0.0;
+            wave_lds_sync();
+            stencil_rows<kGradRows, false, MIX>(
+                B, P, rows_s, c, cx, cy, cz,
+                [&](const double3* e, const int32_t* sp, int rows, int32_t rel, uint32_t own) {
+#pragma unroll
+                    for (int r = 0; r < kGradRows; ++r) {
+                        cx_s[r * kWave + lane] = e[r].x;
+                        cy_s[r * kWave + lane] = e[r].y;
+                        cz_s[r * kWave + lane] = e[r].z;
+                    }
+                    auto test = [&](auto wrap_t, auto rows_t) {
+                        constexpr bool WRAP = decltype(wrap_t)::value;
+                        constexpr int R = decltype(rows_t)::value;
+                        uint32_t tail = 0;
+                        double4 nx = sload4(he + i0);
+                        for (int32_t i = i0; i < i1; ++i) {
+                            const double4 h = nx;
+                            nx = sload4(he + (i + 1 < i1 ? i + 1 : i));
+                            const uint32_t mi = ((uint32_t)(i - i0) << 8) + (MIX ? (uint32_t)(meta_species(h.w) * ns) << 16 : 0u);
+                            uint64_t m[R];
+#pragma unroll
+                            for (int r = 0; r < R; ++r) m[r] = __ballot(pass_r2<WRAP>(P, e[r], h) < P.rc2);
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                if (own & (1u << r)) m[r] &= __ballot(rel + r * kWave != i);   // not itself
+                                if (__builtin_amdgcn_inverse_ballot_w64(m[r]))
+                                    qm[lanes_below(m[r], tail)] =
+                                        (uint32_t)(r * kWave + lane) + (MIX ? (uint32_t)sp[r] << 16 : 0u) + mi;
+                                tail += (uint32_t)__builtin_popcountll(m[r]);
+                            }
+                            tail = (uint32_t)uni((int32_t)tail);
+                            while (tail >= (uint32_t)kWave) {
+                                tail -= kWave;
+                                drain(wrap_t, tail, kWave);
+                            }
+                        }
+                        // the rows' coordinates leave LDS with this block: nothing stays queued
+                        if (tail) drain(wrap_t, 0u, tail);
+                    };
+                    pass_dispatch<kGradRows>(inside, rows, test);
+                });
+            if (grad && lane < i1 - i0) {
+                double f[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < kGradCopies; ++k) {
+                    f[0] += ax[lane * kGradCopies + k];
+                    f[1] += ay[lane * kGradCopies + k];
+                    f[2] += az[lane * kGradCopies + k];
+                }
+#pragma unroll
+                for (int a = 0; a < 3; ++a) grad[a * n + id] = f[a];
+            }
+        }
+    }
+    if (PARAMS) {
+        wave_lds_sync();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (q < ns * ns) {
+                double s1, s2q;
+                if (REGS) {
+                    const int k = S == 1 ? 0 : (q + 1) / 2;
+                    s1 = wave_sum(v1[REGS ? k : 0]) * (q == 1 || q == 2 ? 0.5 : 1.0);
+                    s2q = wave_sum(v2[REGS ? k : 0]) * (q == 1 || q == 2 ? 0.5 : 1.0);
+                } else {
+                    s1 = (pv[8 * q] + pv[8 * q + 1]) + (pv[8 * q + 2] + pv[8 * q + 3]);
+                    s2q = (pv[8 * q + 4] + pv[8 * q + 5]) + (pv[8 * q + 6] + pv[8 * q + 7]);
+                }
+                if (lane == 0) {
+                    partial[(size_t)(2 * q) * gridDim.x + blockIdx.x] = s1;
+                    partial[(size_t)(2 * q + 1) * gridDim.x + blockIdx.x] = s2q;
+                }
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------ finishes
 constexpr int kFinish = 1024;
 
@@ -276,6 +479,26 @@ __global__ __launch_bounds__(kFinish) void k_pair_virial_finish(const DevBox* __
     }
 }
 
+// Block q: the parameter sums of species pair q in a fixed order, and the
+// tail-correction terms: dU/d eps = 4 sum (s12 - s6), dU/d sigma = (24 eps / sigma) sum
+// (2 s12 - s6) over the pairs of the box, half of it from each end of a pair.
+__global__ __launch_bounds__(kFinish) void k_pair_grad_finish(const DevBox* __restrict__ boxp, const double* partial,
+                                                               int64_t np, double* deps, double* dsig) {
+    __shared__ double red[kFinish / kWave];
+    const DevBox& B = *boxp;
+    const int ns = B.ns, q = (int)blockIdx.x, a = q / ns, b = q % ns;
+    const double s1 = finish_sum(partial + (size_t)(2 * q) * np, np, red);
+    __syncthreads();
+    const double s2 = finish_sum(partial + (size_t)(2 * q + 1) * np, np, red);
+    if (threadIdx.x == 0) {
+        const double pre = (8.0 * M_PI / (3.0 * B.V)) * (double)B.st->nsp[a] * (double)B.st->nsp[b];
+        const double e = 0.25 * B.eps4[q], s = sqrt(B.sig2[q]);
+        const double x = s / sqrt(B.rc2), x3 = x * x * x, x9 = x3 * x3 * x3;
+        if (deps) deps[q] = 2.0 * s1 + pre * (s * s * s) * (x9 / 3.0 - x3);
+        if (dsig) dsig[q] = (3.0 * B.eps4[q] / s) * s2 + pre * e * (s * s) * (4.0 * x9 - 6.0 * x3);
+    }
+}
+
 // ------------------------------------------------------------ launchers
 // How a box of n particles is cut.  Parts per home cell: enough for four
 // wavefronts on every SIMD of the 256 compute units, and at most 24 particles each
@@ -329,6 +552,22 @@ int launch_virial(const DevBox& hb, const DevBox* d_box, double* partial, int64_
     auto f = hb.ns > 1 ? k_pair_total<true, true> : k_pair_total<false, true>;
     hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, partial);
     hipLaunchKernelGGL(k_pair_virial_finish, dim3(1), dim3(kFinish), 0, s, d_box, partial, (int64_t)g.blocks, out);
+    return 0;
+}
+
+int64_t grad_partials_needed(const DevBox& hb, int64_t n) { return 2 * hb.ns * hb.ns * pass_partials(hb, n); }
+
+int launch_grad(const DevBox& hb, const DevBox* d_box, double* grad, double* partial, double* deps, double* dsig,
+                hipStream_t s, int64_t n) {
+    const PassGrid g = pass_grid(hb, n);
+    const bool params = deps || dsig;
+    auto f = hb.ns > 2    ? (params ? k_pair_grad<kMaxSpecies, true> : k_pair_grad<kMaxSpecies, false>)
+             : hb.ns == 2 ? (params ? k_pair_grad<2, true> : k_pair_grad<2, false>)
+                          : (params ? k_pair_grad<1, true> : k_pair_grad<1, false>);
+    hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, n, grad, partial);
+    if (params)
+        hipLaunchKernelGGL(k_pair_grad_finish, dim3(hb.ns * hb.ns), dim3(kFinish), 0, s, d_box, partial,
+                           (int64_t)g.blocks, deps, dsig);
     return 0;
 }
 

@@ -1,8 +1,6 @@
-// The all-pairs (no cell list) energy path and the gradient.
-//
-// The all-pairs path (Algorithms 3 and 4 without a cell list) streams the
-// particle records in chunks, one chunk per workgroup, with the same
-// fixed-order second pass.
+// The all-pairs energy path (Algorithms 3 and 4 without a cell list): it streams
+// the particle records in chunks, one chunk per workgroup, with a fixed-order
+// second pass.
 #include "gcmc_internal.h"
 
 namespace gcmc {
@@ -50,115 +48,6 @@ __device__ __forceinline__ double pass_dist2(const PassConst& K, double px, doub
     const double dz = nearest_image(qz - pz, K.L[2], K.hL[2]);
     return (dx * dx + dy * dy) + dz * dz;
 }
-
-__device__ __forceinline__ void load_species_tables(const DevBox& B, double* e4, double* s2) {
-    if (threadIdx.x < kMaxSpecies * kMaxSpecies) {
-        e4[threadIdx.x] = B.eps4[threadIdx.x];
-        s2[threadIdx.x] = B.sig2[threadIdx.x];
-    }
-}
-
-__device__ __forceinline__ void cell_coords(const DevBox& B, int64_t c, int32_t& cx, int32_t& cy, int32_t& cz) {
-    cx = (int32_t)(c % B.M[0]);
-    const int64_t r = c / B.M[0];
-    cy = (int32_t)(r % B.M[1]);
-    cz = (int32_t)(r / B.M[1]);
-}
-
-// ------------------------------------------------ particles in cell order
-// home[off[c] + k] = c * cap + k for k < count[c]: the cell entry of every
-// particle, cell by cell.  off is the exclusive scan of the counters, taken in
-// blocks of kScanCells cells (bsum: the blocks' totals, then their exclusive
-// scan), so the order is a function of the configuration alone.
-constexpr int kScanPer = 4;
-constexpr int kScanCells = kBlk * kScanPer;
-
-__global__ __launch_bounds__(kBlk) void k_scan_cells(const int32_t* __restrict__ count, int64_t ncells,
-                                                      int32_t* off, int32_t* bsum) {
-    __shared__ int32_t sh[kBlk];
-    const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * kScanCells + (int64_t)tid * kScanPer;
-    int32_t v[kScanPer];
-    int32_t tot = 0;
-#pragma unroll
-    for (int u = 0; u < kScanPer; ++u) {
-        v[u] = base + u < ncells ? count[base + u] : 0;
-        tot += v[u];
-    }
-    sh[tid] = tot;
-    __syncthreads();
-    for (int d = 1; d < kBlk; d <<= 1) {
-        const int32_t t = tid >= d ? sh[tid - d] : 0;
-        __syncthreads();
-        sh[tid] += t;
-        __syncthreads();
-    }
-    int32_t run = sh[tid] - tot;
-#pragma unroll
-    for (int u = 0; u < kScanPer; ++u) {
-        if (base + u < ncells) off[base + u] = run;
-        run += v[u];
-    }
-    if (tid == kBlk - 1) bsum[blockIdx.x] = sh[tid];
-}
-
-// Exclusive scan of the block totals, in place (one workgroup; each thread
-// takes a contiguous run of blocks).
-__global__ __launch_bounds__(kBlk) void k_scan_sums(int32_t* bsum, int64_t nb) {
-    __shared__ int32_t sh[kBlk];
-    const int tid = threadIdx.x;
-    const int64_t per = (nb + kBlk - 1) / kBlk;
-    const int64_t b0 = (int64_t)tid * per;
-    int32_t tot = 0;
-    for (int64_t b = b0; b < b0 + per && b < nb; ++b) tot += bsum[b];
-    sh[tid] = tot;
-    __syncthreads();
-    for (int d = 1; d < kBlk; d <<= 1) {
-        const int32_t t = tid >= d ? sh[tid - d] : 0;
-        __syncthreads();
-        sh[tid] += t;
-        __syncthreads();
-    }
-    int32_t run = sh[tid] - tot;
-    for (int64_t b = b0; b < b0 + per && b < nb; ++b) {
-        const int32_t t = bsum[b];
-        bsum[b] = run;
-        run += t;
-    }
-}
-
-__global__ __launch_bounds__(kBlk) void k_home_order(DevBox B, const int32_t* __restrict__ off,
-                                                      const int32_t* __restrict__ bsum, int32_t* home, int64_t n) {
-    for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < B.ncells;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t o = (int64_t)off[c] + bsum[c / kScanCells];
-        const int32_t cnt = B.count[c] < B.cap ? B.count[c] : B.cap;
-        for (int32_t k = 0; k < cnt && o + k < n; ++k) home[o + k] = (int32_t)(c * B.cap + k);
-    }
-}
-
-// ------------------------------------------------------ cell-list total
-constexpr int kUnroll = 4;   // candidate records requested together
-
-// Does the stencil of cell (cx, cy, cz) stay clear of the periodic wrap with room
-// to spare?  Then every candidate lies within (k + 1) S < L/2 of the home
-// particle along each axis (at least 2k + 3 cells per axis: half a cell of
-// margin, far above the rounding of the cell assignment), and the minimum
-// image of a coordinate difference is the difference itself, bit for bit.
-__device__ __forceinline__ bool stencil_inside(const DevBox& B, int32_t cx, int32_t cy, int32_t cz) {
-    const int32_t c[3] = {cx, cy, cz};
-    bool in = true;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        in = in && B.M[a] >= 2 * B.k[a] + 3 && c[a] >= B.k[a] && c[a] <= B.M[a] - 1 - B.k[a];
-    return in;
-}
-
-__device__ __forceinline__ double image_diff(double d, double L, double hL, bool wrap) {
-    return wrap ? nearest_image(d, L, hL) : d;
-}
-
-constexpr int kRing = 128;   // queued pairs per wavefront (at most 63 + 64 at a time)
 
 // --------------------------------------------------------- all-pairs total
 template <bool MIX>
@@ -583,233 +472,7 @@ __device__ int commit_ap(const DevBox& B, const APTrial& T, const double4& rec, 
     return GCMC_OK;
 }
 
-// ------------------------------------------------------------- gradient
-// Per particle: dU/dr_i = sum_j (24 eps / r^2)(2 s12 - s6) d_ij, written by
-// particle id; parameter partials per block: [0, ns^2) d eps, [ns^2, 2 ns^2)
-// d sigma, each pair met twice contributing half from each end.  One lane per
-// particle in cell order, as the total energy.
-
-// Force and parameter-derivative sums of each lane's home particle over its
-// stencil (WRAP: apply the minimum image), organised like the energy pass:
-// the candidate loop only forms the distance vector and r^2, the pairs inside
-// the cutoff wait in a per-wavefront ring in LDS, and every 64 of them are
-// evaluated one per lane (the force coefficient and the two parameter terms)
-// and added to their home particle's sums with LDS atomics, so the pair
-// arithmetic runs at full lane occupancy instead of under a mostly empty mask.
-// teo[q] = eps4 / sigma of species pair q (the sigma derivative's prefactor, so
-// no pair takes a square root).
-struct GradQueue {
-    double* dx;   // [kRing] each: the distance vector (r^2 is formed again from it, bit for bit)
-    double* dy;
-    double* dz;
-    int32_t* meta;   // [kRing] home lane | other species << 8 | species pair << 16
-    double* gx;      // [kWave] force sums of each lane's home particle
-    double* gy;
-    double* gz;
-    double* de;      // [kWave * S] eps and sigma terms by the other particle's species
-    double* ds;
-};
-
-// S: a bound on the number of species (1, 2 or kMaxSpecies), the width of the
-// per-particle parameter sums in LDS.
-template <int S>
-__device__ __forceinline__ void drain_grad(const PassConst& K, const double* te4, const double* ts2,
-                                           const double* teo, const GradQueue& Q, uint32_t head, uint32_t cnt,
-                                           int lane) {
-    // the ring entries written by other lanes of this wavefront are visible to every lane
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    if ((uint32_t)lane < cnt) {
-        constexpr bool MIX = S > 1;
-        const uint32_t e = (head + (uint32_t)lane) & (kRing - 1);
-        const double dx = Q.dx[e], dy = Q.dy[e], dz = Q.dz[e];
-        const double r2 = (dx * dx + dy * dy) + dz * dz;
-        const int32_t mt = Q.meta[e];
-        const int h = mt & (kWave - 1), sb = (mt >> 8) & 0xFF, q = mt >> 16;
-        const double eps4 = MIX ? te4[q] : K.e4, sig2 = MIX ? ts2[q] : K.s2;
-        const double ir2 = 1.0 / r2;
-        const double sr2 = sig2 * ir2;
-        const double s6 = sr2 * sr2 * sr2;
-        const double s12 = s6 * s6;
-        const double coef = (6.0 * eps4 * ir2) * (2.0 * s12 - s6);
-        atomicAdd(&Q.gx[h], coef * dx);
-        atomicAdd(&Q.gy[h], coef * dy);
-        atomicAdd(&Q.gz[h], coef * dz);
-        const int slot = h * S + sb;
-        atomicAdd(&Q.de[slot], 0.5 * 4.0 * (s12 - s6));
-        atomicAdd(&Q.ds[slot], 0.5 * teo[q] * (12.0 * s12 - 6.0 * s6));
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-}
-
-template <int S, bool WRAP>
-__device__ __forceinline__ void home_gradient(const DevBox& B, const PassConst& K, const uint32_t* tab,
-                                              const double* te4, const double* ts2, const double* teo,
-                                              const double4& me, int32_t myid, int sa, int ns, int32_t cx, int32_t cy,
-                                              int32_t cz, bool live, const GradQueue& Q) {
-    constexpr bool MIX = S > 1;
-    const int lane = threadIdx.x & (kWave - 1);
-    Q.gx[lane] = Q.gy[lane] = Q.gz[lane] = 0.0;
-#pragma unroll
-    for (int b = 0; b < S; ++b) {
-        Q.de[lane * S + b] = 0.0;
-        Q.ds[lane * S + b] = 0.0;
-    }
-    uint32_t head = 0, tail = 0;   // wave-uniform positions in the ring
-    for (int t = 0; t < B.nstencil; ++t) {
-        const int64_t nb = stencil_cell(B, tab[t], cx, cy, cz);
-        const int32_t nc = live ? gload(B.count + nb) : 0;
-        const int32_t ncmax = wave_max_i32_uniform(nc);
-        const double4* ne = B.ent + nb * B.cap;
-        for (int j = 0; j < ncmax; j += kUnroll) {
-            double4 ob[kUnroll];
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) ob[u] = gload(ne + (j + u < nc ? j + u : 0));
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const double4& o = ob[u];
-                bool in = false;
-                double dx = 0.0, dy = 0.0, dz = 0.0;
-                int32_t mt = 0;
-                if (j + u < nc && meta_low(o.w) != myid) {
-                    dx = image_diff(o.x - me.x, K.L[0], K.hL[0], WRAP);
-                    dy = image_diff(o.y - me.y, K.L[1], K.hL[1], WRAP);
-                    dz = image_diff(o.z - me.z, K.L[2], K.hL[2], WRAP);
-                    const double r2 = (dx * dx + dy * dy) + dz * dz;
-                    const int sb = MIX ? meta_species(o.w) : 0;
-                    mt = lane | (sb << 8) | ((MIX ? sa * ns + sb : 0) << 16);
-                    in = r2 < K.rc2 && r2 != 0.0;
-                }
-                const uint64_t m = __ballot(in);
-                if (in) {
-                    const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                    const uint32_t e = (tail + below) & (kRing - 1);
-                    Q.dx[e] = dx;
-                    Q.dy[e] = dy;
-                    Q.dz[e] = dz;
-                    Q.meta[e] = mt;
-                }
-                tail += (uint32_t)__builtin_popcountll(m);
-                if (tail - head >= (uint32_t)kWave) {
-                    drain_grad<S>(K, te4, ts2, teo, Q, head, kWave, lane);
-                    head += kWave;
-                }
-            }
-        }
-    }
-    if (tail != head) drain_grad<S>(K, te4, ts2, teo, Q, head, tail - head, lane);
-    // (drain_grad ends with a wavefront fence: every lane's sums are complete and visible)
-}
-
-template <int S>
-__global__ __launch_bounds__(kBlk) void k_grad_cells(const DevBox* __restrict__ boxp, const int32_t* __restrict__ home,
-                                                      int64_t n, double* grad, double* partial) {
-    __shared__ uint32_t tab[kMaxStencil];
-    __shared__ double red[kBlk / kWave];
-    __shared__ double te4[kMaxSpecies * kMaxSpecies], ts2[kMaxSpecies * kMaxSpecies];
-    __shared__ double teo[kMaxSpecies * kMaxSpecies];
-    __shared__ double q_dx[kBlk / kWave][kRing], q_dy[kBlk / kWave][kRing], q_dz[kBlk / kWave][kRing];
-    __shared__ int32_t q_meta[kBlk / kWave][kRing];
-    __shared__ double a_gx[kBlk], a_gy[kBlk], a_gz[kBlk], a_de[kBlk * S], a_ds[kBlk * S];
-    const DevBox& B = *boxp;
-    load_stencil(B, tab);
-    load_species_tables(B, te4, ts2);
-    if (threadIdx.x < kMaxSpecies * kMaxSpecies) teo[threadIdx.x] = B.eps4[threadIdx.x] / sqrt(B.sig2[threadIdx.x]);
-    const PassConst K = pass_const(B);
-    __syncthreads();
-    const int w = threadIdx.x / kWave;
-    const GradQueue Q{q_dx[w], q_dy[w], q_dz[w], q_meta[w], a_gx + w * kWave, a_gy + w * kWave,
-                      a_gz + w * kWave, a_de + w * kWave * S, a_ds + w * kWave * S};
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t h = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    const int ns = uni(B.ns);
-    const bool own = h < n;
-    int32_t slot = own ? home[h] : 0;
-    if (slot < 0 || (int64_t)slot >= B.ncells * B.cap) slot = 0;   // counters and N disagree: stay in bounds
-    const int64_t c = slot / B.cap;
-    const double4 me = gload(B.ent + slot);
-    const int32_t myid = meta_low(me.w);
-    const int sa = own ? meta_species(me.w) : 0;
-    int32_t cx, cy, cz;
-    cell_coords(B, c, cx, cy, cz);
-    // the wrap is skipped when no lane of the wavefront needs it
-    if (__ballot(own && !stencil_inside(B, cx, cy, cz)) != 0)
-        home_gradient<S, true>(B, K, tab, te4, ts2, teo, me, myid, sa, ns, cx, cy, cz, own, Q);
-    else
-        home_gradient<S, false>(B, K, tab, te4, ts2, teo, me, myid, sa, ns, cx, cy, cz, own, Q);
-    if (own && grad) {
-        grad[myid] = Q.gx[lane];
-        grad[n + myid] = Q.gy[lane];
-        grad[2 * n + myid] = Q.gz[lane];
-    }
-    // parameter partials: entry (a, b) gets the lanes with own species a
-    for (int a = 0; a < ns; ++a) {
-        for (int b = 0; b < ns; ++b) {
-            const bool mine = own && sa == a;
-            const int k = lane * S + b;
-            const double ve = block_sum(mine ? Q.de[k] : 0.0, red);
-            const double vs = block_sum(mine ? Q.ds[k] : 0.0, red);
-            if (threadIdx.x == 0) {
-                partial[(size_t)blockIdx.x * 2 * kMaxSpecies * kMaxSpecies + a * ns + b] = ve;
-                partial[(size_t)blockIdx.x * 2 * kMaxSpecies * kMaxSpecies + kMaxSpecies * kMaxSpecies + a * ns + b] =
-                    vs;
-            }
-        }
-    }
-}
-
-// Sum the parameter partials in order and add the tail-correction terms.
-__global__ __launch_bounds__(kBlk) void k_grad_finish(const DevBox* __restrict__ boxp, const double* partial,
-                                                       int64_t np, double* deps, double* dsig) {
-    __shared__ double red[kBlk / kWave];
-    const DevBox& B = *boxp;
-    const int ns = B.ns;
-    const int stride = 2 * kMaxSpecies * kMaxSpecies;
-    for (int q = 0; q < ns * ns; ++q) {
-        double se = 0.0, ss = 0.0;
-        for (int64_t b = threadIdx.x; b < np; b += kBlk) {
-            se += partial[b * stride + q];
-            ss += partial[b * stride + kMaxSpecies * kMaxSpecies + q];
-        }
-        se = block_sum(se, red);
-        ss = block_sum(ss, red);
-        if (threadIdx.x == 0) {
-            const int a = q / ns, b = q % ns;
-            const double pre = (8.0 * M_PI / (3.0 * B.V)) * (double)B.st->nsp[a] * (double)B.st->nsp[b];
-            const double e = 0.25 * B.eps4[q], s = sqrt(B.sig2[q]);
-            const double x = s / sqrt(B.rc2), x3 = x * x * x, x9 = x3 * x3 * x3;
-            if (deps) deps[q] = se + pre * (s * s * s) * (x9 / 3.0 - x3);
-            if (dsig) dsig[q] = ss + pre * e * (s * s) * (4.0 * x9 - 6.0 * x3);
-        }
-    }
-}
-
 // ------------------------------------------------------------ launchers
-// Scratch layout of a cell-list pass (in doubles): the block partials (times
-// `stride` doubles per block), then, as int32, the particles in cell order
-// (n), the cell offsets (ncells) and the scan-block totals.
-static int64_t cell_pass_blocks(int64_t n) { return n > 0 ? (n + kBlk - 1) / kBlk : 1; }
-static int64_t scan_blocks(const DevBox& hb) { return (hb.ncells + kScanCells - 1) / kScanCells; }
-static int64_t cell_pass_doubles(const DevBox& hb, int64_t n, int64_t stride) {
-    const int64_t ints = n + hb.ncells + scan_blocks(hb);
-    return cell_pass_blocks(n) * stride + (ints + 1) / 2 + 1;
-}
-
-// The particles in cell order into the scratch after `partial_doubles`.
-static int32_t* cell_order(const DevBox& hb, int64_t n, double* scratch, int64_t partial_doubles, hipStream_t s) {
-    int32_t* home = reinterpret_cast<int32_t*>(scratch + partial_doubles);
-    int32_t* off = home + n;
-    int32_t* bsum = off + hb.ncells;
-    const int64_t nsb = scan_blocks(hb);
-    hipLaunchKernelGGL(k_scan_cells, dim3((unsigned)nsb), dim3(kBlk), 0, s, hb.count, hb.ncells, off, bsum);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kBlk), 0, s, bsum, nsb);
-    const int64_t g = (hb.ncells + kBlk - 1) / kBlk;
-    hipLaunchKernelGGL(k_home_order, dim3((unsigned)(g < 65535 ? g : 65535)), dim3(kBlk), 0, s, hb, off, bsum, home, n);
-    return home;
-}
-
 int launch_total(const DevBox& hb, const DevBox* d_box, bool all_pairs, double* e_out, double* partial,
                  int64_t partial_len, double* U, hipStream_t s, int64_t n) {
     if (!all_pairs) return launch_total_cells(hb, d_box, e_out, partial, partial_len, U, s, n);
@@ -823,27 +486,6 @@ int launch_total(const DevBox& hb, const DevBox* d_box, bool all_pairs, double* 
 
 int64_t total_partials_needed(const DevBox& hb, bool all_pairs, int64_t n) {
     return all_pairs ? (n + kBlk - 1) / kBlk + 1 : pass_partials(hb, n);
-}
-
-int64_t grad_partials_needed(const DevBox& hb, int64_t n) {
-    return cell_pass_doubles(hb, n, 2 * kMaxSpecies * kMaxSpecies);
-}
-
-int launch_grad(const DevBox& hb, const DevBox* d_box, double* grad, double* partial, double* deps, double* dsig,
-                hipStream_t s, int64_t n) {
-    const int64_t nb = cell_pass_blocks(n);
-    const int32_t* home = cell_order(hb, n, partial, nb * 2 * kMaxSpecies * kMaxSpecies, s);
-    // the width of the per-particle parameter sums in LDS: 1, 2 or up to kMaxSpecies species
-    if (hb.ns > 2)
-        hipLaunchKernelGGL(k_grad_cells<kMaxSpecies>, dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n, grad,
-                           partial);
-    else if (hb.ns == 2)
-        hipLaunchKernelGGL(k_grad_cells<2>, dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n, grad, partial);
-    else
-        hipLaunchKernelGGL(k_grad_cells<1>, dim3((unsigned)nb), dim3(kBlk), 0, s, d_box, home, n, grad, partial);
-    if (deps || dsig)
-        hipLaunchKernelGGL(k_grad_finish, dim3(1), dim3(kBlk), 0, s, d_box, partial, nb, deps, dsig);
-    return 0;
 }
 
 int64_t ap_chunk_len() { return 8 * kBlk; }

@@ -528,14 +528,14 @@ int launch_total_cells(const DevBox& hb, const DevBox* d_box, double* e_out, dou
 void launch_total_finish(const DevBox* d_box, const double* partial, int64_t np, double* U, hipStream_t s);
 int launch_virial(const DevBox& hb, const DevBox* d_box, double* partial, int64_t partial_len, double* out,
                   hipStream_t s, int64_t n);
+int64_t grad_partials_needed(const DevBox& hb, int64_t n);
+int launch_grad(const DevBox& hb, const DevBox* d_box, double* grad, double* partial, double* deps, double* dsig,
+                hipStream_t s, int64_t n);
 
 // energy.hip
 int launch_total(const DevBox& hb, const DevBox* d_box, bool all_pairs, double* e_out, double* partial,
                  int64_t partial_len, double* U, hipStream_t s, int64_t n);
 int64_t total_partials_needed(const DevBox& hb, bool all_pairs, int64_t n);
-int64_t grad_partials_needed(const DevBox& hb, int64_t n);
-int launch_grad(const DevBox& hb, const DevBox* d_box, double* grad, double* partial, double* deps, double* dsig,
-                hipStream_t s, int64_t n);
 int64_t ap_chunk_len();
 int launch_delta_allpairs(const DevBox* d_box, int64_t n, const gcmc_move* moves, int64_t n_moves, double* scratch,
                           double* dp, double* dt, double* dw, hipStream_t s);
