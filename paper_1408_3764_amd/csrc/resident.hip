@@ -17,15 +17,26 @@
 // virial corrected for the earlier accepted moves of the round: removing a
 // particle at a and adding one at b changes the move's sums by f(b) - f(a),
 // f(r) the pair terms of r with the move's new position minus those with its
-// old one, so a few pair terms, one lane per earlier move, replace a new pass
-// over the box.  The accepted moves are written to the LDS copy in order after
-// the round.  Particles with an index of kResCap or more (a box that grows past
-// it) are read from and written to global memory instead: correct, slower.
+// old one, prepared by the move's own wavefront.
+//
+// Lane k of wavefront 0 holds move k of the round and its decision at the current
+// state, so the rejections up to the next accepted or stale move take one ballot,
+// and only an accepted move (about one in eight) costs a serial step: N, the
+// running sums and the LDS copy change, and the later lanes add its corrections and
+// decide again.  Deciding move by move took 0.85 us each, two thirds of a round:
+// 512 particles 1.60 -> 0.84 us per move, 1,400 particles 2.3 -> 1.4.  What bounds
+// it now is the latency of one wavefront's evaluation (rows of 64 particles taken
+// two to four at a time) and about 1 us of decision per round.
+// Particles with an index of kResCap or more (a box that grows past it) are read
+// from and written to global memory instead: correct, slower.
 //
 // The cells are not maintained during the launch.  At its end the workgroup
 // writes the coordinates back and rebuilds the box's cell list in the layout
 // of gcmc_cell_build (entries of a cell in particle-id order, back-pointers in
 // the records), so every other kernel and call finds the box as it expects.
+#include <type_traits>
+
+#include "cell_pass.h"
 #include "spec_eval.h"
 
 namespace gcmc {
@@ -43,55 +54,35 @@ struct ResMove {
     double q[3];
 };
 
-// One move's evaluation against the round's starting state.
-struct ResRec {
-    int32_t type, flags;        // flags bit 0: displacement or deletion in an empty box
-    int64_t idx;                // picked particle (-1 for an insertion)
-    double pold[3], pnew[3];    // old position (displacement, deletion), new (displacement, insertion)
-    double dUp, dWp;            // pair energy and pair virial change against the round's start
-    int32_t cand, evals, incut, pad;
-};
+// Pairs of one wavefront waiting for their energies: at most 63 left over and four
+// rows of 64 more between two looks (four rows for one position, or two for two).
+constexpr int kResQueue = kWave + 4 * kWave;
 
-// An accepted move of the round: it removed a particle at a (displacement,
-// deletion) and added one at b (displacement, insertion); N before it.
-struct ResMod {
-    int32_t type, pad;
-    int64_t idx, n_before;
-    double a[3], b[3];
-};
-
-// The particle a displacement or deletion picks among n >= 1, on wave-uniform
-// integers: the rule of pick_particle with the spare draw's 53 bits given as
-// an integer.
-__device__ __forceinline__ int64_t res_pick(const ResMove& r, int64_t n) {
+// The particle a displacement or deletion picks among n (the rule of
+// pick_particle with the spare draw's 53 bits given as an integer), every lane on
+// its own move or its own n.
+__device__ __forceinline__ int32_t res_pick(uint32_t klo, uint32_t khi, double u2, int64_t n) {
     if (n <= 1) return 0;
-    const uint64_t k = ((uint64_t)(uint32_t)uni((int32_t)r.khi) << 32) | (uint32_t)uni((int32_t)r.klo);
-    const int b = 64 - __clzll((long long)(n - 1));
-    const uint64_t mask = (1ull << b) - 1ull;
-    for (int sh = 53 - b; sh >= 0; sh -= b) {
-        const uint64_t v = (k >> sh) & mask;
-        if (v < (uint64_t)n) return (int64_t)v;
-    }
-    const int64_t i = (int64_t)floor(r.u2 * (double)n);
-    return uni64(i > n - 1 ? n - 1 : i);
-}
-
-// The same pick with every lane on its own move.
-__device__ __forceinline__ int64_t res_pick_lane(const ResMove& r, int64_t n) {
-    if (n <= 1) return 0;
-    const uint64_t k = ((uint64_t)r.khi << 32) | (uint64_t)r.klo;
-    const int b = 64 - __clzll((long long)(n - 1));
-    const uint64_t mask = (1ull << b) - 1ull;
-    int64_t idx = -1;
+    const uint64_t k = ((uint64_t)khi << 32) | (uint64_t)klo;
+    const int b = 32 - __clz((int)(uint32_t)(n - 1));   // n < 2^31
+    const uint32_t mask = (uint32_t)((1ull << b) - 1ull);
+    int32_t idx = -1;
     for (int sh = 53 - b; sh >= 0 && idx < 0; sh -= b) {
-        const uint64_t v = (k >> sh) & mask;
-        if (v < (uint64_t)n) idx = (int64_t)v;
+        const uint32_t v = (uint32_t)(k >> sh) & mask;
+        if (v < (uint32_t)n) idx = (int32_t)v;
     }
     if (idx < 0) {
-        const int64_t i = (int64_t)floor(r.u2 * (double)n);
-        idx = i > n - 1 ? n - 1 : i;
+        const int64_t i = (int64_t)floor(u2 * (double)n);
+        idx = (int32_t)(i > n - 1 ? n - 1 : i);
     }
     return idx;
+}
+
+// Squared minimum-image distance, the bits of dist2 (coordinates in [0, L)): the
+// magnitude of a minimum image is the smaller of |d| and L - |d|.
+__device__ __forceinline__ double res_dist2(const double* L, double px, double py, double pz, const double3& e) {
+    const double dx = image_abs(e.x - px, L[0]), dy = image_abs(e.y - py, L[1]), dz = image_abs(e.z - pz, L[2]);
+    return (dx * dx + dy * dy) + dz * dz;
 }
 
 template <int W>
@@ -104,15 +95,18 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     // log acceptance prefactors for N = lbase + t: insertion V / (Lambda^3 (N + 1)), deletion
     // Lambda^3 N / V (the moves prepared together change N by at most one each)
     __shared__ double lpi[2 * kResRing + 1], lpd[2 * kResRing + 1];
-    __shared__ ResRec rec[W];
-    __shared__ ResMod mods[W];
-    __shared__ double pq[W][kPairRing];   // each wavefront's queue of in-cutoff pairs
-    // corr[k][j]: the change of move k's pair energy and virial if move j < k of the round is
+    __shared__ double pq[W][kResQueue];   // each wavefront's queue of in-cutoff pairs
+    // move k's evaluation: pair energy and virial change against the round's start, pairs inside
+    // the cutoff, and bit o: its pick at N_round - (W - 1) + o is the particle it evaluated
+    __shared__ double ev_u[W], ev_w[W];
+    __shared__ int32_t ev_in[W];
+    __shared__ uint32_t ev_pick[W];
+    // corr[j][k]: the change of move k's pair energy and virial if move j < k of the round is
     // accepted (move j's removed and added positions against move k's positions)
     __shared__ double corr_e[W][W], corr_w[W][W];
     __shared__ int32_t ready[W];          // round whose evaluation wavefront w has published
-    __shared__ int64_t sh_n, sh_k, sh_nacc, sh_err, sh_err_move;
-    __shared__ double sh_u, sh_w;
+    // the state after a round, by round parity (a wavefront may still read the last round's)
+    __shared__ int64_t sh_n[2], sh_m[2], sh_err[2], sh_err_move[2];
     __shared__ int64_t wred[4][W];
     __shared__ int32_t sh_flag;
     const int bi = order ? order[blockIdx.x] : (int)blockIdx.x;
@@ -124,14 +118,15 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
 
     if (ctr0 == GCMC_COUNTER_CONTINUE) ctr0 = (uint64_t)st->counter;
     int64_t N = st->n;
-    double U = st->u_pair;
+    double U = st->u_pair;      // running energy and virial: kept by wavefront 0
     double Wvir = st->w_pair;
     int32_t err = st->error;
     int64_t err_move = st->error_move;
     const double tk = B.tailK[0];
     const double rc2 = B.rc2, eps4 = B.eps4[0], sig2 = B.sig2[0];
     const int32_t spin_cap = wait_bound(B.wait_limit);
-    // statistics, kept by wavefront 0
+    // statistics, kept by wavefront 0: counts per type, and per-lane sums over the moves lane k
+    // decided as move k of a round
     int64_t att0 = 0, att1 = 0, att2 = 0, acc0 = 0, acc1 = 0, acc2 = 0;
     double sum_n = 0.0, sum_u = 0.0, sum_n2 = 0.0, sum_w = 0.0;
     int64_t cand = 0, evals = 0, incut = 0;
@@ -140,23 +135,14 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
         if (j < kResCap) return make_double3(px[j], py[j], pz[j]);
         return gload_xyz(B.pos + j);
     };
-    auto put = [&](int64_t j, const double* q) {
+    auto put = [&](int64_t j, double x, double y, double z) {
         if (j < kResCap) {
-            px[j] = q[0];
-            py[j] = q[1];
-            pz[j] = q[2];
+            px[j] = x;
+            py[j] = y;
+            pz[j] = z;
         } else {
-            gstore(B.pos + j, make_double4(q[0], q[1], q[2], 0.0));
+            gstore(B.pos + j, make_double4(x, y, z, 0.0));
         }
-    };
-    // energy and virial of one pair inside the cutoff, added to (e, v); pairs outside add zero
-    auto pair = [&](double r2, double& e, double& v, int32_t& nin) {
-        const bool in = r2 < rc2;
-        nin += in ? 1 : 0;
-        double w = 0.0;
-        const double u = lj_uw_from_r2(in ? r2 : rc2, rc2, eps4, sig2, w);
-        e += in ? u : 0.0;
-        v += in ? w : 0.0;
     };
 
     {
@@ -219,285 +205,311 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
             __syncthreads();
         }
         const int kend = (n_moves - m) < W ? (int)(n_moves - m) : W;
-        // ------------------------------------------------ evaluate move m + wv
         if (wv < kend) {
-            const int s = (int)((ctr0 + (uint64_t)(m + wv)) & (uint64_t)(kResRing - 1));
-            const ResMove& R = mv[s];
-            const int type = uni(R.type);
-            ResRec out;
-            out.type = type;
-            out.flags = 0;
-            out.idx = -1;
-            out.dUp = out.dWp = 0.0;
-            out.cand = out.evals = out.incut = out.pad = 0;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) out.pold[a] = out.pnew[a] = 0.0;
-            if (type != GCMC_MOVE_INSERT && N == 0) {
-                out.flags = 1;
-            } else {
-                const bool disp = type == GCMC_MOVE_DISPLACE, ins = type == GCMC_MOVE_INSERT;
-                double p0[3], p1[3] = {0.0, 0.0, 0.0};
-                int64_t idx = -1;
-                if (ins) {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) p0[a] = R.q[a];
-                } else {
-                    idx = res_pick(R, N);
+            // ---------------------------------------- the round's moves, lane k: move m + k
+            int32_t type = GCMC_MOVE_INSERT, idx = -1;
+            double u2 = 0.0, lnA = 0.0;
+            uint32_t klo = 0, khi = 0;
+            double ax = 0.0, ay = 0.0, az = 0.0;   // the position it takes away (displacement, deletion)
+            double bx = 0.0, by = 0.0, bz = 0.0;   // the position it adds (displacement, insertion)
+            if (lane < kend) {
+                const ResMove& R = mv[(int)((ctr0 + (uint64_t)(m + lane)) & (uint64_t)(kResRing - 1))];
+                type = R.type;
+                u2 = R.u2;
+                lnA = R.lnA;
+                klo = R.klo;
+                khi = R.khi;
+                bx = R.q[0];
+                by = R.q[1];
+                bz = R.q[2];
+                if (type != GCMC_MOVE_INSERT && N > 0) {
+                    idx = res_pick(klo, khi, u2, N);
                     const double3 o = get(idx);
-                    p0[0] = o.x; p0[1] = o.y; p0[2] = o.z;
-                    if (disp) {
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) p1[a] = wrap_into_box(p0[a] + R.q[a], B.L[a]);
+                    ax = o.x;
+                    ay = o.y;
+                    az = o.z;
+                    if (type == GCMC_MOVE_DISPLACE) {
+                        bx = wrap_into_box(ax + bx, B.L[0]);
+                        by = wrap_into_box(ay + by, B.L[1]);
+                        bz = wrap_into_box(az + bz, B.L[2]);
                     }
                 }
-                double sa = 0.0, sb = 0.0, wa = 0.0, wb = 0.0;
-                uint32_t qhead = 0, qtail = 0;
-                int32_t n_eval = 0, n_c = 0;
-                int64_t n_in = 0;
-                for (int64_t j0 = 0; j0 < N; j0 += kWave) {
-                    const int64_t j = j0 + lane;
-                    const bool valid = j < N && j != idx;
-                    const double3 e = valid ? get(j) : make_double3(0.0, 0.0, 0.0);
-                    n_c += valid ? 1 : 0;
-                    spec_pair_queue(B, type, 0, valid, false, p0, p1, e, true, pq[wv], qhead, qtail, sa, sb, wa, wb,
-                                    n_eval, n_in);
-                }
-                if (qtail != qhead) pair_drain(B, pq[wv], qhead, qtail - qhead, sa, sb, wa, wb);
-                // lane j < wv: the correction if the earlier move j of the round is accepted, from the
-                // positions move j takes (its pick at the round's N, its draws)
-                {
-                    double ce = 0.0, cw = 0.0;
-                    if (lane < wv) {
-                        const ResMove& Rj = mv[(int)((ctr0 + (uint64_t)(m + lane)) & (uint64_t)(kResRing - 1))];
-                        const int tj = Rj.type;
-                        if (tj == GCMC_MOVE_INSERT || N > 0) {
-                            double aj[3] = {0.0, 0.0, 0.0}, bj[3] = {0.0, 0.0, 0.0};
-                            if (tj == GCMC_MOVE_INSERT) {
-#pragma unroll
-                                for (int a = 0; a < 3; ++a) bj[a] = Rj.q[a];
-                            } else {
-                                const double3 o = get(res_pick_lane(Rj, N));
-                                aj[0] = o.x; aj[1] = o.y; aj[2] = o.z;
-                                if (tj == GCMC_MOVE_DISPLACE) {
-#pragma unroll
-                                    for (int a = 0; a < 3; ++a) bj[a] = wrap_into_box(aj[a] + Rj.q[a], B.L[a]);
-                                }
-                            }
-                            // f(r): pair terms with this move's new position minus those with its old one
-                            int32_t dummy = 0;
-                            double enb = 0.0, wnb = 0.0, eob = 0.0, wob = 0.0, ena = 0.0, wna = 0.0, eoa = 0.0, woa = 0.0;
-                            const double* pn = disp ? p1 : p0;
-                            const double3 ja = make_double3(aj[0], aj[1], aj[2]), jb = make_double3(bj[0], bj[1], bj[2]);
-                            if (tj != GCMC_MOVE_DELETE) {
-                                if (!(type == GCMC_MOVE_DELETE)) pair(spec_dist2(B, pn, jb, true), enb, wnb, dummy);
-                                if (!ins) pair(spec_dist2(B, p0, jb, true), eob, wob, dummy);
-                            }
-                            if (tj != GCMC_MOVE_INSERT) {
-                                if (!(type == GCMC_MOVE_DELETE)) pair(spec_dist2(B, pn, ja, true), ena, wna, dummy);
-                                if (!ins) pair(spec_dist2(B, p0, ja, true), eoa, woa, dummy);
-                            }
-                            ce = (enb - eob) - (ena - eoa);
-                            cw = (wnb - wob) - (wna - woa);
-                        }
-                        corr_e[wv][lane] = ce;
-                        corr_w[wv][lane] = cw;
-                    }
-                }
-                sa = wave_sum_uniform(sa);
-                sb = wave_sum_uniform(sb);
-                wa = wave_sum_uniform(wa);
-                wb = wave_sum_uniform(wb);
-                n_c = wave_sum_i32_uniform(n_c);
-                n_eval = wave_sum_i32_uniform(n_eval);
-                const int32_t n_inc = wave_sum_i32_uniform((int32_t)n_in);
-                out.idx = idx;
-                out.dUp = disp ? (sb - sa) : (ins ? sa : -sa);
-                out.dWp = disp ? (wb - wa) : (ins ? wa : -wa);
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    out.pold[a] = ins ? 0.0 : p0[a];
-                    out.pnew[a] = disp ? p1[a] : (ins ? p0[a] : 0.0);
-                }
-                out.cand = n_c;
-                out.evals = n_eval;
-                out.incut = n_inc;
             }
-            if (lane == 0) rec[wv] = out;
-            if (wv == 0) {
-                // its own record, read by every lane of this wavefront below
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-            } else {
+            // ---------------------------------------- evaluate move m + wv
+            const int mt = __builtin_amdgcn_readlane(type, wv);
+            const int32_t mi = __builtin_amdgcn_readlane(idx, wv);
+            if (mt == GCMC_MOVE_INSERT || N > 0) {
+                const bool disp = mt == GCMC_MOVE_DISPLACE, ins = mt == GCMC_MOVE_INSERT;
+                const double p0x = read_lane(ins ? bx : ax, wv), p0y = read_lane(ins ? by : ay, wv),
+                             p0z = read_lane(ins ? bz : az, wv);
+                const double p1x = read_lane(bx, wv), p1y = read_lane(by, wv), p1z = read_lane(bz, wv);
+                double* q = pq[wv];
+                uint32_t tail = 0;
+                int32_t n_in = 0;
+                double su = 0.0, sw = 0.0;   // new position minus old (displacement), else the one position
+                auto drain = [&](uint32_t from, uint32_t cnt) {
+                    wave_lds_sync();
+                    if ((uint32_t)lane < cnt) {
+                        const double v = q[from + lane];   // the sign bit marks a displacement's old position
+                        double w = 0.0;
+                        const double u = lj_uw_from_r2(__builtin_fabs(v), rc2, eps4, sig2, w);
+                        su += __builtin_copysign(1.0, v) * u;
+                        sw += __builtin_copysign(1.0, v) * w;
+                    }
+                    wave_lds_sync();
+                };
+                auto push = [&](double r2, double v) {
+                    const uint64_t mk = __ballot(r2 < rc2);
+                    if (__builtin_amdgcn_inverse_ballot_w64(mk)) q[lanes_below(mk, tail)] = v;
+                    tail += (uint32_t)__builtin_popcountll(mk);
+                };
+                // rows of 64 particles, RB at a time (independent chains); x = 1e300: no candidate
+                auto rows = [&](auto two_t) {
+                    constexpr bool TWO = decltype(two_t)::value;
+                    constexpr int RB = TWO ? 2 : 4;
+                    for (int32_t j0 = 0; j0 < (int32_t)N; j0 += RB * kWave) {
+                        double3 e[RB];
+#pragma unroll
+                        for (int r = 0; r < RB; ++r) {
+                            const int32_t j = j0 + r * kWave + lane;
+                            e[r] = make_double3(1e300, 0.0, 0.0);
+                            if (j0 + r * kWave < kResCap) {
+                                // (reads past the particles stay inside the arrays)
+                                const double3 o = make_double3(px[j], py[j], pz[j]);
+                                if (j < (int32_t)N && j != mi) e[r] = o;
+                            } else if (j < (int32_t)N && j != mi) {
+                                e[r] = gload_xyz(B.pos + j);
+                            }
+                        }
+                        double ra[RB], rb[RB];
+#pragma unroll
+                        for (int r = 0; r < RB; ++r) {
+                            ra[r] = res_dist2(B.L, p0x, p0y, p0z, e[r]);
+                            if (TWO) rb[r] = res_dist2(B.L, p1x, p1y, p1z, e[r]);
+                        }
+                        const uint32_t t0 = tail;
+#pragma unroll
+                        for (int r = 0; r < RB; ++r) {
+                            push(ra[r], TWO ? -ra[r] : ra[r]);
+                            if (TWO) push(rb[r], rb[r]);
+                        }
+                        tail = (uint32_t)uni((int32_t)tail);
+                        n_in += (int32_t)(tail - t0);
+                        while (tail >= (uint32_t)kWave) {
+                            tail -= kWave;
+                            drain(tail, kWave);
+                        }
+                    }
+                };
+                if (disp) rows(std::true_type{});
+                else rows(std::false_type{});
+                if (tail) drain(0, tail);
+                // the correction if the earlier move j of the round is accepted: f(b_j) - f(a_j), f(r) the
+                // pair terms of r with this move's new position minus those with its old one; lane
+                // 16 g + j takes one of the four terms: (new, b), (old, b), (new, a), (old, a)
+                if (wv > 0) {
+                    const int j = lane & 15, g = lane >> 4;
+                    const int32_t tj = __shfl(type, j, kWave);
+                    const double jax = __shfl(ax, j, kWave), jay = __shfl(ay, j, kWave), jaz = __shfl(az, j, kWave);
+                    const double jbx = __shfl(bx, j, kWave), jby = __shfl(by, j, kWave), jbz = __shfl(bz, j, kWave);
+                    const bool b_side = g < 2, new_side = (g & 1) == 0;
+                    const bool has = j < wv && (b_side ? tj != GCMC_MOVE_DELETE : tj != GCMC_MOVE_INSERT) &&
+                                     (new_side ? mt != GCMC_MOVE_DELETE : !ins) && (tj == GCMC_MOVE_INSERT || N > 0);
+                    const bool second = new_side && disp;
+                    double u = 0.0, w = 0.0;
+                    if (has) {
+                        const double r2 = res_dist2(B.L, second ? p1x : p0x, second ? p1y : p0y, second ? p1z : p0z,
+                                                    make_double3(b_side ? jbx : jax, b_side ? jby : jay, b_side ? jbz : jaz));
+                        u = lj_uw_from_r2(r2, rc2, eps4, sig2, w);
+                    }
+                    // (new - old) at b, minus (new - old) at a
+                    u -= __shfl_down(u, 16, kWave);
+                    w -= __shfl_down(w, 16, kWave);
+                    u -= __shfl_down(u, 32, kWave);
+                    w -= __shfl_down(w, 32, kWave);
+                    if (lane < wv) {
+                        corr_e[lane][wv] = u;
+                        corr_w[lane][wv] = w;
+                    }
+                }
+                // the pick at every N the move can meet (lane o: N - (W - 1) + o)
+                uint32_t pm = 0xFFFFFFFFu;
+                if (!ins) {
+                    const uint32_t olo = __builtin_amdgcn_readlane(klo, wv), ohi = __builtin_amdgcn_readlane(khi, wv);
+                    const double ou2 = read_lane(u2, wv);
+                    const int64_t np = N - (W - 1) + lane;
+                    pm = (uint32_t)__ballot(lane < 2 * W - 1 && np >= 0 && res_pick(olo, ohi, ou2, np) == mi);
+                }
+                su = wave_sum_uniform(su);
+                sw = wave_sum_uniform(sw);
+                if (lane == 0) {
+                    ev_u[wv] = mt == GCMC_MOVE_DELETE ? -su : su;
+                    ev_w[wv] = mt == GCMC_MOVE_DELETE ? -sw : sw;
+                    ev_in[wv] = n_in;
+                    ev_pick[wv] = pm;
+                }
+            }
+            if (wv != 0) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
                 if (lane == 0) __hip_atomic_store(&ready[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        }
-        // ------------------------------------------------ decide in order (wavefront 0)
-        if (wv == 0) {
-            int64_t Nc = N;
-            double Uc = U, Wc = Wvir;
-            int nacc = 0;
-            int32_t ntouch = 0;
-            int64_t touched = -1;   // lane t < ntouch: a particle index an accepted move changed
-            uint64_t accbits = 0;   // bit j: move j of the round accepted
-            int k = 0;
-            for (; k < kend; ++k) {
-                const uint64_t ctr = ctr0 + (uint64_t)(m + k);
-                if (k > 0) {
+            } else {
+                // ------------------------------------ decide in order, lane k: move m + k
+                // Every lane keeps its move's decision at the current state.  The moves up to the
+                // first accepted or stale one are rejections; an accepted one changes N and the
+                // corrections of the later lanes, which decide again.
+                int kw = kend;   // moves whose evaluation arrived
+                if (spin_cap < 0) {
+                    kw = 1;
+                } else {
                     int32_t spins = 0;
-                    while (uni(__hip_atomic_load(&ready[k], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) != rnd) {
+                    for (;;) {
+                        const bool wait = lane > 0 && lane < kend &&
+                                          __hip_atomic_load(&ready[lane & (W - 1)], __ATOMIC_ACQUIRE,
+                                                            __HIP_MEMORY_SCOPE_WORKGROUP) != rnd;
+                        const uint64_t late = __ballot(wait);
+                        if (late == 0) break;
                         __builtin_amdgcn_s_sleep(1);
-                        if (++spins > spin_cap) break;
-                    }
-                    if (spins > spin_cap) {
-                        err = GCMC_ERR_INTERNAL;
-                        err_move = (int64_t)ctr;
-                        break;
-                    }
-                }
-                const ResRec& R = rec[k];
-                const int type = uni(R.type);
-                const int s = (int)(ctr & (uint64_t)(kResRing - 1));
-                if (R.flags & 1) {
-                    // the empty-box rejection holds only while the box is still empty
-                    if (Nc != 0) break;
-                    if (type == GCMC_MOVE_DISPLACE) att0 += 1;
-                    else att2 += 1;
-                    sum_u += Uc;
-                    sum_w += Wc;
-                    if (trace && lane == 0) {
-                        gcmc_log r;
-                        r.type = type; r.index = -1; r.accepted = 0; r.flags = 1;
-                        r.dU_pair = 0.0; r.dU_tail = 0.0; r.x = r.y = r.z = 0.0; r.arg = 0.0; r.dW_pair = 0.0;
-                        trace[(size_t)bi * n_moves + (m + k)] = r;
-                    }
-                    continue;
-                }
-                const bool disp = type == GCMC_MOVE_DISPLACE, ins = type == GCMC_MOVE_INSERT;
-                const int64_t idx = uni64(R.idx);
-                if (!ins) {
-                    if (res_pick(mv[s], Nc) != idx) break;
-                    if (__ballot(lane < ntouch && touched == idx) != 0) break;
-                }
-                // corrections for the accepted earlier moves of this round (prepared by this move's
-                // wavefront, one lane each), summed over the lanes in a fixed order
-                double cE = 0.0, cW = 0.0;
-                if (accbits != 0) {
-                    const bool use = lane < k && ((accbits >> lane) & 1ull) != 0;
-                    cE = wave_sum_uniform(use ? corr_e[k][lane] : 0.0);
-                    cW = wave_sum_uniform(use ? corr_w[k][lane] : 0.0);
-                }
-                const double dUp = R.dUp + cE;
-                const double dWp = R.dWp + cW;
-                // ---- decide at the current N (Eqs. 3-5)
-                const double dUt = disp ? 0.0 : tk * (ins ? (2.0 * (double)Nc + 1.0) : (1.0 - 2.0 * (double)Nc));
-                const double dU = dUp + dUt;
-                const double lpref = disp ? 0.0 : (ins ? lpi[Nc - lbase] : lpd[Nc - lbase]);
-                const double arg = disp ? -(B.beta * dU)
-                                        : (ins ? lpref + B.beta * (B.mu - dU) : lpref - B.beta * (B.mu + dU));
-                const bool ok = __builtin_amdgcn_readfirstlane((dU == dU && mv[s].lnA < arg) ? 1 : 0) != 0;
-                if (ok && ins && Nc >= B.max_n) {
-                    err = GCMC_ERR_CAPACITY;
-                    err_move = (int64_t)ctr;
-                    break;
-                }
-                if (disp) att0 += 1;
-                else if (ins) att1 += 1;
-                else att2 += 1;
-                // work counters of the decided moves, kept by lane 0 (the lanes are summed at the end)
-                if (lane == 0) {
-                    cand += R.cand;
-                    evals += R.evals;
-                    incut += R.incut;
-                }
-                const int64_t n_old = Nc;
-                if (ok) {
-                    if (lane == 0) {
-                        ResMod& J = mods[nacc];
-                        J.type = type;
-                        J.pad = 0;
-                        J.idx = ins ? Nc : idx;
-                        J.n_before = Nc;
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            J.a[a] = R.pold[a];
-                            J.b[a] = R.pnew[a];
+                        if (++spins > spin_cap) {
+                            kw = (int)__builtin_ctzll(late);
+                            break;
                         }
                     }
-                    // the indices whose particle changed: the moved or deleted one, the inserted
-                    // one, and the last one a deletion relabels
-                    if (lane == ntouch) touched = ins ? Nc : idx;
-                    ntouch += 1;
-                    if (type == GCMC_MOVE_DELETE) {
-                        if (lane == ntouch) touched = Nc - 1;
-                        ntouch += 1;
-                    }
-                    nacc += 1;
-                    accbits |= 1ull << k;
-                    if (disp) acc0 += 1;
-                    else if (ins) acc1 += 1;
-                    else acc2 += 1;
-                    Nc += ins ? 1 : (disp ? 0 : -1);
-                    Uc += dUp;
-                    Wc += dWp;
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
                 }
-                if (trace && lane == 0) {
-                    gcmc_log r;
-                    r.type = type;
-                    r.index = ins ? (int32_t)n_old : (int32_t)idx;
-                    r.accepted = ok ? 1 : 0;
-                    r.flags = 0;
-                    r.dU_pair = dUp;
-                    r.dU_tail = dUt;
-                    r.x = R.pnew[0]; r.y = R.pnew[1]; r.z = R.pnew[2];
-                    if (type == GCMC_MOVE_DELETE) {
-                        r.x = R.pold[0]; r.y = R.pold[1]; r.z = R.pold[2];
-                    }
-                    r.arg = arg;
-                    r.dW_pair = dWp;
-                    trace[(size_t)bi * n_moves + (m + k)] = r;
+                wave_lds_sync();
+                const bool mine = lane < kw;
+                const bool disp = type == GCMC_MOVE_DISPLACE, ins = type == GCMC_MOVE_INSERT;
+                const bool empty = !ins && N == 0;   // a displacement or deletion in an empty box
+                double dUp = 0.0, dWp = 0.0;
+                uint32_t pick = 0;
+                int32_t n_in = 0;
+                if (mine && !empty) {
+                    dUp = ev_u[lane];
+                    dWp = ev_w[lane];
+                    pick = ev_pick[lane];
+                    n_in = ev_in[lane];
                 }
-                sum_n += (double)Nc;
-                sum_n2 += (double)Nc * (double)Nc;
-                sum_u += Uc + tk * (double)Nc * (double)Nc;
-                sum_w += Wc;
-            }
-            if (lane == 0) {
-                sh_n = Nc;
-                sh_u = Uc;
-                sh_w = Wc;
-                sh_k = k;
-                sh_nacc = nacc;
-                sh_err = err;
-                sh_err_move = err_move;
+                const int64_t n_round = N;
+                bool stale = false;
+                double dUt = 0.0, arg = 0.0;
+                double aft_n = 0.0, aft_u = 0.0, aft_w = 0.0;
+                uint64_t accbits = 0;
+                int k = 0;
+                while (k < kw) {
+                    const uint64_t todo = ((1ull << kw) - 1ull) & ~((1ull << k) - 1ull);
+                    bool ok = false, bad = false;
+                    if (mine && lane >= k) {
+                        if (empty) {
+                            bad = N != 0;   // the empty-box rejection holds only while the box is still empty
+                        } else {
+                            bad = !ins && (stale || ((pick >> (int)(N - n_round + W - 1)) & 1u) == 0);
+                            dUt = disp ? 0.0 : tk * (ins ? (2.0 * (double)N + 1.0) : (1.0 - 2.0 * (double)N));
+                            const double dU = dUp + dUt;
+                            const double lpref = disp ? 0.0 : (ins ? lpi[N - lbase] : lpd[N - lbase]);
+                            arg = disp ? -(B.beta * dU)
+                                       : (ins ? lpref + B.beta * (B.mu - dU) : lpref - B.beta * (B.mu + dU));
+                            ok = dU == dU && lnA < arg;
+                        }
+                    }
+                    const uint64_t bads = __ballot(bad) & todo;
+                    const uint64_t stop = bads | (__ballot(ok) & todo);
+                    const int f = stop ? (int)__builtin_ctzll(stop) : kw;
+                    if (lane >= k && lane < f) {   // rejected: the state after them is the current one
+                        aft_n = (double)N;
+                        aft_u = U;
+                        aft_w = Wvir;
+                    }
+                    k = f;
+                    if (f == kw || ((bads >> f) & 1ull)) break;
+                    // ---- move f is accepted
+                    const int32_t tf = __builtin_amdgcn_readlane(type, f), fi = __builtin_amdgcn_readlane(idx, f);
+                    const bool fins = tf == GCMC_MOVE_INSERT, fdel = tf == GCMC_MOVE_DELETE;
+                    if (fins && N >= B.max_n) {
+                        err = GCMC_ERR_CAPACITY;
+                        err_move = (int64_t)(ctr0 + (uint64_t)(m + f));
+                        break;
+                    }
+                    // into the LDS copy: every evaluation of the round has been read
+                    if (lane == f) {
+                        if (!fdel) {
+                            put(fins ? N : (int64_t)fi, bx, by, bz);
+                        } else if (fi != (int32_t)(N - 1)) {
+                            const double3 l = get(N - 1);
+                            put(fi, l.x, l.y, l.z);
+                        }
+                    }
+                    // the indices whose particle changed: the moved or deleted one, the inserted one,
+                    // and the last one a deletion relabels
+                    stale = stale || idx == (fins ? (int32_t)N : fi) || (fdel && idx == (int32_t)(N - 1));
+                    if (lane > f && lane < kw) {
+                        dUp += corr_e[f][lane];
+                        dWp += corr_w[f][lane];
+                    }
+                    N += fins ? 1 : (fdel ? -1 : 0);
+                    U += read_lane(dUp, f);
+                    Wvir += read_lane(dWp, f);
+                    if (lane == f) {
+                        aft_n = (double)N;
+                        aft_u = U;
+                        aft_w = Wvir;
+                    }
+                    accbits |= 1ull << f;
+                    k = f + 1;
+                }
+                if (err == GCMC_OK && k == kw && kw < kend) {
+                    err = GCMC_ERR_INTERNAL;   // move kw's evaluation did not arrive
+                    err_move = (int64_t)(ctr0 + (uint64_t)(m + kw));
+                }
+                // ---- statistics and log of the k moves decided, lane by lane
+                const bool done = lane < k;
+                const bool acc = done && ((accbits >> lane) & 1ull) != 0;
+                att0 += __builtin_popcountll(__ballot(done && disp));
+                att1 += __builtin_popcountll(__ballot(done && ins));
+                att2 += __builtin_popcountll(__ballot(done && type == GCMC_MOVE_DELETE));
+                acc0 += __builtin_popcountll(__ballot(acc && disp));
+                acc1 += __builtin_popcountll(__ballot(acc && ins));
+                acc2 += __builtin_popcountll(__ballot(acc && type == GCMC_MOVE_DELETE));
+                if (done) {
+                    sum_n += aft_n;
+                    sum_n2 += aft_n * aft_n;
+                    sum_u += aft_u + tk * aft_n * aft_n;
+                    sum_w += aft_w;
+                    if (!empty) {
+                        const int64_t c = n_round - (ins ? 0 : 1);
+                        cand += c;
+                        evals += disp ? 2 * c : c;
+                        incut += n_in;
+                    }
+                    if (trace) {
+                        gcmc_log r;
+                        r.type = type;
+                        const double dn = acc ? (ins ? 1.0 : (disp ? 0.0 : -1.0)) : 0.0;
+                        r.index = empty ? -1 : (ins ? (int32_t)(aft_n - dn) : idx);
+                        r.accepted = acc ? 1 : 0;
+                        r.flags = empty ? 1 : 0;
+                        r.dU_pair = dUp;
+                        r.dU_tail = dUt;
+                        const bool del = type == GCMC_MOVE_DELETE;
+                        r.x = empty ? 0.0 : (del ? ax : bx);
+                        r.y = empty ? 0.0 : (del ? ay : by);
+                        r.z = empty ? 0.0 : (del ? az : bz);
+                        r.arg = arg;
+                        r.dW_pair = dWp;
+                        trace[(size_t)bi * n_moves + (m + lane)] = r;
+                    }
+                }
+                if (lane == 0) {
+                    sh_n[rnd & 1] = N;
+                    sh_m[rnd & 1] = m + k;
+                    sh_err[rnd & 1] = err;
+                    sh_err_move[rnd & 1] = err_move;
+                }
             }
         }
-        __syncthreads();   // every evaluation read the round's state; the decisions published
-        const int64_t nacc = sh_nacc;
-        if (tid == 0) {
-            // the accepted moves into the LDS copy, in order
-            for (int j = 0; j < (int)nacc; ++j) {
-                const ResMod& J = mods[j];
-                if (J.type == GCMC_MOVE_DELETE) {
-                    if (J.idx != J.n_before - 1) {
-                        const double3 l = get(J.n_before - 1);
-                        const double q[3] = {l.x, l.y, l.z};
-                        put(J.idx, q);
-                    }
-                } else {
-                    put(J.idx, J.b);
-                }
-            }
-        }
-        N = sh_n;
-        U = sh_u;
-        Wvir = sh_w;
-        err = (int32_t)sh_err;
-        err_move = sh_err_move;
-        m += sh_k;
         __syncthreads();   // the new state visible to every wavefront
+        N = uni64(sh_n[rnd & 1]);
+        m = uni64(sh_m[rnd & 1]);
+        err = uni((int32_t)sh_err[rnd & 1]);
+        err_move = uni64(sh_err_move[rnd & 1]);
     }
     // ---------------------------------------------------- coordinates back, cells rebuilt
     // (after any move; a launch that ran none changed nothing)
@@ -566,6 +578,12 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
         }
     }
     maxc = wave_max_i32_uniform(maxc);
+    if (wv == 0) {
+        sum_n = wave_sum_vec(sum_n);
+        sum_n2 = wave_sum_vec(sum_n2);
+        sum_u = wave_sum_vec(sum_u);
+        sum_w = wave_sum_vec(sum_w);
+    }
     {
         int64_t c = cand, e = evals, q = incut;
 #pragma unroll
