@@ -61,19 +61,19 @@ constexpr int kResQueue = kWave + 4 * kWave;
 // The particle a displacement or deletion picks among n (the rule of
 // pick_particle with the spare draw's 53 bits given as an integer), every lane on
 // its own move or its own n.
-__device__ __forceinline__ int32_t res_pick(uint32_t klo, uint32_t khi, double u2, int64_t n) {
+__device__ __forceinline__ int32_t res_pick(uint32_t klo, uint32_t khi, double u2, int32_t n) {
     if (n <= 1) return 0;
     const uint64_t k = ((uint64_t)khi << 32) | (uint64_t)klo;
-    const int b = 32 - __clz((int)(uint32_t)(n - 1));   // n < 2^31
-    const uint32_t mask = (uint32_t)((1ull << b) - 1ull);
+    const int b = 32 - __clz(n - 1);
+    const uint32_t mask = (1u << b) - 1u;
     int32_t idx = -1;
     for (int sh = 53 - b; sh >= 0 && idx < 0; sh -= b) {
         const uint32_t v = (uint32_t)(k >> sh) & mask;
         if (v < (uint32_t)n) idx = (int32_t)v;
     }
     if (idx < 0) {
-        const int64_t i = (int64_t)floor(u2 * (double)n);
-        idx = (int32_t)(i > n - 1 ? n - 1 : i);
+        const int32_t i = (int32_t)floor(u2 * (double)n);
+        idx = i > n - 1 ? n - 1 : i;
     }
     return idx;
 }
@@ -83,6 +83,16 @@ __device__ __forceinline__ int32_t res_pick(uint32_t klo, uint32_t khi, double u
 __device__ __forceinline__ double res_dist2(const double* L, double px, double py, double pz, const double3& e) {
     const double dx = image_abs(e.x - px, L[0]), dy = image_abs(e.y - py, L[1]), dz = image_abs(e.z - pz, L[2]);
     return (dx * dx + dy * dy) + dz * dz;
+}
+
+// Pair energy and virial, the operations of lj_uw_from_r2 with selects for branches.
+__device__ __forceinline__ double res_pair(double r2, double rc2, double eps4, double sig2, double& w) {
+    const double sr2 = sig2 / r2;
+    const double s6 = sr2 * sr2 * sr2;
+    const double s12 = s6 * s6;
+    const bool in = r2 < rc2 && eps4 != 0.0, over = r2 == 0.0;
+    w = in ? (over ? __builtin_inf() : 6.0 * eps4 * (2.0 * s12 - s6)) : 0.0;
+    return in ? (over ? __builtin_inf() : eps4 * (s12 - s6)) : 0.0;
 }
 
 template <int W>
@@ -106,8 +116,8 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     __shared__ double corr_e[W][W], corr_w[W][W];
     __shared__ int32_t ready[W];          // round whose evaluation wavefront w has published
     // the state after a round, by round parity (a wavefront may still read the last round's)
-    __shared__ int64_t sh_n[2], sh_m[2], sh_err[2], sh_err_move[2];
-    __shared__ int64_t wred[4][W];
+    __shared__ int4 sh_state[2];   // N, moves decided, error
+    __shared__ int32_t wred[W];
     __shared__ int32_t sh_flag;
     const int bi = order ? order[blockIdx.x] : (int)blockIdx.x;
     const DevBox B = hot_copy(boxes[blockIdx.x]);
@@ -117,7 +127,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     BoxState* st = B.st;
 
     if (ctr0 == GCMC_COUNTER_CONTINUE) ctr0 = (uint64_t)st->counter;
-    int64_t N = st->n;
+    int32_t N = (int32_t)st->n;   // below 2^31
     double U = st->u_pair;      // running energy and virial: kept by wavefront 0
     double Wvir = st->w_pair;
     int32_t err = st->error;
@@ -125,17 +135,17 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     const double tk = B.tailK[0];
     const double rc2 = B.rc2, eps4 = B.eps4[0], sig2 = B.sig2[0];
     const int32_t spin_cap = wait_bound(B.wait_limit);
-    // statistics, kept by wavefront 0: counts per type, and per-lane sums over the moves lane k
-    // decided as move k of a round
-    int64_t att0 = 0, att1 = 0, att2 = 0, acc0 = 0, acc1 = 0, acc2 = 0;
+    // statistics, kept by wavefront 0: per-lane sums over the moves lane k decided as move k of a
+    // round, added up at the end (counts as doubles, exact below 2^53)
+    double att0 = 0.0, att1 = 0.0, att2 = 0.0, acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
     double sum_n = 0.0, sum_u = 0.0, sum_n2 = 0.0, sum_w = 0.0;
-    int64_t cand = 0, evals = 0, incut = 0;
+    double cand = 0.0, evals = 0.0, incut = 0.0;
 
-    auto get = [&](int64_t j) -> double3 {
+    auto get = [&](int32_t j) -> double3 {
         if (j < kResCap) return make_double3(px[j], py[j], pz[j]);
         return gload_xyz(B.pos + j);
     };
-    auto put = [&](int64_t j, double x, double y, double z) {
+    auto put = [&](int32_t j, double x, double y, double z) {
         if (j < kResCap) {
             px[j] = x;
             py[j] = y;
@@ -146,8 +156,8 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     };
 
     {
-        const int64_t nl = N < kResCap ? N : kResCap;
-        for (int64_t j = tid; j < nl; j += blockDim.x) {
+        const int32_t nl = N < kResCap ? N : kResCap;
+        for (int32_t j = tid; j < nl; j += blockDim.x) {
             const double4 r = gload(B.pos + j);
             px[j] = r.x;
             py[j] = r.y;
@@ -163,7 +173,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     __syncthreads();
     int64_t m = 0;
     int64_t prep_end = 0;   // moves m' < prep_end have their draws prepared (with the tables)
-    int64_t lbase = 0;
+    int32_t lbase = 0;
     int32_t rnd = 0;
     while (err == GCMC_OK && m < n_moves) {
         rnd = rnd == INT32_MAX ? 1 : rnd + 1;
@@ -177,7 +187,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
             lbase = N - kResRing;
             for (int t = tid; t < 2 * (2 * kResRing + 1); t += blockDim.x) {
                 const bool del = t > 2 * kResRing;
-                const int64_t n = lbase + (del ? t - (2 * kResRing + 1) : t);
+                const int32_t n = lbase + (del ? t - (2 * kResRing + 1) : t);
                 if (n >= 0) {
                     const double x = del ? (B.lambda3 * (double)n) / B.V : B.V / (B.lambda3 * (double)(n + 1));
                     if (del) lpd[t - (2 * kResRing + 1)] = log(x);
@@ -267,7 +277,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                 auto rows = [&](auto two_t) {
                     constexpr bool TWO = decltype(two_t)::value;
                     constexpr int RB = TWO ? 2 : 4;
-                    for (int32_t j0 = 0; j0 < (int32_t)N; j0 += RB * kWave) {
+                    for (int32_t j0 = 0; j0 < N; j0 += RB * kWave) {
                         double3 e[RB];
 #pragma unroll
                         for (int r = 0; r < RB; ++r) {
@@ -276,8 +286,8 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                             if (j0 + r * kWave < kResCap) {
                                 // (reads past the particles stay inside the arrays)
                                 const double3 o = make_double3(px[j], py[j], pz[j]);
-                                if (j < (int32_t)N && j != mi) e[r] = o;
-                            } else if (j < (int32_t)N && j != mi) {
+                                if (j < N && j != mi) e[r] = o;
+                            } else if (j < N && j != mi) {
                                 e[r] = gload_xyz(B.pos + j);
                             }
                         }
@@ -320,7 +330,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                     if (has) {
                         const double r2 = res_dist2(B.L, second ? p1x : p0x, second ? p1y : p0y, second ? p1z : p0z,
                                                     make_double3(b_side ? jbx : jax, b_side ? jby : jay, b_side ? jbz : jaz));
-                        u = lj_uw_from_r2(r2, rc2, eps4, sig2, w);
+                        u = res_pair(r2, rc2, eps4, sig2, w);
                     }
                     // (new - old) at b, minus (new - old) at a
                     u -= __shfl_down(u, 16, kWave);
@@ -337,8 +347,9 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                 if (!ins) {
                     const uint32_t olo = __builtin_amdgcn_readlane(klo, wv), ohi = __builtin_amdgcn_readlane(khi, wv);
                     const double ou2 = read_lane(u2, wv);
-                    const int64_t np = N - (W - 1) + lane;
-                    pm = (uint32_t)__ballot(lane < 2 * W - 1 && np >= 0 && res_pick(olo, ohi, ou2, np) == mi);
+                    const int32_t np = N - (W - 1) + lane;
+                    const int32_t at = res_pick(olo, ohi, ou2, np > 0 ? np : 0);
+                    pm = (uint32_t)__ballot(lane < 2 * W - 1 && np >= 0 && at == mi);
                 }
                 su = wave_sum_uniform(su);
                 sw = wave_sum_uniform(sw);
@@ -388,7 +399,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                     pick = ev_pick[lane];
                     n_in = ev_in[lane];
                 }
-                const int64_t n_round = N;
+                const int32_t n_round = N;
                 bool stale = false;
                 double dUt = 0.0, arg = 0.0;
                 double aft_n = 0.0, aft_u = 0.0, aft_w = 0.0;
@@ -401,7 +412,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                         if (empty) {
                             bad = N != 0;   // the empty-box rejection holds only while the box is still empty
                         } else {
-                            bad = !ins && (stale || ((pick >> (int)(N - n_round + W - 1)) & 1u) == 0);
+                            bad = !ins && (stale || ((pick >> (N - n_round + W - 1)) & 1u) == 0);
                             dUt = disp ? 0.0 : tk * (ins ? (2.0 * (double)N + 1.0) : (1.0 - 2.0 * (double)N));
                             const double dU = dUp + dUt;
                             const double lpref = disp ? 0.0 : (ins ? lpi[N - lbase] : lpd[N - lbase]);
@@ -431,15 +442,15 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                     // into the LDS copy: every evaluation of the round has been read
                     if (lane == f) {
                         if (!fdel) {
-                            put(fins ? N : (int64_t)fi, bx, by, bz);
-                        } else if (fi != (int32_t)(N - 1)) {
+                            put(fins ? N : fi, bx, by, bz);
+                        } else if (fi != N - 1) {
                             const double3 l = get(N - 1);
                             put(fi, l.x, l.y, l.z);
                         }
                     }
                     // the indices whose particle changed: the moved or deleted one, the inserted one,
                     // and the last one a deletion relabels
-                    stale = stale || idx == (fins ? (int32_t)N : fi) || (fdel && idx == (int32_t)(N - 1));
+                    stale = stale || idx == (fins ? N : fi) || (fdel && idx == N - 1);
                     if (lane > f && lane < kw) {
                         dUp += corr_e[f][lane];
                         dWp += corr_w[f][lane];
@@ -462,23 +473,22 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                 // ---- statistics and log of the k moves decided, lane by lane
                 const bool done = lane < k;
                 const bool acc = done && ((accbits >> lane) & 1ull) != 0;
-                att0 += __builtin_popcountll(__ballot(done && disp));
-                att1 += __builtin_popcountll(__ballot(done && ins));
-                att2 += __builtin_popcountll(__ballot(done && type == GCMC_MOVE_DELETE));
-                acc0 += __builtin_popcountll(__ballot(acc && disp));
-                acc1 += __builtin_popcountll(__ballot(acc && ins));
-                acc2 += __builtin_popcountll(__ballot(acc && type == GCMC_MOVE_DELETE));
                 if (done) {
+                    const double one = 1.0, a = acc ? one : 0.0;
+                    att0 += disp ? one : 0.0;
+                    att1 += ins ? one : 0.0;
+                    att2 += disp || ins ? 0.0 : one;
+                    acc0 += disp ? a : 0.0;
+                    acc1 += ins ? a : 0.0;
+                    acc2 += disp || ins ? 0.0 : a;
                     sum_n += aft_n;
                     sum_n2 += aft_n * aft_n;
                     sum_u += aft_u + tk * aft_n * aft_n;
                     sum_w += aft_w;
-                    if (!empty) {
-                        const int64_t c = n_round - (ins ? 0 : 1);
-                        cand += c;
-                        evals += disp ? 2 * c : c;
-                        incut += n_in;
-                    }
+                    const double c = empty ? 0.0 : (double)(n_round - (ins ? 0 : 1));
+                    cand += c;
+                    evals += disp ? 2.0 * c : c;
+                    incut += (double)n_in;
                     if (trace) {
                         gcmc_log r;
                         r.type = type;
@@ -497,19 +507,14 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                         trace[(size_t)bi * n_moves + (m + lane)] = r;
                     }
                 }
-                if (lane == 0) {
-                    sh_n[rnd & 1] = N;
-                    sh_m[rnd & 1] = m + k;
-                    sh_err[rnd & 1] = err;
-                    sh_err_move[rnd & 1] = err_move;
-                }
+                if (lane == 0) sh_state[rnd & 1] = make_int4(N, k, err, 0);
             }
         }
         __syncthreads();   // the new state visible to every wavefront
-        N = uni64(sh_n[rnd & 1]);
-        m = uni64(sh_m[rnd & 1]);
-        err = uni((int32_t)sh_err[rnd & 1]);
-        err_move = uni64(sh_err_move[rnd & 1]);
+        const int4 after = sh_state[rnd & 1];
+        N = uni(after.x);
+        m += uni(after.y);
+        err = uni(after.z);   // (its move is known to wavefront 0, which reports it)
     }
     // ---------------------------------------------------- coordinates back, cells rebuilt
     // (after any move; a launch that ran none changed nothing)
@@ -583,31 +588,21 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
         sum_n2 = wave_sum_vec(sum_n2);
         sum_u = wave_sum_vec(sum_u);
         sum_w = wave_sum_vec(sum_w);
+        att0 = wave_sum_vec(att0);
+        att1 = wave_sum_vec(att1);
+        att2 = wave_sum_vec(att2);
+        acc0 = wave_sum_vec(acc0);
+        acc1 = wave_sum_vec(acc1);
+        acc2 = wave_sum_vec(acc2);
+        cand = wave_sum_vec(cand);
+        evals = wave_sum_vec(evals);
+        incut = wave_sum_vec(incut);
     }
-    {
-        int64_t c = cand, e = evals, q = incut;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            c += __shfl_xor(c, off, kWave);
-            e += __shfl_xor(e, off, kWave);
-            q += __shfl_xor(q, off, kWave);
-        }
-        if (lane == 0) {
-            wred[0][wv] = c;
-            wred[1][wv] = e;
-            wred[2][wv] = q;
-            wred[3][wv] = maxc;
-        }
-    }
+    if (lane == 0) wred[wv] = maxc;
     __syncthreads();
     if (tid == 0) {
-        int64_t c = 0, e = 0, q = 0, mx = 0;
-        for (int v = 0; v < W; ++v) {
-            c += wred[0][v];
-            e += wred[1][v];
-            q += wred[2][v];
-            mx = wred[3][v] > mx ? wred[3][v] : mx;
-        }
+        int32_t mx = 0;
+        for (int v = 0; v < W; ++v) mx = wred[v] > mx ? wred[v] : mx;
         if (err == GCMC_OK && sh_flag) {
             // a cell of the rebuilt list overflowed: the chain itself is complete; a rebuild with a
             // larger capacity (gcmc_cell_build) restores the cells and clears the error
@@ -617,7 +612,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
         st->n = N;
         st->u_pair = U;
         st->w_pair = Wvir;
-        st->maxcount = (int32_t)mx > st->maxcount ? (int32_t)mx : st->maxcount;
+        st->maxcount = mx > st->maxcount ? mx : st->maxcount;
         st->nsp[0] = N;
         st->counter = (int64_t)(ctr0 + (uint64_t)m);
         if (err != GCMC_OK && st->error == GCMC_OK) {
@@ -626,13 +621,13 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
         }
         ChainSums L;
         L.moves = m;
-        L.att[0] = att0; L.att[1] = att1; L.att[2] = att2;
-        L.acc[0] = acc0; L.acc[1] = acc1; L.acc[2] = acc2;
+        L.att[0] = (int64_t)att0; L.att[1] = (int64_t)att1; L.att[2] = (int64_t)att2;
+        L.acc[0] = (int64_t)acc0; L.acc[1] = (int64_t)acc1; L.acc[2] = (int64_t)acc2;
         L.sum_n = sum_n;
         L.sum_n2 = sum_n2;
         L.sum_u = sum_u;
         L.sum_w = sum_w;
-        finish_launch(B, st, L, N, U, Wvir, 0, c, e, q, stats ? stats + bi : nullptr);
+        finish_launch(B, st, L, N, U, Wvir, 0, (int64_t)cand, (int64_t)evals, (int64_t)incut, stats ? stats + bi : nullptr);
     }
 }
 
