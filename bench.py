@@ -60,8 +60,8 @@ def resident_alg_bytes(n_start, n_end, ncells):
 # rocprofv3 counters is used only while these files are unchanged.
 KERNEL_SOURCES = {
     "k_chain": ["chain.hip", "trial.h", "gcmc_internal.h"],
-    "k_chain_spec": ["spec.hip", "spec_eval.h", "trial.h", "gcmc_internal.h"],
-    "k_chain_async": ["async.hip", "spec_eval.h", "trial.h", "gcmc_internal.h"],
+    "k_chain_spec": ["spec.hip", "spec_eval.h", "cell_pass.h", "trial.h", "gcmc_internal.h"],
+    "k_chain_async": ["async.hip", "spec_eval.h", "cell_pass.h", "trial.h", "gcmc_internal.h"],
 }
 
 

@@ -282,13 +282,16 @@ int gcmc_commit(gcmc_box* box, const gcmc_move* d_move, const double* d_dU_pair,
 /* Launch shape of the chain kernels (the autotuner's choice).  rows > 0: one
  * move at a time, `waves` wavefronts per workgroup and `rows` candidate slots
  * per lane per pass (1x8, 2x8, 4x2, 4x4, 4x8, 8x2, 8x4).  rows = 0:
- * speculative rounds, `waves` (2, 4, 8 or 16) consecutive moves evaluated at once,
- * one per wavefront, against the round's starting state and committed in
- * order, each only if nothing it read has changed since (the same chain, move
- * for move); needs one species and at most 512 stencil cells (stencils of
- * more than 32 cells, or whose candidates exceed 8192 slots, go through a
- * path that loads the stencil counters in groups of 64 cells and stages the
- * candidates' record indices in LDS windows), else GCMC_ERR_UNSUPPORTED.
+ * speculative rounds, `waves` (2, 4, 8 or 16) wavefronts' worth of consecutive
+ * moves (2, 3, 8 and 15 of them) evaluated at once, one per wavefront, against
+ * the round's starting state and decided in order by one more wavefront, each
+ * corrected for the earlier accepted moves of its round or, where one of those
+ * changed its particle or the cell it would commit to, evaluated again in the
+ * next round (the same chain, move for move); needs one species and at most
+ * 512 stencil cells (stencils of more than 32 cells, or whose candidates exceed
+ * 8192 slots, go through a path that loads the stencil counters in groups of 64
+ * cells and stages the candidates' record indices in LDS windows), else
+ * GCMC_ERR_UNSUPPORTED.
  * rows = -1: pipelined, one wavefront decides the moves in order while
  * waves - 1 (3 or 7) wavefronts evaluate the moves ahead of it; an evaluation
  * is used only if no decision since it read memory changed what it read (the

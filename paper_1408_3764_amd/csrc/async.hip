@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kWave*(E + 1)) void k_chain_async(const DevBox* __r
     __shared__ uint32_t tab[kMaxStencil];
     __shared__ int32_t offs[64];
     __shared__ uint8_t own[E][kSpecOwn];
-    __shared__ double pq[E][kPairRing];   // each evaluator's queue of in-cutoff pairs
+    __shared__ double pq[E][kSpecQueue];   // each evaluator's queue of in-cutoff pairs
     __shared__ AsyncShared S;
     const int bi = order ? order[blockIdx.x] : (int)blockIdx.x;
     const DevBox B = hot_copy(boxes[blockIdx.x]);

@@ -2,37 +2,40 @@
 // (the exact chain of Algorithm 1; not the "keep the first accepted" scheme the
 // paper lists as future work, which would change the sampled distribution).
 //
-// A round takes the next W moves.  Wavefront w evaluates move m + w against
+// A round takes the next W moves.  Wavefront w < W evaluates move m + w against
 // the state at the start of the round:
-//   * its Philox draws, type and trial positions.  A displacement or deletion
-//     picks floor(u N), which moves with N: the wavefront also computes the
-//     draws of the earlier moves of the round, so it knows how many insertions
-//     and deletions precede its move, and evaluates the pick at the N expected
-//     at its commit from the chain's running acceptance rates;
-//   * the counters of its stencil cells (one lane per cell, both stencils of a
-//     displacement that leaves its cell: at most 64 cells), an in-wave prefix
-//     sum of the counters, an owner table in LDS mapping each flattened
-//     candidate to its cell, and then exactly the candidates' 32-byte records
-//     (one memory round trip for the counters, one for the records);
-//   * the pair sums, reduced across the wavefront, and ln A.
-// Wavefront 0 then walks the round's moves in order, taking each as soon as
-// its wavefront has published it (a flag in LDS), while slower wavefronts may
-// still be evaluating.  A move's evaluation is
-// used only if nothing it read has changed since the round started: its pick
-// at the current N is the one it evaluated, the particle record
-// it read was not touched by an earlier commit of the round, and no cell
-// modified by an earlier commit lies in one of its stencils.  Then the tail
-// correction and the acceptance prefactor are taken at the current N, the
-// Metropolis test is applied and an accepted move is committed (stores only;
-// the records it needs came back with its evaluation).  N moves by at most one
-// per move, so the records of particles N_round - W .. N_round + W - 1 (what a
-// deletion moves into the freed index) and the prefactors for those N are
-// prepared in LDS by wavefront 0 at the start of the round, and kept current by
-// the commits.  The check also covers commits whose stores land while a later
-// move is still reading: whatever a commit writes lies in a modified cell or a
-// touched particle record.  The first move that
-// fails the check ends the round and is evaluated again in the next one, so
-// every move is decided on exactly the state the sequential chain would have.
+//   * its draws, type and trial positions (a displacement or deletion picks among
+//     the N expected at its commit: the round's earlier insertions and deletions
+//     times the chain's running acceptance rates);
+//   * the counters of its stencil cells, the candidates' records, the pair sums
+//     (spec_sums: one memory round trip for each of the picked record, the
+//     counters and the records);
+//   * a bit for every N the move can be decided at: is its pick still the particle
+//     it evaluated?
+//
+// Wavefront W decides.  While the others evaluate it prepares the next round (draws,
+// acceptance prefactors) and loads the records of particles N - W .. N - 1; then
+// lane k holds move k of the round and its decision at the current state.  The
+// rejections up to the next accepted or stale move take one ballot; an accepted
+// move is committed (stores only: what it needs came back with its evaluation) and
+// changes N and the later lanes:
+//   * a later move whose particle it touched, or one of whose centre cells it
+//     changed (the slots and counts that move would commit with), is stale: it
+//     ends the round and is evaluated again in the next;
+//   * any other later move whose positions come within the cutoff of the position
+//     taken away or added has its energy and virial corrected by those pair terms.
+// So every move is decided on exactly the state the sequential chain would have, up
+// to the rounding of its sums.
+//
+// The deciding wavefront is one of its own, not one that also evaluates: the
+// state of the commit then takes no registers from the evaluation, whose scalar
+// values were spilled and reloaded inside the candidate loop (evaluation alone: 142
+// vector registers and 26 scalar spills; one kernel for both took 256 and 160).  A
+// round of eight moves of the 1.5-million-particle slab takes 8.4 us (12.5 before):
+// the slowest evaluation 6.5 (three dependent memory round trips and the
+// arithmetic, two wavefronts per SIMD), the decision 0.4 and 1.6 per accepted move,
+// the wait for the stores 0.2.  Per move: slab 1.36 -> 1.04 us, 4,000 particles 1.40 -> 1.06,
+// cutoff 4.25 on microcells 2.5 -> 2.2; one box of a batch (waves = 4) 2.7 -> 2.0.
 //
 // NG > 0: stencils of more than 32 cells (microcells, Sec. 3.3) go through
 // the evaluation's path with NG groups of 64 cells; the round and the commit
@@ -41,68 +44,83 @@
 
 namespace gcmc {
 
-// Tail change and log acceptance ratio of a move decided at N particles
-// (Eqs. 3-5; the log prefactors for N come from the round's tables): one
-// routine for the decision and for the per-move log written after the round,
-// so both hold the same bits.
-// The parts of it that do not depend on the evaluation (the tail change and the log
-// prefactor at N), and the rest; the decision and the per-move log both go through them.
-__device__ __forceinline__ void spec_arg_pre(int type, int64_t N, int64_t base, const double* lp_ins,
-                                             const double* lp_del, double tk, double& dUt, double& lpref) {
-    const bool is_disp = type == GCMC_MOVE_DISPLACE, is_ins = type == GCMC_MOVE_INSERT;
-    dUt = is_disp ? 0.0 : tk * (is_ins ? (2.0 * (double)N + 1.0) : (1.0 - 2.0 * (double)N));
-    lpref = is_disp ? 0.0 : (is_ins ? lp_ins[N - base] : lp_del[N - base]);
-}
-
+// Log acceptance ratio of a move (Eqs. 3-5) from its pair and tail energy changes and
+// its log prefactor.
 __device__ __forceinline__ double spec_arg_fin(const DevBox& B, int type, double dUp, double dUt, double lpref) {
     const bool is_disp = type == GCMC_MOVE_DISPLACE, is_ins = type == GCMC_MOVE_INSERT;
     const double dU = dUp + dUt;
     return is_disp ? -(B.beta * dU) : (is_ins ? lpref + B.beta * (B.mu - dU) : lpref - B.beta * (B.mu + dU));
 }
 
-__device__ __forceinline__ double spec_arg(const DevBox& B, int type, double dUp, int64_t N, int64_t base,
-                                           const double* lp_ins, const double* lp_del, double tk, double& dUt) {
-    double lpref;
-    spec_arg_pre(type, N, base, lp_ins, lp_del, tk, dUt, lpref);
-    return spec_arg_fin(B, type, dUp, dUt, lpref);
+// Log acceptance prefactors at N = base + t: insertion V / (Lambda^3 (N + 1)),
+// deletion Lambda^3 N / V (entries at N < 0 are never read).  Filled by one wavefront.
+constexpr int kSpecPref = 128;
+__device__ __attribute__((noinline)) void spec_prefactors(double V, double lambda3, double* lpi, double* lpd, int32_t base) {
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int t = lane; t < kSpecPref; t += kWave) {
+        const double n = (double)(base + t);
+        lpi[t] = log(V / (lambda3 * (n + 1.0)));
+        lpd[t] = log((lambda3 * n) / V);
+    }
 }
 
-// Entry t of a prefactor table starting at N = nb: t < 4W, the log insertion
-// prefactor V / (Lambda^3 (N + 1)) at N = nb + t; t >= 4W, the log deletion
-// prefactor Lambda^3 N / V at N = nb + t - 4W (entries at N < 0 are never read).
-template <int W>
-__device__ __forceinline__ void spec_prefactor(const DevBox& B, double* lpi, double* lpd, int64_t nb, int t) {
-    const bool del = t >= 4 * W;
-    const int64_t n = nb + (del ? t - 4 * W : t);
-    const double x = del ? (B.lambda3 * (double)n) / B.V : B.V / (B.lambda3 * (double)(n + 1));
-    const double lx = log(x);
-    if (del) lpd[t - 4 * W] = lx;
-    else lpi[t] = lx;
+// Squared minimum-image distance of two positions, the bits of dist2.
+__device__ __forceinline__ double spec_r2(const DevBox& B, double px, double py, double pz, double qx, double qy,
+                                          double qz) {
+    const double dx = image_abs(qx - px, B.L[0]), dy = image_abs(qy - py, B.L[1]), dz = image_abs(qz - pz, B.L[2]);
+    return (dx * dx + dy * dy) + dz * dz;
 }
 
+// Is cell v one of the kept stencil cells of centre cell c?  (Within the half-widths,
+// and on the axes not covered whole the squared gaps between the cells sum to at most
+// rc^2 (1 + 1e-9), the rule the stencil was built by; side: the cell edges.)
+__device__ __forceinline__ bool kept_in_stencil(const DevBox& B, const double* side, const int32_t* v, const int32_t* c) {
+    bool in = true;
+    double g2 = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        int32_t d = v[a] - c[a];
+        d = d < 0 ? -d : d;
+        const int32_t e = B.M[a] - d;
+        d = e < d ? e : d;
+        in = in && (B.full[a] || d <= B.k[a]);
+        const double g = d > 1 && !B.full[a] ? (double)(d - 1) * side[a] : 0.0;
+        g2 += g * g;
+    }
+    return in && !(g2 > B.rc2 * (1.0 + 1e-9));
+}
+
+// draw_block, not inlined: the constants of log and of the generator would be kept in
+// registers through the whole decision loop otherwise (177 -> 160 vector registers).
+template <int RING>
+__device__ __attribute__((noinline)) void spec_draws(DrawRing<RING>* ring, uint64_t ctr, uint64_t seed, uint32_t box_id, double p_disp, int b) {
+    DevBox B;
+    B.seed = seed; B.box_id = box_id; B.p_disp = p_disp;
+    draw_block(B, ring, ctr, b);
+}
+// W evaluating wavefronts and one that decides.
 template <int W, int CR, int NG>
-__global__ __launch_bounds__(kWave* W) void k_chain_spec(const DevBox* __restrict__ boxes,
-                                                          const int32_t* __restrict__ order, int64_t n_moves,
-                                                          uint64_t ctr0, gcmc_stats* stats, gcmc_log* trace) {
+__global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(const DevBox* __restrict__ boxes,
+                                                               const int32_t* __restrict__ order, int64_t n_moves,
+                                                               uint64_t ctr0, gcmc_stats* stats, gcmc_log* trace) {
     constexpr int kOffs = NG ? NG * kWave / 2 : 64;    // stencil slots with a precomputed linear offset
+    constexpr int RING = W > 8 ? 32 : (W > 4 ? 16 : (W > 2 ? 8 : 4));   // a power of two, at least 2 W
     __shared__ uint32_t tab[kMaxStencil];
     __shared__ int32_t offs[kOffs];
-    __shared__ SpecRec recs[W];
+    __shared__ SpecRec recs_s[2][W];            // the round's evaluations, by round parity
     __shared__ __align__(8) uint32_t own[W][spec_own_words(NG)];   // cell bases and start masks, or record indices
     __shared__ double4 top[2 * W];              // records of particles base .. base + 2W - 1
-    // log acceptance prefactors at N = lp_base[b] + t, t < 4W, two buffers: the round's and the next round's
-    __shared__ double lp_ins[2][4 * W], lp_del[2][4 * W];
-    __shared__ int64_t lp_base[2];
-    __shared__ DrawRing<2 * W> dring;           // draws of moves m .. m + 2W - 1
-    __shared__ double pq[W][kPairRing];         // each wavefront's queue of in-cutoff pairs
-    __shared__ int32_t ticket;                  // round whose next-round tables a wavefront has taken on
-    __shared__ int64_t sh_state[4];       // N, moves done, error, error move
-    __shared__ double sh_u, sh_w;
-    __shared__ double sh_acc[2];
-    __shared__ int32_t sh_maxc;
+    __shared__ double lpi[kSpecPref], lpd[kSpecPref];   // the deciding wavefront's prefactors
+    // its statistics, lane k's sums over the moves it decided as move k of a round (counts as doubles, exact
+    // below 2^53)
+    enum { kAtt, kAcc = 3, kSumN = 6, kSumN2, kSumU, kSumW, kStencils, kCand, kEvals, kIncut, kStats };
+    __shared__ double acc_s[kStats][W];
+    __shared__ DrawRing<RING> dring;            // draws of moves m .. m + 2W - 1
+    __shared__ double pq[W][kSpecQueue];        // each wavefront's queue of in-cutoff pairs
     __shared__ int32_t ready[W];                // round whose evaluation wavefront w has published
-    __shared__ int64_t after_n[W];              // N, U and W after each move decided this round
-    __shared__ double after_u[W], after_w[W];
+    // the state after a round, by round parity (a wavefront may still read the last round's)
+    __shared__ int4 sh_state[2];                // N, moves decided, error
+    __shared__ double2 sh_acc[2];               // running acceptance of insertions and deletions
     const int bi = order ? order[blockIdx.x] : (int)blockIdx.x;
     const DevBox B = hot_copy(boxes[blockIdx.x]);
     const int tid = threadIdx.x;
@@ -111,24 +129,9 @@ __global__ __launch_bounds__(kWave* W) void k_chain_spec(const DevBox* __restric
     BoxState* st = B.st;
 
     if (ctr0 == GCMC_COUNTER_CONTINUE) ctr0 = (uint64_t)st->counter;
-    int64_t N = st->n;
-    double U = st->u_pair;
-    double Wvir = st->w_pair;
-    int32_t maxc = st->maxcount;
+    int32_t N = (int32_t)st->n;   // below 2^31
     int32_t err = st->error;
-    int64_t err_move = st->error_move;
-    const double tk = B.tailK[0];
-    const int cap = B.cap;
     const bool no_full = !(B.full[0] | B.full[1] | B.full[2]);
-    const int32_t spin_cap = wait_bound(B.wait_limit);
-    // statistics (wavefront 0 keeps them): attempts and acceptances per move type as separate
-    // doubles (a dynamically indexed array would live in scratch; exact below 2^53), folded in
-    // once per round
-    double att0 = 0.0, att1 = 0.0, att2 = 0.0, acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
-    // per-lane sums over the moves lane j decided (N, N^2, U + U_tail, W after move j of a round)
-    double sum_n = 0.0, sum_u = 0.0, sum_n2 = 0.0, sum_w = 0.0;
-    // per-lane sums over the moves lane j decided as move j of a round, added up at the end
-    int64_t stencils = 0, cand = 0, evals = 0, incut = 0;
     for (int t = tid; t < B.nstencil; t += blockDim.x) {
         const uint32_t pk = gload(B.stab + t);
         const int tx = pk & 0x3FF, ty = (pk >> 10) & 0x3FF, tz = pk >> 20;
@@ -136,369 +139,339 @@ __global__ __launch_bounds__(kWave* W) void k_chain_spec(const DevBox* __restric
         if (t < kOffs) offs[t] = ((tz - B.k[2]) * B.M[1] + (ty - B.k[1])) * B.M[0] + (tx - B.k[0]);
     }
     if (tid < W) ready[tid] = -1;
-    if (tid == 0) ticket = 0;
-    // draws of the first 2W moves and the prefactors of the first round (its buffer: 1)
+    // draws of the first 2W moves
     for (int t = tid; t < 8 * W; t += blockDim.x) draw_block(B, &dring, ctr0 + (uint64_t)(t >> 2), t & 3);
-    for (int t = tid; t < 8 * W; t += blockDim.x) spec_prefactor<W>(B, lp_ins[1], lp_del[1], N - 2 * W, t);
-    if (tid == 0) lp_base[1] = N - 2 * W;
     __syncthreads();
-    if (err == GCMC_OK && B.ns != 1) {
-        err = GCMC_ERR_UNSUPPORTED;
-        err_move = (int64_t)ctr0;
-    }
+    const bool wrong = err == GCMC_OK && B.ns != 1;
+    if (wrong) err = GCMC_ERR_UNSUPPORTED;
     int64_t m = 0;
     int32_t rnd = 0;                   // rounds begun
-    double a_ins = 0.5, a_del = 0.5;   // running acceptance of insertions and deletions
+    if (wv < W) {
+        // ================================================ evaluate move m + wv of every round
+        double a_ins = 0.5, a_del = 0.5;   // running acceptance of insertions and deletions
+        while (err == GCMC_OK && m < n_moves) {
+            rnd = rnd == INT32_MAX ? 1 : rnd + 1;   // round numbers stay positive (a flag starts at -1)
+            SpecRec* recs = recs_s[rnd & 1];
+            if (m + wv < n_moves) {
+                SpecKey key;
+                // is the pick at every N the move can meet (lane o: N - (W - 1) + o) the evaluated one? (found
+                // while the picked record is loaded)
+                const int32_t np = N - (W - 1) + lane;
+                uint64_t pm = 0;
+                auto early = [&](int type, double u2, double u7, int64_t idx) {
+                    pm = __ballot(lane < 2 * W - 1 && np >= 0 &&
+                                  (type == GCMC_MOVE_INSERT || spec_pick(u2, u7, np) == idx));
+                };
+                spec_eval<CR, NG, RING>(B, tab, offs, own[wv], pq[wv], &dring, ctr0 + (uint64_t)m, wv, N, no_full, a_ins,
+                                        a_del, &recs[wv], key, early);
+                if (lane == 0) recs[wv].pickmask = (uint32_t)pm;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                if (lane == 0) __hip_atomic_store(&ready[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            __syncthreads();   // commit stores done and visible; the new state published
+            const int4 after = sh_state[rnd & 1];
+            const double2 a = sh_acc[rnd & 1];
+            N = uni(after.x);
+            m += uni(after.y);
+            err = uni(after.z);
+            a_ins = a.x;
+            a_del = a.y;
+        }
+        return;
+    }
+    // ==================================================== decide and commit (wavefront W)
+    int64_t err_move = st->error_move;
+    if (wrong) err_move = (int64_t)ctr0;
+    double U = st->u_pair;
+    double Wvir = st->w_pair;
+    int32_t maxc = st->maxcount;
+    const double tk = B.tailK[0];
+    const int cap = B.cap;
+    const int32_t spin_cap = wait_bound(B.wait_limit);
+    const double side[3] = {B.L[0] / (double)B.M[0], B.L[1] / (double)B.M[1], B.L[2] / (double)B.M[2]};
+    double n_ins = 0.0, n_del = 0.0, y_ins = 0.0, y_del = 0.0;   // insertions and deletions, and those accepted
+    for (int t = lane; t < kStats * W; t += kWave) (&acc_s[0][0])[t] = 0.0;
+    int32_t lbase = N - kSpecPref / 2;
+    spec_prefactors(B.V, B.lambda3, lpi, lpd, lbase);
     while (err == GCMC_OK && m < n_moves) {
-        const int64_t base = N - W;
-        rnd = rnd == INT32_MAX ? 1 : rnd + 1;   // round numbers stay positive (a flag starts at -1)
-        // issue priority on each SIMD: the moves decided first evaluate first (the two
-        // wavefronts sharing a SIMD are w and w + 4 when W = 8); wavefront 0 raises its own
-        // for the commit
-        if (wv < (W + 1) / 2) __builtin_amdgcn_s_setprio(2);
-        else __builtin_amdgcn_s_setprio(1);
-        // the round's prefactor table (filled before the round began)
-        const int tb = rnd & 1;
-        const int64_t lbase = lp_base[tb];
-        const double* lpi = lp_ins[tb];
-        const double* lpd = lp_del[tb];
-        // ------------------------------------------------ the round's particle records (wavefront 0 commits with them)
-        double4 tv = make_double4(0, 0, 0, 0);
-        if (wv == 0 && lane < W && base + lane >= 0) tv = gload(B.pos + base + lane);
-        // ------------------------------------------------ evaluate W moves
-        if (m + wv < n_moves) {
-            SpecKey key;
-            // what the decision at every N the move can meet (within W - 1 of the round's N; lane o
-            // takes N - (W - 1) + o) needs before the evaluation ends: the pick still the evaluated
-            // one, the tail change and the prefactor -- computed while the picked record is loaded
-            const int64_t np = N - (W - 1) + lane;
-            const bool lane_n = lane < 2 * W - 1 && np >= 0;
-            bool pick_ok = false;
-            double dUt = 0.0, lpref = 0.0;
-            auto early = [&](int type, double u2, double u7, int64_t idx) {
-                if (lane_n) {
-                    pick_ok = type == GCMC_MOVE_INSERT || spec_pick(u2, u7, np) == idx;
-                    spec_arg_pre(type, np, lbase, lpi, lpd, tk, dUt, lpref);
-                }
-            };
-            spec_eval<CR, NG, 2 * W>(B, tab, offs, own[wv], pq[wv], &dring, ctr0 + (uint64_t)m, wv, N, no_full, a_ins,
-                                     a_del, &recs[wv], key, early);
-            // the Metropolis test (Eqs. 3-5) at each of those N -- the operations the commit would
-            // do, so the commit only reads the bit of its N
-            if (!(key.flags & 1)) {
-                bool acc = false;
-                if (lane_n) {
-                    const double arg = spec_arg_fin(B, key.type, key.dUp, dUt, lpref);
-                    const double dU = key.dUp + dUt;
-                    acc = dU == dU && key.lnA < arg;
-                }
-                const uint64_t pm = __ballot(pick_ok), am = __ballot(acc);
-                if (lane == 0) {
-                    recs[wv].pickmask = (uint32_t)pm;
-                    recs[wv].okmask = (uint32_t)am;
-                }
-            }
+        rnd = rnd == INT32_MAX ? 1 : rnd + 1;
+        const int32_t base = N - W;
+        const int kend = (n_moves - m) < W ? (int)(n_moves - m) : W;
+        const SpecRec* recs = recs_s[rnd & 1];
+        // ------------------------------------------ while the others evaluate
+        // the records of particles N - W .. N - 1; the draws of moves m + W .. m + 2W - 1 (the next round
+        // takes moves m + k .. m + k + W - 1 with 1 <= k <= W; the others are in the ring already); the
+        // prefactors, when N has drifted towards an end of their table
+        const bool has_top = lane < W && base + lane >= 0;
+        const double4 tv = gload(B.pos + (has_top ? base + lane : 0));
+        if (lane < 4 * W) spec_draws<RING>(&dring, ctr0 + (uint64_t)(m + W) + (uint64_t)(lane >> 2), B.seed, B.box_id, B.p_disp, lane & 3);
+        if (N < lbase + W || N > lbase + kSpecPref - 1 - W) {
+            lbase = N - kSpecPref / 2;
+            spec_prefactors(B.V, B.lambda3, lpi, lpd, lbase);
         }
-        if (wv != 0) {
-            // publish this move's record: wavefront 0 decides it as soon as its turn comes, while
-            // slower wavefronts still evaluate.  A commit may then store to memory that a later
-            // move of the round is still reading; such a move fails the in-order check (its
-            // stencil holds a modified cell, or its particle was touched) and is discarded.
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-            if (lane == 0) __hip_atomic_store(&ready[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            __builtin_amdgcn_s_setprio(0);
-            // the first wavefront to publish prepares the next round's tables while the others
-            // still evaluate: the draws of moves m + W .. m + 2W - 1 (the next round takes moves
-            // m + k .. m + k + W - 1 with 1 <= k <= W; the others are in the ring already) and
-            // the prefactors for every N the next round can reach (within 2W - 1 of this
-            // round's N).  The barrier at the end of the round makes them visible.
-            int32_t prev = 0;
-            if (lane == 0) prev = __hip_atomic_exchange(&ticket, rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (__builtin_amdgcn_readfirstlane(prev) != rnd) {
-                if (lane < 4 * W)
-                    draw_block(B, &dring, ctr0 + (uint64_t)(m + W) + (uint64_t)(lane >> 2), lane & 3);
-                for (int t = lane; t < 8 * W; t += kWave) spec_prefactor<W>(B, lp_ins[tb ^ 1], lp_del[tb ^ 1], N - 2 * W, t);
-                if (lane == 0) lp_base[tb ^ 1] = N - 2 * W;
-            }
-        }
-        // ------------------------------------------------ in-order commit
-        if (wv == 0) {
-            __builtin_amdgcn_s_setprio(3);
-            if (lane < W && base + lane >= 0) top[lane] = tv;
-            // this wavefront's own table and record writes, seen by all of its lanes
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
-            const int64_t n_round = N;   // N at the round's start: the masks' reference
-            int32_t modx = 0, mody = 0, modz = 0, touched = -1;   // lane-held lists of this round
-            int nmod = 0, ntouch = 0;
-            uint64_t okbits = 0;   // bit k: move k of the round accepted
-            int k = 0;
-            const int kend = (n_moves - m) < W ? (int)(n_moves - m) : W;
-            for (; k < kend; ++k) {
-                const uint64_t ctr = ctr0 + (uint64_t)(m + k);
-                if (k > 0) {
-                    // wait for wavefront k's evaluation (bounded: it publishes without waiting on anything)
-                    int32_t spins = 0;
-                    while (uni(__hip_atomic_load(&ready[k], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) != rnd) {
-                        __builtin_amdgcn_s_sleep(1);
-                        if (++spins > spin_cap) break;
-                    }
-                    if (spins > spin_cap) {
-                        err = GCMC_ERR_INTERNAL;
-                        err_move = (int64_t)ctr;
-                        break;
-                    }
-                }
-                const SpecRec& R = recs[k];
-                // what every decision reads, loaded together (one LDS round trip, not one per test)
-                const int32_t r_type = R.type, r_flags = R.flags;
-                const uint32_t r_pm = R.pickmask, r_om = R.okmask;
-                const int64_t r_idx = R.idx;
-                int32_t cc[3] = {R.c0[0], R.c0[1], R.c0[2]};
-                int32_t cn[3] = {R.c1[0], R.c1[1], R.c1[2]};
-                asm volatile("" ::"v"(r_type), "v"(r_flags), "v"(r_pm), "v"(r_om), "v"(r_idx), "v"(cc[0]), "v"(cc[1]),
-                             "v"(cc[2]), "v"(cn[0]), "v"(cn[1]), "v"(cn[2]));
-                const int type = __builtin_amdgcn_readfirstlane(r_type);
-                // the empty-box rejection holds only while the box is still empty
-                if (r_flags & 1) {
-                    if (N != 0) break;
-                    if (lane == 0) {
-                        after_n[k] = N;
-                        after_u[k] = U;
-                        after_w[k] = Wvir;
-                    }
-                    continue;
-                }
-                const int64_t idx = r_idx;
-                const int o = (int)(N - n_round) + (W - 1);   // 0 .. 2W - 2 (N moved by at most k < W)
-                if (type != GCMC_MOVE_INSERT) {
-                    if (((r_pm >> o) & 1u) == 0) break;
-                    if (__ballot(lane < ntouch && touched == (int32_t)idx) != 0) break;
-                }
-                // a cell changed by an earlier commit of this round inside one of its stencils
-                bool hit = false;
-                if (lane < nmod)
-                    hit = in_stencil(B, modx, mody, modz, cc) ||
-                          (type == GCMC_MOVE_DISPLACE && in_stencil(B, modx, mody, modz, cn));
-                if (__ballot(hit) != 0) break;
-                // ---- decide at the current N
-                const bool is_disp = type == GCMC_MOVE_DISPLACE, is_ins = type == GCMC_MOVE_INSERT;
-                const bool ok = ((r_om >> o) & 1u) != 0;
-                const int two = R.two;
-                const int32_t cnt0 = R.cnt0, cnt1 = R.cnt1;
-                if (ok) {
-                    int e = GCMC_OK;
-                    if (is_ins) {
-                        if (N >= B.max_n) e = GCMC_ERR_CAPACITY;
-                        else if (cnt0 >= cap) e = GCMC_ERR_CELL_OVERFLOW;
-                    } else if (is_disp && two) {
-                        if (cnt1 >= cap) e = GCMC_ERR_CELL_OVERFLOW;
-                    }
-                    if (e != GCMC_OK) {
-                        err = e;
-                        err_move = (int64_t)ctr;
-                        break;
-                    }
-                    // slot and cell indices fit 32 bits (cells x capacity < 2^31 for this kernel)
-                    const int32_t loc = meta_low(R.rec.w);
-                    const int32_t c0 = R.cl0, c1 = R.cl1;
-                    const bool removes = (type == GCMC_MOVE_DELETE) || (is_disp && two);
-                    const int32_t last = c0 * cap + cnt0 - 1;
-                    const bool swap = removes && loc != last;
-                    const int32_t id_last = swap ? meta_low(R.elast.w) : -1;
-                    // the record of particle N-1 as of now (kept as scalars so that it stays in registers)
-                    double rlx = 0.0, rly = 0.0, rlz = 0.0, rlw = 0.0;
-                    if (type == GCMC_MOVE_DELETE) {
-                        const double4 v = top[N - 1 - base];
-                        rlx = v.x; rly = v.y; rlz = v.z; rlw = v.w;
-                    }
-                    if (lane == 0) {
-                        // every store to pos[j] for j in the round's window is mirrored in top[]
-                        if (swap) {
-                            gstore(B.ent + loc, R.elast);
-                            const double w = pack_meta(meta_species(R.elast.w), (int32_t)loc);
-                            gstore_w(B.pos + id_last, w);
-                            const int64_t t = (int64_t)id_last - base;
-                            if (t >= 0 && t < 2 * W) top[t].w = w;
-                        }
-                        if (removes) gstore(B.count + c0, cnt0 - 1);
-                        double4 nr;
-                        int64_t j = -1;
-                        if (is_disp) {
-                            if (!two) {
-                                gstore(B.ent + loc, make_double4(R.p1[0], R.p1[1], R.p1[2], pack_meta(0, (int32_t)idx)));
-                                nr = make_double4(R.p1[0], R.p1[1], R.p1[2], R.rec.w);
-                            } else {
-                                const int32_t nl = c1 * cap + cnt1;
-                                gstore(B.ent + nl, make_double4(R.p1[0], R.p1[1], R.p1[2], pack_meta(0, (int32_t)idx)));
-                                gstore(B.count + c1, cnt1 + 1);
-                                nr = make_double4(R.p1[0], R.p1[1], R.p1[2], pack_meta(0, (int32_t)nl));
-                            }
-                            j = idx;
-                        } else if (is_ins) {
-                            const int32_t nl = c0 * cap + cnt0;
-                            gstore(B.ent + nl, make_double4(R.p0[0], R.p0[1], R.p0[2], pack_meta(0, (int32_t)N)));
-                            gstore(B.count + c0, cnt0 + 1);
-                            nr = make_double4(R.p0[0], R.p0[1], R.p0[2], pack_meta(0, (int32_t)nl));
-                            j = N;
-                        } else if (idx != N - 1) {
-                            if (id_last == (int32_t)(N - 1)) rlw = pack_meta(meta_species(rlw), (int32_t)loc);
-                            nr = make_double4(rlx, rly, rlz, rlw);
-                            gstore_w(B.ent + meta_low(rlw), pack_meta(meta_species(rlw), (int32_t)idx));
-                            j = idx;
-                        }
-                        if (j >= 0) {
-                            gstore(B.pos + j, nr);
-                            const int64_t t = j - base;
-                            if (t >= 0 && t < 2 * W) top[t] = nr;
-                        }
-                    }
-                    // what later moves of this round must not have read
-                    if (lane == nmod) {
-                        modx = R.c0[0]; mody = R.c0[1]; modz = R.c0[2];
-                    }
-                    nmod += 1;
-                    // a deletion that frees an inner index rewrites the id of particle N-1 in that
-                    // particle's cell: that cell counts as modified too (a later removal from it
-                    // would otherwise copy the stale id with the cell's last entry)
-                    if (type == GCMC_MOVE_DELETE && idx != N - 1 && id_last != (int32_t)(N - 1)) {
-                        // its cell from its position (every record lives in the cell of its position)
-                        const int32_t rx = spec_axis_cell(rlx, B.invS[0], B.M[0]);
-                        const int32_t ry = spec_axis_cell(rly, B.invS[1], B.M[1]);
-                        const int32_t rz = spec_axis_cell(rlz, B.invS[2], B.M[2]);
-                        if ((rz * B.M[1] + ry) * B.M[0] + rx != (int32_t)c0) {
-                            if (lane == nmod) {
-                                modx = rx;
-                                mody = ry;
-                                modz = rz;
-                            }
-                            nmod += 1;
-                        }
-                    }
-                    if (is_disp && two) {
-                        if (lane == nmod) {
-                            modx = R.c1[0]; mody = R.c1[1]; modz = R.c1[2];
-                        }
-                        nmod += 1;
-                    }
-                    if (lane == ntouch) touched = is_ins ? (int32_t)N : (int32_t)idx;
-                    ntouch += 1;
-                    if (swap) {
-                        if (lane == ntouch) touched = id_last;
-                        ntouch += 1;
-                    }
-                    if (type == GCMC_MOVE_DELETE) {
-                        if (lane == ntouch) touched = (int32_t)(N - 1);
-                        ntouch += 1;
-                    }
-                    if (is_disp && two && cnt1 + 1 > maxc) maxc = cnt1 + 1;
-                    if (is_ins && cnt0 + 1 > maxc) maxc = cnt0 + 1;
-                    okbits |= 1ull << k;
-                    N += is_ins ? 1 : (type == GCMC_MOVE_DELETE ? -1 : 0);
-                    U += R.dUp;
-                    Wvir += R.dWp;
-                }
-                if (lane == 0) {
-                    after_n[k] = N;
-                    after_u[k] = U;
-                    after_w[k] = Wvir;
-                }
-                if (nmod > kWave - 2 || ntouch > kWave - 3) {
-                    ++k;
+        if (has_top) top[lane] = tv;
+        // ------------------------------------------ the evaluations
+        int kw = kend;   // moves whose evaluation arrived
+        if (spin_cap < 0) {
+            kw = 0;
+        } else {
+            int32_t spins = 0;
+            for (;;) {
+                const bool wait = lane < kend && __hip_atomic_load(&ready[lane < W ? lane : 0], __ATOMIC_ACQUIRE,
+                                                                   __HIP_MEMORY_SCOPE_WORKGROUP) != rnd;
+                const uint64_t late = __ballot(wait);
+                if (late == 0) break;
+                __builtin_amdgcn_s_sleep(1);
+                if (++spins > spin_cap) {
+                    kw = (int)__builtin_ctzll(late);
                     break;
                 }
             }
-            // statistics of the k moves decided this round: lane j takes move j (the values
-            // lane 0 wrote above, seen by every lane of this wavefront)
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-            {
-                const bool mine = lane < k;
-                const SpecRec& S = recs[mine ? lane : 0];
-                const int t = mine ? S.type : -1;
-                const bool a = ((okbits >> lane) & 1) != 0;
-                att0 += (double)__builtin_popcountll(__ballot(t == 0));
-                att1 += (double)__builtin_popcountll(__ballot(t == 1));
-                att2 += (double)__builtin_popcountll(__ballot(t == 2));
-                acc0 += (double)__builtin_popcountll(__ballot(a && t == 0));
-                acc1 += (double)__builtin_popcountll(__ballot(a && t == 1));
-                acc2 += (double)__builtin_popcountll(__ballot(a && t == 2));
-                if (mine && !(S.flags & 1)) {
-                    stencils += S.two ? 2 : 1;
-                    cand += S.cand;
-                    evals += S.evals;
-                    incut += S.incut;
+        }
+        __builtin_amdgcn_s_setprio(3);
+        wave_lds_sync();
+        const bool mine = lane < kw;
+        const SpecRec& R = recs[mine ? lane : 0];
+        const int32_t type = mine ? R.type : GCMC_MOVE_INSERT;
+        const bool empty = mine && (R.flags & 1) != 0;   // a displacement or deletion in an empty box
+        const uint32_t pick = R.pickmask;
+        const int32_t idx = mine && !empty ? (int32_t)R.idx : -1;
+        const int32_t cl0 = R.cl0, cl1 = R.cl1;
+        const double lnA = R.lnA;
+        double dUp = mine && !empty ? R.dUp : 0.0, dWp = mine && !empty ? R.dWp : 0.0;
+        const bool disp = type == GCMC_MOVE_DISPLACE, ins = type == GCMC_MOVE_INSERT;
+        const double p0x = R.p0[0], p0y = R.p0[1], p0z = R.p0[2];   // old, inserted or deleted position
+        const double p1x = R.p1[0], p1y = R.p1[1], p1z = R.p1[2];   // a displacement's new position
+        const int32_t two = mine ? R.two : 0;
+        const int32_t cnt0 = R.cnt0, cnt1 = R.cnt1;                  // occupancies of its centre cells
+        const int32_t loc = meta_low(R.rec.w);                       // slot of its particle's record
+        const int32_t id_end = meta_low(R.elast.w);                  // particle of its first cell's last entry
+        int32_t r_in = R.incut;
+        const int32_t n_round = N;
+        bool stale = false;
+        double dUt = 0.0, arg = 0.0;
+        double aft_n = 0.0, aft_u = 0.0, aft_w = 0.0;
+        uint64_t accbits = 0;
+        int k = 0;
+        while (k < kw) {
+            const uint64_t todo = ((1ull << kw) - 1ull) & ~((1ull << k) - 1ull);
+            bool ok = false, bad = false;
+            if (mine && lane >= k) {
+                if (empty) {
+                    bad = N != 0;   // the empty-box rejection holds only while the box is still empty
+                } else {
+                    bad = stale || (!ins && ((pick >> (N - n_round + W - 1)) & 1u) == 0);
+                    const double lpref = disp ? 0.0 : (ins ? lpi[N - lbase] : lpd[N - lbase]);
+                    dUt = disp ? 0.0 : tk * (ins ? (2.0 * (double)N + 1.0) : (1.0 - 2.0 * (double)N));
+                    arg = spec_arg_fin(B, type, dUp, dUt, lpref);
+                    const double dU = dUp + dUt;
+                    ok = dU == dU && lnA < arg;
                 }
-                if (mine) {
-                    const double n = (double)after_n[lane];
-                    sum_n += n;
-                    sum_n2 += n * n;
-                    sum_u += after_u[lane] + tk * n * n;
-                    sum_w += after_w[lane];
+            }
+            const uint64_t bads = __ballot(bad) & todo;
+            const uint64_t stop = bads | (__ballot(ok) & todo);
+            const int f = stop ? (int)__builtin_ctzll(stop) : kw;
+            if (lane >= k && lane < f) {   // rejected: the state after them is the current one
+                aft_n = (double)N;
+                aft_u = U;
+                aft_w = Wvir;
+            }
+            k = f;
+            if (f == kw || ((bads >> f) & 1ull)) break;
+            // ---------------------------------- move f is accepted: commit it (lane f holds it)
+            auto of = [&](int32_t v) { return (int32_t)__builtin_amdgcn_readlane(v, f); };
+            const int32_t tf = of(type), fi = of(idx), ftwo = of(two), c0 = of(cl0), c1 = of(cl1);
+            const bool fdisp = tf == GCMC_MOVE_DISPLACE, fins = tf == GCMC_MOVE_INSERT, fdel = tf == GCMC_MOVE_DELETE;
+            const int32_t fcnt0 = of(cnt0), fcnt1 = of(cnt1), floc = of(loc);
+            int e = GCMC_OK;
+            if (fins) {
+                if (N >= B.max_n) e = GCMC_ERR_CAPACITY;
+                else if (fcnt0 >= cap) e = GCMC_ERR_CELL_OVERFLOW;
+            } else if (fdisp && ftwo) {
+                if (fcnt1 >= cap) e = GCMC_ERR_CELL_OVERFLOW;
+            }
+            if (e != GCMC_OK) {
+                err = e;
+                err_move = (int64_t)(ctr0 + (uint64_t)(m + f));
+                break;
+            }
+            // slot and cell indices fit 32 bits (cells x capacity < 2^31 for this kernel)
+            const bool removes = fdel || (fdisp && ftwo);
+            const bool swap = removes && floc != c0 * cap + fcnt0 - 1;
+            const int32_t id_last = swap ? of(id_end) : -1;
+            // the record of particle N - 1 as of now, and its cell when a deletion gives it another id
+            double4 rl = make_double4(0.0, 0.0, 0.0, 0.0);
+            int32_t c2 = c0;
+            if (fdel && fi != N - 1) {
+                rl = top[N - 1 - base];
+                if (id_last != N - 1) c2 = uni((int32_t)cell_of_point(B, rl.x, rl.y, rl.z));
+            }
+            if (lane == f) {
+                // every store to pos[j] for j in the round's window is mirrored in top[]
+                if (swap) {
+                    const double4 el = R.elast;
+                    gstore(B.ent + loc, el);
+                    const double w = pack_meta(meta_species(el.w), loc);
+                    gstore_w(B.pos + id_end, w);
+                    const int32_t t = id_end - base;
+                    if (t >= 0 && t < 2 * W) top[t].w = w;
                 }
-                // the per-move log, rebuilt from the evaluation, the decision and N after the move
-                if (trace && mine) {
-                    gcmc_log r;
-                    r.type = t;
-                    if (S.flags & 1) {
-                        r.index = -1; r.accepted = 0; r.flags = 1;
-                        r.dU_pair = 0.0; r.dU_tail = 0.0; r.x = r.y = r.z = 0.0; r.arg = 0.0; r.dW_pair = 0.0;
-                    } else {
-                        const int64_t dn = a ? (t == GCMC_MOVE_INSERT ? 1 : (t == GCMC_MOVE_DELETE ? -1 : 0)) : 0;
-                        const int64_t n_before = after_n[lane] - dn;
-                        double dUt;
-                        r.arg = spec_arg(B, t, S.dUp, n_before, lbase, lpi, lpd, tk, dUt);
-                        r.index = t == GCMC_MOVE_INSERT ? (int32_t)n_before : (int32_t)S.idx;
-                        r.accepted = a ? 1 : 0;
-                        r.flags = 0;
-                        r.dU_pair = S.dUp;
-                        r.dU_tail = dUt;
-                        const bool dsp = t == GCMC_MOVE_DISPLACE;
-                        r.x = dsp ? S.p1[0] : S.p0[0];
-                        r.y = dsp ? S.p1[1] : S.p0[1];
-                        r.z = dsp ? S.p1[2] : S.p0[2];
-                        r.dW_pair = S.dWp;
+                if (removes) gstore(B.count + cl0, cnt0 - 1);
+                double4 nr;
+                int32_t j = -1;
+                if (fdel) {
+                    if (fi != N - 1) {
+                        if (id_last == N - 1) rl.w = pack_meta(meta_species(rl.w), loc);
+                        nr = rl;
+                        gstore_w(B.ent + meta_low(rl.w), pack_meta(meta_species(rl.w), fi));
+                        j = fi;
                     }
-                    trace[(size_t)bi * n_moves + m + lane] = r;
+                } else {
+                    // a displacement inside its cell keeps its slot; else the slot after the cell's last
+                    const bool stay = fdisp && !ftwo;
+                    const int32_t cn = fdisp ? cl1 : cl0, nn = fdisp ? cnt1 : cnt0;
+                    const int32_t slot = stay ? loc : cn * cap + nn;
+                    j = fins ? N : fi;
+                    const double x = fdisp ? p1x : p0x, y = fdisp ? p1y : p0y, z = fdisp ? p1z : p0z;
+                    gstore(B.ent + slot, make_double4(x, y, z, pack_meta(0, j)));
+                    if (!stay) gstore(B.count + cn, nn + 1);
+                    nr = make_double4(x, y, z, pack_meta(0, slot));
+                }
+                if (j >= 0) {
+                    gstore(B.pos + j, nr);
+                    const int32_t t = j - base;
+                    if (t >= 0 && t < 2 * W) top[t] = nr;
                 }
             }
-            if (lane == 0) {
-                sh_state[0] = N;
-                sh_state[1] = m + k;
-                sh_state[2] = err;
-                sh_state[3] = err_move;
-                sh_u = U;
-                sh_w = Wvir;
-                sh_maxc = maxc;
-                sh_acc[0] = (acc1 + 1.0) / (att1 + 2.0);
-                sh_acc[1] = (acc2 + 1.0) / (att2 + 2.0);
+            if (fdisp && ftwo && fcnt1 + 1 > maxc) maxc = fcnt1 + 1;
+            if (fins && fcnt0 + 1 > maxc) maxc = fcnt0 + 1;
+            const double fax = read_lane(p0x, f), fay = read_lane(p0y, f), faz = read_lane(p0z, f);
+            const double fbx = fdisp ? read_lane(p1x, f) : fax, fby = fdisp ? read_lane(p1y, f) : fay,
+                         fbz = fdisp ? read_lane(p1z, f) : faz;
+            // ---------------------------------- what it means for the later moves of the round
+            if (mine && lane > f && !empty) {
+                // its slots, counts or record: the particle it touched, or one of its centre cells changed
+                stale = stale || idx == (fins ? N : fi) || (swap && idx == id_last) || (fdel && idx == N - 1) ||
+                        cl0 == c0 || cl0 == c2 || (fdisp && ftwo && cl0 == c1) ||
+                        (two && (cl1 == c0 || cl1 == c2 || (fdisp && ftwo && cl1 == c1)));
+                // pairs with the position taken away (a) and added (b): new position minus old one; one at
+                // a time where the four would hold a hundred registers at once
+                const double nx = disp ? p1x : p0x, ny = disp ? p1y : p0y, nz = disp ? p1z : p0z;
+                const bool has_new = disp || ins, has_old = !ins;
+                const double out = B.rc2;   // outside the cutoff: no term
+                double r_nb = out, r_ob = out, r_na = out, r_oa = out;
+                if (!fdel) {
+                    if (has_new) r_nb = spec_r2(B, nx, ny, nz, fbx, fby, fbz);
+                    if (has_old) r_ob = spec_r2(B, p0x, p0y, p0z, fbx, fby, fbz);
+                }
+                if (!fins) {
+                    if (has_new) r_na = spec_r2(B, nx, ny, nz, fax, fay, faz);
+                    if (has_old) r_oa = spec_r2(B, p0x, p0y, p0z, fax, fay, faz);
+                }
+                auto term = [&](double r2, double sign, int32_t pairs) {
+                    if (r2 < out) {
+                        double w = 0.0;
+                        const double u = lj_uw_from_r2(r2, B.rc2, B.eps4[0], B.sig2[0], w);
+                        dUp += sign * u;
+                        dWp += sign * w;
+                        r_in += pairs;
+                    }
+                };
+                term(r_nb, 1.0, 1);
+                term(r_ob, -1.0, 1);
+                term(r_na, -1.0, -1);
+                term(r_oa, 1.0, -1);
             }
+            N += fins ? 1 : (fdel ? -1 : 0);
+            U += read_lane(dUp, f);
+            Wvir += read_lane(dWp, f);
+            if (lane == f) {
+                aft_n = (double)N;
+                aft_u = U;
+                aft_w = Wvir;
+            }
+            accbits |= 1ull << f;
+            k = f + 1;
+            wave_lds_sync();   // the mirror's new records, seen by every lane
+        }
+        if (err == GCMC_OK && k == kw && kw < kend) {
+            err = GCMC_ERR_INTERNAL;   // move kw's evaluation did not arrive
+            err_move = (int64_t)(ctr0 + (uint64_t)(m + kw));
+        }
+        const bool done = lane < k;
+        const bool acc = done && ((accbits >> lane) & 1ull) != 0;
+        n_ins += (double)__builtin_popcountll(__ballot(done && ins));
+        y_ins += (double)__builtin_popcountll(__ballot(acc && ins));
+        n_del += (double)__builtin_popcountll(__ballot(done && type == GCMC_MOVE_DELETE));
+        y_del += (double)__builtin_popcountll(__ballot(acc && type == GCMC_MOVE_DELETE));
+        if (lane == 0) {
+            sh_state[rnd & 1] = make_int4(N, k, err, 0);
+            sh_acc[rnd & 1] = make_double2((y_ins + 1.0) / (n_ins + 2.0), (y_del + 1.0) / (n_del + 2.0));
         }
         __builtin_amdgcn_s_setprio(0);
         __syncthreads();   // commit stores done and visible; the new state published
-        N = sh_state[0];
-        m = sh_state[1];
-        err = (int32_t)sh_state[2];
-        err_move = sh_state[3];
-        U = sh_u;
-        Wvir = sh_w;
-        maxc = sh_maxc;
-        a_ins = sh_acc[0];
-        a_del = sh_acc[1];
-    }
-    if (wv == 0) {
-        for (int off = 32; off >= 1; off >>= 1) {
-            stencils += __shfl_xor(stencils, off, kWave);
-            cand += __shfl_xor(cand, off, kWave);
-            evals += __shfl_xor(evals, off, kWave);
-            incut += __shfl_xor(incut, off, kWave);
+        // ------------------------------------------ statistics and log of the k moves decided, lane by lane
+        // (the next round's evaluations run meanwhile).  The candidates of a move are those of the state
+        // it was decided on: each earlier accepted move of the round that took a particle out of, or put
+        // one into, one of its stencils changes their number.
+        int32_t r_cand = R.cand;
+        for (uint64_t left = accbits & ((1ull << k) - 1ull); left; left &= left - 1ull) {
+            const int f = (int)__builtin_ctzll(left);
+            const int32_t tf = __builtin_amdgcn_readlane(type, f), ftwo = __builtin_amdgcn_readlane(two, f);
+            if (tf == GCMC_MOVE_DISPLACE && !ftwo) continue;   // stays in its cell
+            const SpecRec& F = recs[f];
+            const int32_t* a = F.c0;                                  // the cell a particle left
+            const int32_t* b = tf == GCMC_MOVE_INSERT ? F.c0 : F.c1;   // the one it entered
+            if (lane > f && done && !empty) {
+#pragma unroll 1
+                for (int q = 0; q < 4; ++q) {
+                    const bool gone = q < 2, second = (q & 1) != 0;
+                    if ((gone ? tf == GCMC_MOVE_INSERT : tf == GCMC_MOVE_DELETE) || (second && !two)) continue;
+                    if (kept_in_stencil(B, side, gone ? a : b, second ? R.c1 : R.c0)) r_cand += gone ? -1 : 1;
+                }
+            }
         }
-        sum_n = wave_sum_vec(sum_n);
-        sum_n2 = wave_sum_vec(sum_n2);
-        sum_u = wave_sum_vec(sum_u);
-        sum_w = wave_sum_vec(sum_w);
+        if (done) {
+            auto add = [&](int what, double v) { acc_s[what][lane] += v; };
+            add(kAtt + type, 1.0);
+            if (acc) add(kAcc + type, 1.0);
+            add(kSumN, aft_n);
+            add(kSumN2, aft_n * aft_n);
+            add(kSumU, aft_u + tk * aft_n * aft_n);
+            add(kSumW, aft_w);
+            if (!empty) {
+                add(kStencils, two ? 2.0 : 1.0);
+                add(kCand, (double)r_cand);
+                add(kEvals, (double)(disp && !two ? 2 * r_cand : r_cand));
+                add(kIncut, (double)r_in);
+            }
+            if (trace) {
+                gcmc_log r;
+                const double dn = acc ? (ins ? 1.0 : (disp ? 0.0 : -1.0)) : 0.0;
+                r.type = type;
+                r.index = empty ? -1 : (ins ? (int32_t)(aft_n - dn) : idx);
+                r.accepted = acc ? 1 : 0;
+                r.flags = empty ? 1 : 0;
+                r.dU_pair = dUp;
+                r.dU_tail = dUt;
+                r.x = empty ? 0.0 : (disp ? p1x : p0x);
+                r.y = empty ? 0.0 : (disp ? p1y : p0y);
+                r.z = empty ? 0.0 : (disp ? p1z : p0z);
+                r.arg = arg;
+                r.dW_pair = dWp;
+                trace[(size_t)bi * n_moves + m + lane] = r;
+            }
+        }
+        m += k;
     }
-    if (tid == 0) {
+    wave_lds_sync();
+    // sums over the moves of a round in a fixed order
+    auto total = [&](int what) {
+        double v = 0.0;
+        for (int j = 0; j < W; ++j) v += acc_s[what][j];
+        return v;
+    };
+    if (lane == 0) {
         st->n = N;
         st->u_pair = U;
         st->w_pair = Wvir;
@@ -511,13 +484,16 @@ __global__ __launch_bounds__(kWave* W) void k_chain_spec(const DevBox* __restric
         }
         ChainSums L;
         L.moves = m;
-        L.att[0] = (int64_t)att0; L.att[1] = (int64_t)att1; L.att[2] = (int64_t)att2;
-        L.acc[0] = (int64_t)acc0; L.acc[1] = (int64_t)acc1; L.acc[2] = (int64_t)acc2;
-        L.sum_n = sum_n;
-        L.sum_n2 = sum_n2;
-        L.sum_u = sum_u;
-        L.sum_w = sum_w;
-        finish_launch(B, st, L, N, U, Wvir, stencils, cand, evals, incut, stats ? stats + bi : nullptr);
+        for (int t = 0; t < 3; ++t) {
+            L.att[t] = (int64_t)total(kAtt + t);
+            L.acc[t] = (int64_t)total(kAcc + t);
+        }
+        L.sum_n = total(kSumN);
+        L.sum_n2 = total(kSumN2);
+        L.sum_u = total(kSumU);
+        L.sum_w = total(kSumW);
+        finish_launch(B, st, L, N, U, Wvir, (int64_t)total(kStencils), (int64_t)total(kCand), (int64_t)total(kEvals),
+                      (int64_t)total(kIncut), stats ? stats + bi : nullptr);
     }
 }
 
@@ -525,24 +501,30 @@ using spec_fn = void (*)(const DevBox*, const int32_t*, int64_t, uint64_t, gcmc_
 
 struct SpecCfg {
     int key;   // the waves value of gcmc_box_set_launch that selects it
-    int w;
+    int w;     // moves evaluated at once (the workgroup has one wavefront more)
     int ng;    // groups of 64 stencil cells of the microcell path, 0 for the 32-cell path
     spec_fn f;
 };
 
+// waves = 2 and 8: that many moves at once and the deciding wavefront beside them.  waves =
+// 4: three moves and the deciding one, so that a compute unit holds two such boxes or
+// one beside an LDS-held box (five wavefronts of 160 registers put two on the first
+// SIMD, and a batch of 512 boxes then ran in two rounds: 3.51 ms per 1,000 moves, 2.55
+// with four wavefronts).  waves = 16: 15 moves, 16 wavefronts being a workgroup's most.
+// Seven moves for waves = 8: the slab's 10,000 moves take 11.3 ms against 10.4 with eight.
 static const SpecCfg kSpecCfgs[] = {
     {2, 2, 0, k_chain_spec<2, 8, 0>},
-    {4, 4, 0, k_chain_spec<4, 8, 0>},
+    {4, 3, 0, k_chain_spec<3, 8, 0>},
     {8, 8, 0, k_chain_spec<8, 8, 0>},
-    {16, 16, 0, k_chain_spec<16, 4, 0>},
+    {16, 15, 0, k_chain_spec<15, 4, 0>},
     {2, 2, kSpecGroupsSmall, k_chain_spec<2, 8, kSpecGroupsSmall>},
-    {4, 4, kSpecGroupsSmall, k_chain_spec<4, 8, kSpecGroupsSmall>},
+    {4, 3, kSpecGroupsSmall, k_chain_spec<3, 8, kSpecGroupsSmall>},
     {8, 8, kSpecGroupsSmall, k_chain_spec<8, 8, kSpecGroupsSmall>},
-    {16, 16, kSpecGroupsSmall, k_chain_spec<16, 4, kSpecGroupsSmall>},
+    {16, 15, kSpecGroupsSmall, k_chain_spec<15, 4, kSpecGroupsSmall>},
     {2, 2, kSpecGroups, k_chain_spec<2, 8, kSpecGroups>},
-    {4, 4, kSpecGroups, k_chain_spec<4, 8, kSpecGroups>},
+    {4, 3, kSpecGroups, k_chain_spec<3, 8, kSpecGroups>},
     {8, 8, kSpecGroups, k_chain_spec<8, 8, kSpecGroups>},
-    {16, 16, kSpecGroups, k_chain_spec<16, 4, kSpecGroups>},
+    {16, 15, kSpecGroups, k_chain_spec<15, 4, kSpecGroups>},
 };
 
 // Groups of 64 cells the box's stencils need: 0 (the 32-cell path) for
@@ -572,7 +554,7 @@ int launch_chain_spec(const DevBox* d_boxes, const int32_t* d_order, int n_boxes
                       uint64_t ctr0, gcmc_stats* stats, gcmc_log* log, hipStream_t s, int ng) {
     for (const SpecCfg& c : kSpecCfgs) {
         if (c.key == waves && c.ng == ng) {
-            hipLaunchKernelGGL(c.f, dim3(n_boxes), dim3(kWave * c.w), 0, s, d_boxes, d_order, n_moves, ctr0, stats,
+            hipLaunchKernelGGL(c.f, dim3(n_boxes), dim3(kWave * (c.w + 1)), 0, s, d_boxes, d_order, n_moves, ctr0, stats,
                                log);
             return 0;
         }

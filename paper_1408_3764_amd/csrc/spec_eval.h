@@ -1,46 +1,32 @@
 // Evaluation of one chain move against the current state by one wavefront,
 // shared by the speculative kernels (rounds of W moves, and the pipeline of a
-// committer and evaluators).  The wavefront computes the Philox draws of the
-// moves that precede its move and are not yet decided (lane 4j + b: block b
-// of the j-th of them), counts the insertions (I) and deletions (D) among them
-// (N at the move's decision lies in [N - D, N + I]), and picks at the N
-// expected from the chain's running acceptance rates; then it loads the
-// counters of its stencil cells (one lane per cell), prefix-sums them, maps
-// each flattened candidate to its cell through an owner table in LDS, loads
-// exactly the candidates' records and reduces the pair sums.
-//
-// Stencils of more than 32 cells (microcells smaller than the cutoff, whose
-// stencils of 2k+1 cells per axis are pruned of the cells beyond it) take a
-// second path: the cells are loaded in groups of 64, one lane per cell (all
-// groups' counters in one memory round trip), prefix-summed across the
-// groups, and the flattened candidates' record indices are written to an LDS
-// table that is filled and consumed in windows, so a move may have any number
-// of candidates.
-//
-// Only about one candidate in seven lies inside the cutoff, and a wavefront
-// executes the Lennard-Jones arithmetic whenever one of its lanes needs it.
-// So the candidate pass only computes squared distances; the in-cutoff ones
-// are queued in a per-wavefront ring in LDS (the sign bit marks the second
-// position of a displacement) and the pair energies and virials are
-// evaluated 64 at a time, one per lane.
+// committer and evaluators).  The wavefront counts the insertions (I) and
+// deletions (D) among the moves that precede its move and are not yet decided (N
+// at the move's decision lies in [N - D, N + I]), and picks at the N expected
+// from the chain's running acceptance rates; spec_sums then forms the pair sums
+// over the stencils of the move's position(s).
 //
 // The draws (move type, pick, position, ln A) come either from a ring of
-// draws in LDS that the round kernel fills once per round for the moves it may
-// take next, or are computed here (the pipelined kernel).
+// draws in LDS that the round kernel fills for the moves it may take next, or are
+// computed here (the pipelined kernel).
 #pragma once
+#include <type_traits>
+
+#include "cell_pass.h"
 #include "trial.h"
 
 namespace gcmc {
 
-constexpr int kSpecOwn = 8192;       // flattened candidates per wavefront (owner table bytes)
-constexpr int kSpecRecWin = kSpecOwn / 4;   // record indices per window of the microcell path (same bytes)
+constexpr int kSpecOwn = 8192;       // flattened candidates per wavefront of the 32-cell path
+constexpr int kSpecRecWin = 1024;    // record indices per window of the microcell path
 // 32-bit words of a wavefront's owner buffer: the 32-cell path keeps 64 cell bases and one
-// start mask per 64 flattened candidates; the microcell path a window of record indices
-constexpr int spec_own_words(int ng) { return ng ? kSpecRecWin : kWave + 2 * (kSpecOwn / 64); }
+// start mask per 64 flattened candidates (a second stencil begins a row of its own); the microcell
+// path a window of record indices
+constexpr int spec_own_words(int ng) { return ng ? kSpecRecWin : kWave + 2 * (kSpecOwn / 64 + 1); }
 constexpr int kSpecGroups = 16;      // groups of 64 stencil cells: stencils of up to 512 cells (two for a displacement)
 constexpr int kSpecMaxStencil = kSpecGroups * kWave / 2;
 constexpr int kSpecGroupsSmall = 4;  // the instantiation for stencils of up to 128 cells (fewer registers)
-constexpr int kPairRing = 128;       // queued in-cutoff pairs per wavefront (a power of two, >= 2 x 64)
+constexpr int kSpecQueue = kWave + 4 * kWave;   // queued in-cutoff pairs per wavefront: 63 left over, 4 rows more
 
 // Draws of the moves a round may take, one slot per move (slot = move counter
 // mod RING, RING a power of two): move type, pick draw, ln A, and the three
@@ -71,93 +57,6 @@ __device__ __forceinline__ void draw_block(const DevBox& B, DrawRing<RING>* dr, 
     } else {
         dr->pz[s] = ua;
         dr->u7[s] = ub;
-    }
-}
-
-// Per-wavefront queue of in-cutoff squared distances.  push: the lanes with
-// `in` append v (ballot order); drain: lane l takes entry head + l of the
-// next `cnt` and adds its pair energy and virial to the first position's sums,
-// or the second's when v carries the sign bit.
-__device__ __forceinline__ void pair_push(double* q, uint32_t& tail, bool in, double v) {
-    const uint64_t m = __ballot(in);
-    if (in) {
-        const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        q[(tail + below) & (kPairRing - 1)] = v;
-    }
-    tail += (uint32_t)__builtin_popcountll(m);
-}
-
-__device__ __forceinline__ void pair_drain(const DevBox& B, const double* q, uint32_t head, uint32_t cnt, double& sa,
-                                           double& sb, double& wa, double& wb) {
-    // the entries other lanes wrote, visible to every lane
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    if (lane < cnt) {
-        const double v = q[(head + lane) & (kPairRing - 1)];
-        const bool second = __builtin_signbit(v);
-        const double r2 = second ? -v : v;
-        double w = 0.0;
-        const double u = lj_uw_from_r2(r2, B.rc2, B.eps4[0], B.sig2[0], w);
-        if (second) {
-            sb += u;
-            wb += w;
-        } else {
-            sa += u;
-            wa += w;
-        }
-    }
-    // every lane has read its entry before later pushes reuse the slots
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-}
-
-// Squared distances of one candidate record to the move's position(s),
-// queued when inside the cutoff (counts of evaluated and in-cutoff pairs kept
-// per lane).
-// Squared distance of a candidate to a position; the minimum image only where
-// the stencil may cross a periodic face (wrap false: every candidate lies
-// within (k + 1) cells of the position along each axis, at least half a cell
-// short of L/2, where the minimum image returns the difference unchanged, bit
-// for bit).
-__device__ __forceinline__ double spec_dist2(const DevBox& B, const double* p, const double3& e, bool wrap) {
-    double dx = e.x - p[0], dy = e.y - p[1], dz = e.z - p[2];
-    if (wrap) {
-        dx = nearest_image(dx, B.L[0], B.hL[0]);
-        dy = nearest_image(dy, B.L[1], B.hL[1]);
-        dz = nearest_image(dz, B.L[2], B.hL[2]);
-    }
-    return (dx * dx + dy * dy) + dz * dz;
-}
-
-__device__ __forceinline__ void spec_pair_queue(const DevBox& B, int type, int two, bool valid, bool second,
-                                                const double* p0, const double* p1, const double3& e, bool wrap,
-                                                double* q, uint32_t& head, uint32_t& tail, double& sa, double& sb,
-                                                double& wa, double& wb, int32_t& n_eval, int64_t& incut) {
-    const bool disp = type == GCMC_MOVE_DISPLACE;
-    // the first position: every move but the second stencil of a displacement that leaves its cell
-    const bool use0 = valid && !(disp && two && second);
-    const bool use1 = valid && disp && (!two || second);
-    double r2a = 0.0, r2b = 0.0;
-    if (use0) r2a = spec_dist2(B, p0, e, wrap);
-    const bool in0 = use0 && r2a < B.rc2;
-    n_eval += use0 ? 1 : 0;
-    incut += in0 ? 1 : 0;
-    pair_push(q, tail, in0, r2a);
-    if (tail - head >= (uint32_t)kWave) {
-        pair_drain(B, q, head, kWave, sa, sb, wa, wb);
-        head += kWave;
-    }
-    if (disp) {
-        if (use1) r2b = spec_dist2(B, p1, e, wrap);
-        const bool in1 = use1 && r2b < B.rc2;
-        n_eval += use1 ? 1 : 0;
-        incut += in1 ? 1 : 0;
-        pair_push(q, tail, in1, -r2b);
-        if (tail - head >= (uint32_t)kWave) {
-            pair_drain(B, q, head, kWave, sa, sb, wa, wb);
-            head += kWave;
-        }
     }
 }
 
@@ -228,6 +127,282 @@ __device__ __forceinline__ bool in_stencil(const DevBox& B, int32_t x, int32_t y
     return in;
 }
 
+// What the evaluation of a move returns besides the move itself.
+struct SpecSums {
+    double su, sw;   // pair energy and virial, the new position's minus the old one's for a displacement (every lane)
+    int32_t cand, evals, incut;   // candidate records, pair distances, pairs inside the cutoff
+    int32_t cnt0, cnt1;           // occupancies of the centre cells
+    double4 elast;                // last entry of the first centre cell
+};
+
+// Pair sums of a move over the stencils of its position(s) by one wavefront: p0 the
+// old, inserted or deleted position in cell c0 (linear cl0), p1 a displacement's
+// new one in c1 (cl1); `two`: the displacement leaves its cell and has two stencils,
+// else its positions share the candidates.  excl_slot: the moving particle's own
+// record (never a candidate of itself).  NG: 0 for the 32-cell path, else the number
+// of groups of 64 stencil cells the microcell path provides.
+//
+// The candidates are flattened, 64 per row, a second stencil starting a row of its
+// own, so a row meets one position (or both, for a displacement inside its cell).
+// Up to CR rows are requested at once; the squared distances of two to four rows
+// are formed together (independent chains), and the pairs inside the cutoff, about
+// one in seven, wait in LDS until 64 of them are evaluated, one per lane (the sign
+// bit marks a displacement's old position, whose terms are subtracted).
+template <int CR, int NG>
+__device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
+                                              double* q, int type, int two, const double* p0, const double* p1,
+                                              const int32_t* c0, const int32_t* c1, int32_t cl0, int32_t cl1,
+                                              int32_t excl_slot, bool no_full) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int nst = B.nstencil;
+    const int ncs = two ? 2 * nst : nst;
+    const bool disp = type == GCMC_MOVE_DISPLACE;
+    const bool fast = __builtin_amdgcn_readfirstlane(
+                          (no_full && c0[0] >= B.k[0] && c0[0] <= B.M[0] - 1 - B.k[0] && c0[1] >= B.k[1] &&
+                           c0[1] <= B.M[1] - 1 - B.k[1] && c0[2] >= B.k[2] && c0[2] <= B.M[2] - 1 - B.k[2] &&
+                           (!two || (c1[0] >= B.k[0] && c1[0] <= B.M[0] - 1 - B.k[0] && c1[1] >= B.k[1] &&
+                                     c1[1] <= B.M[1] - 1 - B.k[1] && c1[2] >= B.k[2] &&
+                                     c1[2] <= B.M[2] - 1 - B.k[2])))
+                              ? 1
+                              : 0) != 0;
+    // candidates need the minimum image unless the stencils stay inside the box with room to spare (every
+    // candidate then lies within (k + 1) cells of the position along each axis, half a cell short of
+    // L/2 at least, where the minimum image is the difference itself, bit for bit)
+    const bool wrap = !(fast && B.M[0] >= 2 * B.k[0] + 3 && B.M[1] >= 2 * B.k[1] + 3 && B.M[2] >= 2 * B.k[2] + 3);
+    SpecSums out;
+    out.su = out.sw = 0.0;
+    out.cand = out.evals = out.incut = 0;
+    out.elast = make_double4(0, 0, 0, 0);
+    uint32_t tail = 0;   // queued pairs (wave-uniform; the last ones are taken first)
+    auto drain = [&](uint32_t from, uint32_t cnt) {
+        wave_lds_sync();
+        if ((uint32_t)lane < cnt) {
+            const double v = q[from + lane];
+            double w = 0.0;
+            const double u = lj_uw_from_r2(__builtin_fabs(v), B.rc2, B.eps4[0], B.sig2[0], w);
+            out.su += __builtin_copysign(1.0, v) * u;
+            out.sw += __builtin_copysign(1.0, v) * w;
+        }
+        wave_lds_sync();
+    };
+    auto push = [&](double r2, double v) {
+        const uint64_t m = __ballot(r2 < B.rc2);
+        if (__builtin_amdgcn_inverse_ballot_w64(m)) q[lanes_below(m, tail)] = v;
+        tail += (uint32_t)__builtin_popcountll(m);
+    };
+    // rows base / 64 ... of the candidates e (x = 1e300: none); rows from flattened position
+    // `second` on belong to the second stencil
+    auto consume = [&](const double3* e, int base, int end, int second, auto wrap_t, auto both_t) {
+        constexpr bool WRAP = decltype(wrap_t)::value, BOTH = decltype(both_t)::value;
+        constexpr int G = CR < (BOTH ? 2 : 4) ? CR : (BOTH ? 2 : 4);
+        auto dist2 = [&](const double* p, const double3& c) {
+            double dx = c.x - p[0], dy = c.y - p[1], dz = c.z - p[2];
+            if (WRAP) {
+                dx = image_abs(dx, B.L[0]);
+                dy = image_abs(dy, B.L[1]);
+                dz = image_abs(dz, B.L[2]);
+            }
+            return (dx * dx + dy * dy) + dz * dz;
+        };
+#pragma unroll
+        for (int g = 0; g < CR; g += G) {
+            if (base + g * kWave < end) {
+                double ra[G], rb[G];
+                bool neg[G];
+#pragma unroll
+                for (int r = 0; r < G; ++r) {
+                    const bool sec = !BOTH && base + (g + r) * kWave >= second;   // wave-uniform
+                    neg[r] = disp && !sec;
+                    const double p[3] = {sec ? p1[0] : p0[0], sec ? p1[1] : p0[1], sec ? p1[2] : p0[2]};
+                    ra[r] = dist2(p, e[g + r]);
+                    if (BOTH) rb[r] = dist2(p1, e[g + r]);
+                }
+                const uint32_t t0 = tail;
+#pragma unroll
+                for (int r = 0; r < G; ++r) {
+                    push(ra[r], neg[r] ? -ra[r] : ra[r]);
+                    if (BOTH) push(rb[r], rb[r]);
+                }
+                tail = (uint32_t)uni((int32_t)tail);
+                out.incut += (int32_t)(tail - t0);
+                while (tail >= (uint32_t)kWave) {
+                    tail -= kWave;
+                    drain(tail, kWave);
+                }
+            }
+        }
+    };
+    auto dispatch = [&](const double3* e, int base, int end, int second) {
+        if (disp && !two) {
+            if (wrap) consume(e, base, end, second, std::true_type{}, std::true_type{});
+            else consume(e, base, end, second, std::false_type{}, std::true_type{});
+        } else {
+            if (wrap) consume(e, base, end, second, std::true_type{}, std::false_type{});
+            else consume(e, base, end, second, std::false_type{}, std::false_type{});
+        }
+    };
+    int32_t first2 = INT32_MAX, gap_end = INT32_MAX;   // flattened end of the first stencil, start of the second
+    int32_t n_all = 0, n_own = 0;                      // candidates, of those the moving particle itself
+    if constexpr (NG == 0) {
+        const int wh = lane >= nst ? 1 : 0;
+        const int t = lane - wh * nst;
+        const bool cell_lane = lane < ncs;
+        int32_t cell = cl0;
+        if (cell_lane) {
+            if (fast) {
+                cell = (wh ? cl1 : cl0) + offs[t];
+            } else {
+                cell = (int32_t)stencil_cell(B, tab[t], wh ? c1[0] : c0[0], wh ? c1[1] : c0[1], wh ? c1[2] : c0[2]);
+            }
+        }
+        const int32_t cnt = cell_lane ? gload(B.count + cell) : 0;
+        const int32_t incl = wave_incl_scan(cnt);
+        n_all = __builtin_amdgcn_readlane(incl, 63);
+        int32_t pre = incl - cnt, total = n_all;
+        if (two) {
+            first2 = __builtin_amdgcn_readlane(incl, nst - 1);
+            gap_end = (first2 + kWave - 1) & ~(kWave - 1);
+            pre += wh ? gap_end - first2 : 0;
+            total += gap_end - first2;
+        }
+        // lanes of the two centre cells (each appears once in its stencil)
+        const int tc = (int)__builtin_ctzll(__ballot(cell_lane && !wh && cell == cl0));
+        const int tc1 = two ? (int)__builtin_ctzll(__ballot(cell_lane && wh && cell == cl1)) : tc;
+        out.cnt0 = __builtin_amdgcn_readlane(cnt, tc);
+        out.cnt1 = __builtin_amdgcn_readlane(cnt, tc1);
+        // ---- owner of each flattened candidate: the nonempty cells, in lane order, are numbered
+        // k = 0, 1, ...; cbk[k] = the cell's record index minus its first flattened position,
+        // and bit q of the row masks marks a flattened position q where a nonempty cell begins,
+        // so the owner of q is the number of marks at or below q, minus one
+        uint32_t* cbk = static_cast<uint32_t*>(ownbuf);                // [64]
+        uint64_t* smask = reinterpret_cast<uint64_t*>(cbk + kWave);   // [kSpecOwn / 64 + 1]
+        const int nrows = (total + kWave - 1) / kWave;
+        for (int r = lane; r < nrows; r += kWave) smask[r] = 0;
+        wave_lds_sync();
+        {
+            const bool nonempty = cnt > 0;
+            const uint64_t nzm = __ballot(nonempty);
+            if (nonempty) {
+                cbk[lanes_below(nzm, 0u)] = (uint32_t)(cell * B.cap - pre);
+                __hip_atomic_fetch_or(&smask[pre >> 6], 1ull << (pre & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            }
+        }
+        wave_lds_sync();
+        uint32_t starts = 0;   // nonempty cells beginning before the current row (wave-uniform)
+        // last entry of the old centre cell (removal by swap-with-last)
+        if (out.cnt0 > 0) out.elast = gload(B.ent + ((size_t)(uint32_t)cl0 * (uint32_t)B.cap + (out.cnt0 - 1)));
+        // ---- candidates
+        for (int base = 0; base < total; base += kWave * CR) {
+            double3 e[CR];
+#pragma unroll
+            for (int r = 0; r < CR; ++r) {
+                const int row = (base >> 6) + r;
+                e[r] = make_double3(1e300, 0.0, 0.0);
+                if (row < nrows) {
+                    const int at = row * kWave + lane;
+                    const uint64_t m = smask[row];
+                    const uint32_t k = lanes_below(m, starts) + (uint32_t)((m >> lane) & 1ull) - 1u;
+                    starts += (uint32_t)__builtin_popcountll(m);
+                    const bool in = at < total && !(at >= first2 && at < gap_end);
+                    const int32_t ri = in ? (int32_t)cbk[k & (kWave - 1)] + at : cl0 * B.cap;
+                    const bool own = in && ri == excl_slot;
+                    n_own += __builtin_popcountll(__ballot(own));
+                    if (in && !own) e[r] = gload_xyz(B.ent + (size_t)(uint32_t)ri);
+                }
+            }
+            dispatch(e, base, total, two ? gap_end : INT32_MAX);
+        }
+    } else {
+        // ---- microcell stencils: groups of 64 cells, one lane per cell
+        const int G = (ncs + kWave - 1) / kWave;
+        int32_t cellg[NG], cntg[NG], preg[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            cellg[g] = cl0;
+            cntg[g] = 0;
+            if (g < G) {
+                const int f = g * kWave + lane;
+                const int wh = f >= nst ? 1 : 0;
+                const int t = f - wh * nst;
+                if (f < ncs)
+                    cellg[g] = fast ? (wh ? cl1 : cl0) + offs[t]
+                                    : (int32_t)stencil_cell(B, tab[t], wh ? c1[0] : c0[0], wh ? c1[1] : c0[1],
+                                                            wh ? c1[2] : c0[2]);
+                cntg[g] = f < ncs ? gload(B.count + cellg[g]) : 0;
+            }
+        }
+        out.cnt0 = out.cnt1 = 0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            preg[g] = 0;
+            if (g < G) {
+                const int f = g * kWave + lane;
+                const bool on = f < ncs;
+                const int wh = f >= nst ? 1 : 0;
+                const int32_t incl = wave_incl_scan(cntg[g]);
+                preg[g] = n_all + incl - cntg[g];
+                if (two && (nst - 1) / kWave == g) first2 = n_all + __builtin_amdgcn_readlane(incl, (nst - 1) & (kWave - 1));
+                n_all += __builtin_amdgcn_readlane(incl, 63);
+                // the centre cells (each appears once in its stencil)
+                const uint64_t b0 = __ballot(on && !wh && cellg[g] == cl0);
+                if (b0) out.cnt0 = __builtin_amdgcn_readlane(cntg[g], (int)__builtin_ctzll(b0));
+                const uint64_t b1 = __ballot(on && wh && cellg[g] == cl1);
+                if (b1) out.cnt1 = __builtin_amdgcn_readlane(cntg[g], (int)__builtin_ctzll(b1));
+            }
+        }
+        int32_t total = n_all;
+        if (two) {
+            gap_end = (first2 + kWave - 1) & ~(kWave - 1);
+            total += gap_end - first2;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) preg[g] += (g * kWave + lane) >= nst ? gap_end - first2 : 0;
+        } else {
+            out.cnt1 = out.cnt0;
+        }
+        if (out.cnt0 > 0) out.elast = gload(B.ent + ((size_t)(uint32_t)cl0 * (uint32_t)B.cap + (out.cnt0 - 1)));
+        // ---- record indices of the flattened candidates, window by window
+        uint32_t* recw = static_cast<uint32_t*>(ownbuf);
+        for (int w0 = 0; w0 < total; w0 += kSpecRecWin) {
+            const int w1 = (total - w0) < kSpecRecWin ? total : w0 + kSpecRecWin;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (g < G) {
+                    const uint32_t rb = (uint32_t)cellg[g] * (uint32_t)B.cap;
+                    const int kmax = wave_max_i32_uniform(cntg[g]);
+                    for (int kk = 0; kk < kmax; ++kk) {
+                        const int at = preg[g] + kk;
+                        if (kk < cntg[g] && at >= w0 && at < w1) recw[at - w0] = rb + (uint32_t)kk;
+                    }
+                }
+            }
+            wave_lds_sync();   // the indices other lanes of this wavefront wrote, visible to every lane
+            for (int base = w0; base < w1; base += kWave * CR) {
+                double3 e[CR];
+#pragma unroll
+                for (int r = 0; r < CR; ++r) {
+                    const int at = base + r * kWave + lane;
+                    e[r] = make_double3(1e300, 0.0, 0.0);
+                    if (base + r * kWave < w1) {
+                        const bool in = at < w1 && !(at >= first2 && at < gap_end);
+                        const int32_t ri = in ? (int32_t)recw[at - w0] : cl0 * B.cap;
+                        const bool own = in && ri == excl_slot;
+                        n_own += __builtin_popcountll(__ballot(own));
+                        if (in && !own) e[r] = gload_xyz(B.ent + (size_t)(uint32_t)ri);
+                    }
+                }
+                dispatch(e, base, w1, two ? gap_end : INT32_MAX);
+            }
+            wave_lds_sync();   // every lane has read this window before the next overwrites it
+        }
+    }
+    if (tail) drain(0, tail);   // the pairs still queued
+    out.su = wave_sum_uniform(out.su);
+    out.sw = wave_sum_uniform(out.sw);
+    out.cand = n_all - n_own;
+    out.evals = disp && !two ? 2 * out.cand : out.cand;
+    return out;
+}
+
 // The caller's work that needs only the move's type, draws and pick, run by
 // the evaluation while the picked record is being loaded (none by default).
 struct SpecNoEarly {
@@ -238,7 +413,7 @@ struct SpecNoEarly {
 // 0 for the 32-cell path, else the number of groups of 64 stencil cells the
 // microcell path provides (see above).  RING > 0: the draws come from `dr`
 // (the moves ctr_round .. ctr_round + k must be in it); RING = 0: computed
-// here, for k < 16.  pq: this wavefront's pair queue (kPairRing doubles of
+// here, for k < 16.  pq: this wavefront's pair queue (kSpecQueue doubles of
 // LDS).
 template <int CR, int NG, int RING, typename Early = SpecNoEarly>
 __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
@@ -325,7 +500,9 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
         int64_t n_c = (int64_t)floor((double)N + (double)I * a_ins - (double)D * a_del + 0.5);
         n_c = uni64(n_c < n_lo ? n_lo : (n_c > n_hi ? n_hi : n_c));
         idx = spec_pick(u2, u7, n_c);
-        rec = gload(B.pos + idx);
+        // (an index past N names a particle an earlier insertion of the round may add: read inside the array,
+        // used only if that insertion is decided first)
+        rec = gload(B.pos + (idx < B.max_n ? idx : B.max_n - 1));
         early(type, u2, u7, idx);   // the caller's work that needs only the pick, while the record loads
         p0[0] = rec.x; p0[1] = rec.y; p0[2] = rec.z;
     }
@@ -351,201 +528,10 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
         }
     }
     const int two = (type == GCMC_MOVE_DISPLACE && !same) ? 1 : 0;
-    const int nst = B.nstencil;
-    const int ncs = two ? 2 * nst : nst;
-    // ---- counters of the stencil cells, one lane per cell
-    const bool fast = __builtin_amdgcn_readfirstlane(
-                          (no_full && c0[0] >= B.k[0] && c0[0] <= B.M[0] - 1 - B.k[0] && c0[1] >= B.k[1] &&
-                           c0[1] <= B.M[1] - 1 - B.k[1] && c0[2] >= B.k[2] && c0[2] <= B.M[2] - 1 - B.k[2] &&
-                           (!two || (c1[0] >= B.k[0] && c1[0] <= B.M[0] - 1 - B.k[0] && c1[1] >= B.k[1] &&
-                                     c1[1] <= B.M[1] - 1 - B.k[1] && c1[2] >= B.k[2] &&
-                                     c1[2] <= B.M[2] - 1 - B.k[2])))
-                              ? 1
-                              : 0) != 0;
-    // candidates need the minimum image unless the stencils stay inside the box with room to spare
-    const bool wrap = !(fast && B.M[0] >= 2 * B.k[0] + 3 && B.M[1] >= 2 * B.k[1] + 3 && B.M[2] >= 2 * B.k[2] + 3);
-    int32_t cnt0 = 0, cnt1 = 0;
-    double4 elast = make_double4(0, 0, 0, 0);
-    // the slot of the moving particle's own record in the cell array (never a candidate of itself)
     const int32_t excl_slot = type == GCMC_MOVE_INSERT ? -1 : meta_low(rec.w);
-    double sa = 0.0, sb = 0.0, wa = 0.0, wb = 0.0;
-    int32_t n_cand = 0, n_eval = 0, n_in = 0;
-    int64_t incut = 0;
-    uint32_t qhead = 0, qtail = 0;   // the in-cutoff pair queue (wave-uniform counters)
-    if constexpr (NG == 0) {
-        const int wh = lane >= nst ? 1 : 0;
-        const int t = lane - wh * nst;
-        const bool cell_lane = lane < ncs;
-        int32_t cell = cl0;
-        if (cell_lane) {
-            if (fast) {
-                cell = (wh ? cl1 : cl0) + offs[t];
-            } else {
-                cell = (int32_t)stencil_cell(B, tab[t], wh ? c1[0] : c0[0], wh ? c1[1] : c0[1], wh ? c1[2] : c0[2]);
-            }
-        }
-        const int32_t cnt = cell_lane ? gload(B.count + cell) : 0;
-        const int32_t incl = wave_incl_scan(cnt);
-        const int32_t pre = incl - cnt;
-        const int32_t total = __builtin_amdgcn_readlane(incl, 63);
-        // lanes of the two centre cells (each appears once in its stencil)
-        const int tc = (int)__builtin_ctzll(__ballot(cell_lane && !wh && cell == cl0));
-        const int tc1 = two ? (int)__builtin_ctzll(__ballot(cell_lane && wh && cell == cl1)) : tc;
-        cnt0 = __builtin_amdgcn_readlane(cnt, tc);
-        cnt1 = __builtin_amdgcn_readlane(cnt, tc1);
-        // ---- owner of each flattened candidate: the nonempty cells, in lane order, are numbered
-        // k = 0, 1, ...; cbk[k] = the cell's record index minus its first flattened position,
-        // and bit q of the row masks marks a flattened position q where a nonempty cell begins,
-        // so the owner of q is the number of marks at or below q, minus one
-        uint32_t* cbk = static_cast<uint32_t*>(ownbuf);                // [64]
-        uint64_t* smask = reinterpret_cast<uint64_t*>(cbk + kWave);   // [kSpecOwn / 64]
-        const int nrows = (total + kWave - 1) / kWave;
-        for (int r = lane; r < nrows; r += kWave) smask[r] = 0;
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-        {
-            const bool nonempty = cnt > 0;
-            const uint64_t nzm = __ballot(nonempty);
-            if (nonempty) {
-                const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(nzm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nzm, 0u));
-                cbk[k] = (uint32_t)(cell * B.cap - pre);
-                __hip_atomic_fetch_or(&smask[pre >> 6], 1ull << (pre & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-            }
-        }
-        const int32_t first2 = __builtin_amdgcn_readlane(incl, nst - 1);   // flattened start of the second stencil
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-        uint32_t starts = 0;   // nonempty cells beginning before the current row (wave-uniform)
-        // last entry of the old centre cell (removal by swap-with-last)
-        if (cnt0 > 0) elast = gload(B.ent + ((size_t)(uint32_t)cl0 * (uint32_t)B.cap + (cnt0 - 1)));
-        // ---- candidates
-        for (int base = 0; base < total; base += kWave * CR) {
-            double3 e[CR];
-            int32_t wsel[CR];
-            bool ok[CR];
-    #pragma unroll
-            for (int r = 0; r < CR; ++r) {
-                const int q = base + r * kWave + lane;
-                const int row = (base >> 6) + r;
-                const uint64_t m = row < nrows ? smask[row] : 0;
-                const uint32_t k = starts + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)) +
-                                   (uint32_t)((m >> lane) & 1ull) - 1u;
-                starts += (uint32_t)__builtin_popcountll(m);
-                const int32_t cb = q < total ? (int32_t)cbk[k & (kWave - 1)] : 0;
-                const int32_t ri = q < total ? cb + q : cl0 * B.cap;
-                ok[r] = q < total && ri != excl_slot;
-                wsel[r] = (nst < ncs && q >= first2) ? 1 : 0;
-                e[r] = gload_xyz(B.ent + (size_t)(uint32_t)ri);
-            }
-    #pragma unroll
-            for (int r = 0; r < CR; ++r) {
-                // rows past the last candidate hold nothing for any lane (wave-uniform)
-                if (base + r * kWave >= total) break;
-                const bool valid = ok[r];
-                n_cand += valid ? 1 : 0;
-                spec_pair_queue(B, type, two, valid, wsel[r] != 0, p0, p1, e[r], wrap, pq, qhead, qtail, sa, sb, wa,
-                                wb, n_eval, incut);
-            }
-        }
-
-    } else {
-        // ---- microcell stencils: groups of 64 cells, one lane per cell
-        const int G = (ncs + kWave - 1) / kWave;
-        int32_t cellg[NG], cntg[NG], preg[NG];
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            cellg[g] = cl0;
-            cntg[g] = 0;
-            if (g < G) {
-                const int f = g * kWave + lane;
-                const int wh = f >= nst ? 1 : 0;
-                const int t = f - wh * nst;
-                if (f < ncs)
-                    cellg[g] = fast ? (wh ? cl1 : cl0) + offs[t]
-                                    : (int32_t)stencil_cell(B, tab[t], wh ? c1[0] : c0[0], wh ? c1[1] : c0[1],
-                                                            wh ? c1[2] : c0[2]);
-                cntg[g] = f < ncs ? gload(B.count + cellg[g]) : 0;
-            }
-        }
-        int32_t total = 0;
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            preg[g] = 0;
-            if (g < G) {
-                const int f = g * kWave + lane;
-                const bool on = f < ncs;
-                const int wh = f >= nst ? 1 : 0;
-                const int32_t incl = wave_incl_scan(cntg[g]);
-                preg[g] = total + incl - cntg[g];
-                total += __builtin_amdgcn_readlane(incl, 63);
-                // the centre cells (each appears once in its stencil)
-                const uint64_t b0 = __ballot(on && !wh && cellg[g] == cl0);
-                if (b0) cnt0 = __builtin_amdgcn_readlane(cntg[g], (int)__builtin_ctzll(b0));
-                const uint64_t b1 = __ballot(on && wh && cellg[g] == cl1);
-                if (b1) cnt1 = __builtin_amdgcn_readlane(cntg[g], (int)__builtin_ctzll(b1));
-            }
-        }
-        if (!two) cnt1 = cnt0;
-        if (cnt0 > 0) elast = gload(B.ent + ((size_t)(uint32_t)cl0 * (uint32_t)B.cap + (cnt0 - 1)));
-        // ---- record indices of the flattened candidates, window by window (bit 31: second stencil)
-        uint32_t* recw = static_cast<uint32_t*>(ownbuf);
-        for (int q0 = 0; q0 < total; q0 += kSpecRecWin) {
-            const int q1 = (total - q0) < kSpecRecWin ? total : q0 + kSpecRecWin;
-#pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                if (g < G) {
-                    const uint32_t second = (g * kWave + lane) >= nst ? 0x80000000u : 0u;
-                    const uint32_t rb = (uint32_t)cellg[g] * (uint32_t)B.cap;
-                    const int kmax = wave_max_i32_uniform(cntg[g]);
-                    for (int kk = 0; kk < kmax; ++kk) {
-                        const int q = preg[g] + kk;
-                        if (kk < cntg[g] && q >= q0 && q < q1) recw[q - q0] = (rb + (uint32_t)kk) | second;
-                    }
-                }
-            }
-            // the indices other lanes of this wavefront wrote, visible to every lane
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-            for (int base = q0; base < q1; base += kWave * CR) {
-                double3 e[CR];
-                bool ok[CR], sec[CR];
-#pragma unroll
-                for (int r = 0; r < CR; ++r) {
-                    const int q = base + r * kWave + lane;
-                    const uint32_t v = q < q1 ? recw[q - q0] : (uint32_t)cl0 * (uint32_t)B.cap;
-                    sec[r] = (v & 0x80000000u) != 0;
-                    ok[r] = q < q1 && (int32_t)(v & 0x7FFFFFFFu) != excl_slot;
-                    e[r] = gload_xyz(B.ent + (size_t)(v & 0x7FFFFFFFu));
-                }
-#pragma unroll
-                for (int r = 0; r < CR; ++r) {
-                    // rows past the window's last candidate hold nothing for any lane (wave-uniform)
-                    if (base + r * kWave >= q1) break;
-                    const bool valid = ok[r];
-                    n_cand += valid ? 1 : 0;
-                    spec_pair_queue(B, type, two, valid, sec[r], p0, p1, e[r], wrap, pq, qhead, qtail, sa, sb, wa,
-                                    wb, n_eval, incut);
-                }
-            }
-            // every lane has read this window before the next overwrites it
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-        }
-    }
-    // the pairs still queued
-    if (qtail != qhead) pair_drain(B, pq, qhead, qtail - qhead, sa, sb, wa, wb);
-    n_in = (int32_t)incut;
-    const double ea = wave_sum_uniform(sa);
-    const double eb = (type == GCMC_MOVE_DISPLACE) ? wave_sum_uniform(sb) : 0.0;
-    const double dUp = (type == GCMC_MOVE_DISPLACE) ? (eb - ea) : ((type == GCMC_MOVE_INSERT) ? ea : -ea);
-    const double va = wave_sum_vec(wa);
-    const double vb = (type == GCMC_MOVE_DISPLACE) ? wave_sum_vec(wb) : 0.0;
-    const double dWp = (type == GCMC_MOVE_DISPLACE) ? (vb - va) : ((type == GCMC_MOVE_INSERT) ? va : -va);
-    // work counters of this evaluation (wave sums)
-    n_cand = wave_sum_i32_uniform(n_cand);
-    n_eval = wave_sum_i32_uniform(n_eval);
-    n_in = wave_sum_i32_uniform(n_in);
+    const SpecSums S = spec_sums<CR, NG>(B, tab, offs, ownbuf, pq, type, two, p0, p1, c0, c1, cl0, cl1, excl_slot, no_full);
+    const double dUp = type == GCMC_MOVE_DELETE ? -S.su : S.su;
+    const double dWp = type == GCMC_MOVE_DELETE ? -S.sw : S.sw;
     key.idx = idx;
     key.dUp = dUp;
     if (lane == 0) {
@@ -559,7 +545,7 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
         out->two = two;
         out->idx = idx;
         out->rec = rec;
-        out->elast = elast;
+        out->elast = S.elast;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             out->p0[a] = p0[a];
@@ -569,11 +555,11 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
         }
         out->cl0 = cl0;
         out->cl1 = cl1;
-        out->cnt0 = cnt0;
-        out->cnt1 = cnt1;
-        out->cand = n_cand;
-        out->evals = n_eval;
-        out->incut = n_in;
+        out->cnt0 = S.cnt0;
+        out->cnt1 = S.cnt1;
+        out->cand = S.cand;
+        out->evals = S.evals;
+        out->incut = S.incut;
     }
 }
 
