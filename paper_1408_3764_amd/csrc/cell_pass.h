@@ -128,10 +128,10 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
 }
 
-// Call f(e, sp, rows, rel, own) for every block of up to CR rows of candidates
+// Call f(e, mw, rows, rel, own) for every block of up to CR rows of candidates
 // of home cell c at (cx, cy, cz): e[r] the coordinates of this lane's candidate
-// in row r (x = 1e300 past the last candidate: outside any cutoff), sp[r] its
-// species, rows the rows in use, rel the position of this lane's row-0
+// in row r (x = 1e300 past the last candidate: outside any cutoff), mw[r] its
+// packed species and id (META only), rows the rows in use, rel the position of this lane's row-0
 // candidate relative to the home cell's first particle, bit r of own set when
 // row r holds particles of the home cell.
 //
@@ -140,7 +140,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 // belong to the two sides, so exactly one of them takes the pair, whatever the
 // stencil (axes it covers whole included; a stencil is symmetric and names a cell
 // once).
-template <int CR, bool HALF, bool MIX, typename F>
+template <int CR, bool HALF, bool META, typename F>
 __device__ __forceinline__ void stencil_rows(const DevBox& B, const PassBox& P, PassRows& W, int32_t c, int32_t cx,
                                              int32_t cy, int32_t cz, const F& f) {
     const int lane = threadIdx.x & (kWave - 1);
@@ -181,14 +181,14 @@ __device__ __forceinline__ void stencil_rows(const DevBox& B, const PassBox& P, 
             wave_lds_sync();
             for (int b0 = w0; b0 < w1; b0 += CR * kWave) {
                 double3 e[CR];
-                int32_t sp[CR];
+                double mw[CR];
                 const int left = (w1 - b0 + kWave - 1) / kWave;
                 const int rows = left < CR ? left : CR;
                 uint32_t own = 0;
 #pragma unroll
                 for (int r = 0; r < CR; ++r) {
                     e[r] = make_double3(1e300, 0.0, 0.0);
-                    sp[r] = 0;
+                    mw[r] = 0.0;
                     if (r < rows) {
                         const int q0 = b0 + r * kWave, q = q0 + lane;
                         const uint64_t m = W.starts[(q0 - w0) >> 6];
@@ -196,10 +196,10 @@ __device__ __forceinline__ void stencil_rows(const DevBox& B, const PassBox& P, 
                         begun += (uint32_t)__builtin_popcountll(m);
                         if (q < w1) {
                             const double4* p = P.ent + (size_t)(W.base[k & (kWave - 1)] + (uint32_t)q);
-                            if (MIX) {
+                            if (META) {
                                 const double4 v = gload(p);
                                 e[r] = make_double3(v.x, v.y, v.z);
-                                sp[r] = meta_species(v.w);
+                                mw[r] = v.w;
                             } else {
                                 const GCMC_GLOBAL_AS double* s = (const GCMC_GLOBAL_AS double*)(const double*)p;
                                 typedef double d2v __attribute__((ext_vector_type(2)));
@@ -210,7 +210,7 @@ __device__ __forceinline__ void stencil_rows(const DevBox& B, const PassBox& P, 
                         if (q0 < pe && q0 + kWave > ph) own |= 1u << r;
                     }
                 }
-                f(e, sp, rows, b0 + lane - ph, own);
+                f(e, mw, rows, b0 + lane - ph, own);
             }
         }
     }

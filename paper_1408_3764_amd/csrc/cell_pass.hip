@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kWave) void k_pair_total(const DevBox* __restrict__
         const bool inside = uni(pass_inside(B, cx, cy, cz) ? 1 : 0) != 0;
         stencil_rows<kTotalRows, true, MIX>(
             B, P, rows_s, c, cx, cy, cz,
-            [&](const double3* e, const int32_t* sp, int rows, int32_t rel, uint32_t own) {
+            [&](const double3* e, const double* mw, int rows, int32_t rel, uint32_t own) {
                 auto test = [&](auto wrap_t, auto rows_t) {
                     constexpr bool WRAP = decltype(wrap_t)::value;
                     constexpr int R = decltype(rows_t)::value;
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kWave) void k_pair_total(const DevBox* __restrict__
                             if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
                                 const uint32_t at = lanes_below(m[r], tail);
                                 qr[at] = r2[r];
-                                if (MIX) qp[at] = (uint8_t)(sa + sp[r]);
+                                if (MIX) qp[at] = (uint8_t)(sa + meta_species(mw[r]));
                             }
                             tail += (uint32_t)__builtin_popcountll(m[r]);
                         }
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kWave) void k_pair_each(const DevBox* __restrict__ 
             wave_lds_sync();
             stencil_rows<kEachRows, false, MIX>(
                 B, P, rows_s, c, cx, cy, cz,
-                [&](const double3* e, const int32_t* sp, int rows, int32_t rel, uint32_t own) {
+                [&](const double3* e, const double* mw, int rows, int32_t rel, uint32_t own) {
                     auto test = [&](auto wrap_t, auto rows_t) {
                         constexpr bool WRAP = decltype(wrap_t)::value;
                         constexpr int R = decltype(rows_t)::value;
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kWave) void k_pair_each(const DevBox* __restrict__ 
                                 if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
                                     const uint32_t at = lanes_below(m[r], tail);
                                     qr[at] = r2[r];
-                                    qm[at] = (uint16_t)((i - i0) | (MIX ? (sa + sp[r]) << 8 : 0));
+                                    qm[at] = (uint16_t)((i - i0) | (MIX ? (sa + meta_species(mw[r])) << 8 : 0));
                                 }
                                 tail += (uint32_t)__builtin_popcountll(m[r]);
                             }
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kWave, 5) void k_pair_grad(const DevBox* __restrict
             wave_lds_sync();
             stencil_rows<kGradRows, false, MIX>(
                 B, P, rows_s, c, cx, cy, cz,
-                [&](const double3* e, const int32_t* sp, int rows, int32_t rel, uint32_t own) {
+                [&](const double3* e, const double* mw, int rows, int32_t rel, uint32_t own) {
 #pragma unroll
                     for (int r = 0; r < kGradRows; ++r) {
                         cx_s[r * kWave + lane] = e[r].x;
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(kWave, 5) void k_pair_grad(const DevBox* __restrict
                                 if (own & (1u << r)) m[r] &= __ballot(rel + r * kWave != i);   // not itself
                                 if (__builtin_amdgcn_inverse_ballot_w64(m[r]))
                                     qm[lanes_below(m[r], tail)] =
-                                        (uint32_t)(r * kWave + lane) + (MIX ? (uint32_t)sp[r] << 16 : 0u) + mi;
+                                        (uint32_t)(r * kWave + lane) + (MIX ? (uint32_t)meta_species(mw[r]) << 16 : 0u) + mi;
                                 tail += (uint32_t)__builtin_popcountll(m[r]);
                             }
                             tail = (uint32_t)uni((int32_t)tail);
