@@ -458,6 +458,15 @@ int gcmc_import_state(gcmc_box* box, const double* d_x, const double* d_y, const
  * `stream`. */
 int gcmc_clear_averages(gcmc_box* box, void* stream);
 
+/* Copy `bytes` of device memory to host memory behind the work queued on
+ * `stream`; returns when they are there.  Up to 4 KB (energies, statistics, a
+ * box's state) go through pinned memory that the host polls, more than that by
+ * a copy and a synchronisation of the stream. */
+int gcmc_read(void* h_dst, const void* d_src, int64_t bytes, void* stream);
+/* Copy `bytes` of host memory to device memory, ordered on `stream`; h_src may be
+ * reused on return.  Up to 2 KB are enqueued without waiting. */
+int gcmc_write(void* d_dst, const void* h_src, int64_t bytes, void* stream);
+
 /* Block until the box's queued work is done; returns its latched error (a
  * device error of the kind the paper's kernels would report to the host after
  * a move: cell over capacity, N at max_n). */

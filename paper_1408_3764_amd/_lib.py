@@ -36,7 +36,7 @@ EXPORTS = [
     "gcmc_batch_create",
     "gcmc_batch_destroy",
     "gcmc_batch_step", "gcmc_get_particles", "gcmc_get_cells", "gcmc_neighbor_ids", "gcmc_export_state",
-    "gcmc_import_state", "gcmc_clear_averages", "gcmc_sync_status", "gcmc_last_error", "gcmc_version",
+    "gcmc_import_state", "gcmc_clear_averages", "gcmc_read", "gcmc_write", "gcmc_sync_status", "gcmc_last_error", "gcmc_version",
 ]
 
 
@@ -111,6 +111,8 @@ def lib():
         "gcmc_set_positions": [vp, dp, dp, dp, i64, vp],
         "gcmc_set_params": [vp, C.POINTER(C.c_double), C.POINTER(C.c_double)],
         "gcmc_box_rescale": [vp, C.POINTER(C.c_double), vp, vp],
+        "gcmc_read": [vp, vp, i64, vp],
+        "gcmc_write": [vp, vp, i64, vp],
         "gcmc_delta_energy": [vp, dp, i64, dp, dp, dp, vp],
         "gcmc_delta_energy_allpairs": [vp, dp, i64, dp, dp, dp, vp],
         "gcmc_commit": [vp, dp, dp, dp, vp],
@@ -200,6 +202,16 @@ def gcmc_set_params(box, eps, sigma):
 def gcmc_box_rescale(box, L_new, out, stream=None):
     Lh = np.ascontiguousarray(np.broadcast_to(np.asarray(L_new, dtype=np.float64), (3,)))
     check(lib().gcmc_box_rescale(box, Lh.ctypes.data_as(C.POINTER(C.c_double)), ptr(out), stream_handle(stream)))
+
+
+def gcmc_read(dst, src, stream=None):
+    """Fill the contiguous numpy array dst from the contiguous tensor src of the same bytes."""
+    check(lib().gcmc_read(dst.ctypes.data, src.data_ptr(), dst.nbytes, stream_handle(stream)))
+
+
+def gcmc_write(dst, src, stream=None):
+    """Fill the contiguous tensor dst from the contiguous numpy array src of the same bytes."""
+    check(lib().gcmc_write(dst.data_ptr(), src.ctypes.data, src.nbytes, stream_handle(stream)))
 
 
 def gcmc_delta_energy(box, moves, n, dU_pair, dU_tail, dW_pair=None, stream=None):

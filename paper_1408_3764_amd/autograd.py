@@ -13,7 +13,13 @@ from __future__ import annotations
 
 import torch
 
-from .box import Box
+from .box import Box, _host
+
+
+def _table(t: torch.Tensor):
+    t = t.detach()
+    plain = t.is_cuda and t.dtype == torch.float64 and t.is_contiguous() and not t.is_neg()
+    return _host(t) if plain else t.cpu().numpy()
 
 
 class LJEnergy(torch.autograd.Function):
@@ -21,7 +27,7 @@ class LJEnergy(torch.autograd.Function):
     def forward(ctx, pos: torch.Tensor, eps: torch.Tensor, sigma: torch.Tensor, box: Box):
         if pos.dtype != torch.float64 or not pos.is_cuda:
             raise TypeError("positions must be a float64 device tensor")
-        box.set_params(eps.detach().cpu().numpy(), sigma.detach().cpu().numpy())
+        box.set_params(_table(eps), _table(sigma))
         box.set_positions_device(pos.detach())
         U = box.total_energy_device()
         ctx.box = box
@@ -37,7 +43,7 @@ class LJEnergy(torch.autograd.Function):
             # the box was changed after this forward (another forward, new parameters, moves):
             # the gradient is taken at the saved inputs, put back into the box
             pos, eps, sigma = ctx.saved_tensors
-            box.set_params(eps.cpu().numpy(), sigma.cpu().numpy())
+            box.set_params(_table(eps), _table(sigma))
             box.set_positions_device(pos)
         g, de, ds = box.backward_device(ctx.n)
         return gU * g, gU * de, gU * ds, None

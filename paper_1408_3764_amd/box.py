@@ -19,12 +19,28 @@ def _dev(a, dtype, device):
     return torch.as_tensor(np.ascontiguousarray(a), dtype=dtype, device=device)
 
 
-def _struct_to_device(arr: np.ndarray, device) -> torch.Tensor:
-    return torch.from_numpy(np.ascontiguousarray(arr).view(np.uint8).copy()).to(device)
+def _struct_to_device(arr: np.ndarray, device, stream=None) -> torch.Tensor:
+    a = np.ascontiguousarray(arr)
+    if stream is not None or a.nbytes > 2048:
+        # another stream than the tensor's own: a copy the host waits for
+        return torch.from_numpy(a.view(np.uint8).copy()).to(device)
+    t = torch.empty(a.nbytes, dtype=torch.uint8, device=device)
+    _lib.gcmc_write(t, a)
+    return t
 
 
-def _struct_from_device(t: torch.Tensor, dtype) -> np.ndarray:
-    return t.cpu().numpy().view(dtype).copy()
+def _host(t: torch.Tensor, stream=None) -> np.ndarray:
+    """NumPy copy of a contiguous device tensor written on `stream` (default: the current one)."""
+    out = np.empty(tuple(t.shape), dtype=_NUMPY[t.dtype])
+    _lib.gcmc_read(out, t, stream)
+    return out
+
+
+_NUMPY = {torch.float64: np.float64, torch.int32: np.int32, torch.uint8: np.uint8}
+
+
+def _struct_from_device(t: torch.Tensor, dtype, stream=None) -> np.ndarray:
+    return _host(t, stream).view(dtype)
 
 
 class Box:
@@ -106,19 +122,15 @@ class Box:
         """(dU_pair, dU_tail[, dW_pair]) of each move against the current configuration."""
         moves = np.asarray(moves, dtype=MOVE_DTYPE)
         m = len(moves)
-        dm = _struct_to_device(moves, self.device)
-        dp = torch.empty(m, dtype=torch.float64, device=self.device)
-        dt = torch.empty(m, dtype=torch.float64, device=self.device)
-        dw = torch.empty(m, dtype=torch.float64, device=self.device) if virial else None
+        dm = _struct_to_device(moves, self.device, self.stream)
+        out = torch.empty((3 if virial else 2, m), dtype=torch.float64, device=self.device)
         f = _lib.gcmc_delta_energy_allpairs if all_pairs else _lib.gcmc_delta_energy
-        f(self.handle, dm, m, dp, dt, dw, self.stream)
-        if virial:
-            return dp.cpu().numpy(), dt.cpu().numpy(), dw.cpu().numpy()
-        return dp.cpu().numpy(), dt.cpu().numpy()
+        f(self.handle, dm, m, out[0], out[1], out[2] if virial else None, self.stream)
+        return tuple(_host(out, self.stream))
 
     def commit(self, move, dU_pair, dW_pair=None):
         mv = np.asarray([move], dtype=MOVE_DTYPE) if not isinstance(move, np.ndarray) else move.reshape(1)
-        dm = _struct_to_device(mv, self.device)
+        dm = _struct_to_device(mv, self.device, self.stream)
         du = torch.tensor([float(dU_pair)], dtype=torch.float64, device=self.device)
         dw = None if dW_pair is None else torch.tensor([float(dW_pair)], dtype=torch.float64, device=self.device)
         _lib.gcmc_commit(self.handle, dm, du, dw, self.stream)
@@ -131,20 +143,20 @@ class Box:
         f = _lib.gcmc_step_allpairs if all_pairs else _lib.gcmc_step
         f(self.handle, n_moves, counter0, st, lg, self.stream)
         self.version += 1
-        stats = _struct_from_device(st, STATS_DTYPE)[0]
-        lgs = _struct_from_device(lg, LOG_DTYPE)[:n_moves] if log else None
+        stats = _struct_from_device(st, STATS_DTYPE, self.stream)[0]
+        lgs = _struct_from_device(lg, LOG_DTYPE, self.stream)[:n_moves] if log else None
         return stats, lgs
 
     # --------------------------------------------------------------- energy
     def total_energy(self, all_pairs=False, per_particle=False):
-        U = torch.zeros(2, dtype=torch.float64, device=self.device)
-        n = self.n
+        U = torch.empty(2, dtype=torch.float64, device=self.device)
+        n = self.n if per_particle else 0
         e = torch.zeros(max(n, 1), dtype=torch.float64, device=self.device) if per_particle else None
         _lib.gcmc_total_energy(self.handle, 1 if all_pairs else 0, U, e, self.stream)
-        u = U.cpu().numpy()
+        u = _host(U, self.stream)
         out = {"U_pair": float(u[0]), "U_tail": float(u[1])}
         if per_particle:
-            out["e"] = e[:n].cpu().numpy()
+            out["e"] = _host(e[:n], self.stream)
         return out
 
     def backward(self, positions=True, params=True):
@@ -157,16 +169,16 @@ class Box:
         if positions:
             out["grad"] = g[: 3 * n].view(3, n).t().cpu().numpy()
         if params:
-            out["d_eps"] = de.view(self.ns, self.ns).cpu().numpy()
-            out["d_sigma"] = ds.view(self.ns, self.ns).cpu().numpy()
+            out["d_eps"] = _host(de.view(self.ns, self.ns), self.stream)
+            out["d_sigma"] = _host(ds.view(self.ns, self.ns), self.stream)
         return out
 
     def virial(self):
         """{"W": pair virial, "P": pressure with the ideal and tail terms}; also sets the
         running virial the chain keeps current."""
-        out = torch.zeros(2, dtype=torch.float64, device=self.device)
+        out = torch.empty(2, dtype=torch.float64, device=self.device)
         _lib.gcmc_virial(self.handle, out, self.stream)
-        v = out.cpu().numpy()
+        v = _host(out, self.stream)
         return {"W": float(v[0]), "P": float(v[1])}
 
     # ----------------------------------------------------------- inspection
@@ -266,11 +278,11 @@ class Box:
         """Scale the box to edges L_new (coordinates scaled with it), rebuild the
         cell list and return the cell-list energies {"U_pair", "U_tail"} at the
         new volume and {"U_pair_old", "U_tail_old"} at the old one."""
-        out = torch.zeros(4, dtype=torch.float64, device=self.device)
+        out = torch.empty(4, dtype=torch.float64, device=self.device)
         _lib.gcmc_box_rescale(self.handle, L_new, out, self.stream)
         self.version += 1
         self.L = np.broadcast_to(np.asarray(L_new, dtype=np.float64), (3,)).copy()
-        v = out.cpu().numpy()
+        v = _host(out, self.stream)
         return {"U_pair": float(v[0]), "U_tail": float(v[1]), "U_pair_old": float(v[2]), "U_tail_old": float(v[3])}
 
     def set_params(self, eps, sigma):
@@ -279,13 +291,21 @@ class Box:
 
     def set_positions_device(self, pos: torch.Tensor, n=None):
         """pos: (N, 3) float64 device tensor with the current N (n: that N, if the caller knows it)."""
-        n = self.n if n is None else int(n)
+        # a tensor of the right kind carries its own N to the library, which compares it with the
+        # box's in the read it makes anyhow; N is read here only to say what was wrong
+        own = n is None and pos.dim() == 2 and pos.shape[1] == 3 and pos.dtype == torch.float64 and pos.is_cuda
+        n = pos.shape[0] if own else self.n if n is None else int(n)
         if tuple(pos.shape) != (n, 3):
             raise ValueError("positions must have shape (%d, 3), got %s" % (n, tuple(pos.shape)))
         if pos.dtype != torch.float64 or not pos.is_cuda:
             raise TypeError("positions must be a float64 device tensor")
-        x, y, z = (pos[:, a].contiguous() for a in range(3))
-        _lib.gcmc_set_positions(self.handle, x, y, z, n, self.stream)
+        x, y, z = pos.t().contiguous()
+        try:
+            _lib.gcmc_set_positions(self.handle, x, y, z, n, self.stream)
+        except _lib.GcmcError:
+            if own and self.n != n:
+                raise ValueError("positions must have shape (%d, 3), got %s" % (self.n, tuple(pos.shape))) from None
+            raise
         self.version += 1
 
     def total_energy_device(self, all_pairs=False):
@@ -345,7 +365,7 @@ class Batch:
     def step(self, moves_per_box, counter0=0, stream=None):
         st = torch.zeros(len(self.boxes) * STATS_DTYPE.itemsize, dtype=torch.uint8, device=self.device)
         _lib.gcmc_batch_step(self.handle, moves_per_box, counter0, st, stream)
-        return _struct_from_device(st, STATS_DTYPE)
+        return _struct_from_device(st, STATS_DTYPE, stream)
 
     def close(self):
         if getattr(self, "handle", None) is not None and self.handle.value:

@@ -205,12 +205,14 @@ __global__ void k_reset_state(BoxState* st, int64_t n, double u_pair, double w_p
     }
 }
 
-// Running energy and virial (a NaN marks a value no longer describing the configuration).
-__global__ void k_set_running(BoxState* st, double u_pair, double w_pair) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        st->u_pair = u_pair;
-        st->w_pair = w_pair;
-    }
+// A new descriptor, and the running energy and virial no longer those of the
+// configuration (NaN).  The descriptor travels in the kernel's arguments: a launch
+// where a copy from pageable memory waits for the device.
+__global__ __launch_bounds__(256) void k_set_desc(DevBox B, DevBox* dst) {
+    static_assert(sizeof(DevBox) % 4 == 0 && sizeof(DevBox) <= 2048, "the descriptor fits a launch's arguments");
+    const uint32_t* w = (const uint32_t*)&B;
+    for (int i = threadIdx.x; i < (int)(sizeof(DevBox) / 4); i += blockDim.x) ((uint32_t*)dst)[i] = w[i];
+    if (threadIdx.x == 0) B.st->u_pair = B.st->w_pair = __builtin_nan("");
 }
 
 // The chain part of a checkpoint: running energy and virial, move counter,
@@ -455,9 +457,7 @@ static int sync_desc(gcmc_box* box) {
 }
 
 static int read_state(gcmc_box* box, BoxState* h, hipStream_t s) {
-    GCMC_HIP(hipMemcpyAsync(h, box->d.st, sizeof(BoxState), hipMemcpyDeviceToHost, s));
-    GCMC_HIP(hipStreamSynchronize(s));
-    return GCMC_OK;
+    return read_back(h, box->d.st, sizeof(BoxState), s);
 }
 
 namespace gcmc {
@@ -490,6 +490,7 @@ static void free_box(gcmc_box* box) {
     if (box->d_desc) (void)hipFree(box->d_desc);
     if (box->scratch) (void)hipFree(box->scratch);
     if (box->ap_chain) (void)hipFree(box->ap_chain);
+    transfer_release();
     delete box;
 }
 
@@ -510,6 +511,7 @@ int gcmc_box_create(const gcmc_box_desc* desc, const double* d_x, const double* 
     hipStream_t s = (hipStream_t)stream;
     gcmc_box* box = new gcmc_box();
     memset(box, 0, sizeof(*box));
+    transfer_retain();
     for (int a = 0; a < 3; ++a) box->req_m[a] = desc->cell_m[a];
     for (int a = 0; a < desc->n_species * desc->n_species; ++a) {
         box->h_eps[a] = desc->eps[a];
@@ -687,10 +689,10 @@ int gcmc_set_params(gcmc_box* box, const double* h_eps, const double* h_sigma) {
         box->h_sig[a] = h_sigma[a];
     }
     // the running energy and virial belong to the old force field
-    k_set_running<<<1, 1>>>(box->d.st, std::nan(""), std::nan(""));
+    k_set_desc<<<1, 256>>>(box->d, box->d_desc);
     GCMC_HIP(hipGetLastError());
     GCMC_HIP(hipDeviceSynchronize());
-    return sync_desc(box);
+    return GCMC_OK;
 }
 
 int gcmc_box_set_wait_limit(gcmc_box* box, int32_t polls) {

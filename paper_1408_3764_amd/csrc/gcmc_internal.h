@@ -547,6 +547,10 @@ void launch_ap_chain_end(const DevBox* d_box, const void* ch, gcmc_stats* stats,
 
 // box.hip
 int read_box_state(gcmc_box* box, BoxState* h, hipStream_t s);
+// Device memory to host memory behind the stream's work; returns when it is there.
+int read_back(void* dst, const void* src, size_t bytes, hipStream_t s);
+void transfer_retain();    // one per live box: the pinned slots of the small reads
+void transfer_release();
 int ensure_scratch(gcmc_box* box, int64_t len);
 }  // namespace gcmc
 
