@@ -34,6 +34,7 @@ struct BoxState {
     int64_t nsp[kMaxSpecies];  // particles per species
     int64_t counter;      // move counter after the last move the chain ran
     double w_pair;        // running pair virial
+    int64_t gate;         // ticket of the last re-binning in place that was let through (+ 1: refused)
     ChainSums cum;        // cumulative statistics (part of a checkpoint)
 };
 
@@ -463,6 +464,7 @@ struct gcmc_box {
     void* ap_chain;          // all-pairs chain bookkeeping (device)
     int device;
     int waves, rows;         // launch shape of the move kernels
+    int64_t gate;            // ticket of the last re-binning in place (even)
     int32_t req_m[3];        // cells per axis asked for at create (0 = the paper's rule)
     double h_eps[gcmc::kMaxSpecies * gcmc::kMaxSpecies];   // force-field tables as given (host)
     double h_sig[gcmc::kMaxSpecies * gcmc::kMaxSpecies];
@@ -549,6 +551,7 @@ void launch_ap_chain_end(const DevBox* d_box, const void* ch, gcmc_stats* stats,
 int read_box_state(gcmc_box* box, BoxState* h, hipStream_t s);
 // Device memory to host memory behind the stream's work; returns when it is there.
 int read_back(void* dst, const void* src, size_t bytes, hipStream_t s);
+bool stream_capturing(hipStream_t s);
 void transfer_retain();    // one per live box: the pinned slots of the small reads
 void transfer_release();
 int ensure_scratch(gcmc_box* box, int64_t len);

@@ -105,15 +105,6 @@ ReadSlots& slots() {
     return *s;
 }
 
-// A capturing stream (or a capture that forbids work on this one) goes to the copy,
-// which reports it as it always did.
-bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
-}
-
 int read_by_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
     GCMC_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
     GCMC_HIP(hipStreamSynchronize(s));
@@ -122,12 +113,21 @@ int read_by_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
 
 }  // namespace
 
+// A capturing stream (or a capture that forbids work on this one) goes to the copy,
+// which reports it as it always did.
+bool stream_capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 void transfer_retain() { slots().retain(); }
 void transfer_release() { slots().release(); }
 
 int read_back(void* dst, const void* src, size_t bytes, hipStream_t s) {
     if (bytes == 0) return GCMC_OK;
-    if (bytes > 4 * kReadWords || bytes % 4 != 0 || (uintptr_t)src % 4 != 0 || capturing(s))
+    if (bytes > 4 * kReadWords || bytes % 4 != 0 || (uintptr_t)src % 4 != 0 || stream_capturing(s))
         return read_by_copy(dst, src, bytes, s);
     ReadSlot* slot = nullptr;
     uint32_t ticket = 0;
@@ -171,7 +171,7 @@ int gcmc_write(void* d_dst, const void* h_src, int64_t bytes, void* stream) {
     if (bytes < 0 || (bytes > 0 && (!d_dst || !h_src))) return set_error(GCMC_ERR_INVALID_ARG, "bad arguments");
     if (bytes == 0) return GCMC_OK;
     hipStream_t s = (hipStream_t)stream;
-    if (bytes > kWriteBytes || bytes % 4 != 0 || (uintptr_t)d_dst % 4 != 0 || capturing(s)) {
+    if (bytes > kWriteBytes || bytes % 4 != 0 || (uintptr_t)d_dst % 4 != 0 || stream_capturing(s)) {
         GCMC_HIP(hipMemcpyAsync(d_dst, h_src, (size_t)bytes, hipMemcpyHostToDevice, s));
         GCMC_HIP(hipStreamSynchronize(s));
         return GCMC_OK;

@@ -1,0 +1,131 @@
+"""Re-binning in place (new positions, a new volume, a checkpoint) where its passes
+can go wrong: boxes of many cells (several cells a wavefront) and of few, cells of
+more than 64 places, empty cells, species counts kept or counted; a refusal leaves
+the box alone; a cell that a new volume overflows.  Cells and ids are compared
+exactly with the oracle's, energies within 1e-10 of the magnitude sum."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1408_3764_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+#        n, edges, rc, cells, species, cell_cap
+CASES = {
+    "27 cells": (200, (8.0, 8.0, 8.0), 2.5, None, 1, 0),
+    "4,096 cells": (3000, (40.0, 40.0, 40.0), 2.5, None, 1, 0),
+    "4,095 cells, last group cut": (3000, (33.0, 33.0, 47.0), 2.0, [15, 13, 21], 2, 0),
+    "7,000 cells": (900, (14.0, 14.0, 700.0), 2.5, None, 1, 0),
+    "5,491 cells, mostly empty": (40, (47.6, 42.6, 42.6), 2.5, [19, 17, 17], 3, 0),
+    "cells of 92, 4 wide": (2500, (15.4, 15.4, 15.4), 5.0, None, 2, 0),
+    "65 places": (300, (8.0, 8.0, 8.0), 2.5, None, 2, 65),
+    "64 places": (300, (8.0, 8.0, 8.0), 2.5, None, 2, 64),
+}
+
+
+def _make(name):
+    n, L, rc, cm, ns, cap = CASES[name]
+    kw = {}
+    if ns > 1:
+        kw["eps"], kw["sigma"] = workloads.lorentz_berthelot([1.0, 1.2, 0.9][:ns], [1.0, 0.8, 1.1][:ns])
+        kw["species_counts"] = [n // ns] * (ns - 1) + [n - n // ns * (ns - 1)]
+    wb = workloads.random_box(n, L, rc=rc, seed=n, **kw)
+    from paper_1408_3764_amd.box import Box
+    b = Box.from_workload(wb, max_n=n + 3, cell_m=cm, cell_cap=cap)
+    return wb, b, oracle.make_params(wb.L, wb.rc, eps=wb.eps, sigma=wb.sigma, beta=wb.beta)
+
+
+def _check(b, pos, species, p):
+    cell_of, count, ids = b.cells()
+    m = b.info()["cell_m"]
+    inv = [mm / e for mm, e in zip(m, b.L)]
+    c = np.minimum((np.asarray(pos) * np.array(inv)).astype(np.int64), np.array(m) - 1)
+    want = (c[:, 2] * m[1] + c[:, 1]) * m[0] + c[:, 0]
+    assert np.array_equal(cell_of, want)
+    assert np.array_equal(count, np.bincount(want, minlength=len(count)))
+    for k in np.nonzero(count)[0]:
+        assert np.array_equal(ids[k, : count[k]], np.nonzero(want == k)[0])     # in id order
+    ref = oracle.total_energy(pos, p, species=species)
+    got = b.total_energy()
+    assert abs(got["U_pair"] - ref["U_pair"]) <= 1e-10 * max(ref["sumabs"], 1e-300)
+    assert got["U_tail"] == pytest.approx(ref["U_tail"], rel=1e-12, abs=1e-300)   # the species counts
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_rebinned_in_place(name):
+    wb, b, p = _make(name)
+    _check(b, wb.pos, wb.species, p)
+    rng = np.random.default_rng(1)
+    # small steps, so that no cell runs over its places (none could with the exact 64 and 65)
+    new = np.mod(wb.pos + rng.uniform(-0.02, 0.02, wb.pos.shape), wb.L)
+    new[new >= np.asarray(wb.L)] = 0.0
+    b.set_positions_device(torch.tensor(new, device="cuda"))
+    _check(b, new, wb.species, p)
+    pos, sp, ck = b.export_state()
+    b.set_positions(wb.pos)
+    b.import_state(pos, ck, species=sp)
+    _check(b, new, wb.species, p)
+
+
+def test_refusals_leave_the_box_alone():
+    from paper_1408_3764_amd import _lib
+    wb, b, p = _make("4,096 cells")
+    u0 = b.total_energy()["U_pair"]
+    before = b.cells()
+    x = torch.zeros(wb.n + 1, dtype=torch.float64, device="cuda")
+    for n in (wb.n - 1, wb.n + 1, 0):
+        with pytest.raises(_lib.GcmcError) as e:
+            _lib.gcmc_set_positions(b.handle, x, x, x, n)
+        assert e.value.code == _lib.GCMC_ERR_INVALID_ARG
+        assert b.checkpoint()["u_pair"] == u0 and all(np.array_equal(s, t) for s, t in zip(before, b.cells()))
+    # a coordinate outside: latched, the cells not rebuilt, and from then on refused as poisoned
+    for code in (_lib.GCMC_ERR_INVALID_ARG, _lib.GCMC_ERR_POISONED):
+        bad = wb.pos.copy()
+        bad[-1, 2] = wb.L[2]
+        with pytest.raises(_lib.GcmcError) as e:
+            b.set_positions(bad)
+        assert e.value.code == code
+        assert b.status() == _lib.GCMC_ERR_INVALID_ARG and b.checkpoint()["u_pair"] == u0
+        assert np.array_equal(b.cells()[1], before[1])
+    ck = dict(b.checkpoint(), error=0, error_move=-1)
+    b.import_state(wb.pos, ck)
+    _check(b, wb.pos, None, p)
+
+
+def test_positions_that_overflow_a_cell():
+    from paper_1408_3764_amd import _lib
+    wb, b, p = _make("27 cells")
+    cap = b.info()["cell_cap"]
+    new = wb.pos.copy()
+    new[: cap + 3] = np.random.default_rng(3).uniform(0.1, 2.4, (cap + 3, 3))
+    with pytest.raises(_lib.GcmcError) as e:
+        b.set_positions(new)
+    assert e.value.code == _lib.GCMC_ERR_CELL_OVERFLOW
+    b.cell_build(cap + 60)
+    _check(b, new, None, p)
+
+
+def test_volume_that_overflows_a_cell():
+    """A particle on a cell border that the scaling rounds into a full cell: the capacity grows."""
+    from paper_1408_3764_amd.box import Box
+    L, L2, m = 11.0, 11.0818, 4
+    x = 5.5
+    while int(x * (m / L)) != 1:
+        x = np.nextafter(x, 0.0)
+    assert int((x * (L2 / L)) * (m / L2)) == 2
+    # cells (1, 0, 0) and (2, 0, 0) of 3 places: the second full, the border particle in the first
+    pos = np.array([[6.0, 1.0, 1.0], [7.2, 1.0, 1.0], [6.6, 2.2, 1.4], [x, 1.0, 2.2], [9.0, 9.0, 9.0]])
+    b = Box(pos, [L] * 3, 2.5, max_n=8, cell_cap=3)
+    assert b.info()["cell_m"] == [4, 4, 4] and b.cells()[1].max() == 3
+    got = b.rescale([L2] * 3)
+    p = oracle.make_params([L2] * 3, 2.5)
+    new = pos * (L2 / L)
+    assert b.info()["cell_cap"] > 3 and b.cells()[1].max() == 4
+    ref = oracle.total_energy(new, p)
+    assert abs(got["U_pair"] - ref["U_pair"]) <= 1e-10 * ref["sumabs"]
+    old = oracle.total_energy(pos, oracle.make_params([L] * 3, 2.5))
+    assert abs(got["U_pair_old"] - old["U_pair"]) <= 1e-10 * old["sumabs"]
+    assert b.status() == 0 and b.checkpoint()["u_pair"] == got["U_pair"]
+    _check(b, new, None, p)
