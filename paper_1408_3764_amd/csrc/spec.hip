@@ -39,7 +39,12 @@
 //
 // NG > 0: stencils of more than 32 cells (microcells, Sec. 3.3) go through
 // the evaluation's path with NG groups of 64 cells; the round and the commit
-// are the same.
+// are the same.  There a round waits for its displacements, which sum over two
+// stencils of several hundred candidates each, so H helpers take the new positions of
+// the round's first H displacements (cutoff 4.25 on microcells, 87,296 particles: 2.31 ->
+// 2.12 us a move with three, all that 160 registers leave room for).  With the short
+// stencils of NG = 0 the helpers' own draws and counters cost what they save (slab
+// 10.19 ms without, 10.45 with three; helpers at a raised wave priority 10.6).
 #include "spec_eval.h"
 
 namespace gcmc {
@@ -98,9 +103,9 @@ __device__ __attribute__((noinline)) void spec_draws(DrawRing<RING>* ring, uint6
     B.seed = seed; B.box_id = box_id; B.p_disp = p_disp;
     draw_block(B, ring, ctr, b);
 }
-// W evaluating wavefronts and one that decides.
-template <int W, int CR, int NG>
-__global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(const DevBox* __restrict__ boxes,
+// W evaluating wavefronts, H helpers and one that decides.
+template <int W, int H, int CR, int NG>
+__global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spec(const DevBox* __restrict__ boxes,
                                                                const int32_t* __restrict__ order, int64_t n_moves,
                                                                uint64_t ctr0, gcmc_stats* stats, gcmc_log* trace) {
     constexpr int kOffs = NG ? NG * kWave / 2 : 64;    // stencil slots with a precomputed linear offset
@@ -108,7 +113,8 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
     __shared__ uint32_t tab[kMaxStencil];
     __shared__ int32_t offs[kOffs];
     __shared__ SpecRec recs_s[2][W];            // the round's evaluations, by round parity
-    __shared__ __align__(8) uint32_t own[W][spec_own_words(NG)];   // cell bases and start masks, or record indices
+    __shared__ SpecHalf half_s[2][H ? H : 1];   // the helpers', the same
+    __shared__ __align__(8) uint32_t own[W + H][spec_own_words(NG)];   // cell bases and start masks, or record indices
     __shared__ double4 top[2 * W];              // records of particles base .. base + 2W - 1
     __shared__ double lpi[kSpecPref], lpd[kSpecPref];   // the deciding wavefront's prefactors
     // its statistics, lane k's sums over the moves it decided as move k of a round (counts as doubles, exact
@@ -116,8 +122,8 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
     enum { kAtt, kAcc = 3, kSumN = 6, kSumN2, kSumU, kSumW, kStencils, kCand, kEvals, kIncut, kStats };
     __shared__ double acc_s[kStats][W];
     __shared__ DrawRing<RING> dring;            // draws of moves m .. m + 2W - 1
-    __shared__ double pq[W][kSpecQueue];        // each wavefront's queue of in-cutoff pairs
-    __shared__ int32_t ready[W];                // round whose evaluation wavefront w has published
+    __shared__ double pq[W + H][kSpecQueue];    // each wavefront's queue of in-cutoff pairs
+    __shared__ int32_t ready[W + H];            // round whose evaluation wavefront w has published
     // the state after a round, by round parity (a wavefront may still read the last round's)
     __shared__ int4 sh_state[2];                // N, moves decided, error
     __shared__ double2 sh_acc[2];               // running acceptance of insertions and deletions
@@ -138,7 +144,7 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
         tab[t] = pk;
         if (t < kOffs) offs[t] = ((tz - B.k[2]) * B.M[1] + (ty - B.k[1])) * B.M[0] + (tx - B.k[0]);
     }
-    if (tid < W) ready[tid] = -1;
+    if (tid < W + H) ready[tid] = -1;
     // draws of the first 2W moves
     for (int t = tid; t < 8 * W; t += blockDim.x) draw_block(B, &dring, ctr0 + (uint64_t)(t >> 2), t & 3);
     __syncthreads();
@@ -146,25 +152,48 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
     if (wrong) err = GCMC_ERR_UNSUPPORTED;
     int64_t m = 0;
     int32_t rnd = 0;                   // rounds begun
-    if (wv < W) {
-        // ================================================ evaluate move m + wv of every round
+    // the displacements among the round's moves m + j, j < n (bit j)
+    auto displacements = [&](int64_t m0, int n) {
+        const int t = lane < n ? dring.type[(int)((ctr0 + (uint64_t)m0 + (uint64_t)lane) & (uint64_t)(RING - 1))] : -1;
+        return (uint32_t)__ballot(t == GCMC_MOVE_DISPLACE);
+    };
+    // the h-th of them (W if there are no more)
+    auto nth = [&](uint32_t bits, int h) {
+        for (int i = 0; i < h && bits; ++i) bits &= bits - 1u;
+        return bits ? (int)__builtin_ctz(bits) : W;
+    };
+    if (wv < W + H) {
+        // ================================================ evaluate move m + wv of every round, or as helper
+        // h = wv - W the new position of its h-th displacement
         double a_ins = 0.5, a_del = 0.5;   // running acceptance of insertions and deletions
         while (err == GCMC_OK && m < n_moves) {
             rnd = rnd == INT32_MAX ? 1 : rnd + 1;   // round numbers stay positive (a flag starts at -1)
             SpecRec* recs = recs_s[rnd & 1];
-            if (m + wv < n_moves) {
+            int mv = wv, role = kSpecWhole;
+            if constexpr (H > 0) {
+                const uint32_t dm = displacements(m, n_moves - m < W ? (int)(n_moves - m) : W);
+                if (wv >= W) {
+                    mv = nth(dm, wv - W);
+                    role = kSpecNew;
+                } else if ((dm >> wv & 1u) != 0 && __builtin_popcount(dm & ((1u << wv) - 1u)) < H) {
+                    role = kSpecOld;
+                }
+                mv = uni(mv);
+                role = uni(role);
+            }
+            if (mv < W && m + mv < n_moves) {
                 SpecKey key;
                 // is the pick at every N the move can meet (lane o: N - (W - 1) + o) the evaluated one? (found
                 // while the picked record is loaded)
                 const int32_t np = N - (W - 1) + lane;
                 uint64_t pm = 0;
                 auto early = [&](int type, double u2, double u7, int64_t idx) {
-                    pm = __ballot(lane < 2 * W - 1 && np >= 0 &&
+                    if (role != kSpecNew) pm = __ballot(lane < 2 * W - 1 && np >= 0 &&
                                   (type == GCMC_MOVE_INSERT || spec_pick(u2, u7, np) == idx));
                 };
-                spec_eval<CR, NG, RING>(B, tab, offs, own[wv], pq[wv], &dring, ctr0 + (uint64_t)m, wv, N, no_full, a_ins,
-                                        a_del, &recs[wv], key, early);
-                if (lane == 0) recs[wv].pickmask = (uint32_t)pm;
+                spec_eval<CR, NG, RING>(B, tab, offs, own[wv], pq[wv], &dring, ctr0 + (uint64_t)m, mv, N, no_full, a_ins,
+                                        a_del, &recs[mv], key, early, role, &half_s[rnd & 1][H && wv >= W ? wv - W : 0]);
+                if (lane == 0 && role != kSpecNew) recs[mv].pickmask = (uint32_t)pm;
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
                 if (lane == 0) __hip_atomic_store(&ready[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -179,7 +208,7 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
         }
         return;
     }
-    // ==================================================== decide and commit (wavefront W)
+    // ==================================================== decide and commit (wavefront W + H)
     int64_t err_move = st->error_move;
     if (wrong) err_move = (int64_t)ctr0;
     double U = st->u_pair;
@@ -210,6 +239,13 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
             spec_prefactors(B.V, B.lambda3, lpi, lpd, lbase);
         }
         if (has_top) top[lane] = tv;
+        // lane w's wavefront evaluates (part of) move from[w] of this round, kend if none of it
+        int from = lane < kend ? lane : kend;
+        if constexpr (H > 0) {
+            const uint32_t dm = displacements(m, kend);
+            if (lane >= W && lane < W + H) from = nth(dm, lane - W);
+            from = from < kend ? from : kend;
+        }
         // ------------------------------------------ the evaluations
         int kw = kend;   // moves whose evaluation arrived
         if (spin_cap < 0) {
@@ -217,13 +253,14 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
         } else {
             int32_t spins = 0;
             for (;;) {
-                const bool wait = lane < kend && __hip_atomic_load(&ready[lane < W ? lane : 0], __ATOMIC_ACQUIRE,
+                const bool wait = from < kend && __hip_atomic_load(&ready[lane < W + H ? lane : 0], __ATOMIC_ACQUIRE,
                                                                    __HIP_MEMORY_SCOPE_WORKGROUP) != rnd;
                 const uint64_t late = __ballot(wait);
                 if (late == 0) break;
                 __builtin_amdgcn_s_sleep(1);
                 if (++spins > spin_cap) {
-                    kw = (int)__builtin_ctzll(late);
+                    for (int j = kend - 1; j >= 0; --j)
+                        if (__ballot(wait && from == j)) kw = j;   // the first move not whole
                     break;
                 }
             }
@@ -243,10 +280,26 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
         const double p0x = R.p0[0], p0y = R.p0[1], p0z = R.p0[2];   // old, inserted or deleted position
         const double p1x = R.p1[0], p1y = R.p1[1], p1z = R.p1[2];   // a displacement's new position
         const int32_t two = mine ? R.two : 0;
-        const int32_t cnt0 = R.cnt0, cnt1 = R.cnt1;                  // occupancies of its centre cells
+        const int32_t cnt0 = R.cnt0;                                 // occupancies of its centre cells
+        int32_t cnt1 = R.cnt1;
         const int32_t loc = meta_low(R.rec.w);                       // slot of its particle's record
         const int32_t id_end = meta_low(R.elast.w);                  // particle of its first cell's last entry
-        int32_t r_in = R.incut;
+        int32_t r_in = R.incut, r_cand = R.cand;
+        if constexpr (H > 0) {
+            // a displacement's other half
+            const uint64_t dm = __ballot(mine && disp);
+            const int h = (int)lanes_below(dm, 0u);
+            if (mine && disp && !empty && h < H) {
+                const SpecHalf& F = half_s[rnd & 1][h];
+                dUp += F.su;
+                dWp += F.sw;
+                r_in += F.incut;
+                if (two) {
+                    r_cand += F.cand;
+                    cnt1 = F.cnt1;
+                }
+            }
+        }
         const int32_t n_round = N;
         bool stale = false;
         double dUt = 0.0, arg = 0.0;
@@ -414,7 +467,6 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : 1) void k_chain_spec(co
         // (the next round's evaluations run meanwhile).  The candidates of a move are those of the state
         // it was decided on: each earlier accepted move of the round that took a particle out of, or put
         // one into, one of its stencils changes their number.
-        int32_t r_cand = R.cand;
         for (uint64_t left = accbits & ((1ull << k) - 1ull); left; left &= left - 1ull) {
             const int f = (int)__builtin_ctzll(left);
             const int32_t tf = __builtin_amdgcn_readlane(type, f), ftwo = __builtin_amdgcn_readlane(two, f);
@@ -501,30 +553,31 @@ using spec_fn = void (*)(const DevBox*, const int32_t*, int64_t, uint64_t, gcmc_
 
 struct SpecCfg {
     int key;   // the waves value of gcmc_box_set_launch that selects it
-    int w;     // moves evaluated at once (the workgroup has one wavefront more)
+    int w;     // moves evaluated at once
+    int h;     // helpers
     int ng;    // groups of 64 stencil cells of the microcell path, 0 for the 32-cell path
     spec_fn f;
 };
 
-// waves = 2 and 8: that many moves at once and the deciding wavefront beside them.  waves =
-// 4: three moves and the deciding one, so that a compute unit holds two such boxes or
-// one beside an LDS-held box (five wavefronts of 160 registers put two on the first
+// waves = 2 and 8: that many moves at once and the deciding wavefront beside them
+// (and helpers for the microcell path).  waves = 4: three moves and the deciding one,
+// so that a compute unit holds two such boxes or one beside an LDS-held box (five wavefronts of 160 registers put two on the first
 // SIMD, and a batch of 512 boxes then ran in two rounds: 3.51 ms per 1,000 moves, 2.55
 // with four wavefronts).  waves = 16: 15 moves, 16 wavefronts being a workgroup's most.
 // Seven moves for waves = 8: the slab's 10,000 moves take 11.3 ms against 10.4 with eight.
 static const SpecCfg kSpecCfgs[] = {
-    {2, 2, 0, k_chain_spec<2, 8, 0>},
-    {4, 3, 0, k_chain_spec<3, 8, 0>},
-    {8, 8, 0, k_chain_spec<8, 8, 0>},
-    {16, 15, 0, k_chain_spec<15, 4, 0>},
-    {2, 2, kSpecGroupsSmall, k_chain_spec<2, 8, kSpecGroupsSmall>},
-    {4, 3, kSpecGroupsSmall, k_chain_spec<3, 8, kSpecGroupsSmall>},
-    {8, 8, kSpecGroupsSmall, k_chain_spec<8, 8, kSpecGroupsSmall>},
-    {16, 15, kSpecGroupsSmall, k_chain_spec<15, 4, kSpecGroupsSmall>},
-    {2, 2, kSpecGroups, k_chain_spec<2, 8, kSpecGroups>},
-    {4, 3, kSpecGroups, k_chain_spec<3, 8, kSpecGroups>},
-    {8, 8, kSpecGroups, k_chain_spec<8, 8, kSpecGroups>},
-    {16, 15, kSpecGroups, k_chain_spec<15, 4, kSpecGroups>},
+    {2, 2, 0, 0, k_chain_spec<2, 0, 8, 0>},
+    {4, 3, 0, 0, k_chain_spec<3, 0, 8, 0>},
+    {8, 8, 0, 0, k_chain_spec<8, 0, 8, 0>},
+    {16, 15, 0, 0, k_chain_spec<15, 0, 4, 0>},
+    {2, 2, 1, kSpecGroupsSmall, k_chain_spec<2, 1, 8, kSpecGroupsSmall>},
+    {4, 3, 0, kSpecGroupsSmall, k_chain_spec<3, 0, 8, kSpecGroupsSmall>},
+    {8, 8, 3, kSpecGroupsSmall, k_chain_spec<8, 3, 8, kSpecGroupsSmall>},
+    {16, 15, 0, kSpecGroupsSmall, k_chain_spec<15, 0, 4, kSpecGroupsSmall>},
+    {2, 2, 1, kSpecGroups, k_chain_spec<2, 1, 8, kSpecGroups>},
+    {4, 3, 0, kSpecGroups, k_chain_spec<3, 0, 8, kSpecGroups>},
+    {8, 8, 3, kSpecGroups, k_chain_spec<8, 3, 8, kSpecGroups>},
+    {16, 15, 0, kSpecGroups, k_chain_spec<15, 0, 4, kSpecGroups>},
 };
 
 // Groups of 64 cells the box's stencils need: 0 (the 32-cell path) for
@@ -554,7 +607,7 @@ int launch_chain_spec(const DevBox* d_boxes, const int32_t* d_order, int n_boxes
                       uint64_t ctr0, gcmc_stats* stats, gcmc_log* log, hipStream_t s, int ng) {
     for (const SpecCfg& c : kSpecCfgs) {
         if (c.key == waves && c.ng == ng) {
-            hipLaunchKernelGGL(c.f, dim3(n_boxes), dim3(kWave * (c.w + 1)), 0, s, d_boxes, d_order, n_moves, ctr0, stats,
+            hipLaunchKernelGGL(c.f, dim3(n_boxes), dim3(kWave * (c.w + c.h + 1)), 0, s, d_boxes, d_order, n_moves, ctr0, stats,
                                log);
             return 0;
         }

@@ -83,6 +83,14 @@ struct SpecRec {
     int32_t cand, evals, incut, pad2;
 };
 
+// Which part of a displacement an evaluation takes: both positions, the old one
+// (the move's own record), or the new one (a helper's sums alone).
+enum { kSpecWhole = 0, kSpecOld = 1, kSpecNew = 2 };
+struct SpecHalf {
+    double su, sw;                      // pair energy and virial at the new position
+    int32_t cand, incut, cnt1, pad;     // of its stencil; the occupancy of its centre cell
+};
+
 // The values of an evaluation the round kernel decides with in advance.
 struct SpecKey {
     int32_t type, flags;
@@ -147,12 +155,13 @@ struct SpecSums {
 // Up to CR rows are requested at once; the squared distances of two to four rows
 // are formed together (independent chains), and the pairs inside the cutoff, about
 // one in seven, wait in LDS until 64 of them are evaluated, one per lane (the sign
-// bit marks a displacement's old position, whose terms are subtracted).
-template <int CR, int NG>
+// bit marks a displacement's old position, whose terms are subtracted).  mid() runs
+// once while the counters are on their way.
+template <int CR, int NG, typename Mid>
 __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
                                               double* q, int type, int two, const double* p0, const double* p1,
                                               const int32_t* c0, const int32_t* c1, int32_t cl0, int32_t cl1,
-                                              int32_t excl_slot, bool no_full) {
+                                              int32_t excl_slot, bool no_full, const Mid& mid) {
     const int lane = threadIdx.x & (kWave - 1);
     const int nst = B.nstencil;
     const int ncs = two ? 2 * nst : nst;
@@ -256,6 +265,7 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
             }
         }
         const int32_t cnt = cell_lane ? gload(B.count + cell) : 0;
+        mid();
         const int32_t incl = wave_incl_scan(cnt);
         n_all = __builtin_amdgcn_readlane(incl, 63);
         int32_t pre = incl - cnt, total = n_all;
@@ -331,6 +341,7 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
                 cntg[g] = f < ncs ? gload(B.count + cellg[g]) : 0;
             }
         }
+        mid();
         out.cnt0 = out.cnt1 = 0;
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
@@ -414,12 +425,14 @@ struct SpecNoEarly {
 // microcell path provides (see above).  RING > 0: the draws come from `dr`
 // (the moves ctr_round .. ctr_round + k must be in it); RING = 0: computed
 // here, for k < 16.  pq: this wavefront's pair queue (kSpecQueue doubles of
-// LDS).
+// LDS).  role: the part of a displacement (any other move: kSpecWhole); for kSpecNew
+// the sums go to `half` and nothing to `out`.
 template <int CR, int NG, int RING, typename Early = SpecNoEarly>
 __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
                                           double* pq, const DrawRing<RING>* dr, uint64_t ctr_round, int k, int64_t N,
                                           bool no_full, double a_ins, double a_del, SpecRec* out, SpecKey& key,
-                                          const Early& early = Early()) {
+                                          const Early& early = Early(), int role = kSpecWhole,
+                                          SpecHalf* half = nullptr) {
     const int lane = threadIdx.x & (kWave - 1);
     int type;
     double u2, u7, lnA, ux, uy, uz;
@@ -477,7 +490,7 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
     key.dUp = 0.0;
     if (type != GCMC_MOVE_INSERT && N == 0) {
         key.flags = 1;
-        if (lane == 0) {
+        if (lane == 0 && role != kSpecNew) {
             out->type = type;
             out->flags = 1;
             out->lnA = 0.0;
@@ -529,32 +542,55 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
     }
     const int two = (type == GCMC_MOVE_DISPLACE && !same) ? 1 : 0;
     const int32_t excl_slot = type == GCMC_MOVE_INSERT ? -1 : meta_low(rec.w);
-    const SpecSums S = spec_sums<CR, NG>(B, tab, offs, ownbuf, pq, type, two, p0, p1, c0, c1, cl0, cl1, excl_slot, no_full);
-    const double dUp = type == GCMC_MOVE_DELETE ? -S.su : S.su;
-    const double dWp = type == GCMC_MOVE_DELETE ? -S.sw : S.sw;
+    // everything of the record but the sums, written while the counters are loaded
+    auto mid = [&]() {
+        if (lane == 0 && role != kSpecNew) {
+            out->lnA = lnA;
+            out->u2 = u2;
+            out->u7 = u7;
+            out->type = type;
+            out->flags = 0;
+            out->two = two;
+            out->idx = idx;
+            out->rec = rec;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                out->p0[a] = p0[a];
+                out->p1[a] = p1[a];
+                out->c0[a] = c0[a];
+                out->c1[a] = c1[a];
+            }
+            out->cl0 = cl0;
+            out->cl1 = cl1;
+        }
+    };
+    // half a displacement is the sum at one position, like an insertion's or a deletion's
+    const bool nw = role == kSpecNew;
+    const double q0[3] = {nw ? p1[0] : p0[0], nw ? p1[1] : p0[1], nw ? p1[2] : p0[2]};
+    const int32_t d0[3] = {nw ? c1[0] : c0[0], nw ? c1[1] : c0[1], nw ? c1[2] : c0[2]};
+    const int eff = role == kSpecWhole ? type : (int)GCMC_MOVE_INSERT;
+    const int eff_two = role == kSpecWhole ? two : 0;
+    const SpecSums S = spec_sums<CR, NG>(B, tab, offs, ownbuf, pq, eff, eff_two, q0, p1, d0, c1, nw ? cl1 : cl0, cl1,
+                                         excl_slot, no_full, mid);
+    if (nw) {
+        if (lane == 0) {
+            half->su = S.su;
+            half->sw = S.sw;
+            half->cand = S.cand;
+            half->incut = S.incut;
+            half->cnt1 = S.cnt0;
+        }
+        return;
+    }
+    const bool minus = type == GCMC_MOVE_DELETE || role == kSpecOld;
+    const double dUp = minus ? -S.su : S.su;
+    const double dWp = minus ? -S.sw : S.sw;
     key.idx = idx;
     key.dUp = dUp;
     if (lane == 0) {
         out->dUp = dUp;
         out->dWp = dWp;
-        out->lnA = lnA;
-        out->u2 = u2;
-        out->u7 = u7;
-        out->type = type;
-        out->flags = 0;
-        out->two = two;
-        out->idx = idx;
-        out->rec = rec;
         out->elast = S.elast;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            out->p0[a] = p0[a];
-            out->p1[a] = p1[a];
-            out->c0[a] = c0[a];
-            out->c1[a] = c1[a];
-        }
-        out->cl0 = cl0;
-        out->cl1 = cl1;
         out->cnt0 = S.cnt0;
         out->cnt1 = S.cnt1;
         out->cand = S.cand;
