@@ -13,17 +13,18 @@
 //   * a bit for every N the move can be decided at: is its pick still the particle
 //     it evaluated?
 //
-// Wavefront W decides.  While the others evaluate it prepares the next round (draws,
-// acceptance prefactors) and loads the records of particles N - W .. N - 1; then
-// lane k holds move k of the round and its decision at the current state.  The
-// rejections up to the next accepted or stale move take one ballot; an accepted
-// move is committed (stores only: what it needs came back with its evaluation) and
-// changes N and the later lanes:
+// The last wavefront decides.  While the others evaluate it prepares the next round
+// (draws, acceptance prefactors), loads the records of particles N - W .. N - 1 and,
+// once every move is known but for its sums, finds what each would add to the later
+// ones if it is accepted (the pair terms with the position taken away and the one
+// added, which come within the cutoff of few); then lane k holds move k of the round
+// and its decision at the current state.  The rejections up to the next accepted or
+// stale move take one ballot; an accepted move is committed (stores only: what it
+// needs came back with its evaluation) and changes N and the later lanes:
 //   * a later move whose particle it touched, or one of whose centre cells it
 //     changed (the slots and counts that move would commit with), is stale: it
 //     ends the round and is evaluated again in the next;
-//   * any other later move whose positions come within the cutoff of the position
-//     taken away or added has its energy and virial corrected by those pair terms.
+//   * any other later move has its energy and virial corrected by those pair terms.
 // So every move is decided on exactly the state the sequential chain would have, up
 // to the rounding of its sums.
 //
@@ -31,11 +32,12 @@
 // state of the commit then takes no registers from the evaluation, whose scalar
 // values were spilled and reloaded inside the candidate loop (evaluation alone: 142
 // vector registers and 26 scalar spills; one kernel for both took 256 and 160).  A
-// round of eight moves of the 1.5-million-particle slab takes 8.4 us (12.5 before):
-// the slowest evaluation 6.5 (three dependent memory round trips and the
-// arithmetic, two wavefronts per SIMD), the decision 0.4 and 1.6 per accepted move,
-// the wait for the stores 0.2.  Per move: slab 1.36 -> 1.04 us, 4,000 particles 1.40 -> 1.06,
-// cutoff 4.25 on microcells 2.5 -> 2.2; one box of a batch (waves = 4) 2.7 -> 2.0.
+// round of eight moves of the 1.5-million-particle slab takes 7.6 us (12.5 with the
+// decisions in the first evaluating wavefront, 8.1 with the pair terms computed after
+// each accepted move): the slowest evaluation 6 (three dependent memory round trips
+// and the arithmetic, two wavefronts per SIMD that the vector unit is half busy
+// with), the decision 0.8 and 0.8 per accepted move.  Per move: slab 1.36 -> 0.96 us,
+// 4,000 particles 1.40 -> 0.94, cutoff 4.25 on microcells 2.5 -> 2.08.
 //
 // NG > 0: stencils of more than 32 cells (microcells, Sec. 3.3) go through
 // the evaluation's path with NG groups of 64 cells; the round and the commit
@@ -124,6 +126,10 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
     __shared__ DrawRing<RING> dring;            // draws of moves m .. m + 2W - 1
     __shared__ double pq[W + H][kSpecQueue];    // each wavefront's queue of in-cutoff pairs
     __shared__ int32_t ready[W + H];            // round whose evaluation wavefront w has published
+    __shared__ int32_t known[W];                // round whose move w is known but for its sums
+    // what move j of the round adds to move k's energy and virial changes if it is accepted, and to its pairs
+    __shared__ double corr_u[W][W], corr_w[W][W];
+    __shared__ int32_t corr_n[W][W];
     // the state after a round, by round parity (a wavefront may still read the last round's)
     __shared__ int4 sh_state[2];                // N, moves decided, error
     __shared__ double2 sh_acc[2];               // running acceptance of insertions and deletions
@@ -145,6 +151,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
         if (t < kOffs) offs[t] = ((tz - B.k[2]) * B.M[1] + (ty - B.k[1])) * B.M[0] + (tx - B.k[0]);
     }
     if (tid < W + H) ready[tid] = -1;
+    if (tid < W) known[tid] = -1;
     // draws of the first 2W moves
     for (int t = tid; t < 8 * W; t += blockDim.x) draw_block(B, &dring, ctr0 + (uint64_t)(t >> 2), t & 3);
     __syncthreads();
@@ -191,9 +198,17 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
                     if (role != kSpecNew) pm = __ballot(lane < 2 * W - 1 && np >= 0 &&
                                   (type == GCMC_MOVE_INSERT || spec_pick(u2, u7, np) == idx));
                 };
+                auto pub = [&]() {
+                    if (lane == 0) recs[mv].pickmask = (uint32_t)pm;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                    if (lane == 0) __hip_atomic_store(&known[mv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                };
                 spec_eval<CR, NG, RING>(B, tab, offs, own[wv], pq[wv], &dring, ctr0 + (uint64_t)m, mv, N, no_full, a_ins,
-                                        a_del, &recs[mv], key, early, role, &half_s[rnd & 1][H && wv >= W ? wv - W : 0]);
-                if (lane == 0 && role != kSpecNew) recs[mv].pickmask = (uint32_t)pm;
+                                        a_del, &recs[mv], key, early, role, &half_s[rnd & 1][H && wv >= W ? wv - W : 0],
+                                        pub);
+                if (key.flags & 1) {   // an empty box: nothing to evaluate
+                    if (role != kSpecNew) pub();
+                }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
                 if (lane == 0) __hip_atomic_store(&ready[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -247,47 +262,98 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
             from = from < kend ? from : kend;
         }
         // ------------------------------------------ the evaluations
-        int kw = kend;   // moves whose evaluation arrived
-        if (spin_cap < 0) {
-            kw = 0;
-        } else {
-            int32_t spins = 0;
-            for (;;) {
-                const bool wait = from < kend && __hip_atomic_load(&ready[lane < W + H ? lane : 0], __ATOMIC_ACQUIRE,
-                                                                   __HIP_MEMORY_SCOPE_WORKGROUP) != rnd;
-                const uint64_t late = __ballot(wait);
-                if (late == 0) break;
+        int kw = spin_cap < 0 ? 0 : kend;   // moves whose evaluation arrived
+        int32_t spins = 0;
+        auto wait_for = [&](const int32_t* flag, int move) {   // lane's flag, of that move (kend: none)
+            while (kw > 0) {
+                const bool wait = move < kw && __hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != rnd;
+                if (__ballot(wait) == 0) break;
                 __builtin_amdgcn_s_sleep(1);
                 if (++spins > spin_cap) {
-                    for (int j = kend - 1; j >= 0; --j)
-                        if (__ballot(wait && from == j)) kw = j;   // the first move not whole
+                    for (int j = kw - 1; j >= 0; --j)
+                        if (__ballot(wait && move == j)) kw = j;   // the first move not whole
                     break;
                 }
             }
+            wave_lds_sync();
+        };
+        // the moves but for their sums; meanwhile what each would change in the later ones
+        wait_for(&known[lane < W ? lane : 0], lane < kend ? lane : kend);
+        for (int t = lane; t < W * W; t += kWave) {
+            const int j = t / W, k = t - j * W;
+            if (j < k && k < kw) {
+                const SpecRec& F = recs[j];
+                const SpecRec& G = recs[k];
+                double u = 0.0, w = 0.0;
+                int32_t n = 0;
+                if (((F.flags | G.flags) & 1) == 0) {
+                    const bool fdel = F.type == GCMC_MOVE_DELETE, fins = F.type == GCMC_MOVE_INSERT;
+                    const bool has_new = G.type != GCMC_MOVE_DELETE, has_old = G.type != GCMC_MOVE_INSERT;
+                    const double* fb = F.p1;   // the position added (an insertion's is in p0 and p1)
+                    const double* gn = G.p1;   // the new position
+                    const double out = B.rc2;   // outside the cutoff: no term
+                    // new position minus old one, with the position added (b) and the one taken away (a)
+                    double r_nb = out, r_ob = out, r_na = out, r_oa = out;
+                    if (!fdel) {
+                        if (has_new) r_nb = spec_r2(B, gn[0], gn[1], gn[2], fb[0], fb[1], fb[2]);
+                        if (has_old) r_ob = spec_r2(B, G.p0[0], G.p0[1], G.p0[2], fb[0], fb[1], fb[2]);
+                    }
+                    if (!fins) {
+                        if (has_new) r_na = spec_r2(B, gn[0], gn[1], gn[2], F.p0[0], F.p0[1], F.p0[2]);
+                        if (has_old) r_oa = spec_r2(B, G.p0[0], G.p0[1], G.p0[2], F.p0[0], F.p0[1], F.p0[2]);
+                    }
+                    auto term = [&](double r2, double sign, int32_t pairs) {
+                        if (r2 < out) {
+                            double tw = 0.0;
+                            const double tu = lj_uw_from_r2(r2, B.rc2, B.eps4[0], B.sig2[0], tw);
+                            u += sign * tu;
+                            w += sign * tw;
+                            n += pairs;
+                        }
+                    };
+                    term(r_nb, 1.0, 1);
+                    term(r_ob, -1.0, 1);
+                    term(r_na, -1.0, -1);
+                    term(r_oa, 1.0, -1);
+                }
+                corr_u[j][k] = u;
+                corr_w[j][k] = w;
+                corr_n[j][k] = n;
+            }
         }
-        __builtin_amdgcn_s_setprio(3);
-        wave_lds_sync();
-        const bool mine = lane < kw;
-        const SpecRec& R = recs[mine ? lane : 0];
-        const int32_t type = mine ? R.type : GCMC_MOVE_INSERT;
-        const bool empty = mine && (R.flags & 1) != 0;   // a displacement or deletion in an empty box
+        const bool known_k = lane < kw;
+        const SpecRec& R = recs[known_k ? lane : 0];
+        const int32_t type = known_k ? R.type : GCMC_MOVE_INSERT;
+        const bool empty = known_k && (R.flags & 1) != 0;   // a displacement or deletion in an empty box
         const uint32_t pick = R.pickmask;
-        const int32_t idx = mine && !empty ? (int32_t)R.idx : -1;
+        const int32_t idx = known_k && !empty ? (int32_t)R.idx : -1;
         const int32_t cl0 = R.cl0, cl1 = R.cl1;
         const double lnA = R.lnA;
-        double dUp = mine && !empty ? R.dUp : 0.0, dWp = mine && !empty ? R.dWp : 0.0;
         const bool disp = type == GCMC_MOVE_DISPLACE, ins = type == GCMC_MOVE_INSERT;
         const double p0x = R.p0[0], p0y = R.p0[1], p0z = R.p0[2];   // old, inserted or deleted position
         const double p1x = R.p1[0], p1y = R.p1[1], p1z = R.p1[2];   // a displacement's new position
-        const int32_t two = mine ? R.two : 0;
+        const int32_t two = known_k ? R.two : 0;
+        const int32_t loc = meta_low(R.rec.w);                       // slot of its particle's record
+        // the log prefactor and the tail energy change at the current N, of moves first .. W - 1
+        double lpref = 0.0, dUt = 0.0;
+        auto at_n = [&](int first) {
+            if (disp || lane < first) return;
+            lpref = ins ? lpi[N - lbase] : lpd[N - lbase];
+            dUt = tk * (ins ? (2.0 * (double)N + 1.0) : (1.0 - 2.0 * (double)N));
+        };
+        at_n(0);
+        // the sums
+        wait_for(&ready[lane < W + H ? lane : 0], from);
+        __builtin_amdgcn_s_setprio(3);
+        const bool mine = lane < kw;
+        double dUp = mine && !empty ? R.dUp : 0.0, dWp = mine && !empty ? R.dWp : 0.0;
         const int32_t cnt0 = R.cnt0;                                 // occupancies of its centre cells
         int32_t cnt1 = R.cnt1;
-        const int32_t loc = meta_low(R.rec.w);                       // slot of its particle's record
         const int32_t id_end = meta_low(R.elast.w);                  // particle of its first cell's last entry
         int32_t r_in = R.incut, r_cand = R.cand;
         if constexpr (H > 0) {
             // a displacement's other half
-            const uint64_t dm = __ballot(mine && disp);
+            const uint64_t dm = __ballot(known_k && disp);
             const int h = (int)lanes_below(dm, 0u);
             if (mine && disp && !empty && h < H) {
                 const SpecHalf& F = half_s[rnd & 1][h];
@@ -302,7 +368,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
         }
         const int32_t n_round = N;
         bool stale = false;
-        double dUt = 0.0, arg = 0.0;
+        double arg = 0.0;
         double aft_n = 0.0, aft_u = 0.0, aft_w = 0.0;
         uint64_t accbits = 0;
         int k = 0;
@@ -314,8 +380,6 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
                     bad = N != 0;   // the empty-box rejection holds only while the box is still empty
                 } else {
                     bad = stale || (!ins && ((pick >> (N - n_round + W - 1)) & 1u) == 0);
-                    const double lpref = disp ? 0.0 : (ins ? lpi[N - lbase] : lpd[N - lbase]);
-                    dUt = disp ? 0.0 : tk * (ins ? (2.0 * (double)N + 1.0) : (1.0 - 2.0 * (double)N));
                     arg = spec_arg_fin(B, type, dUp, dUt, lpref);
                     const double dU = dUp + dUt;
                     ok = dU == dU && lnA < arg;
@@ -398,44 +462,19 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
             }
             if (fdisp && ftwo && fcnt1 + 1 > maxc) maxc = fcnt1 + 1;
             if (fins && fcnt0 + 1 > maxc) maxc = fcnt0 + 1;
-            const double fax = read_lane(p0x, f), fay = read_lane(p0y, f), faz = read_lane(p0z, f);
-            const double fbx = fdisp ? read_lane(p1x, f) : fax, fby = fdisp ? read_lane(p1y, f) : fay,
-                         fbz = fdisp ? read_lane(p1z, f) : faz;
             // ---------------------------------- what it means for the later moves of the round
             if (mine && lane > f && !empty) {
                 // its slots, counts or record: the particle it touched, or one of its centre cells changed
                 stale = stale || idx == (fins ? N : fi) || (swap && idx == id_last) || (fdel && idx == N - 1) ||
                         cl0 == c0 || cl0 == c2 || (fdisp && ftwo && cl0 == c1) ||
                         (two && (cl1 == c0 || cl1 == c2 || (fdisp && ftwo && cl1 == c1)));
-                // pairs with the position taken away (a) and added (b): new position minus old one; one at
-                // a time where the four would hold a hundred registers at once
-                const double nx = disp ? p1x : p0x, ny = disp ? p1y : p0y, nz = disp ? p1z : p0z;
-                const bool has_new = disp || ins, has_old = !ins;
-                const double out = B.rc2;   // outside the cutoff: no term
-                double r_nb = out, r_ob = out, r_na = out, r_oa = out;
-                if (!fdel) {
-                    if (has_new) r_nb = spec_r2(B, nx, ny, nz, fbx, fby, fbz);
-                    if (has_old) r_ob = spec_r2(B, p0x, p0y, p0z, fbx, fby, fbz);
-                }
-                if (!fins) {
-                    if (has_new) r_na = spec_r2(B, nx, ny, nz, fax, fay, faz);
-                    if (has_old) r_oa = spec_r2(B, p0x, p0y, p0z, fax, fay, faz);
-                }
-                auto term = [&](double r2, double sign, int32_t pairs) {
-                    if (r2 < out) {
-                        double w = 0.0;
-                        const double u = lj_uw_from_r2(r2, B.rc2, B.eps4[0], B.sig2[0], w);
-                        dUp += sign * u;
-                        dWp += sign * w;
-                        r_in += pairs;
-                    }
-                };
-                term(r_nb, 1.0, 1);
-                term(r_ob, -1.0, 1);
-                term(r_na, -1.0, -1);
-                term(r_oa, 1.0, -1);
+                // its pairs with the position taken away and the one added
+                dUp += corr_u[f][lane];
+                dWp += corr_w[f][lane];
+                r_in += corr_n[f][lane];
             }
             N += fins ? 1 : (fdel ? -1 : 0);
+            at_n(f + 1);
             U += read_lane(dUp, f);
             Wvir += read_lane(dWp, f);
             if (lane == f) {

@@ -420,6 +420,11 @@ struct SpecNoEarly {
     __device__ __forceinline__ void operator()(int, double, double, int64_t) const {}
 };
 
+// The caller's work once the record holds everything but the sums (none by default).
+struct SpecNoPub {
+    __device__ __forceinline__ void operator()() const {}
+};
+
 // Wavefront k evaluates move ctr_round + k against the current state.  NG:
 // 0 for the 32-cell path, else the number of groups of 64 stencil cells the
 // microcell path provides (see above).  RING > 0: the draws come from `dr`
@@ -427,12 +432,12 @@ struct SpecNoEarly {
 // here, for k < 16.  pq: this wavefront's pair queue (kSpecQueue doubles of
 // LDS).  role: the part of a displacement (any other move: kSpecWhole); for kSpecNew
 // the sums go to `half` and nothing to `out`.
-template <int CR, int NG, int RING, typename Early = SpecNoEarly>
+template <int CR, int NG, int RING, typename Early = SpecNoEarly, typename Pub = SpecNoPub>
 __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
                                           double* pq, const DrawRing<RING>* dr, uint64_t ctr_round, int k, int64_t N,
                                           bool no_full, double a_ins, double a_del, SpecRec* out, SpecKey& key,
                                           const Early& early = Early(), int role = kSpecWhole,
-                                          SpecHalf* half = nullptr) {
+                                          SpecHalf* half = nullptr, const Pub& pub = Pub()) {
     const int lane = threadIdx.x & (kWave - 1);
     int type;
     double u2, u7, lnA, ux, uy, uz;
@@ -563,6 +568,7 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
             out->cl0 = cl0;
             out->cl1 = cl1;
         }
+        if (role != kSpecNew) pub();
     };
     // half a displacement is the sum at one position, like an insertion's or a deletion's
     const bool nw = role == kSpecNew;
