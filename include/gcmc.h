@@ -282,8 +282,10 @@ int gcmc_commit(gcmc_box* box, const gcmc_move* d_move, const double* d_dU_pair,
 /* Launch shape of the chain kernels (the autotuner's choice).  rows > 0: one
  * move at a time, `waves` wavefronts per workgroup and `rows` candidate slots
  * per lane per pass (1x8, 2x8, 4x2, 4x4, 4x8, 8x2, 8x4).  rows = 0:
- * speculative rounds, `waves` (2, 4, 8 or 16) wavefronts' worth of consecutive
- * moves (2, 3, 8 and 15 of them) evaluated at once, one per wavefront, against
+ * speculative rounds, `waves` (2, 4, 8 or 16) choosing how many consecutive
+ * moves are evaluated at once, one per wavefront (2, 7, 11 and 15 of them; 15 for
+ * 8 too where the stencil has more than 32 cells; 2 and 4 let several boxes of a
+ * batch share a compute unit), against
  * the round's starting state and decided in order by one more wavefront, each
  * corrected for the earlier accepted moves of its round or, where one of those
  * changed its particle or the cell it would commit to, evaluated again in the

@@ -24,6 +24,8 @@
 //   * a later move whose particle it touched, or one of whose centre cells it
 //     changed (the slots and counts that move would commit with), is stale: it
 //     ends the round and is evaluated again in the next;
+//   * so is one with a pair term so large (an overlap, beyond 64 times the well depth's
+//     four) that adding and taking it away again would cost its sums digits;
 //   * any other later move has its energy and virial corrected by those pair terms.
 // So every move is decided on exactly the state the sequential chain would have, up
 // to the rounding of its sums.
@@ -31,22 +33,18 @@
 // The deciding wavefront is one of its own, not one that also evaluates: the
 // state of the commit then takes no registers from the evaluation, whose scalar
 // values were spilled and reloaded inside the candidate loop (evaluation alone: 142
-// vector registers and 26 scalar spills; one kernel for both took 256 and 160).  A
-// round of eight moves of the 1.5-million-particle slab takes 7.6 us (12.5 with the
-// decisions in the first evaluating wavefront, 8.1 with the pair terms computed after
-// each accepted move): the slowest evaluation 6 (three dependent memory round trips
-// and the arithmetic, two wavefronts per SIMD that the vector unit is half busy
-// with), the decision 0.8 and 0.8 per accepted move.  Per move: slab 1.36 -> 0.96 us,
-// 4,000 particles 1.40 -> 0.94, cutoff 4.25 on microcells 2.5 -> 2.08.
+// vector registers and 26 scalar spills; one kernel for both took 256 and 160).
+// With eight moves a round of the 1.5-million-particle slab took 7.6 us (12.5 with
+// the decisions in the first evaluating wavefront, 8.1 with the pair terms computed
+// after each accepted move): the slowest evaluation 6 (three dependent memory round
+// trips and the arithmetic; a wavefront issues an instruction every eight cycles or
+// so, so more of them side by side cost little), the decision 0.8 and 0.8 per
+// accepted move.  Per move, waves = 8: slab 1.36 -> 0.83 us, 4,000 particles 1.40 -> 0.87,
+// cutoff 4.25 on microcells 2.5 -> 1.7.
 //
 // NG > 0: stencils of more than 32 cells (microcells, Sec. 3.3) go through
 // the evaluation's path with NG groups of 64 cells; the round and the commit
-// are the same.  There a round waits for its displacements, which sum over two
-// stencils of several hundred candidates each, so H helpers take the new positions of
-// the round's first H displacements (cutoff 4.25 on microcells, 87,296 particles: 2.31 ->
-// 2.12 us a move with three, all that 160 registers leave room for).  With the short
-// stencils of NG = 0 the helpers' own draws and counters cost what they save (slab
-// 10.19 ms without, 10.45 with three; helpers at a raised wave priority 10.6).
+// are the same.
 #include "spec_eval.h"
 
 namespace gcmc {
@@ -62,6 +60,7 @@ __device__ __forceinline__ double spec_arg_fin(const DevBox& B, int type, double
 // Log acceptance prefactors at N = base + t: insertion V / (Lambda^3 (N + 1)),
 // deletion Lambda^3 N / V (entries at N < 0 are never read).  Filled by one wavefront.
 constexpr int kSpecPref = 128;
+constexpr int32_t kSpecAgain = INT32_MIN;   // in place of a pair count: evaluate the later move again
 __device__ __attribute__((noinline)) void spec_prefactors(double V, double lambda3, double* lpi, double* lpd, int32_t base) {
     const int lane = threadIdx.x & (kWave - 1);
     for (int t = lane; t < kSpecPref; t += kWave) {
@@ -105,9 +104,9 @@ __device__ __attribute__((noinline)) void spec_draws(DrawRing<RING>* ring, uint6
     B.seed = seed; B.box_id = box_id; B.p_disp = p_disp;
     draw_block(B, ring, ctr, b);
 }
-// W evaluating wavefronts, H helpers and one that decides.
-template <int W, int H, int CR, int NG>
-__global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spec(const DevBox* __restrict__ boxes,
+// W evaluating wavefronts and one that decides.
+template <int W, int CR, int NG>
+__global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void k_chain_spec(const DevBox* __restrict__ boxes,
                                                                const int32_t* __restrict__ order, int64_t n_moves,
                                                                uint64_t ctr0, gcmc_stats* stats, gcmc_log* trace) {
     constexpr int kOffs = NG ? NG * kWave / 2 : 64;    // stencil slots with a precomputed linear offset
@@ -115,8 +114,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
     __shared__ uint32_t tab[kMaxStencil];
     __shared__ int32_t offs[kOffs];
     __shared__ SpecRec recs_s[2][W];            // the round's evaluations, by round parity
-    __shared__ SpecHalf half_s[2][H ? H : 1];   // the helpers', the same
-    __shared__ __align__(8) uint32_t own[W + H][spec_own_words(NG)];   // cell bases and start masks, or record indices
+    __shared__ __align__(8) uint32_t own[W][spec_own_words(NG)];   // cell bases and start masks, or record indices
     __shared__ double4 top[2 * W];              // records of particles base .. base + 2W - 1
     __shared__ double lpi[kSpecPref], lpd[kSpecPref];   // the deciding wavefront's prefactors
     // its statistics, lane k's sums over the moves it decided as move k of a round (counts as doubles, exact
@@ -124,8 +122,8 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
     enum { kAtt, kAcc = 3, kSumN = 6, kSumN2, kSumU, kSumW, kStencils, kCand, kEvals, kIncut, kStats };
     __shared__ double acc_s[kStats][W];
     __shared__ DrawRing<RING> dring;            // draws of moves m .. m + 2W - 1
-    __shared__ double pq[W + H][kSpecQueue];    // each wavefront's queue of in-cutoff pairs
-    __shared__ int32_t ready[W + H];            // round whose evaluation wavefront w has published
+    __shared__ double pq[W][kSpecQueue];    // each wavefront's queue of in-cutoff pairs
+    __shared__ int32_t ready[W];            // round whose evaluation wavefront w has published
     __shared__ int32_t known[W];                // round whose move w is known but for its sums
     // what move j of the round adds to move k's energy and virial changes if it is accepted, and to its pairs
     __shared__ double corr_u[W][W], corr_w[W][W];
@@ -150,7 +148,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
         tab[t] = pk;
         if (t < kOffs) offs[t] = ((tz - B.k[2]) * B.M[1] + (ty - B.k[1])) * B.M[0] + (tx - B.k[0]);
     }
-    if (tid < W + H) ready[tid] = -1;
+    if (tid < W) ready[tid] = -1;
     if (tid < W) known[tid] = -1;
     // draws of the first 2W moves
     for (int t = tid; t < 8 * W; t += blockDim.x) draw_block(B, &dring, ctr0 + (uint64_t)(t >> 2), t & 3);
@@ -159,56 +157,30 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
     if (wrong) err = GCMC_ERR_UNSUPPORTED;
     int64_t m = 0;
     int32_t rnd = 0;                   // rounds begun
-    // the displacements among the round's moves m + j, j < n (bit j)
-    auto displacements = [&](int64_t m0, int n) {
-        const int t = lane < n ? dring.type[(int)((ctr0 + (uint64_t)m0 + (uint64_t)lane) & (uint64_t)(RING - 1))] : -1;
-        return (uint32_t)__ballot(t == GCMC_MOVE_DISPLACE);
-    };
-    // the h-th of them (W if there are no more)
-    auto nth = [&](uint32_t bits, int h) {
-        for (int i = 0; i < h && bits; ++i) bits &= bits - 1u;
-        return bits ? (int)__builtin_ctz(bits) : W;
-    };
-    if (wv < W + H) {
-        // ================================================ evaluate move m + wv of every round, or as helper
-        // h = wv - W the new position of its h-th displacement
+    if (wv < W) {
+        // ================================================ evaluate move m + wv of every round
         double a_ins = 0.5, a_del = 0.5;   // running acceptance of insertions and deletions
         while (err == GCMC_OK && m < n_moves) {
             rnd = rnd == INT32_MAX ? 1 : rnd + 1;   // round numbers stay positive (a flag starts at -1)
             SpecRec* recs = recs_s[rnd & 1];
-            int mv = wv, role = kSpecWhole;
-            if constexpr (H > 0) {
-                const uint32_t dm = displacements(m, n_moves - m < W ? (int)(n_moves - m) : W);
-                if (wv >= W) {
-                    mv = nth(dm, wv - W);
-                    role = kSpecNew;
-                } else if ((dm >> wv & 1u) != 0 && __builtin_popcount(dm & ((1u << wv) - 1u)) < H) {
-                    role = kSpecOld;
-                }
-                mv = uni(mv);
-                role = uni(role);
-            }
-            if (mv < W && m + mv < n_moves) {
+            if (m + wv < n_moves) {
                 SpecKey key;
                 // is the pick at every N the move can meet (lane o: N - (W - 1) + o) the evaluated one? (found
                 // while the picked record is loaded)
                 const int32_t np = N - (W - 1) + lane;
                 uint64_t pm = 0;
                 auto early = [&](int type, double u2, double u7, int64_t idx) {
-                    if (role != kSpecNew) pm = __ballot(lane < 2 * W - 1 && np >= 0 &&
+                    pm = __ballot(lane < 2 * W - 1 && np >= 0 &&
                                   (type == GCMC_MOVE_INSERT || spec_pick(u2, u7, np) == idx));
                 };
                 auto pub = [&]() {
-                    if (lane == 0) recs[mv].pickmask = (uint32_t)pm;
+                    if (lane == 0) recs[wv].pickmask = (uint32_t)pm;
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                    if (lane == 0) __hip_atomic_store(&known[mv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (lane == 0) __hip_atomic_store(&known[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 };
-                spec_eval<CR, NG, RING>(B, tab, offs, own[wv], pq[wv], &dring, ctr0 + (uint64_t)m, mv, N, no_full, a_ins,
-                                        a_del, &recs[mv], key, early, role, &half_s[rnd & 1][H && wv >= W ? wv - W : 0],
-                                        pub);
-                if (key.flags & 1) {   // an empty box: nothing to evaluate
-                    if (role != kSpecNew) pub();
-                }
+                spec_eval<CR, NG, RING>(B, tab, offs, own[wv], pq[wv], &dring, ctr0 + (uint64_t)m, wv, N, no_full, a_ins,
+                                        a_del, &recs[wv], key, early, pub);
+                if (key.flags & 1) pub();   // an empty box: nothing to evaluate
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
                 if (lane == 0) __hip_atomic_store(&ready[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -223,7 +195,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
         }
         return;
     }
-    // ==================================================== decide and commit (wavefront W + H)
+    // ==================================================== decide and commit (wavefront W)
     int64_t err_move = st->error_move;
     if (wrong) err_move = (int64_t)ctr0;
     double U = st->u_pair;
@@ -254,31 +226,24 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
             spec_prefactors(B.V, B.lambda3, lpi, lpd, lbase);
         }
         if (has_top) top[lane] = tv;
-        // lane w's wavefront evaluates (part of) move from[w] of this round, kend if none of it
-        int from = lane < kend ? lane : kend;
-        if constexpr (H > 0) {
-            const uint32_t dm = displacements(m, kend);
-            if (lane >= W && lane < W + H) from = nth(dm, lane - W);
-            from = from < kend ? from : kend;
-        }
         // ------------------------------------------ the evaluations
         int kw = spin_cap < 0 ? 0 : kend;   // moves whose evaluation arrived
         int32_t spins = 0;
-        auto wait_for = [&](const int32_t* flag, int move) {   // lane's flag, of that move (kend: none)
+        auto wait_for = [&](const int32_t* flag) {   // lane's flag, of move m + lane
             while (kw > 0) {
-                const bool wait = move < kw && __hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != rnd;
-                if (__ballot(wait) == 0) break;
+                const bool wait = lane < kw && __hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != rnd;
+                const uint64_t late = __ballot(wait);
+                if (late == 0) break;
                 __builtin_amdgcn_s_sleep(1);
                 if (++spins > spin_cap) {
-                    for (int j = kw - 1; j >= 0; --j)
-                        if (__ballot(wait && move == j)) kw = j;   // the first move not whole
+                    kw = (int)__builtin_ctzll(late);
                     break;
                 }
             }
             wave_lds_sync();
         };
         // the moves but for their sums; meanwhile what each would change in the later ones
-        wait_for(&known[lane < W ? lane : 0], lane < kend ? lane : kend);
+        wait_for(&known[lane < W ? lane : 0]);
         for (int t = lane; t < W * W; t += kWave) {
             const int j = t / W, k = t - j * W;
             if (j < k && k < kw) {
@@ -286,6 +251,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
                 const SpecRec& G = recs[k];
                 double u = 0.0, w = 0.0;
                 int32_t n = 0;
+                bool big = false;   // a term that would take digits from the sum it is added to
                 if (((F.flags | G.flags) & 1) == 0) {
                     const bool fdel = F.type == GCMC_MOVE_DELETE, fins = F.type == GCMC_MOVE_INSERT;
                     const bool has_new = G.type != GCMC_MOVE_DELETE, has_old = G.type != GCMC_MOVE_INSERT;
@@ -303,12 +269,13 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
                         if (has_old) r_oa = spec_r2(B, G.p0[0], G.p0[1], G.p0[2], F.p0[0], F.p0[1], F.p0[2]);
                     }
                     auto term = [&](double r2, double sign, int32_t pairs) {
-                        if (r2 < out) {
+                        if (r2 < out) {   // (at most a handful of the round's pairs)
                             double tw = 0.0;
                             const double tu = lj_uw_from_r2(r2, B.rc2, B.eps4[0], B.sig2[0], tw);
                             u += sign * tu;
                             w += sign * tw;
                             n += pairs;
+                            big = big || !(__builtin_fabs(tu) <= 64.0 * B.eps4[0]);
                         }
                     };
                     term(r_nb, 1.0, 1);
@@ -318,7 +285,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
                 }
                 corr_u[j][k] = u;
                 corr_w[j][k] = w;
-                corr_n[j][k] = n;
+                corr_n[j][k] = big ? kSpecAgain : n;
             }
         }
         const bool known_k = lane < kw;
@@ -343,29 +310,13 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
         };
         at_n(0);
         // the sums
-        wait_for(&ready[lane < W + H ? lane : 0], from);
+        wait_for(&ready[lane < W ? lane : 0]);
         __builtin_amdgcn_s_setprio(3);
         const bool mine = lane < kw;
         double dUp = mine && !empty ? R.dUp : 0.0, dWp = mine && !empty ? R.dWp : 0.0;
-        const int32_t cnt0 = R.cnt0;                                 // occupancies of its centre cells
-        int32_t cnt1 = R.cnt1;
+        const int32_t cnt0 = R.cnt0, cnt1 = R.cnt1;                  // occupancies of its centre cells
         const int32_t id_end = meta_low(R.elast.w);                  // particle of its first cell's last entry
-        int32_t r_in = R.incut, r_cand = R.cand;
-        if constexpr (H > 0) {
-            // a displacement's other half
-            const uint64_t dm = __ballot(known_k && disp);
-            const int h = (int)lanes_below(dm, 0u);
-            if (mine && disp && !empty && h < H) {
-                const SpecHalf& F = half_s[rnd & 1][h];
-                dUp += F.su;
-                dWp += F.sw;
-                r_in += F.incut;
-                if (two) {
-                    r_cand += F.cand;
-                    cnt1 = F.cnt1;
-                }
-            }
-        }
+        int32_t r_in = R.incut;
         const int32_t n_round = N;
         bool stale = false;
         double arg = 0.0;
@@ -472,6 +423,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
                 dUp += corr_u[f][lane];
                 dWp += corr_w[f][lane];
                 r_in += corr_n[f][lane];
+                stale = stale || corr_n[f][lane] == kSpecAgain;
             }
             N += fins ? 1 : (fdel ? -1 : 0);
             at_n(f + 1);
@@ -506,6 +458,7 @@ __global__ __launch_bounds__(kWave*(W + H + 1), W <= 4 ? 3 : 1) void k_chain_spe
         // (the next round's evaluations run meanwhile).  The candidates of a move are those of the state
         // it was decided on: each earlier accepted move of the round that took a particle out of, or put
         // one into, one of its stencils changes their number.
+        int32_t r_cand = R.cand;
         for (uint64_t left = accbits & ((1ull << k) - 1ull); left; left &= left - 1ull) {
             const int f = (int)__builtin_ctzll(left);
             const int32_t tf = __builtin_amdgcn_readlane(type, f), ftwo = __builtin_amdgcn_readlane(two, f);
@@ -593,30 +546,35 @@ using spec_fn = void (*)(const DevBox*, const int32_t*, int64_t, uint64_t, gcmc_
 struct SpecCfg {
     int key;   // the waves value of gcmc_box_set_launch that selects it
     int w;     // moves evaluated at once
-    int h;     // helpers
     int ng;    // groups of 64 stencil cells of the microcell path, 0 for the 32-cell path
     spec_fn f;
 };
 
-// waves = 2 and 8: that many moves at once and the deciding wavefront beside them
-// (and helpers for the microcell path).  waves = 4: three moves and the deciding one,
-// so that a compute unit holds two such boxes or one beside an LDS-held box (five wavefronts of 160 registers put two on the first
-// SIMD, and a batch of 512 boxes then ran in two rounds: 3.51 ms per 1,000 moves, 2.55
-// with four wavefronts).  waves = 16: 15 moves, 16 wavefronts being a workgroup's most.
-// Seven moves for waves = 8: the slab's 10,000 moves take 11.3 ms against 10.4 with eight.
+// What waves selects: how many moves are evaluated at once, the deciding wavefront
+// beside them.  More moves hide each other's latencies and share the decision, but
+// an accepted move makes more of them stale, and a wavefront has fewer registers.
+// 2: two.  4: seven in 128 registers, so that a compute unit holds two such boxes, or
+// one and an LDS-held one: 64 boxes, 1,000 moves 2.35 ms with three moves (160
+// registers, three boxes), 1.38 with seven; 512 boxes 2.7 and 1.9; 1,024 boxes 3.7 and 3.1.
+// 8: eleven, the most that leave 160 registers: eight took 9.6 ms for the slab's
+// 10,000 moves, eleven 8.3, and 15 (128 registers) 7.9, but at a density of 0.3, where
+// one move in four is accepted, 1.37 ms for 1,000 moves with eleven, 1.43 with 15, and in
+// a box of 128 particles 1.42 and 1.74.  On microcells, where the evaluation is longer,
+// 15: 4,000 moves at a cutoff of 4.25 took 8.3 ms with eight, 7.8 with eleven, 7.1 with 13 and
+// 6.8 with 15.  16: 15, a workgroup having 16 wavefronts at most.
 static const SpecCfg kSpecCfgs[] = {
-    {2, 2, 0, 0, k_chain_spec<2, 0, 8, 0>},
-    {4, 3, 0, 0, k_chain_spec<3, 0, 8, 0>},
-    {8, 8, 0, 0, k_chain_spec<8, 0, 8, 0>},
-    {16, 15, 0, 0, k_chain_spec<15, 0, 4, 0>},
-    {2, 2, 1, kSpecGroupsSmall, k_chain_spec<2, 1, 8, kSpecGroupsSmall>},
-    {4, 3, 0, kSpecGroupsSmall, k_chain_spec<3, 0, 8, kSpecGroupsSmall>},
-    {8, 8, 3, kSpecGroupsSmall, k_chain_spec<8, 3, 8, kSpecGroupsSmall>},
-    {16, 15, 0, kSpecGroupsSmall, k_chain_spec<15, 0, 4, kSpecGroupsSmall>},
-    {2, 2, 1, kSpecGroups, k_chain_spec<2, 1, 8, kSpecGroups>},
-    {4, 3, 0, kSpecGroups, k_chain_spec<3, 0, 8, kSpecGroups>},
-    {8, 8, 3, kSpecGroups, k_chain_spec<8, 3, 8, kSpecGroups>},
-    {16, 15, 0, kSpecGroups, k_chain_spec<15, 0, 4, kSpecGroups>},
+    {2, 2, 0, k_chain_spec<2, 8, 0>},
+    {4, 7, 0, k_chain_spec<7, 4, 0>},
+    {8, 11, 0, k_chain_spec<11, 8, 0>},
+    {16, 15, 0, k_chain_spec<15, 4, 0>},
+    {2, 2, kSpecGroupsSmall, k_chain_spec<2, 8, kSpecGroupsSmall>},
+    {4, 7, kSpecGroupsSmall, k_chain_spec<7, 4, kSpecGroupsSmall>},
+    {8, 15, kSpecGroupsSmall, k_chain_spec<15, 4, kSpecGroupsSmall>},
+    {16, 15, kSpecGroupsSmall, k_chain_spec<15, 4, kSpecGroupsSmall>},
+    {2, 2, kSpecGroups, k_chain_spec<2, 8, kSpecGroups>},
+    {4, 7, kSpecGroups, k_chain_spec<7, 4, kSpecGroups>},
+    {8, 15, kSpecGroups, k_chain_spec<15, 4, kSpecGroups>},
+    {16, 15, kSpecGroups, k_chain_spec<15, 4, kSpecGroups>},
 };
 
 // Groups of 64 cells the box's stencils need: 0 (the 32-cell path) for
@@ -646,7 +604,7 @@ int launch_chain_spec(const DevBox* d_boxes, const int32_t* d_order, int n_boxes
                       uint64_t ctr0, gcmc_stats* stats, gcmc_log* log, hipStream_t s, int ng) {
     for (const SpecCfg& c : kSpecCfgs) {
         if (c.key == waves && c.ng == ng) {
-            hipLaunchKernelGGL(c.f, dim3(n_boxes), dim3(kWave * (c.w + c.h + 1)), 0, s, d_boxes, d_order, n_moves, ctr0, stats,
+            hipLaunchKernelGGL(c.f, dim3(n_boxes), dim3(kWave * (c.w + 1)), 0, s, d_boxes, d_order, n_moves, ctr0, stats,
                                log);
             return 0;
         }

@@ -83,14 +83,6 @@ struct SpecRec {
     int32_t cand, evals, incut, pad2;
 };
 
-// Which part of a displacement an evaluation takes: both positions, the old one
-// (the move's own record), or the new one (a helper's sums alone).
-enum { kSpecWhole = 0, kSpecOld = 1, kSpecNew = 2 };
-struct SpecHalf {
-    double su, sw;                      // pair energy and virial at the new position
-    int32_t cand, incut, cnt1, pad;     // of its stencil; the occupancy of its centre cell
-};
-
 // The values of an evaluation the round kernel decides with in advance.
 struct SpecKey {
     int32_t type, flags;
@@ -430,14 +422,12 @@ struct SpecNoPub {
 // microcell path provides (see above).  RING > 0: the draws come from `dr`
 // (the moves ctr_round .. ctr_round + k must be in it); RING = 0: computed
 // here, for k < 16.  pq: this wavefront's pair queue (kSpecQueue doubles of
-// LDS).  role: the part of a displacement (any other move: kSpecWhole); for kSpecNew
-// the sums go to `half` and nothing to `out`.
+// LDS).
 template <int CR, int NG, int RING, typename Early = SpecNoEarly, typename Pub = SpecNoPub>
 __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
                                           double* pq, const DrawRing<RING>* dr, uint64_t ctr_round, int k, int64_t N,
                                           bool no_full, double a_ins, double a_del, SpecRec* out, SpecKey& key,
-                                          const Early& early = Early(), int role = kSpecWhole,
-                                          SpecHalf* half = nullptr, const Pub& pub = Pub()) {
+                                          const Early& early = Early(), const Pub& pub = Pub()) {
     const int lane = threadIdx.x & (kWave - 1);
     int type;
     double u2, u7, lnA, ux, uy, uz;
@@ -495,7 +485,7 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
     key.dUp = 0.0;
     if (type != GCMC_MOVE_INSERT && N == 0) {
         key.flags = 1;
-        if (lane == 0 && role != kSpecNew) {
+        if (lane == 0) {
             out->type = type;
             out->flags = 1;
             out->lnA = 0.0;
@@ -549,7 +539,7 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
     const int32_t excl_slot = type == GCMC_MOVE_INSERT ? -1 : meta_low(rec.w);
     // everything of the record but the sums, written while the counters are loaded
     auto mid = [&]() {
-        if (lane == 0 && role != kSpecNew) {
+        if (lane == 0) {
             out->lnA = lnA;
             out->u2 = u2;
             out->u7 = u7;
@@ -568,29 +558,12 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
             out->cl0 = cl0;
             out->cl1 = cl1;
         }
-        if (role != kSpecNew) pub();
+        pub();
     };
-    // half a displacement is the sum at one position, like an insertion's or a deletion's
-    const bool nw = role == kSpecNew;
-    const double q0[3] = {nw ? p1[0] : p0[0], nw ? p1[1] : p0[1], nw ? p1[2] : p0[2]};
-    const int32_t d0[3] = {nw ? c1[0] : c0[0], nw ? c1[1] : c0[1], nw ? c1[2] : c0[2]};
-    const int eff = role == kSpecWhole ? type : (int)GCMC_MOVE_INSERT;
-    const int eff_two = role == kSpecWhole ? two : 0;
-    const SpecSums S = spec_sums<CR, NG>(B, tab, offs, ownbuf, pq, eff, eff_two, q0, p1, d0, c1, nw ? cl1 : cl0, cl1,
-                                         excl_slot, no_full, mid);
-    if (nw) {
-        if (lane == 0) {
-            half->su = S.su;
-            half->sw = S.sw;
-            half->cand = S.cand;
-            half->incut = S.incut;
-            half->cnt1 = S.cnt0;
-        }
-        return;
-    }
-    const bool minus = type == GCMC_MOVE_DELETE || role == kSpecOld;
-    const double dUp = minus ? -S.su : S.su;
-    const double dWp = minus ? -S.sw : S.sw;
+    const SpecSums S = spec_sums<CR, NG>(B, tab, offs, ownbuf, pq, type, two, p0, p1, c0, c1, cl0, cl1, excl_slot, no_full,
+                                         mid);
+    const double dUp = type == GCMC_MOVE_DELETE ? -S.su : S.su;
+    const double dWp = type == GCMC_MOVE_DELETE ? -S.sw : S.sw;
     key.idx = idx;
     key.dUp = dUp;
     if (lane == 0) {

@@ -43,3 +43,26 @@ def test_rounds(name, waves):
         ref.set_launch(4, 4)
         st, _ = ref.step(moves, counter0=0)
         assert [int(r["stats"][f]) for f in WORK] == [int(st[f]) for f in WORK]
+
+
+@pytest.mark.parametrize("waves", [2, 4, 8, 16])
+def test_rounds_with_overlaps(waves):
+    """So hot that overlaps are accepted: an accepted move takes away or adds pair terms of 1e9 and
+    more to later moves of its round, whose own sums are of order 100 and are compared as such."""
+    from paper_1408_3764_amd.box import Box
+    wb = workloads.random_box(120, 6.5, rc=2.5, T=1e9, seed=77, mu=0.0)
+    moves, max_n = 600, 900
+    p = oracle.make_params(wb.L, 2.5, beta=wb.beta, mu=0.0)
+    b = Box.from_workload(wb, max_n=max_n, cell_cap=96)
+    b.set_launch(waves, 0)
+    b.total_energy()
+    _, log = b.step(moves, counter0=0, log=True)
+    _, _, olog = oracle.chain(wb.pos, moves, p, seed=wb.seed, max_n=max_n)
+    big = 0
+    for g, o in zip(log, olog):
+        assert int(g["accepted"]) == int(o["accepted"]) and int(g["index"]) == int(o["index"])
+        if int(o["flags"]) & 1:
+            continue
+        assert abs(g["dU_pair"] - o["dU_pair"]) <= 1e-10 * max(abs(o["dU_pair"]), o["sumabs"])
+        big += abs(o["dU_pair"]) > 1e6
+    assert big > 20
