@@ -24,7 +24,7 @@
 // and only an accepted move (about one in eight) costs a serial step: N, the
 // running sums and the LDS copy change, and the later lanes add its corrections and
 // decide again.  Deciding move by move took 0.85 us each, two thirds of a round:
-// 512 particles 1.60 -> 0.84 us per move, 1,400 particles 2.3 -> 1.4.  What bounds
+// 512 particles 1.60 -> 0.84 us per move, 1,400 particles 2.3 -> 1.4 (waves = 8).  What bounds
 // it now is the latency of one wavefront's evaluation (rows of 64 particles taken
 // two to four at a time) and about 1 us of decision per round.
 // Particles with an index of kResCap or more (a box that grows past it) are read
@@ -95,8 +95,10 @@ __device__ __forceinline__ double res_pair(double r2, double rc2, double eps4, d
     return in ? (over ? __builtin_inf() : eps4 * (s12 - s6)) : 0.0;
 }
 
-template <int W>
-__global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __restrict__ boxes,
+// W moves at a time, S wavefronts for each; OCC: wavefronts a SIMD must have room for
+// (the register bound).
+template <int W, int S, int OCC>
+__global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBox* __restrict__ boxes,
                                                               const int32_t* __restrict__ order, int64_t n_moves,
                                                               uint64_t ctr0, gcmc_stats* stats, gcmc_log* trace) {
     __shared__ double px[kResCap], py[kResCap], pz[kResCap];
@@ -105,19 +107,20 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     // log acceptance prefactors for N = lbase + t: insertion V / (Lambda^3 (N + 1)), deletion
     // Lambda^3 N / V (the moves prepared together change N by at most one each)
     __shared__ double lpi[2 * kResRing + 1], lpd[2 * kResRing + 1];
-    __shared__ double pq[W][kResQueue];   // each wavefront's queue of in-cutoff pairs
-    // move k's evaluation: pair energy and virial change against the round's start, pairs inside
-    // the cutoff, and bit o: its pick at N_round - (W - 1) + o is the particle it evaluated
-    __shared__ double ev_u[W], ev_w[W];
-    __shared__ int32_t ev_in[W];
+    __shared__ double pq[W * S][kResQueue];   // each wavefront's queue of in-cutoff pairs
+    // move k's evaluation by each of its wavefronts: pair energy and virial change against the
+    // round's start, pairs inside the cutoff, and bit o: its pick at N_round - (W - 1) + o is the
+    // particle it evaluated
+    __shared__ double ev_u[S][W], ev_w[S][W];
+    __shared__ int32_t ev_in[S][W];
     __shared__ uint32_t ev_pick[W];
     // corr[j][k]: the change of move k's pair energy and virial if move j < k of the round is
     // accepted (move j's removed and added positions against move k's positions)
     __shared__ double corr_e[W][W], corr_w[W][W];
-    __shared__ int32_t ready[W];          // round whose evaluation wavefront w has published
+    __shared__ int32_t ready[W * S];      // round whose evaluation wavefront w has published
     // the state after a round, by round parity (a wavefront may still read the last round's)
     __shared__ int4 sh_state[2];   // N, moves decided, error
-    __shared__ int32_t wred[W];
+    __shared__ int32_t wred[W * S];
     __shared__ int32_t sh_flag;
     const int bi = order ? order[blockIdx.x] : (int)blockIdx.x;
     const DevBox B = hot_copy(boxes[blockIdx.x]);
@@ -135,6 +138,9 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     const double tk = B.tailK[0];
     const double rc2 = B.rc2, eps4 = B.eps4[0], sig2 = B.sig2[0];
     const int32_t spin_cap = wait_bound(B.wait_limit);
+    // wavefront wv takes part `part` of move `own` of a round: every parts-th group of rows (a bound
+    // that lets nobody wait leaves a move to one wavefront)
+    const int parts = spin_cap < 0 ? 1 : S, part = wv / W, own = wv - part * W;
     // statistics, kept by wavefront 0: per-lane sums over the moves lane k decided as move k of a
     // round, added up at the end (counts as doubles, exact below 2^53)
     double att0 = 0.0, att1 = 0.0, att2 = 0.0, acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
@@ -165,7 +171,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
         }
     }
     if (tid == 0) sh_flag = 0;
-    if (tid < W) ready[tid] = -1;
+    if (tid < W * S) ready[tid] = -1;
     if (err == GCMC_OK && B.ns != 1) {
         err = GCMC_ERR_UNSUPPORTED;
         err_move = (int64_t)ctr0;
@@ -215,7 +221,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
             __syncthreads();
         }
         const int kend = (n_moves - m) < W ? (int)(n_moves - m) : W;
-        if (wv < kend) {
+        if (own < kend && part < parts) {
             // ---------------------------------------- the round's moves, lane k: move m + k
             int32_t type = GCMC_MOVE_INSERT, idx = -1;
             double u2 = 0.0, lnA = 0.0;
@@ -245,14 +251,14 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                     }
                 }
             }
-            // ---------------------------------------- evaluate move m + wv
-            const int mt = __builtin_amdgcn_readlane(type, wv);
-            const int32_t mi = __builtin_amdgcn_readlane(idx, wv);
+            // ---------------------------------------- evaluate move m + own, or part of it
+            const int mt = __builtin_amdgcn_readlane(type, own);
+            const int32_t mi = __builtin_amdgcn_readlane(idx, own);
             if (mt == GCMC_MOVE_INSERT || N > 0) {
                 const bool disp = mt == GCMC_MOVE_DISPLACE, ins = mt == GCMC_MOVE_INSERT;
-                const double p0x = read_lane(ins ? bx : ax, wv), p0y = read_lane(ins ? by : ay, wv),
-                             p0z = read_lane(ins ? bz : az, wv);
-                const double p1x = read_lane(bx, wv), p1y = read_lane(by, wv), p1z = read_lane(bz, wv);
+                const double p0x = read_lane(ins ? bx : ax, own), p0y = read_lane(ins ? by : ay, own),
+                             p0z = read_lane(ins ? bz : az, own);
+                const double p1x = read_lane(bx, own), p1y = read_lane(by, own), p1z = read_lane(bz, own);
                 double* q = pq[wv];
                 uint32_t tail = 0;
                 int32_t n_in = 0;
@@ -277,7 +283,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                 auto rows = [&](auto two_t) {
                     constexpr bool TWO = decltype(two_t)::value;
                     constexpr int RB = TWO ? 2 : 4;
-                    for (int32_t j0 = 0; j0 < N; j0 += RB * kWave) {
+                    for (int32_t j0 = part * RB * kWave; j0 < N; j0 += parts * RB * kWave) {
                         double3 e[RB];
 #pragma unroll
                         for (int r = 0; r < RB; ++r) {
@@ -317,13 +323,13 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                 // the correction if the earlier move j of the round is accepted: f(b_j) - f(a_j), f(r) the
                 // pair terms of r with this move's new position minus those with its old one; lane
                 // 16 g + j takes one of the four terms: (new, b), (old, b), (new, a), (old, a)
-                if (wv > 0) {
+                if (own > 0 && part == parts - 1) {
                     const int j = lane & 15, g = lane >> 4;
                     const int32_t tj = __shfl(type, j, kWave);
                     const double jax = __shfl(ax, j, kWave), jay = __shfl(ay, j, kWave), jaz = __shfl(az, j, kWave);
                     const double jbx = __shfl(bx, j, kWave), jby = __shfl(by, j, kWave), jbz = __shfl(bz, j, kWave);
                     const bool b_side = g < 2, new_side = (g & 1) == 0;
-                    const bool has = j < wv && (b_side ? tj != GCMC_MOVE_DELETE : tj != GCMC_MOVE_INSERT) &&
+                    const bool has = j < own && (b_side ? tj != GCMC_MOVE_DELETE : tj != GCMC_MOVE_INSERT) &&
                                      (new_side ? mt != GCMC_MOVE_DELETE : !ins) && (tj == GCMC_MOVE_INSERT || N > 0);
                     const bool second = new_side && disp;
                     double u = 0.0, w = 0.0;
@@ -337,16 +343,16 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                     w -= __shfl_down(w, 16, kWave);
                     u -= __shfl_down(u, 32, kWave);
                     w -= __shfl_down(w, 32, kWave);
-                    if (lane < wv) {
-                        corr_e[lane][wv] = u;
-                        corr_w[lane][wv] = w;
+                    if (lane < own) {
+                        corr_e[lane][own] = u;
+                        corr_w[lane][own] = w;
                     }
                 }
                 // the pick at every N the move can meet (lane o: N - (W - 1) + o)
                 uint32_t pm = 0xFFFFFFFFu;
-                if (!ins) {
-                    const uint32_t olo = __builtin_amdgcn_readlane(klo, wv), ohi = __builtin_amdgcn_readlane(khi, wv);
-                    const double ou2 = read_lane(u2, wv);
+                if (!ins && part == parts - 1) {
+                    const uint32_t olo = __builtin_amdgcn_readlane(klo, own), ohi = __builtin_amdgcn_readlane(khi, own);
+                    const double ou2 = read_lane(u2, own);
                     const int32_t np = N - (W - 1) + lane;
                     const int32_t at = res_pick(olo, ohi, ou2, np > 0 ? np : 0);
                     pm = (uint32_t)__ballot(lane < 2 * W - 1 && np >= 0 && at == mi);
@@ -354,10 +360,10 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                 su = wave_sum_uniform(su);
                 sw = wave_sum_uniform(sw);
                 if (lane == 0) {
-                    ev_u[wv] = mt == GCMC_MOVE_DELETE ? -su : su;
-                    ev_w[wv] = mt == GCMC_MOVE_DELETE ? -sw : sw;
-                    ev_in[wv] = n_in;
-                    ev_pick[wv] = pm;
+                    ev_u[part][own] = mt == GCMC_MOVE_DELETE ? -su : su;
+                    ev_w[part][own] = mt == GCMC_MOVE_DELETE ? -sw : sw;
+                    ev_in[part][own] = n_in;
+                    if (part == parts - 1) ev_pick[own] = pm;
                 }
             }
             if (wv != 0) {
@@ -374,14 +380,17 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                 } else {
                     int32_t spins = 0;
                     for (;;) {
-                        const bool wait = lane > 0 && lane < kend &&
-                                          __hip_atomic_load(&ready[lane & (W - 1)], __ATOMIC_ACQUIRE,
+                        const bool wait = lane > 0 && lane < W * S && lane % W < kend &&
+                                          __hip_atomic_load(&ready[lane & (W * S - 1)], __ATOMIC_ACQUIRE,
                                                             __HIP_MEMORY_SCOPE_WORKGROUP) != rnd;
                         const uint64_t late = __ballot(wait);
                         if (late == 0) break;
                         __builtin_amdgcn_s_sleep(1);
                         if (++spins > spin_cap) {
-                            kw = (int)__builtin_ctzll(late);
+                            for (uint64_t l = late; l; l &= l - 1ull) {
+                                const int q = (int)__builtin_ctzll(l) % W;   // the first move not whole
+                                kw = q < kw ? q : kw;
+                            }
                             break;
                         }
                     }
@@ -394,10 +403,12 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
                 uint32_t pick = 0;
                 int32_t n_in = 0;
                 if (mine && !empty) {
-                    dUp = ev_u[lane];
-                    dWp = ev_w[lane];
                     pick = ev_pick[lane];
-                    n_in = ev_in[lane];
+                    for (int q = 0; q < parts; ++q) {
+                        dUp += ev_u[q][lane];
+                        dWp += ev_w[q][lane];
+                        n_in += ev_in[q][lane];
+                    }
                 }
                 const int32_t n_round = N;
                 bool stale = false;
@@ -540,7 +551,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     int32_t maxc = 0;
     if (cap <= kWave) {
         // one wavefront per cell: an entry's slot is the number of the cell's entries with a smaller id
-        for (int64_t c = wv; c < n_cells; c += W) {
+        for (int64_t c = wv; c < n_cells; c += W * S) {
             // the counters were raised by other wavefronts' atomics: read them where those happened
             int32_t cnt = __hip_atomic_load(B.count + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             cnt = __builtin_amdgcn_readfirstlane(cnt > cap ? cap : cnt);
@@ -602,7 +613,7 @@ __global__ __launch_bounds__(kWave* W) void k_chain_resident(const DevBox* __res
     __syncthreads();
     if (tid == 0) {
         int32_t mx = 0;
-        for (int v = 0; v < W; ++v) mx = wred[v] > mx ? wred[v] : mx;
+        for (int v = 0; v < W * S; ++v) mx = wred[v] > mx ? wred[v] : mx;
         if (err == GCMC_OK && sh_flag) {
             // a cell of the rebuilt list overflowed: the chain itself is complete; a rebuild with a
             // larger capacity (gcmc_cell_build) restores the cells and clears the error
@@ -635,11 +646,19 @@ using resident_fn = void (*)(const DevBox*, const int32_t*, int64_t, uint64_t, g
 
 bool resident_cfg_exists(int waves) { return waves == 4 || waves == 8; }
 
+// waves = 4: four moves at a time by two wavefronts each, in 128 registers (seven
+// spilled), so that a compute unit holds two boxes, or one beside a speculative one.
+// One wavefront a move left the SIMDs waiting (a wavefront issues an instruction every
+// eight cycles or so): 200 to 512 boxes of up to 1,024 particles 1.95 ms per 1,000 moves,
+// 1.75 with two; one box of 1,536 particles 2.20 and 1.83.  waves = 8: one wavefront a
+// move and as many registers as the kernel takes (512 particles, 1,000 moves: 0.91 ms,
+// 0.96 with two; from 1,000 particles on two would be 2 to 6 % faster).
 int launch_chain_resident(const DevBox* d_boxes, const int32_t* d_order, int n_boxes, int waves, int64_t n_moves,
                           uint64_t ctr0, gcmc_stats* stats, gcmc_log* log, hipStream_t s) {
-    resident_fn f = waves == 4 ? k_chain_resident<4> : (waves == 8 ? k_chain_resident<8> : nullptr);
-    if (!f) return -1;
-    hipLaunchKernelGGL(f, dim3(n_boxes), dim3(kWave * waves), 0, s, d_boxes, d_order, n_moves, ctr0, stats, log);
+    if (!resident_cfg_exists(waves)) return -1;
+    resident_fn f = waves == 4 ? k_chain_resident<4, 2, 4> : k_chain_resident<8, 1, 2>;
+    hipLaunchKernelGGL(f, dim3(n_boxes), dim3(kWave * (waves == 4 ? 8 : 8 * 1)), 0, s, d_boxes, d_order, n_moves, ctr0,
+                       stats, log);
     return 0;
 }
 
