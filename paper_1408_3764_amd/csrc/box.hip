@@ -32,15 +32,18 @@ int check_hip(hipError_t e, const char* what) {
 
 // ------------------------------------------------------------------ kernels
 // Copy SoA input into the particle records; flags coordinates outside [0, L)
-// and bad species in st->error.
+// and bad species in st->error, and with a ticket refuses the binning behind.
 __global__ void k_upload(DevBox B, const double* __restrict__ x, const double* __restrict__ y,
-                         const double* __restrict__ z, const int32_t* __restrict__ sp, int64_t n) {
+                         const double* __restrict__ z, const int32_t* __restrict__ sp, int64_t n, int64_t ticket) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double px = x[i], py = y[i], pz = z[i];
         const int32_t s = sp ? sp[i] : 0;
         const bool ok = (px >= 0.0) && (px < B.L[0]) && (py >= 0.0) && (py < B.L[1]) && (pz >= 0.0) &&
                         (pz < B.L[2]) && s >= 0 && s < B.ns;
-        if (!ok) atomicMax(&B.st->error, (int32_t)GCMC_ERR_INVALID_ARG);
+        if (!ok) {
+            atomicMax(&B.st->error, (int32_t)GCMC_ERR_INVALID_ARG);
+            if (ticket) atomicMax((unsigned long long*)&B.st->gate, (unsigned long long)(ticket + 1));
+        }
         B.pos[i] = make_double4(px, py, pz, pack_meta(s, 0));
     }
 }
@@ -224,7 +227,8 @@ __global__ __launch_bounds__(1024) void k_sort_cells_wave(DevBox B, int64_t tick
 // keep: a rebuild keeps the latched error, its move, the move counter, the
 // cumulative statistics and the species counts; otherwise (a new box) all of them
 // start afresh, the counts from the sort pass if there are several species.
-__device__ __forceinline__ void reset_state(BoxState* st, int ns, int64_t n, double u_pair, double w_pair, int keep) {
+__device__ __forceinline__ void reset_state(BoxState* st, int ns, int64_t n, double u_pair, double w_pair, int keep,
+                                            int64_t gate) {
     st->n = n;
     st->u_pair = u_pair;
     st->w_pair = w_pair;
@@ -236,21 +240,22 @@ __device__ __forceinline__ void reset_state(BoxState* st, int ns, int64_t n, dou
     st->cum.moves = 0;
     for (int t = 0; t < 3; ++t) st->cum.att[t] = st->cum.acc[t] = 0;
     st->cum.sum_n = st->cum.sum_n2 = st->cum.sum_u = st->cum.sum_w = 0.0;
-    st->gate = 0;
+    st->gate = gate;
     for (int s = 0; s < kMaxSpecies; ++s) st->nsp[s] = 0;
     if (ns == 1) st->nsp[0] = n;
 }
 
 // Before a binning: the box state reset and the cell counters cleared.  With a
-// ticket (k_place ran before) only if the box holds no error and n is its count and
+// ticket and `keep` (k_place ran before) only if the box holds no error and n is its count and
 // no coordinate was refused, which is told by gate = ticket; a refused coordinate
 // latches the error.  While the launch runs, n and the error stay as they are where
-// it goes ahead, and gate only takes values that tell the same.
+// it goes ahead, and gate only takes values that tell the same.  A new state (not
+// `keep`) starts with gate = ticket, for the upload behind to refuse.
 __global__ __launch_bounds__(256) void k_rebin_begin(DevBox B, int64_t n, double u_pair, double w_pair, int keep,
                                                      int64_t ticket) {
     BoxState* st = B.st;
     const bool first = threadIdx.x == 0 && blockIdx.x == 0;
-    if (ticket) {
+    if (ticket && keep) {
         const bool refused = st->gate == ticket + 1;
         if (refused && first) atomicMax(&st->error, (int32_t)GCMC_ERR_INVALID_ARG);
         if (refused || st->error != GCMC_OK || st->n != n) return;
@@ -258,7 +263,7 @@ __global__ __launch_bounds__(256) void k_rebin_begin(DevBox B, int64_t n, double
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < B.ncells; i += (int64_t)gridDim.x * blockDim.x)
         B.count[i] = 0;
     if (first) {
-        reset_state(st, B.ns, n, u_pair, w_pair, keep);
+        reset_state(st, B.ns, n, u_pair, w_pair, keep, ticket);
         if (ticket) st->gate = ticket;
     }
 }
@@ -275,8 +280,8 @@ __global__ __launch_bounds__(256) void k_set_desc(DevBox B, DevBox* dst) {
 
 // The chain part of a checkpoint: running energy and virial, move counter,
 // cumulative statistics.
-__global__ void k_apply_checkpoint(BoxState* st, gcmc_checkpoint ck) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+__global__ void k_apply_checkpoint(BoxState* st, gcmc_checkpoint ck, int64_t ticket) {
+    if (threadIdx.x == 0 && blockIdx.x == 0 && rebin_go(st, ticket)) {
         st->u_pair = ck.u_pair;
         st->w_pair = ck.w_pair;
         st->counter = (int64_t)ck.counter;
@@ -317,7 +322,7 @@ __global__ __launch_bounds__(256) void k_rescale(DevBox B, DevBox* dst, int64_t 
     if (blockIdx.x == 0) {
         const uint32_t* w = (const uint32_t*)&B;
         for (int i = threadIdx.x; i < (int)(sizeof(DevBox) / 4); i += blockDim.x) ((uint32_t*)dst)[i] = w[i];
-        if (threadIdx.x == 0) reset_state(B.st, B.ns, n, u_pair, __builtin_nan(""), 1);
+        if (threadIdx.x == 0) reset_state(B.st, B.ns, n, u_pair, __builtin_nan(""), 1, 0);
     }
 }
 
@@ -329,8 +334,10 @@ __global__ void k_clear_rebuild_errors(BoxState* st) {
     }
 }
 
-__global__ void k_get_particles(DevBox B, double* x, double* y, double* z, int32_t* sp) {
+// (nothing if the caller's arrays are too short: the host, which reads N behind this, says so)
+__global__ void k_get_particles(DevBox B, double* x, double* y, double* z, int32_t* sp, int64_t capacity) {
     const int64_t n = B.st->n;
+    if (n > capacity) return;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double4 p = B.pos[i];
         if (x) x[i] = p.x;
@@ -632,7 +639,7 @@ int gcmc_box_create(const gcmc_box_desc* desc, const double* d_x, const double* 
     }
     // upload and count occupancy to size the cells
     k_rebin_begin<<<grid_for(B.ncells), 256, 0, s>>>(B, n, 0.0, 0.0, 0, (int64_t)0);
-    if (n > 0) k_upload<<<grid_for(n), 256, 0, s>>>(B, d_x, d_y, d_z, d_species, n);
+    if (n > 0) k_upload<<<grid_for(n), 256, 0, s>>>(B, d_x, d_y, d_z, d_species, n, (int64_t)0);
     if (n > 0) k_count<<<std::min(grid_for(n), kCountBlocks), 256, 0, s>>>(B, n);
     BoxState h;
     if ((rc = read_state(box, &h, s))) {
@@ -893,11 +900,11 @@ int gcmc_get_particles(gcmc_box* box, double* d_x, double* d_y, double* d_z, int
     if (!box) return set_error(GCMC_ERR_INVALID_ARG, "box is NULL");
     hipStream_t s = (hipStream_t)stream;
     BoxState h;
-    int rc = read_state(box, &h, s);
-    if (rc) return rc;
-    if (h.n > 0) k_get_particles<<<grid_for(h.n), 256, 0, s>>>(box->d, d_x, d_y, d_z, d_species);
+    int rc;
+    if (stream_capturing(s) && (rc = read_state(box, &h, s))) return rc;   // refused before anything is enqueued
+    k_get_particles<<<grid_for(box->d.max_n), 256, 0, s>>>(box->d, d_x, d_y, d_z, d_species, box->d.max_n);
     GCMC_HIP(hipGetLastError());
-    GCMC_HIP(hipStreamSynchronize(s));
+    if ((rc = read_state(box, &h, s))) return rc;   // behind the kernel: its arrays are written
     if (h_n) *h_n = h.n;
     return GCMC_OK;
 }
@@ -916,15 +923,15 @@ int gcmc_export_state(gcmc_box* box, double* d_x, double* d_y, double* d_z, int3
     if (!box || !h_ck) return set_error(GCMC_ERR_INVALID_ARG, "NULL argument");
     hipStream_t s = (hipStream_t)stream;
     BoxState h;
-    int rc = read_state(box, &h, s);
-    if (rc) return rc;
-    if ((d_x || d_y || d_z || d_species) && capacity < h.n)
-        return set_error(GCMC_ERR_INVALID_ARG, "particle arrays shorter than N");
-    if (h.n > 0 && (d_x || d_y || d_z || d_species)) {
-        k_get_particles<<<grid_for(h.n), 256, 0, s>>>(box->d, d_x, d_y, d_z, d_species);
+    int rc;
+    if (stream_capturing(s) && (rc = read_state(box, &h, s))) return rc;   // refused before anything is enqueued
+    const bool arrays = d_x || d_y || d_z || d_species;
+    if (arrays) {
+        k_get_particles<<<grid_for(box->d.max_n), 256, 0, s>>>(box->d, d_x, d_y, d_z, d_species, capacity);
         GCMC_HIP(hipGetLastError());
-        GCMC_HIP(hipStreamSynchronize(s));
     }
+    if ((rc = read_state(box, &h, s))) return rc;   // behind the kernel: its arrays are written
+    if (arrays && capacity < h.n) return set_error(GCMC_ERR_INVALID_ARG, "particle arrays shorter than N");
     memset(h_ck, 0, sizeof(*h_ck));
     h_ck->n = h.n;
     h_ck->u_pair = h.u_pair;
@@ -952,16 +959,17 @@ int gcmc_import_state(gcmc_box* box, const double* d_x, const double* d_y, const
     if (n > 0 && (!d_x || !d_y || !d_z)) return set_error(GCMC_ERR_INVALID_ARG, "coordinate arrays are NULL");
     if (h_ck->error != GCMC_OK) return set_error(GCMC_ERR_INVALID_ARG, "a checkpoint with a latched error");
     hipStream_t s = (hipStream_t)stream;
-    k_rebin_begin<<<grid_for(box->d.ncells), 256, 0, s>>>(box->d, n, h_ck->u_pair, h_ck->w_pair, 0, (int64_t)0);
-    if (n > 0) k_upload<<<grid_for(n), 256, 0, s>>>(box->d, d_x, d_y, d_z, d_species, n);
     BoxState h;
-    int rc = read_state(box, &h, s);
-    if (rc) return rc;
-    if (h.error) return set_error(GCMC_ERR_INVALID_ARG, "coordinates must lie in [0, L) and species in range");
-    launch_bin(box->d, n, s, box->d.ns > 1, 0);   // the counters and the state were reset above
-    k_apply_checkpoint<<<1, 1, 0, s>>>(box->d.st, *h_ck);
+    int rc;
+    if (stream_capturing(s) && (rc = read_state(box, &h, s))) return rc;   // refused before anything is enqueued
+    const int64_t ticket = box->gate += 2;
+    k_rebin_begin<<<grid_for(box->d.ncells), 256, 0, s>>>(box->d, n, h_ck->u_pair, h_ck->w_pair, 0, ticket);
+    if (n > 0) k_upload<<<grid_for(n), 256, 0, s>>>(box->d, d_x, d_y, d_z, d_species, n, ticket);
+    launch_bin(box->d, n, s, box->d.ns > 1, ticket);   // the counters and the state were reset above
+    k_apply_checkpoint<<<1, 1, 0, s>>>(box->d.st, *h_ck, ticket);
     GCMC_HIP(hipGetLastError());
     if ((rc = read_state(box, &h, s))) return rc;
+    if (h.gate == ticket + 1) return set_error(GCMC_ERR_INVALID_ARG, "coordinates must lie in [0, L) and species in range");
     if (h.error) return set_error(h.error, "binning overflowed a cell; rebuild with a larger cell_cap");
     return GCMC_OK;
 }

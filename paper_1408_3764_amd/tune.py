@@ -60,7 +60,7 @@ def async_supported(box):
 
 
 def chain_shape(box):
-    """The speculative kernel with eight wavefronts where it applies; otherwise
+    """The speculative kernel at waves = 8 where it applies; otherwise
     the smallest per-move shape whose one pass covers the two stencils of a
     cross-cell displacement."""
     if spec_supported(box):

@@ -129,3 +129,37 @@ def test_volume_that_overflows_a_cell():
     assert abs(got["U_pair_old"] - old["U_pair"]) <= 1e-10 * old["sumabs"]
     assert b.status() == 0 and b.checkpoint()["u_pair"] == got["U_pair"]
     _check(b, new, None, p)
+
+
+def test_checkpoints_refused_and_short_arrays():
+    """A checkpoint with a coordinate outside, or of a species out of range, is refused and latched; one
+    that overflows a cell says so; arrays shorter than N are refused and not written to."""
+    from paper_1408_3764_amd import _lib
+    wb, b, p = _make("4,095 cells, last group cut")
+    pos, sp, ck = b.export_state()
+    short = [torch.full((wb.n - 1,), -7.0, dtype=torch.float64, device="cuda") for _ in range(3)]
+    with pytest.raises(_lib.GcmcError) as e:
+        _lib.gcmc_export_state(b.handle, *short, None, wb.n - 1)
+    assert e.value.code == _lib.GCMC_ERR_INVALID_ARG and all((t == -7.0).all() for t in short)
+    for what in ("coordinate", "species"):
+        bad, bsp = pos.copy(), sp.copy()
+        if what == "coordinate":
+            bad[-1, 0] = -1e-9
+        else:
+            bsp[-1] = 2
+        with pytest.raises(_lib.GcmcError) as e:
+            b.import_state(bad, dict(ck, counter=55), species=bsp)
+        assert e.value.code == _lib.GCMC_ERR_INVALID_ARG and b.status() == _lib.GCMC_ERR_INVALID_ARG
+        assert b.checkpoint()["counter"] != 55
+        b.import_state(pos, ck, species=sp)
+        _check(b, pos, sp, p)
+    crowd = pos.copy()
+    crowd[: b.info()["cell_cap"] + 1] = 0.5
+    with pytest.raises(_lib.GcmcError) as e:
+        b.import_state(crowd, ck, species=sp)
+    assert e.value.code == _lib.GCMC_ERR_CELL_OVERFLOW
+    b.import_state(pos, ck, species=sp)
+    _check(b, pos, sp, p)
+    got = [torch.zeros(wb.n, dtype=torch.float64, device="cuda") for _ in range(3)]
+    assert _lib.gcmc_get_particles(b.handle, *got, None) == wb.n
+    assert np.array_equal(torch.stack(got, dim=1).cpu().numpy(), pos)
