@@ -1,6 +1,6 @@
 // Host-driven move kernels: energy deltas of caller-given trial moves, the
-// commit of one accepted move, and the neighbour-candidate gather (the same
-// stencil mapping as the energy evaluation, for checking it).
+// commit of one accepted move, and the neighbour-candidate gather (for checking
+// the cell list).
 #include <type_traits>
 
 #include "cell_pass.h"
@@ -169,7 +169,7 @@ __global__ void k_commit(const DevBox* __restrict__ boxp, const gcmc_move* move,
     st->w_pair = dW_pair ? st->w_pair + *dW_pair : __builtin_nan("");
 }
 
-// Candidate ids of points (the same slot mapping as eval_trial).
+// Candidate ids of points (a slot for every place of the fullest cell).
 __global__ __launch_bounds__(256) void k_neighbors(const DevBox* __restrict__ boxp, const double* pts,
                                                    const int32_t* excl, int64_t n, int32_t max_ids, int32_t* ids,
                                                    int32_t* counts) {

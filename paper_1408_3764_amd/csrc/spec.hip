@@ -164,7 +164,6 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
             rnd = rnd == INT32_MAX ? 1 : rnd + 1;   // round numbers stay positive (a flag starts at -1)
             SpecRec* recs = recs_s[rnd & 1];
             if (m + wv < n_moves) {
-                SpecKey key;
                 // is the pick at every N the move can meet (lane o: N - (W - 1) + o) the evaluated one? (found
                 // while the picked record is loaded)
                 const int32_t np = N - (W - 1) + lane;
@@ -179,8 +178,7 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
                     if (lane == 0) __hip_atomic_store(&known[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 };
                 spec_eval<CR, NG, RING>(B, tab, offs, own[wv], pq[wv], &dring, ctr0 + (uint64_t)m, wv, N, no_full, a_ins,
-                                        a_del, &recs[wv], key, early, pub);
-                if (key.flags & 1) pub();   // an empty box: nothing to evaluate
+                                        a_del, &recs[wv], early, pub);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
                 if (lane == 0) __hip_atomic_store(&ready[wv], rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }

@@ -72,7 +72,7 @@ __device__ __forceinline__ double3 gload_xyz(const double4* p) {
 struct SpecRec {
     // what the in-order commit reads for every move, first
     int32_t type, flags;
-    uint32_t pickmask, okmask;   // bit o: the pick still valid / the move accepted at N = N_round - (W - 1) + o
+    uint32_t pickmask;   // bit o: the pick still valid at N = N_round - (W - 1) + o
     int64_t idx;
     int32_t c0[3], c1[3];
     // what it reads for an accepted move
@@ -81,13 +81,6 @@ struct SpecRec {
     double p0[3], p1[3];
     double4 rec, elast;
     int32_t cand, evals, incut, pad2;
-};
-
-// The values of an evaluation the round kernel decides with in advance.
-struct SpecKey {
-    int32_t type, flags;
-    int64_t idx;
-    double u2, u7, lnA, dUp;
 };
 
 // Inclusive prefix sum over the wavefront's lanes (DPP row shifts, then the
@@ -426,7 +419,7 @@ struct SpecNoPub {
 template <int CR, int NG, int RING, typename Early = SpecNoEarly, typename Pub = SpecNoPub>
 __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
                                           double* pq, const DrawRing<RING>* dr, uint64_t ctr_round, int k, int64_t N,
-                                          bool no_full, double a_ins, double a_del, SpecRec* out, SpecKey& key,
+                                          bool no_full, double a_ins, double a_del, SpecRec* out,
                                           const Early& early = Early(), const Pub& pub = Pub()) {
     const int lane = threadIdx.x & (kWave - 1);
     int type;
@@ -476,15 +469,7 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
         I = __popcll(__ballot(earlier && tj == GCMC_MOVE_INSERT));
     }
     const double ud[3] = {ux, uy, uz};
-    key.type = type;
-    key.flags = 0;
-    key.u2 = u2;
-    key.u7 = u7;
-    key.lnA = lnA;
-    key.idx = -1;
-    key.dUp = 0.0;
     if (type != GCMC_MOVE_INSERT && N == 0) {
-        key.flags = 1;
         if (lane == 0) {
             out->type = type;
             out->flags = 1;
@@ -493,6 +478,7 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
             out->u7 = u7;
             out->cand = out->evals = out->incut = 0;
         }
+        pub();
         return;
     }
     int64_t idx = -1;
@@ -564,8 +550,6 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
                                          mid);
     const double dUp = type == GCMC_MOVE_DELETE ? -S.su : S.su;
     const double dWp = type == GCMC_MOVE_DELETE ? -S.sw : S.sw;
-    key.idx = idx;
-    key.dUp = dUp;
     if (lane == 0) {
         out->dUp = dUp;
         out->dWp = dWp;

@@ -1,8 +1,8 @@
-// Trial moves: their setup, the energy evaluation over the cell stencil, and
-// the incremental cell update on acceptance (shared by the host-driven move
-// kernels and the persistent chain kernel).
+// Trial moves: their setup, the pair terms, and the incremental cell update on
+// acceptance (shared by the host-driven move kernels and the chain kernels).
 //
-// Mapping (gfx950, wave64).  One workgroup of W wavefronts evaluates one move.
+// Mapping of the per-move chain (gfx950, wave64).  One workgroup of W wavefronts
+// evaluates one move.
 // The stencil of a position is its cell plus the cells within k cells of it
 // (Sec. 3.2: the 27 adjoining cells for S >= rc).  Every stencil cell owns G
 // consecutive "slots", G = the power of two at or above the largest cell
@@ -43,34 +43,12 @@ __device__ __forceinline__ int log2_ceil(int v) {
     return v <= 1 ? 0 : 32 - __clz(v - 1);
 }
 
-template <bool MIX>
-__device__ __forceinline__ double pair_energy(const DevBox& B, const double* p, int sp, const double4& e) {
-    const double r2 = dist2(B, p[0], p[1], p[2], e.x, e.y, e.z);
-    if (MIX) {
-        const int q = sp * B.ns + meta_species(e.w);
-        return lj_from_r2(r2, B.rc2, B.eps4[q], B.sig2[q]);
-    }
-    return lj_from_r2(r2, B.rc2, B.eps4[0], B.sig2[0]);
-}
-
 // Per-lane work counters, summed over a whole launch.
 struct Work {
     int64_t cand = 0;   // candidate records read (valid slots)
     int64_t evals = 0;  // pair distances evaluated
     int64_t incut = 0;  // pairs inside the cutoff
 };
-
-template <bool MIX>
-__device__ __forceinline__ double pair_energy_w(const DevBox& B, const double* p, int sp, const double4& e,
-                                                int64_t& incut) {
-    const double r2 = dist2(B, p[0], p[1], p[2], e.x, e.y, e.z);
-    incut += (r2 < B.rc2) ? 1 : 0;
-    if (MIX) {
-        const int q = sp * B.ns + meta_species(e.w);
-        return lj_from_r2(r2, B.rc2, B.eps4[q], B.sig2[q]);
-    }
-    return lj_from_r2(r2, B.rc2, B.eps4[0], B.sig2[0]);
-}
 
 // Pair energy and pair virial together (the virial added to `w`).
 template <bool MIX>
@@ -83,95 +61,6 @@ __device__ __forceinline__ double pair_uw(const DevBox& B, const double* p, int 
         return lj_uw_from_r2(r2, B.rc2, B.eps4[q], B.sig2[q], w);
     }
     return lj_uw_from_r2(r2, B.rc2, B.eps4[0], B.sig2[0], w);
-}
-
-// Block-wide: ea = sum over candidates of u(p[0], .), eb = sum of u(p[1], .)
-// (eb only for displacements), va and vb the same sums of the pair virial.
-// `red` holds 4*W doubles of LDS.
-template <int W, int R, bool MIX>
-__device__ __forceinline__ void eval_trial(const DevBox& B, const uint32_t* tab, int lg, const Trial& T,
-                                           double& ea, double& eb, double& va, double& vb, double* red, Work& wk) {
-    const int tid = threadIdx.x;
-    const int NS = B.nstencil << lg;
-    const int two = (T.npos == 2 && !T.same) ? 1 : 0;
-    const int total = NS << two;
-    const int gmask = (1 << lg) - 1;
-    const int32_t excl = (int32_t)T.idx;
-    double sa = 0.0, sb = 0.0, wa = 0.0, wb = 0.0;
-    for (int base = 0; base < total; base += kWave * W * R) {
-        double4 e[R];
-        int32_t cnt[R], kk[R], which[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int s = base + r * kWave * W + tid;
-            const bool in = s < total;
-            const int w = (two && s >= NS) ? 1 : 0;
-            const int q = in ? s - w * NS : 0;
-            const int t = q >> lg;
-            const int k = q & gmask;
-            const int32_t cx = w ? T.c[1][0] : T.c[0][0];
-            const int32_t cy = w ? T.c[1][1] : T.c[0][1];
-            const int32_t cz = w ? T.c[1][2] : T.c[0][2];
-            const int64_t c = stencil_cell(B, tab[t], cx, cy, cz);
-            const int kc = k < B.cap ? k : B.cap - 1;
-            cnt[r] = in ? gload(B.count + c) : 0;
-            e[r] = gload(B.ent + (c * B.cap + kc));
-            kk[r] = k;
-            which[r] = w;
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const bool valid = kk[r] < cnt[r] && meta_low(e[r].w) != excl;
-            if (valid) {
-                wk.cand += 1;
-                if (T.npos == 1) {
-                    sa += pair_uw<MIX>(B, T.p[0], T.sp, e[r], wk.incut, wa);
-                    wk.evals += 1;
-                } else if (!two) {
-                    sa += pair_uw<MIX>(B, T.p[0], T.sp, e[r], wk.incut, wa);
-                    sb += pair_uw<MIX>(B, T.p[1], T.sp, e[r], wk.incut, wb);
-                    wk.evals += 2;
-                } else if (which[r]) {
-                    sb += pair_uw<MIX>(B, T.p[1], T.sp, e[r], wk.incut, wb);
-                    wk.evals += 1;
-                } else {
-                    sa += pair_uw<MIX>(B, T.p[0], T.sp, e[r], wk.incut, wa);
-                    wk.evals += 1;
-                }
-            }
-        }
-    }
-    sa = wave_sum(sa);
-    sb = wave_sum(sb);
-    wa = wave_sum(wa);
-    wb = wave_sum(wb);
-    if (W == 1) {
-        ea = sa;
-        eb = sb;
-        va = wa;
-        vb = wb;
-        return;
-    }
-    const int wv = tid / kWave;
-    if ((tid & (kWave - 1)) == 0) {
-        red[4 * wv] = sa;
-        red[4 * wv + 1] = sb;
-        red[4 * wv + 2] = wa;
-        red[4 * wv + 3] = wb;
-    }
-    __syncthreads();
-    double ta = 0.0, tb = 0.0, ua = 0.0, ub = 0.0;
-#pragma unroll
-    for (int v = 0; v < W; ++v) {
-        ta += red[4 * v];
-        tb += red[4 * v + 1];
-        ua += red[4 * v + 2];
-        ub += red[4 * v + 3];
-    }
-    ea = ta;
-    eb = tb;
-    va = ua;
-    vb = ub;
 }
 
 // Remove the entry at `loc` of cell `c`: the cell's last entry takes its place
