@@ -62,36 +62,36 @@ __global__ __launch_bounds__(256) void k_place(DevBox B, const double* __restric
     }
 }
 
-// The block's species counts (wave-uniform per-wavefront totals, if counted) and
-// largest occupancy, added to the box state with one atomic each per block:
-// atomics on the same few words serialise at the memory side and took most of a
-// cell build's time, so a block whose cells are no fuller than what is already
-// there leaves the word alone.  Every thread of the block calls it.
-template <int BLK, bool SPECIES>
-__device__ __forceinline__ void publish_counts(BoxState* st, int ns, const int64_t* nsp, int32_t maxc) {
-    __shared__ int64_t s_nsp[BLK / kWave][SPECIES ? kMaxSpecies : 1];
+// The block's largest occupancy, and its species counts, added to the box state with
+// one atomic each per block: atomics on the same few words serialise at the memory side
+// and took most of a cell build's time, so a block whose cells are no fuller than what
+// is already there leaves the word alone.  Every thread of the block calls these.
+template <int BLK>
+__device__ __forceinline__ void publish_max(BoxState* st, int32_t maxc) {   // maxc: wave-uniform
     __shared__ int32_t s_max[BLK / kWave];
-    const int w = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-        if (SPECIES) {
-#pragma unroll
-            for (int q = 0; q < kMaxSpecies; ++q) s_nsp[w][q] = nsp[q];
-        }
-        s_max[w] = maxc;
-    }
+    if ((threadIdx.x & (kWave - 1)) == 0) s_max[threadIdx.x / kWave] = maxc;
     __syncthreads();
     if (threadIdx.x == 0) {
         int32_t mx = 0;
         for (int v = 0; v < BLK / kWave; ++v) mx = s_max[v] > mx ? s_max[v] : mx;
-        if (SPECIES) {
-            for (int q = 0; q < ns; ++q) {
-                int64_t t = 0;
-                for (int v = 0; v < BLK / kWave; ++v) t += s_nsp[v][q];
-                if (t) atomicAdd((unsigned long long*)&st->nsp[q], (unsigned long long)t);
-            }
-        }
         if (mx > __hip_atomic_load(&st->maxcount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             atomicMax(&st->maxcount, mx);
+    }
+}
+
+// nsp: this thread's counts; a block of 256.
+__device__ __forceinline__ void publish_species(BoxState* st, int ns, const int32_t* nsp) {
+    __shared__ int32_t s_nsp[256 / kWave][kMaxSpecies];
+#pragma unroll
+    for (int q = 0; q < kMaxSpecies; ++q) {
+        const int32_t t = wave_sum_i32_uniform(nsp[q]);
+        if ((threadIdx.x & (kWave - 1)) == 0) s_nsp[threadIdx.x / kWave][q] = t;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < ns) {
+        int64_t t = 0;
+        for (int v = 0; v < 256 / kWave; ++v) t += s_nsp[v][threadIdx.x];
+        if (t) atomicAdd((unsigned long long*)&st->nsp[threadIdx.x], (unsigned long long)t);
     }
 }
 
@@ -108,17 +108,26 @@ __global__ __launch_bounds__(256) void k_count(DevBox B, int64_t n) {
         mx = k + 1 > mx ? k + 1 : mx;
     }
     mx = wave_max_i32_uniform(mx);
-    publish_counts<256, false>(B.st, 0, nullptr, mx);
+    publish_max<256>(B.st, mx);
 }
 
 // Whether a re-binning in place was let through (ticket 0: nothing to ask).
 __device__ __forceinline__ bool rebin_go(const BoxState* st, int64_t ticket) { return !ticket || st->gate == ticket; }
 
-// Pass 2: claim a slot and write the cell entry.
-__global__ void k_bin(DevBox B, int64_t n, int64_t ticket) {
+// Pass 2: claim a slot and write the cell entry.  For a new set of particles of several
+// species it counts them too (SPECIES): this pass sees every particle, also one that
+// its full cell has no slot for.
+template <bool SPECIES>
+__global__ __launch_bounds__(256) void k_bin(DevBox B, int64_t n, int64_t ticket) {
     if (!rebin_go(B.st, ticket)) return;
+    int32_t nsp[kMaxSpecies] = {0, 0, 0, 0};
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double4 p = B.pos[i];
+        if (SPECIES) {
+            const int sp = meta_species(p.w);
+#pragma unroll
+            for (int q = 0; q < kMaxSpecies; ++q) nsp[q] += (sp == q) ? 1 : 0;
+        }
         const int64_t c = cell_of_point(B, p.x, p.y, p.z);
         const int32_t k = atomicAdd(&B.count[c], 1);
         if (k < B.cap) {
@@ -127,15 +136,14 @@ __global__ void k_bin(DevBox B, int64_t n, int64_t ticket) {
             atomicMax(&B.st->error, (int32_t)GCMC_ERR_CELL_OVERFLOW);
         }
     }
+    if (SPECIES) publish_species(B.st, B.ns, nsp);
 }
 
 // Pass 3 (capacities above 64): order each cell by particle id, set the
-// back-pointers, and gather the maximum occupancy and, for a new box, the species
-// counts (kept per thread, summed per wavefront, published once per block).
-template <bool SPECIES>
+// back-pointers, and gather the maximum occupancy (kept per thread, published once
+// per block).
 __global__ __launch_bounds__(256) void k_sort_cells(DevBox B, int64_t ticket) {
     if (!rebin_go(B.st, ticket)) return;
-    int32_t nsp[kMaxSpecies] = {0, 0, 0, 0};
     int32_t maxc = 0;
     for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < B.ncells;
          c += (int64_t)gridDim.x * blockDim.x) {
@@ -155,22 +163,12 @@ __global__ __launch_bounds__(256) void k_sort_cells(DevBox B, int64_t ticket) {
         for (int32_t a = 0; a < cnt; ++a) {
             const double4 v = e[a];
             const int32_t id = meta_low(v.w);
-            const int sp = meta_species(v.w);
-            B.pos[id].w = pack_meta(sp, (int32_t)(c * B.cap + a));
-            if (SPECIES) {
-#pragma unroll
-                for (int q = 0; q < kMaxSpecies; ++q) nsp[q] += (sp == q) ? 1 : 0;
-            }
+            B.pos[id].w = pack_meta(meta_species(v.w), (int32_t)(c * B.cap + a));
         }
         maxc = cnt > maxc ? cnt : maxc;
     }
-    int64_t tot[kMaxSpecies] = {0, 0, 0, 0};
-    if (SPECIES) {
-#pragma unroll
-        for (int q = 0; q < kMaxSpecies; ++q) tot[q] = wave_sum_i32_uniform(nsp[q]);
-    }
     maxc = wave_max_i32_uniform(maxc);
-    publish_counts<256, SPECIES>(B.st, B.ns, tot, maxc);
+    publish_max<256>(B.st, maxc);
 }
 
 // Pass 3 for capacities up to 64, one wavefront per cell: lane k holds the cell's
@@ -180,13 +178,12 @@ __global__ __launch_bounds__(256) void k_sort_cells(DevBox B, int64_t ticket) {
 // cell's count, entries and stores are a chain of latencies, so a wavefront has U
 // cells in flight: 262,144 particles in 15,625 cells 41 us before, 20 with one cell
 // at a time and fewer atomics, 12 with four.
-template <int U, bool SPECIES>
+template <int U>
 __global__ __launch_bounds__(1024) void k_sort_cells_wave(DevBox B, int64_t ticket) {
     if (!rebin_go(B.st, ticket)) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
-    int64_t nsp[kMaxSpecies] = {0, 0, 0, 0};
     int32_t maxc = 0;
     for (int64_t c0 = wave0 * U; c0 < B.ncells; c0 += nwaves * U) {
         int32_t mine = 0;
@@ -210,23 +207,18 @@ __global__ __launch_bounds__(1024) void k_sort_cells_wave(DevBox B, int64_t tick
             int32_t rank = 0;
             for (int j = 0; j < cnt[u]; ++j) rank += (__builtin_amdgcn_readlane(id[u], j) < id[u]) ? 1 : 0;
             // every lane's load has completed (the ranks read all ids) before any store below
-            const int sp = meta_species(v[u].w);
             if (lane < cnt[u]) {
                 gstore(B.ent + (c0 + u) * B.cap + rank, v[u]);
-                gstore_w(B.pos + id[u], pack_meta(sp, (int32_t)((c0 + u) * B.cap + rank)));
-            }
-            if (SPECIES) {
-#pragma unroll
-                for (int q = 0; q < kMaxSpecies; ++q) nsp[q] += __popcll(__ballot(lane < cnt[u] && sp == q));
+                gstore_w(B.pos + id[u], pack_meta(meta_species(v[u].w), (int32_t)((c0 + u) * B.cap + rank)));
             }
         }
     }
-    publish_counts<1024, SPECIES>(B.st, B.ns, nsp, maxc);
+    publish_max<1024>(B.st, maxc);
 }
 
 // keep: a rebuild keeps the latched error, its move, the move counter, the
 // cumulative statistics and the species counts; otherwise (a new box) all of them
-// start afresh, the counts from the sort pass if there are several species.
+// start afresh, the counts from k_bin if there are several species.
 __device__ __forceinline__ void reset_state(BoxState* st, int ns, int64_t n, double u_pair, double w_pair, int keep,
                                             int64_t gate) {
     st->n = n;
@@ -495,24 +487,26 @@ static int auto_cap(int32_t maxcount) {
 // Cells per wavefront at a time: four where that still leaves 64 blocks of sixteen
 // wavefronts, one below, where the chip has wavefronts to spare (four against one:
 // 15,625 cells 11.9 and 20.0 us, 2,744 cells 8.2 and 6.2, 64 cells 6.6 and 3.6).
-static void launch_sort(const DevBox& B, hipStream_t s, bool species, int64_t ticket) {
+static void launch_sort(const DevBox& B, hipStream_t s, int64_t ticket) {
     if (B.cap > kWave) {
-        auto f = species ? k_sort_cells<true> : k_sort_cells<false>;
-        hipLaunchKernelGGL(f, dim3(std::min(grid_for(B.ncells), kCountBlocks)), dim3(256), 0, s, B, ticket);
+        hipLaunchKernelGGL(k_sort_cells, dim3(std::min(grid_for(B.ncells), kCountBlocks)), dim3(256), 0, s, B, ticket);
         return;
     }
     constexpr int kMany = 4;
     const int64_t per = B.ncells >= 16 * 256 ? 16 * kMany : 16;
-    auto f = per > 16 ? (species ? k_sort_cells_wave<kMany, true> : k_sort_cells_wave<kMany, false>)
-                      : (species ? k_sort_cells_wave<1, true> : k_sort_cells_wave<1, false>);
+    auto f = per > 16 ? k_sort_cells_wave<kMany> : k_sort_cells_wave<1>;
     const int64_t blocks = std::min<int64_t>((B.ncells + per - 1) / per, kCountBlocks);
     hipLaunchKernelGGL(f, dim3((unsigned)blocks), dim3(1024), 0, s, B, ticket);
 }
 
-// Claim and sort, the counters cleared and the state reset before.
+// Claim and sort, the counters cleared and the state reset before.  species: a new set
+// of particles, whose species counts were reset to none.
 static void launch_bin(const DevBox& B, int64_t n, hipStream_t s, bool species, int64_t ticket) {
-    if (n > 0) k_bin<<<grid_for(n), 256, 0, s>>>(B, n, ticket);
-    launch_sort(B, s, species, ticket);
+    if (n > 0) {
+        auto f = species ? k_bin<true> : k_bin<false>;
+        hipLaunchKernelGGL(f, dim3(grid_for(n)), dim3(256), 0, s, B, n, ticket);
+    }
+    launch_sort(B, s, ticket);
 }
 
 // Bin the first n particles of B.pos into a fresh cell array.
