@@ -17,7 +17,10 @@
 // virial corrected for the earlier accepted moves of the round: removing a
 // particle at a and adding one at b changes the move's sums by f(b) - f(a),
 // f(r) the pair terms of r with the move's new position minus those with its
-// old one, prepared by the move's own wavefront.
+// old one, prepared by the move's own wavefront.  An overlap's term taken away again would leave
+// its rounding in place of the sums' digits (4 (sigma / r)^12 is 1e16 at r = 0.05), so the terms of
+// particles that overlap the move's positions and that an earlier move would take away are kept apart
+// from its sums and added while their particles are there.
 //
 // Lane k of wavefront 0 holds move k of the round and its decision at the current
 // state, so the rejections up to the next accepted or stale move take one ballot,
@@ -43,6 +46,9 @@ namespace gcmc {
 
 constexpr int kResCap = 2048;   // particles whose coordinates live in LDS
 constexpr int kResRing = 64;    // moves prepared at once
+// (r / sigma)^2 below which a term is kept apart from the sums: there it passes 256 well depths, where
+// (sigma / r)^6 = 1 / 2 + sqrt(64.25), and its rounding 3e-14 of them
+constexpr double kApart2 = 0.49;
 
 // What a move needs from its draws, prepared for kResRing moves at a time:
 // the type, ln A, the 53 bits of the pick fields as an integer, the floor
@@ -110,10 +116,12 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
     __shared__ double pq[W * S][kResQueue];   // each wavefront's queue of in-cutoff pairs
     // move k's evaluation by each of its wavefronts: pair energy and virial change against the
     // round's start, pairs inside the cutoff, and bit o: its pick at N_round - (W - 1) + o is the
-    // particle it evaluated
+    // particle it evaluated; bit 16 + j: the terms of the particle that move j takes away are in
+    // apart[j][k], not in its sums
     __shared__ double ev_u[S][W], ev_w[S][W];
     __shared__ int32_t ev_in[S][W];
     __shared__ uint32_t ev_pick[W];
+    __shared__ double apart_e[W][W], apart_w[W][W];
     // corr[j][k]: the change of move k's pair energy and virial if move j < k of the round is
     // accepted (move j's removed and added positions against move k's positions)
     __shared__ double corr_e[W][W], corr_w[W][W];
@@ -138,14 +146,15 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
     const double tk = B.tailK[0];
     const double rc2 = B.rc2, eps4 = B.eps4[0], sig2 = B.sig2[0];
     const int32_t spin_cap = wait_bound(B.wait_limit);
+    const double apart2 = eps4 != 0.0 ? fmin(kApart2 * sig2, rc2) : 0.0;
     // wavefront wv takes part `part` of move `own` of a round: every parts-th group of rows (a bound
     // that lets nobody wait leaves a move to one wavefront)
     const int parts = spin_cap < 0 ? 1 : S, part = wv / W, own = wv - part * W;
-    // statistics, kept by wavefront 0: per-lane sums over the moves lane k decided as move k of a
-    // round, added up at the end (counts as doubles, exact below 2^53)
-    double att0 = 0.0, att1 = 0.0, att2 = 0.0, acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
-    double sum_n = 0.0, sum_u = 0.0, sum_n2 = 0.0, sum_w = 0.0;
-    double cand = 0.0, evals = 0.0, incut = 0.0;
+    // statistics of wavefront 0, lane k's sums over the moves it decided as move k of a round (counts as
+    // doubles, exact below 2^53): in local memory, as registers they would be spilled through the rounds
+    enum { kAtt, kAcc = 3, kSumN = 6, kSumN2, kSumU, kSumW, kCand, kEvals, kIncut, kStats };
+    __shared__ double acc_s[kStats][W];
+    for (int t = tid; t < kStats * W; t += blockDim.x) (&acc_s[0][0])[t] = 0.0;
 
     auto get = [&](int32_t j) -> double3 {
         if (j < kResCap) return make_double3(px[j], py[j], pz[j]);
@@ -263,6 +272,8 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                 uint32_t tail = 0;
                 int32_t n_in = 0;
                 double su = 0.0, sw = 0.0;   // new position minus old (displacement), else the one position
+                uint32_t first = 0;          // earlier moves whose particle's terms are kept apart (each particle once)
+                int rp = part, rs = parts;   // its share of the rows
                 auto drain = [&](uint32_t from, uint32_t cnt) {
                     wave_lds_sync();
                     if ((uint32_t)lane < cnt) {
@@ -283,7 +294,7 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                 auto rows = [&](auto two_t) {
                     constexpr bool TWO = decltype(two_t)::value;
                     constexpr int RB = TWO ? 2 : 4;
-                    for (int32_t j0 = part * RB * kWave; j0 < N; j0 += parts * RB * kWave) {
+                    for (int32_t j0 = rp * RB * kWave; j0 < N; j0 += rs * RB * kWave) {
                         double3 e[RB];
 #pragma unroll
                         for (int r = 0; r < RB; ++r) {
@@ -296,6 +307,8 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                             } else if (j < N && j != mi) {
                                 e[r] = gload_xyz(B.pos + j);
                             }
+                            for (uint32_t l = first; l; l &= l - 1u)
+                                if (j == __builtin_amdgcn_readlane(idx, (int)__builtin_ctz(l))) e[r].x = 1e300;
                         }
                         double ra[RB], rb[RB];
 #pragma unroll
@@ -320,23 +333,49 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                 if (disp) rows(std::true_type{});
                 else rows(std::false_type{});
                 if (tail) drain(0, tail);
+                tail = 0;
                 // the correction if the earlier move j of the round is accepted: f(b_j) - f(a_j), f(r) the
                 // pair terms of r with this move's new position minus those with its old one; lane
                 // 16 g + j takes one of the four terms: (new, b), (old, b), (new, a), (old, a)
                 if (own > 0 && part == parts - 1) {
                     const int j = lane & 15, g = lane >> 4;
-                    const int32_t tj = __shfl(type, j, kWave);
+                    const int32_t tc = __shfl(type + (idx == mi ? 4 : 0), j, kWave), tj = tc & 3;
                     const double jax = __shfl(ax, j, kWave), jay = __shfl(ay, j, kWave), jaz = __shfl(az, j, kWave);
                     const double jbx = __shfl(bx, j, kWave), jby = __shfl(by, j, kWave), jbz = __shfl(bz, j, kWave);
                     const bool b_side = g < 2, new_side = (g & 1) == 0;
                     const bool has = j < own && (b_side ? tj != GCMC_MOVE_DELETE : tj != GCMC_MOVE_INSERT) &&
-                                     (new_side ? mt != GCMC_MOVE_DELETE : !ins) && (tj == GCMC_MOVE_INSERT || N > 0);
+                                     (new_side ? mt != GCMC_MOVE_DELETE : !ins) && (tj == GCMC_MOVE_INSERT || N > 0) &&
+                                     (b_side || tc < 4);   // (moves of its own particle, accepted, make it stale)
                     const bool second = new_side && disp;
-                    double u = 0.0, w = 0.0;
+                    double u = 0.0, w = 0.0, r2 = rc2;
                     if (has) {
-                        const double r2 = res_dist2(B.L, second ? p1x : p0x, second ? p1y : p0y, second ? p1z : p0z,
-                                                    make_double3(b_side ? jbx : jax, b_side ? jby : jay, b_side ? jbz : jaz));
+                        r2 = res_dist2(B.L, second ? p1x : p0x, second ? p1y : p0y, second ? p1z : p0z,
+                                       make_double3(b_side ? jbx : jax, b_side ? jby : jay, b_side ? jbz : jaz));
                         u = res_pair(r2, rc2, eps4, sig2, w);
+                    }
+                    const uint64_t close = __ballot(!b_side && r2 < apart2);
+                    if (close) {
+                        // (seldom) the sums again, without the particles that would be taken away from that close
+                        const uint32_t apart = (uint32_t)((close >> 32) | (close >> 48)) & 0xFFFFu;
+                        const double du = u - __shfl_down(u, 16, kWave), dw = w - __shfl_down(w, 16, kWave);
+                        for (uint32_t l = apart; l; l &= l - 1u) {
+                            const int a = (int)__builtin_ctz(l);
+                            const uint64_t same = __ballot(idx == __builtin_amdgcn_readlane(idx, a)) & apart;
+                            if ((int)__builtin_ctzll(same) == a) first |= 1u << a;
+                        }
+                        if (g == 2 && ((first >> j) & 1u)) {
+                            apart_e[j][own] = du;
+                            apart_w[j][own] = dw;
+                        }
+                        if (!b_side && ((apart >> j) & 1u)) u = w = 0.0;
+                        const int32_t pairs = n_in;
+                        su = sw = 0.0;
+                        rp = 0;
+                        rs = 1;
+                        if (disp) rows(std::true_type{});
+                        else rows(std::false_type{});
+                        if (tail) drain(0, tail);
+                        n_in = pairs;
                     }
                     // (new - old) at b, minus (new - old) at a
                     u -= __shfl_down(u, 16, kWave);
@@ -363,7 +402,7 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                     ev_u[part][own] = mt == GCMC_MOVE_DELETE ? -su : su;
                     ev_w[part][own] = mt == GCMC_MOVE_DELETE ? -sw : sw;
                     ev_in[part][own] = n_in;
-                    if (part == parts - 1) ev_pick[own] = pm;
+                    if (part == parts - 1) ev_pick[own] = (pm & 0xFFFFu) | first << 16;
                 }
             }
             if (wv != 0) {
@@ -400,18 +439,36 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                 const bool disp = type == GCMC_MOVE_DISPLACE, ins = type == GCMC_MOVE_INSERT;
                 const bool empty = !ins && N == 0;   // a displacement or deletion in an empty box
                 double dUp = 0.0, dWp = 0.0;
-                uint32_t pick = 0;
+                uint32_t pick = 0;   // and, from bit 16 on, the moves whose particle's terms are kept apart
                 int32_t n_in = 0;
                 if (mine && !empty) {
                     pick = ev_pick[lane];
                     for (int q = 0; q < parts; ++q) {
-                        dUp += ev_u[q][lane];
-                        dWp += ev_w[q][lane];
+                        // (the sums without the particles kept apart were taken by one wavefront)
+                        const bool use = pick < 0x10000u || q == parts - 1;
+                        dUp += use ? ev_u[q][lane] : 0.0;
+                        dWp += use ? ev_w[q][lane] : 0.0;
                         n_in += ev_in[q][lane];
                     }
                 }
                 const int32_t n_round = N;
                 bool stale = false;
+                // sums with the terms kept apart of the particles that are still there, the sums without in
+                // ev_u[0], ev_w[0] from here on
+                const bool any_apart = __ballot(pick >= 0x10000u) != 0;
+                auto with_apart = [&]() {
+                    dUp = ev_u[0][lane];
+                    dWp = ev_w[0][lane];
+                    for (uint32_t l = pick >> 16; l; l &= l - 1u) {
+                        dUp += apart_e[__builtin_ctz(l)][lane];
+                        dWp += apart_w[__builtin_ctz(l)][lane];
+                    }
+                };
+                if (any_apart && mine) {
+                    ev_u[0][lane] = dUp;
+                    ev_w[0][lane] = dWp;
+                    with_apart();
+                }
                 double dUt = 0.0, arg = 0.0;
                 double aft_n = 0.0, aft_u = 0.0, aft_w = 0.0;
                 uint64_t accbits = 0;
@@ -469,6 +526,15 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                     N += fins ? 1 : (fdel ? -1 : 0);
                     U += read_lane(dUp, f);
                     Wvir += read_lane(dWp, f);
+                    if (any_apart) {   // (seldom)
+                        const uint32_t gone = fins ? 0u : (uint32_t)__ballot(idx == fi) << 16;
+                        if (lane > f && lane < kw) {
+                            pick &= ~gone;
+                            ev_u[0][lane] += corr_e[f][lane];
+                            ev_w[0][lane] += corr_w[f][lane];
+                            with_apart();
+                        }
+                    }
                     if (lane == f) {
                         aft_n = (double)N;
                         aft_u = U;
@@ -485,21 +551,19 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                 const bool done = lane < k;
                 const bool acc = done && ((accbits >> lane) & 1ull) != 0;
                 if (done) {
-                    const double one = 1.0, a = acc ? one : 0.0;
-                    att0 += disp ? one : 0.0;
-                    att1 += ins ? one : 0.0;
-                    att2 += disp || ins ? 0.0 : one;
-                    acc0 += disp ? a : 0.0;
-                    acc1 += ins ? a : 0.0;
-                    acc2 += disp || ins ? 0.0 : a;
-                    sum_n += aft_n;
-                    sum_n2 += aft_n * aft_n;
-                    sum_u += aft_u + tk * aft_n * aft_n;
-                    sum_w += aft_w;
+                    auto add = [&](int what, double v) {   // (an LDS instruction nobody waits for)
+                        __hip_atomic_fetch_add(&acc_s[what][lane], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    };
+                    add(kAtt + type, 1.0);
+                    if (acc) add(kAcc + type, 1.0);
+                    add(kSumN, aft_n);
+                    add(kSumN2, aft_n * aft_n);
+                    add(kSumU, aft_u + tk * aft_n * aft_n);
+                    add(kSumW, aft_w);
                     const double c = empty ? 0.0 : (double)(n_round - (ins ? 0 : 1));
-                    cand += c;
-                    evals += disp ? 2.0 * c : c;
-                    incut += (double)n_in;
+                    add(kCand, c);
+                    add(kEvals, disp ? 2.0 * c : c);
+                    add(kIncut, (double)n_in);
                     if (trace) {
                         gcmc_log r;
                         r.type = type;
@@ -594,23 +658,11 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
         }
     }
     maxc = wave_max_i32_uniform(maxc);
-    if (wv == 0) {
-        sum_n = wave_sum_vec(sum_n);
-        sum_n2 = wave_sum_vec(sum_n2);
-        sum_u = wave_sum_vec(sum_u);
-        sum_w = wave_sum_vec(sum_w);
-        att0 = wave_sum_vec(att0);
-        att1 = wave_sum_vec(att1);
-        att2 = wave_sum_vec(att2);
-        acc0 = wave_sum_vec(acc0);
-        acc1 = wave_sum_vec(acc1);
-        acc2 = wave_sum_vec(acc2);
-        cand = wave_sum_vec(cand);
-        evals = wave_sum_vec(evals);
-        incut = wave_sum_vec(incut);
-    }
     if (lane == 0) wred[wv] = maxc;
     __syncthreads();
+    double t[kStats];
+    if (wv == 0)
+        for (int what = 0; what < kStats; ++what) t[what] = wave_sum_vec(lane < W ? acc_s[what][lane] : 0.0);
     if (tid == 0) {
         int32_t mx = 0;
         for (int v = 0; v < W * S; ++v) mx = wred[v] > mx ? wred[v] : mx;
@@ -632,13 +684,16 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
         }
         ChainSums L;
         L.moves = m;
-        L.att[0] = (int64_t)att0; L.att[1] = (int64_t)att1; L.att[2] = (int64_t)att2;
-        L.acc[0] = (int64_t)acc0; L.acc[1] = (int64_t)acc1; L.acc[2] = (int64_t)acc2;
-        L.sum_n = sum_n;
-        L.sum_n2 = sum_n2;
-        L.sum_u = sum_u;
-        L.sum_w = sum_w;
-        finish_launch(B, st, L, N, U, Wvir, 0, (int64_t)cand, (int64_t)evals, (int64_t)incut, stats ? stats + bi : nullptr);
+        for (int k = 0; k < 3; ++k) {
+            L.att[k] = (int64_t)t[kAtt + k];
+            L.acc[k] = (int64_t)t[kAcc + k];
+        }
+        L.sum_n = t[kSumN];
+        L.sum_n2 = t[kSumN2];
+        L.sum_u = t[kSumU];
+        L.sum_w = t[kSumW];
+        finish_launch(B, st, L, N, U, Wvir, 0, (int64_t)t[kCand], (int64_t)t[kEvals], (int64_t)t[kIncut],
+                      stats ? stats + bi : nullptr);
     }
 }
 
@@ -646,7 +701,7 @@ using resident_fn = void (*)(const DevBox*, const int32_t*, int64_t, uint64_t, g
 
 bool resident_cfg_exists(int waves) { return waves == 4 || waves == 8; }
 
-// waves = 4: four moves at a time by two wavefronts each, in 128 registers (seven
+// waves = 4: four moves at a time by two wavefronts each, in 128 registers (three
 // spilled), so that a compute unit holds two boxes, or one beside a speculative one.
 // One wavefront a move left the SIMDs waiting (a wavefront issues an instruction every
 // eight cycles or so): 200 to 512 boxes of up to 1,024 particles 1.95 ms per 1,000 moves,
