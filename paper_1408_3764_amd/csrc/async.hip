@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kWave*(E + 1)) void k_chain_async(const DevBox* __r
                                                                 uint64_t ctr0, gcmc_stats* stats, gcmc_log* trace) {
     __shared__ uint32_t tab[kMaxStencil];
     __shared__ int32_t offs[64];
-    __shared__ uint8_t own[E][kSpecOwn];
+    __shared__ SpecOwn<0> own[E];
     __shared__ double pq[E][kSpecQueue];   // each evaluator's queue of in-cutoff pairs
     __shared__ AsyncShared S;
     const int bi = order ? order[blockIdx.x] : (int)blockIdx.x;

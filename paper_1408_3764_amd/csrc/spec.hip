@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
     __shared__ uint32_t tab[kMaxStencil];
     __shared__ int32_t offs[kOffs];
     __shared__ SpecRec recs_s[2][W];            // the round's evaluations, by round parity
-    __shared__ __align__(8) uint32_t own[W][spec_own_words(NG)];   // cell bases and start masks, or record indices
+    __shared__ SpecOwn<NG> own[W];              // cell bases and start masks, or record indices
     __shared__ double4 top[2 * W];              // records of particles base .. base + 2W - 1
     __shared__ double lpi[kSpecPref], lpd[kSpecPref];   // the deciding wavefront's prefactors
     // its statistics, lane k's sums over the moves it decided as move k of a round (counts as doubles, exact

@@ -19,10 +19,18 @@ namespace gcmc {
 
 constexpr int kSpecOwn = 8192;       // flattened candidates per wavefront of the 32-cell path
 constexpr int kSpecRecWin = 1024;    // record indices per window of the microcell path
-// 32-bit words of a wavefront's owner buffer: the 32-cell path keeps 64 cell bases and one
-// start mask per 64 flattened candidates (a second stencil begins a row of its own); the microcell
-// path a window of record indices
-constexpr int spec_own_words(int ng) { return ng ? kSpecRecWin : kWave + 2 * (kSpecOwn / 64 + 1); }
+// A wavefront's owner buffer in LDS.  The 32-cell path keeps 64 cell bases and one start mask per 64
+// flattened candidates (a second stencil begins a row of its own), written by 64-bit atomics;
+// the microcell path a window of record indices.
+template <int NG>
+struct SpecOwn {
+    uint32_t rec[kSpecRecWin];
+};
+template <>
+struct SpecOwn<0> {
+    uint32_t base[kWave];
+    uint64_t starts[kSpecOwn / 64 + 1];
+};
 constexpr int kSpecGroups = 16;      // groups of 64 stencil cells: stencils of up to 512 cells (two for a displacement)
 constexpr int kSpecMaxStencil = kSpecGroups * kWave / 2;
 constexpr int kSpecGroupsSmall = 4;  // the instantiation for stencils of up to 128 cells (fewer registers)
@@ -143,7 +151,7 @@ struct SpecSums {
 // bit marks a displacement's old position, whose terms are subtracted).  mid() runs
 // once while the counters are on their way.
 template <int CR, int NG, typename Mid>
-__device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
+__device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* tab, const int32_t* offs, SpecOwn<NG>& ownbuf,
                                               double* q, int type, int two, const double* p0, const double* p1,
                                               const int32_t* c0, const int32_t* c1, int32_t cl0, int32_t cl1,
                                               int32_t excl_slot, bool no_full, const Mid& mid) {
@@ -269,8 +277,8 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
         // k = 0, 1, ...; cbk[k] = the cell's record index minus its first flattened position,
         // and bit q of the row masks marks a flattened position q where a nonempty cell begins,
         // so the owner of q is the number of marks at or below q, minus one
-        uint32_t* cbk = static_cast<uint32_t*>(ownbuf);                // [64]
-        uint64_t* smask = reinterpret_cast<uint64_t*>(cbk + kWave);   // [kSpecOwn / 64 + 1]
+        uint32_t* cbk = ownbuf.base;
+        uint64_t* smask = ownbuf.starts;
         const int nrows = (total + kWave - 1) / kWave;
         for (int r = lane; r < nrows; r += kWave) smask[r] = 0;
         wave_lds_sync();
@@ -357,7 +365,7 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
         }
         if (out.cnt0 > 0) out.elast = gload(B.ent + ((size_t)(uint32_t)cl0 * (uint32_t)B.cap + (out.cnt0 - 1)));
         // ---- record indices of the flattened candidates, window by window
-        uint32_t* recw = static_cast<uint32_t*>(ownbuf);
+        uint32_t* recw = ownbuf.rec;
         for (int w0 = 0; w0 < total; w0 += kSpecRecWin) {
             const int w1 = (total - w0) < kSpecRecWin ? total : w0 + kSpecRecWin;
 #pragma unroll
@@ -417,7 +425,7 @@ struct SpecNoPub {
 // here, for k < 16.  pq: this wavefront's pair queue (kSpecQueue doubles of
 // LDS).
 template <int CR, int NG, int RING, typename Early = SpecNoEarly, typename Pub = SpecNoPub>
-__device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, const int32_t* offs, void* ownbuf,
+__device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, const int32_t* offs, SpecOwn<NG>& ownbuf,
                                           double* pq, const DrawRing<RING>* dr, uint64_t ctr_round, int k, int64_t N,
                                           bool no_full, double a_ins, double a_del, SpecRec* out,
                                           const Early& early = Early(), const Pub& pub = Pub()) {
