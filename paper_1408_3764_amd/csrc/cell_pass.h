@@ -35,9 +35,6 @@ __device__ __forceinline__ double4 sload4(const double4* p) {
     const gcmc_d4v v = *(cptr)(uintptr_t)p;
     return make_double4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ int32_t sload_i32(const int32_t* p) {
-    return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p;
-}
 
 // Box constants of a pass in scalar registers.
 struct PassBox {
