@@ -144,7 +144,7 @@ int gcmc_total_energy(gcmc_box* box, int32_t all_pairs, double* d_U, double* d_e
     const int64_t need = total_partials_needed(box->d, all_pairs != 0, h.n);
     if ((rc = ensure_scratch(box, need))) return rc;
     const int r = launch_total(box->d, box->d_desc, all_pairs != 0, d_e, box->scratch, box->scratch_len,
-                               d_U, s, h.n);
+                               d_U, s, h.n, h.maxcount);
     if (r) return set_error(GCMC_ERR_INVALID_ARG, "scratch too small");
     GCMC_HIP(hipGetLastError());
     return GCMC_OK;
@@ -157,7 +157,7 @@ int gcmc_virial(gcmc_box* box, double* d_out, void* stream) {
     int rc = poisoned_check(box, s, &h);
     if (rc) return rc;
     if ((rc = ensure_scratch(box, total_partials_needed(box->d, false, h.n)))) return rc;
-    const int r = launch_virial(box->d, box->d_desc, box->scratch, box->scratch_len, d_out, s, h.n);
+    const int r = launch_virial(box->d, box->d_desc, box->scratch, box->scratch_len, d_out, s, h.n, h.maxcount);
     if (r) return set_error(GCMC_ERR_INVALID_ARG, "scratch too small");
     GCMC_HIP(hipGetLastError());
     return GCMC_OK;
@@ -170,7 +170,7 @@ int gcmc_backward(gcmc_box* box, double* d_grad, double* d_deps, double* d_dsig,
     int rc = poisoned_check(box, s, &h);
     if (rc) return rc;
     if ((rc = ensure_scratch(box, grad_partials_needed(box->d, h.n)))) return rc;
-    const int r = launch_grad(box->d, box->d_desc, d_grad, box->scratch, d_deps, d_dsig, s, h.n);
+    const int r = launch_grad(box->d, box->d_desc, d_grad, box->scratch, d_deps, d_dsig, s, h.n, h.maxcount);
     if (r) return set_error(GCMC_ERR_INVALID_ARG, "scratch too small");
     GCMC_HIP(hipGetLastError());
     return GCMC_OK;

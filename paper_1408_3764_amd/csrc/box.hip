@@ -798,7 +798,7 @@ int gcmc_box_rescale(gcmc_box* box, const double* h_L, double* d_U, void* stream
     if (h.error) return set_error(GCMC_ERR_POISONED, "box holds a latched error");
     // energies at the old volume
     if ((rc_ = ensure_scratch(box, total_partials_needed(B, false, h.n)))) return rc_;
-    int r = launch_total(B, box->d_desc, false, nullptr, box->scratch, box->scratch_len, d_U + 2, s, h.n);
+    int r = launch_total(B, box->d_desc, false, nullptr, box->scratch, box->scratch_len, d_U + 2, s, h.n, h.maxcount);
     if (r) return set_error(GCMC_ERR_INVALID_ARG, "scratch too small");
     // the new grid (the box's rule for cells per axis) and force-field constants
     gcmc_box_desc d;
@@ -857,7 +857,7 @@ int gcmc_box_rescale(gcmc_box* box, const double* h_L, double* d_U, void* stream
         // energies at the new volume (the running pair energy is reset to U_pair); a cell that
         // overflowed is summed up to its capacity, and what that gives is computed again below
         if ((rc_ = ensure_scratch(box, total_partials_needed(B, false, h.n)))) return rc_;
-        r = launch_total(B, box->d_desc, false, nullptr, box->scratch, box->scratch_len, d_U, s, h.n);
+        r = launch_total(B, box->d_desc, false, nullptr, box->scratch, box->scratch_len, d_U, s, h.n, h.maxcount);
         if (r) return set_error(GCMC_ERR_INVALID_ARG, "scratch too small");
         GCMC_HIP(hipGetLastError());
         if ((rc_ = read_state(box, &h2, s))) return rc_;
@@ -881,7 +881,7 @@ int gcmc_box_rescale(gcmc_box* box, const double* h_L, double* d_U, void* stream
         if (h2.error) return set_error(h2.error, "re-binning failed");
         if ((rc_ = sync_desc(box))) return rc_;
         if ((rc_ = ensure_scratch(box, total_partials_needed(B, false, h.n)))) return rc_;
-        r = launch_total(B, box->d_desc, false, nullptr, box->scratch, box->scratch_len, d_U, s, h.n);
+        r = launch_total(B, box->d_desc, false, nullptr, box->scratch, box->scratch_len, d_U, s, h.n, h2.maxcount);
         if (r) return set_error(GCMC_ERR_INVALID_ARG, "scratch too small");
         GCMC_HIP(hipGetLastError());
         GCMC_HIP(hipStreamSynchronize(s));

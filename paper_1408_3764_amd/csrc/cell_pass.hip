@@ -250,6 +250,35 @@ __device__ __forceinline__ double image_signed(double d, double L, double hL) {
     return __builtin_fabs(d) > hL ? t : d;
 }
 
+// The wavefront's sums for the eps and sigma derivatives of each species pair q, v1 = s12 - s6 and
+// v2 = 2 s12 - s6: in registers per unordered pair for up to two species, else in LDS;
+// partial[(2 q + v) * gridDim.x + block].
+template <int S>
+__device__ __forceinline__ void pass_param_sums(const double* v1, const double* v2, const double* pv, int ns,
+                                                double* partial) {
+    constexpr bool REGS = S <= 2;
+    const int lane = threadIdx.x;
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < S * S; ++q) {
+        if (q < ns * ns) {
+            double s1, s2q;
+            if (REGS) {
+                const int k = S == 1 ? 0 : (q + 1) / 2;
+                s1 = wave_sum(v1[REGS ? k : 0]) * (q == 1 || q == 2 ? 0.5 : 1.0);
+                s2q = wave_sum(v2[REGS ? k : 0]) * (q == 1 || q == 2 ? 0.5 : 1.0);
+            } else {
+                s1 = (pv[8 * q] + pv[8 * q + 1]) + (pv[8 * q + 2] + pv[8 * q + 3]);
+                s2q = (pv[8 * q + 4] + pv[8 * q + 5]) + (pv[8 * q + 6] + pv[8 * q + 7]);
+            }
+            if (lane == 0) {
+                partial[(size_t)(2 * q) * gridDim.x + blockIdx.x] = s1;
+                partial[(size_t)(2 * q + 1) * gridDim.x + blockIdx.x] = s2q;
+            }
+        }
+    }
+}
+
 // S: a bound on the number of species (1, 2 or kMaxSpecies).  PARAMS: also the
 // sums for the eps and sigma derivatives of each species pair q: v1 = s12 - s6 and
 // v2 = 2 s12 - s6, in registers for up to two species, else in LDS;
@@ -399,27 +428,165 @@ __global__ __launch_bounds__(kWave, 5) void k_pair_grad(const DevBox* __restrict
             }
         }
     });
-    if (PARAMS) {
-        wave_lds_sync();
+    if (PARAMS) pass_param_sums<S>(v1, v2, pv, ns, partial);
+}
+
+// ------------------------------------------------------- sparse boxes
+// The same passes for a vapour.  With a particle or two in a cell a wavefront of the
+// kernels above gathers the candidates of a whole stencil (some 400 instructions) for one or two
+// home particles.  Here each lane has a home particle of its own and walks its stencil: a
+// wavefront reads the counters of 64 cells at once, lists their particles in LDS and takes 64
+// of the list at a time.  A total meets each pair from one side, as above; energies and forces
+// take the full stencil.  Bound by the latency of the counters and records, so the next
+// counter and two records are requested ahead.  262,144 particles at a density of 0.02, calls of
+// total energy / energies / gradient: 264, 332 and 399 us with the kernels above and empty cells one
+// by one, 170, 174 and 255 with the counters of 64 cells at once, 76, 90 and 98 so.
+constexpr int kSparseStep = 8;     // places of a cell listed at once
+constexpr int kSparseAtOnce = 2;   // records requested together (one: 3 to 9 % slower, four level)
+constexpr int kSparseHome = kWave - 1 + kWave * kSparseStep;
+enum { kPairU, kPairW, kPairEach, kPairGrad };
+
+// out: the energies (kPairEach) or gradients (kPairGrad, may be NULL) by particle id; partial as in the
+// kernels above (S, PARAMS: as in k_pair_grad).
+template <int S, int MODE, bool PARAMS>
+__global__ __launch_bounds__(kWave) void k_pair_sparse(const DevBox* __restrict__ boxp, int32_t span, int64_t n,
+                                                       double* out, double* partial) {
+    constexpr bool MIX = S > 1, HALF = MODE <= kPairW;
+    constexpr int Q = S * S, K = S == 1 ? 1 : 3;
+    constexpr bool REGS = S <= 2;
+    __shared__ uint32_t home[kSparseHome];
+    __shared__ double te4[Q], ts2[Q];
+    __shared__ double pv[REGS || !PARAMS ? 1 : 2 * Q * 4];
+    const DevBox& B = *boxp;
+    const PassBox P = pass_box(B);
+    const int lane = threadIdx.x;
+    const int ns = uni(B.ns);
+    if (MIX && lane < Q) {
+        te4[lane] = B.eps4[lane];
+        ts2[lane] = B.sig2[lane];
+    }
+    if (!REGS && PARAMS)
+        for (int t = lane; t < 2 * Q * 4; t += kWave) pv[t] = 0.0;
+    const double e4 = unid(B.eps4[0]), s2 = unid(B.sig2[0]);
+    const double hL[3] = {unid(B.hL[0]), unid(B.hL[1]), unid(B.hL[2])};
+    double acc = 0.0;   // energies or virials of this lane's pairs
+    double v1[K], v2[K];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            if (q < ns * ns) {
-                double s1, s2q;
-                if (REGS) {
-                    const int k = S == 1 ? 0 : (q + 1) / 2;
-                    s1 = wave_sum(v1[REGS ? k : 0]) * (q == 1 || q == 2 ? 0.5 : 1.0);
-                    s2q = wave_sum(v2[REGS ? k : 0]) * (q == 1 || q == 2 ? 0.5 : 1.0);
-                } else {
-                    s1 = (pv[8 * q] + pv[8 * q + 1]) + (pv[8 * q + 2] + pv[8 * q + 3]);
-                    s2q = (pv[8 * q + 4] + pv[8 * q + 5]) + (pv[8 * q + 6] + pv[8 * q + 7]);
+    for (int k = 0; k < K; ++k) v1[k] = v2[k] = 0.0;
+
+    // home particle h meets o: ei and f are its energy and force so far
+    auto pair = [&](const double4& h, const double4& o, int sa, double& ei, double* f) {
+        const double dx = image_signed(o.x - h.x, P.L[0], hL[0]), dy = image_signed(o.y - h.y, P.L[1], hL[1]),
+                     dz = image_signed(o.z - h.z, P.L[2], hL[2]);
+        const double r2 = (dx * dx + dy * dy) + dz * dz;
+        if (!(r2 < P.rc2)) return;
+        const int q = MIX ? sa + meta_species(o.w) : 0;
+        const double a = MIX ? te4[q] : e4, b = MIX ? ts2[q] : s2;
+        if (MODE == kPairU) acc += lj_from_r2(r2, P.rc2, a, b);
+        if (MODE == kPairW) acc += lj_virial_from_r2(r2, P.rc2, a, b);
+        if (MODE == kPairEach) ei += lj_from_r2(r2, P.rc2, a, b);
+        if (MODE == kPairGrad && r2 != 0.0) {   // (overlapping particles: no direction, no term)
+            const double ir2 = 1.0 / r2;
+            const double sr2 = b * ir2;
+            const double s6 = sr2 * sr2 * sr2;
+            const double s12 = s6 * s6;
+            const double w = 2.0 * s12 - s6;
+            const double coef = (6.0 * a * ir2) * w;
+            f[0] += coef * dx;
+            f[1] += coef * dy;
+            f[2] += coef * dz;
+            if (PARAMS && REGS) {
+#pragma unroll
+                for (int m = 0; m < K; ++m) {   // pairs 00, 01 and 10, 11
+                    const bool mine = K == 1 || (m == 0 ? q == 0 : (m == 2 ? q == 3 : q == 1 || q == 2));
+                    v1[m] += mine ? s12 - s6 : 0.0;
+                    v2[m] += mine ? w : 0.0;
                 }
-                if (lane == 0) {
-                    partial[(size_t)(2 * q) * gridDim.x + blockIdx.x] = s1;
-                    partial[(size_t)(2 * q + 1) * gridDim.x + blockIdx.x] = s2q;
+            }
+            if (PARAMS && !REGS) {
+                atomicAdd(&pv[(2 * q) * 4 + (lane & 3)], s12 - s6);
+                atomicAdd(&pv[(2 * q + 1) * 4 + (lane & 3)], w);
+            }
+        }
+    };
+    // the listed particles from .. from + cnt - 1, one per lane
+    auto batch = [&](uint32_t from, uint32_t cnt) {
+        wave_lds_sync();
+        if ((uint32_t)lane < cnt) {
+            const uint32_t slot = home[from + lane];
+            const double4 h = gload(P.ent + slot);
+            const int32_t c = (int32_t)(slot / (uint32_t)P.cap), own = (int32_t)slot - c * P.cap;
+            const int32_t cz = c / P.M01, cy = (c - cz * P.M01) / P.M0, cx = c - cz * P.M01 - cy * P.M0;
+            const int sa = MIX ? meta_species(h.w) * ns : 0;
+            double f[3] = {0.0, 0.0, 0.0}, ei = 0.0;
+            // (the next cell's counter is on its way while this one's particles are met)
+            auto counter = [&](int t, int32_t& nb) {
+                nb = (int32_t)stencil_cell(B, gload(P.stab + t), cx, cy, cz);
+                bool take = true;
+                if (HALF && nb != c) {
+                    int32_t d = nb - c;
+                    d += d < 0 ? P.ncells : 0;
+                    const uint32_t d2 = 2u * (uint32_t)d;
+                    take = d2 < (uint32_t)P.ncells || (d2 == (uint32_t)P.ncells && c < nb);
                 }
+                return take ? gload(P.count + nb) : 0;
+            };
+            int32_t next = c, after = counter(0, next);
+            for (int t = 0; t < P.nst; ++t) {
+                const int32_t nb = next, nc = after > P.cap ? P.cap : after;
+                if (t + 1 < P.nst) after = counter(t + 1, next);
+                const double4* e = P.ent + (size_t)nb * (uint32_t)P.cap;
+                const int32_t skip = nb == c ? own : -1;
+                for (int32_t k0 = HALF ? skip + 1 : 0; k0 < nc; k0 += kSparseAtOnce) {
+                    double4 o[kSparseAtOnce];
+#pragma unroll
+                    for (int u = 0; u < kSparseAtOnce; ++u)
+                        if (k0 + u < nc) o[u] = gload(e + k0 + u);
+#pragma unroll
+                    for (int u = 0; u < kSparseAtOnce; ++u) {
+                        if (k0 + u >= nc || (!HALF && k0 + u == skip)) continue;
+                        pair(h, o[u], sa, ei, f);
+                    }
+                }
+            }
+            const int32_t id = meta_low(h.w);
+            if (MODE == kPairEach) {
+                out[id] = ei;
+                acc += 0.5 * ei;
+            }
+            if (MODE == kPairGrad && out) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) out[a * n + id] = f[a];
+            }
+        }
+        wave_lds_sync();
+    };
+    uint32_t tail = 0;   // listed particles (wave-uniform; the last ones are taken first)
+    const uint32_t x = blockIdx.x & 7u;
+    for (uint32_t j = blockIdx.x >> 3;; j += gridDim.x >> 3) {
+        const uint32_t q = j / (uint32_t)span, b = (q * 8u + x) * (uint32_t)span + (j - q * (uint32_t)span);
+        if ((uint64_t)b * kWave >= (uint64_t)P.ncells) break;   // b grows with j
+        const int32_t c = (int32_t)(b * kWave) + lane;
+        int32_t nc = c < P.ncells ? gload(P.count + c) : 0;
+        nc = nc > P.cap ? P.cap : nc;
+        for (int32_t k0 = 0; __ballot(k0 < nc); k0 += kSparseStep) {
+            const int32_t left = nc - k0, m = left < 0 ? 0 : (left > kSparseStep ? kSparseStep : left);
+            const int32_t incl = pass_scan(m);
+            for (int32_t k = 0; k < m; ++k)
+                home[tail + (uint32_t)(incl - m + k)] = (uint32_t)c * (uint32_t)P.cap + (uint32_t)(k0 + k);
+            tail += (uint32_t)__builtin_amdgcn_readlane(incl, kWave - 1);
+            while (tail >= (uint32_t)kWave) {
+                tail -= kWave;
+                batch(tail, kWave);
             }
         }
     }
+    if (tail) batch(0u, tail);
+    if (MODE != kPairGrad) {
+        acc = wave_sum(acc);
+        if (lane == 0) partial[blockIdx.x] = acc;
+    }
+    if (PARAMS) pass_param_sums<S>(v1, v2, pv, ns, partial);
 }
 
 // ------------------------------------------------------------ finishes
@@ -514,14 +681,31 @@ constexpr int kPassChunks = 8 * 16;   // chunks of cells dealt to the XCDs
 struct PassGrid {
     int32_t parts, span;
     unsigned blocks;
+    bool sparse;
 };
 
-static PassGrid pass_grid(const DevBox& hb, int64_t n) {
+static PassGrid pass_grid(const DevBox& hb, int64_t n, int32_t maxcount) {
     const int64_t cells = hb.ncells > 0 ? hb.ncells : 1;
     const int64_t mean = n / cells;
+    PassGrid g;
+    // One lane per particle: fewer particles than cells and enough of them that a wavefront per cell would
+    // come round several times, or up to two a cell in a large box, and no dense part (a drop, a slab), where a
+    // lane would walk full cells.  us, wavefront per cell against lane per particle, gradient: 32,768 particles
+    // at a mean of 0.3 80 and 60, of 0.8 64 and 73; 65,536 at 0.8 90 and 80; 262,144 at 0.8 227 and 106, at 1.6
+    // 174 and 174 (energies 123 and 169); 524,288 at 1.6 300 and 222 (207 and 210).
+    g.sparse = ((n >= 65536 && n < cells) || (n >= 524288 && n < 2 * cells)) && maxcount <= 16;
+    if (g.sparse) {
+        // groups of 64 cells in place of cells; half a listful of particles for each wavefront (one batch then
+        // takes them, twice the wavefronts are in flight), a whole one where the wavefronts would run out
+        const int64_t groups = (cells + kWave - 1) / kWave, half = n / (kWave / 2);
+        const int64_t waves = std::min(groups, half <= 16384 ? half : n / kWave);
+        g.parts = 1;
+        g.span = (int32_t)((groups + kPassChunks - 1) / kPassChunks);
+        g.blocks = 8u * (unsigned)std::min<int64_t>((waves + 7) / 8, 2048);
+        return g;
+    }
     int64_t parts = std::max<int64_t>((4096 + cells - 1) / cells, (mean + 23) / 24);
     parts = std::max<int64_t>(1, std::min(parts, mean / 2));
-    PassGrid g;
     g.parts = (int32_t)parts;
     g.span = (int32_t)((cells + kPassChunks - 1) / kPassChunks);
     g.blocks = 8u * (unsigned)std::min<int64_t>((cells + 7) / 8 * parts, 2048);
@@ -532,14 +716,24 @@ void launch_total_finish(const DevBox* d_box, const double* partial, int64_t np,
     hipLaunchKernelGGL(k_pair_total_finish, dim3(1), dim3(kFinish), 0, s, d_box, partial, np, U);
 }
 
-int64_t pass_partials(const DevBox& hb, int64_t n) { return pass_grid(hb, n).blocks; }
+int64_t pass_partials(const DevBox& hb, int64_t n) { return pass_grid(hb, n, INT32_MAX).blocks; }   // (sparse: fewer)
+
+template <int MODE>
+static void launch_sparse(const DevBox& hb, const DevBox* d_box, const PassGrid& g, int64_t n, double* out,
+                          double* partial, hipStream_t s) {
+    auto f = hb.ns > 1 ? k_pair_sparse<kMaxSpecies, MODE, false> : k_pair_sparse<1, MODE, false>;
+    hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.span, n, out, partial);
+}
 
 int launch_total_cells(const DevBox& hb, const DevBox* d_box, double* e_out, double* partial, int64_t partial_len,
-                       double* U, hipStream_t s, int64_t n) {
-    const PassGrid g = pass_grid(hb, n);
+                       double* U, hipStream_t s, int64_t n, int32_t maxcount) {
+    const PassGrid g = pass_grid(hb, n, maxcount);
     if (g.blocks > partial_len) return -1;
     const bool mix = hb.ns > 1;
-    if (e_out) {
+    if (g.sparse) {
+        if (e_out) launch_sparse<kPairEach>(hb, d_box, g, n, e_out, partial, s);
+        else launch_sparse<kPairU>(hb, d_box, g, n, nullptr, partial, s);
+    } else if (e_out) {
         auto f = mix ? k_pair_each<true> : k_pair_each<false>;
         hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, g.span, e_out, partial);
     } else {
@@ -551,25 +745,40 @@ int launch_total_cells(const DevBox& hb, const DevBox* d_box, double* e_out, dou
 }
 
 int launch_virial(const DevBox& hb, const DevBox* d_box, double* partial, int64_t partial_len, double* out,
-                  hipStream_t s, int64_t n) {
-    const PassGrid g = pass_grid(hb, n);
+                  hipStream_t s, int64_t n, int32_t maxcount) {
+    const PassGrid g = pass_grid(hb, n, maxcount);
     if (g.blocks > partial_len) return -1;
-    auto f = hb.ns > 1 ? k_pair_total<true, true> : k_pair_total<false, true>;
-    hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, g.span, partial);
+    if (g.sparse) {
+        launch_sparse<kPairW>(hb, d_box, g, n, nullptr, partial, s);
+    } else {
+        auto f = hb.ns > 1 ? k_pair_total<true, true> : k_pair_total<false, true>;
+        hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, g.span, partial);
+    }
     hipLaunchKernelGGL(k_pair_virial_finish, dim3(1), dim3(kFinish), 0, s, d_box, partial, (int64_t)g.blocks, out);
     return 0;
 }
 
 int64_t grad_partials_needed(const DevBox& hb, int64_t n) { return 2 * hb.ns * hb.ns * pass_partials(hb, n); }
 
+template <int S>
+static void launch_grad_of(const DevBox* d_box, const PassGrid& g, int64_t n, bool params, double* grad, double* partial,
+                           hipStream_t s) {
+    if (g.sparse) {
+        auto f = params ? k_pair_sparse<S, kPairGrad, true> : k_pair_sparse<S, kPairGrad, false>;
+        hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.span, n, grad, partial);
+    } else {
+        auto f = params ? k_pair_grad<S, true> : k_pair_grad<S, false>;
+        hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, g.span, n, grad, partial);
+    }
+}
+
 int launch_grad(const DevBox& hb, const DevBox* d_box, double* grad, double* partial, double* deps, double* dsig,
-                hipStream_t s, int64_t n) {
-    const PassGrid g = pass_grid(hb, n);
+                hipStream_t s, int64_t n, int32_t maxcount) {
+    const PassGrid g = pass_grid(hb, n, maxcount);
     const bool params = deps || dsig;
-    auto f = hb.ns > 2    ? (params ? k_pair_grad<kMaxSpecies, true> : k_pair_grad<kMaxSpecies, false>)
-             : hb.ns == 2 ? (params ? k_pair_grad<2, true> : k_pair_grad<2, false>)
-                          : (params ? k_pair_grad<1, true> : k_pair_grad<1, false>);
-    hipLaunchKernelGGL(f, dim3(g.blocks), dim3(kWave), 0, s, d_box, g.parts, g.span, n, grad, partial);
+    if (hb.ns > 2) launch_grad_of<kMaxSpecies>(d_box, g, n, params, grad, partial, s);
+    else if (hb.ns == 2) launch_grad_of<2>(d_box, g, n, params, grad, partial, s);
+    else launch_grad_of<1>(d_box, g, n, params, grad, partial, s);
     if (params)
         hipLaunchKernelGGL(k_pair_grad_finish, dim3(hb.ns * hb.ns), dim3(kFinish), 0, s, d_box, partial,
                            (int64_t)g.blocks, deps, dsig);

@@ -474,8 +474,8 @@ __device__ int commit_ap(const DevBox& B, const APTrial& T, const double4& rec, 
 
 // ------------------------------------------------------------ launchers
 int launch_total(const DevBox& hb, const DevBox* d_box, bool all_pairs, double* e_out, double* partial,
-                 int64_t partial_len, double* U, hipStream_t s, int64_t n) {
-    if (!all_pairs) return launch_total_cells(hb, d_box, e_out, partial, partial_len, U, s, n);
+                 int64_t partial_len, double* U, hipStream_t s, int64_t n, int32_t maxcount) {
+    if (!all_pairs) return launch_total_cells(hb, d_box, e_out, partial, partial_len, U, s, n, maxcount);
     const int64_t nb = n > 0 ? (n + kBlk - 1) / kBlk : 1;
     if (nb > partial_len) return -1;
     auto f = hb.ns > 1 ? k_total_allpairs<true> : k_total_allpairs<false>;

@@ -526,17 +526,17 @@ void launch_neighbors(const DevBox* d_box, const double* pts, const int32_t* exc
 // cell_pass.hip
 int64_t pass_partials(const DevBox& hb, int64_t n);
 int launch_total_cells(const DevBox& hb, const DevBox* d_box, double* e_out, double* partial, int64_t partial_len,
-                       double* U, hipStream_t s, int64_t n);
+                       double* U, hipStream_t s, int64_t n, int32_t maxcount);
 void launch_total_finish(const DevBox* d_box, const double* partial, int64_t np, double* U, hipStream_t s);
 int launch_virial(const DevBox& hb, const DevBox* d_box, double* partial, int64_t partial_len, double* out,
-                  hipStream_t s, int64_t n);
+                  hipStream_t s, int64_t n, int32_t maxcount);
 int64_t grad_partials_needed(const DevBox& hb, int64_t n);
 int launch_grad(const DevBox& hb, const DevBox* d_box, double* grad, double* partial, double* deps, double* dsig,
-                hipStream_t s, int64_t n);
+                hipStream_t s, int64_t n, int32_t maxcount);
 
 // energy.hip
 int launch_total(const DevBox& hb, const DevBox* d_box, bool all_pairs, double* e_out, double* partial,
-                 int64_t partial_len, double* U, hipStream_t s, int64_t n);
+                 int64_t partial_len, double* U, hipStream_t s, int64_t n, int32_t maxcount);
 int64_t total_partials_needed(const DevBox& hb, bool all_pairs, int64_t n);
 int64_t ap_chunk_len();
 int launch_delta_allpairs(const DevBox* d_box, int64_t n, const gcmc_move* moves, int64_t n_moves, double* scratch,

@@ -67,7 +67,7 @@ int gcmc_total_energy_noalloc(gcmc_box* box, int32_t all_pairs, double* d_U, dou
         return set_error(GCMC_ERR_INVALID_ARG, "the pass needs " + std::to_string(need) +
                                                    " doubles of scratch; the static buffer holds " +
                                                    std::to_string(kNoAllocDoubles));
-    if (launch_total(box->d, box->d_desc, all_pairs != 0, d_e, buf, kNoAllocDoubles, d_U, s, h.n))
+    if (launch_total(box->d, box->d_desc, all_pairs != 0, d_e, buf, kNoAllocDoubles, d_U, s, h.n, h.maxcount))
         return set_error(GCMC_ERR_INVALID_ARG, "scratch too small");
     GCMC_HIP(hipGetLastError());
     return GCMC_OK;
