@@ -48,7 +48,7 @@ int gcmc_delta_energy(gcmc_box* box, const gcmc_move* d_moves, int64_t n_moves, 
         return set_error(GCMC_ERR_INVALID_ARG, "bad arguments");
     if (n_moves == 0) return GCMC_OK;
     hipStream_t s = (hipStream_t)stream;
-    launch_delta(box->d_desc, box->d.ns > 1, n_moves, d_moves, d_dU_pair, d_dU_tail, d_dW_pair, s);
+    launch_delta(box->d, box->d_desc, n_moves, d_moves, d_dU_pair, d_dU_tail, d_dW_pair, s);
     GCMC_HIP(hipGetLastError());
     return GCMC_OK;
 }

@@ -136,11 +136,12 @@ __device__ __forceinline__ void wave_lds_sync() {
 // of cells, c takes c' when 2 d < cells (c < c' at equality): d and cells - d
 // belong to the two sides, so exactly one of them takes the pair, whatever the
 // stencil (axes it covers whole included; a stencil is symmetric and names a cell
-// once).
-template <int CR, bool HALF, bool META, typename F>
+// once).  SHARES > 1: only every SHARES-th block, from the `share`-th on.
+template <int CR, bool HALF, bool META, int SHARES = 1, typename F>
 __device__ __forceinline__ void stencil_rows(const DevBox& B, const PassBox& P, PassRows& W, int32_t c, int32_t cx,
-                                             int32_t cy, int32_t cz, const F& f) {
+                                             int32_t cy, int32_t cz, const F& f, uint32_t share = 0) {
     const int lane = threadIdx.x & (kWave - 1);
+    uint32_t block = 0;
     for (int g0 = 0; g0 < P.nst; g0 += kWave) {
         const int t = g0 + lane;
         const bool on = t < P.nst;
@@ -181,6 +182,10 @@ __device__ __forceinline__ void stencil_rows(const DevBox& B, const PassBox& P, 
                 double mw[CR];
                 const int left = (w1 - b0 + kWave - 1) / kWave;
                 const int rows = left < CR ? left : CR;
+                if (SHARES > 1 && block++ % SHARES != share) {
+                    for (int r = 0; r < rows; ++r) begun += (uint32_t)__builtin_popcountll(W.starts[((b0 - w0) >> 6) + r]);
+                    continue;
+                }
                 uint32_t own = 0;
 #pragma unroll
                 for (int r = 0; r < CR; ++r) {

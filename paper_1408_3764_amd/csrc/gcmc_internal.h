@@ -517,7 +517,7 @@ int launch_chain_async(const DevBox* d_boxes, const int32_t* d_order, int n_boxe
 int launch_chain_spec(const DevBox* d_boxes, const int32_t* d_order, int n_boxes, int waves, int64_t n_moves,
                       uint64_t ctr0, gcmc_stats* stats, gcmc_log* log, hipStream_t s, int ng);
 int spec_needs_groups(const DevBox& hb);
-int launch_delta(const DevBox* d_box, bool mix, int64_t n_moves, const gcmc_move* moves, double* dp, double* dt,
+int launch_delta(const DevBox& hb, const DevBox* d_box, int64_t n_moves, const gcmc_move* moves, double* dp, double* dt,
                  double* dw, hipStream_t s);
 void launch_commit(const DevBox* d_box, const gcmc_move* move, const double* dU, const double* dW, hipStream_t s);
 void launch_neighbors(const DevBox* d_box, const double* pts, const int32_t* excl, int64_t n, int32_t max_ids,

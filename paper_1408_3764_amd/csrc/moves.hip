@@ -15,25 +15,32 @@ namespace gcmc {
 // both positions against the same candidates (Sec. 3.2.4).  Bound by vector issue.
 // Four wavefronts per move with a slot for every place of the fullest cell spent
 // most lanes on empty slots: 16,384 moves of 262,144 particles 103 -> 45 us, one
-// move of 4,000 5.3 -> 4.1 us.
+// move of 4,000 5.3 -> 4.1 us.  W > 1: a few moves of wide stencils, where the rows of
+// one wavefront would be a serial chain: W wavefronts a move, each a share of the rows.
 constexpr int kDeltaRows = 4;
 constexpr int kDeltaQueue = kWave + 2 * kDeltaRows * kWave;
+constexpr int kDeltaWide = 8;
 
-template <bool MIX>
-__global__ __launch_bounds__(kWave) void k_delta(const DevBox* __restrict__ boxp, const gcmc_move* __restrict__ moves,
+template <bool MIX, int W>
+__global__ __launch_bounds__(kWave* W) void k_delta(const DevBox* __restrict__ boxp, const gcmc_move* __restrict__ moves,
                                                  int64_t n_moves, double* dU_pair, double* dU_tail, double* dW_pair) {
-    __shared__ PassRows rows_s;
-    __shared__ double q[kDeltaQueue];
-    __shared__ uint8_t qp[MIX ? kDeltaQueue : 1];
+    __shared__ PassRows rows_w[W];
+    __shared__ double q_w[W][kDeltaQueue];
+    __shared__ uint8_t qp_w[W][MIX ? kDeltaQueue : 1];
     __shared__ double te4[kMaxSpecies * kMaxSpecies], ts2[kMaxSpecies * kMaxSpecies];
+    __shared__ double sum_w[W][2];
     const DevBox& B = *boxp;
     const PassBox P = pass_box(B);
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1), wv = W > 1 ? uni((int32_t)threadIdx.x / kWave) : 0;
+    PassRows& rows_s = rows_w[wv];
+    double* const q = q_w[wv];
+    uint8_t* const qp = qp_w[wv];
     const int ns = uni(B.ns);
-    if (MIX && lane < kMaxSpecies * kMaxSpecies) {
-        te4[lane] = B.eps4[lane];
-        ts2[lane] = B.sig2[lane];
+    if (MIX && threadIdx.x < kMaxSpecies * kMaxSpecies) {
+        te4[threadIdx.x] = B.eps4[threadIdx.x];
+        ts2[threadIdx.x] = B.sig2[threadIdx.x];
     }
+    if (W > 1) __syncthreads();
     const double e4 = unid(B.eps4[0]), s2 = unid(B.sig2[0]);
     const int64_t n = B.st->n;
     for (int64_t m = blockIdx.x; m < n_moves; m += gridDim.x) {
@@ -67,7 +74,7 @@ __global__ __launch_bounds__(kWave) void k_delta(const DevBox* __restrict__ boxp
                 const bool neg = disp && which == 0;
                 const double4 p = make_double4(unid(T.p[which][0]), unid(T.p[which][1]), unid(T.p[which][2]), 0.0);
                 const double4 p1 = make_double4(unid(T.p[1][0]), unid(T.p[1][1]), unid(T.p[1][2]), 0.0);
-                stencil_rows<kDeltaRows, false, true>(
+                stencil_rows<kDeltaRows, false, true, W>(
                     B, P, rows_s, cl, c[0], c[1], c[2],
                     [&](const double3* e, const double* mw, int rows, int32_t rel, uint32_t own) {
                         auto test = [&](auto wrap_t, auto rows_t) {
@@ -101,7 +108,7 @@ __global__ __launch_bounds__(kWave) void k_delta(const DevBox* __restrict__ boxp
                             }
                         };
                         pass_dispatch<kDeltaRows>(inside, rows, test);
-                    });
+                    }, (uint32_t)wv);
             };
             if (both) {
                 stencil(0, std::true_type{});
@@ -113,7 +120,20 @@ __global__ __launch_bounds__(kWave) void k_delta(const DevBox* __restrict__ boxp
             su = wave_sum(su);
             sw = wave_sum(sw);
         }
-        if (lane == 0) {
+        if (W > 1) {
+            __syncthreads();   // the last move's sums have been read
+            if (lane == 0) {
+                sum_w[wv][0] = su;
+                sum_w[wv][1] = sw;
+            }
+            __syncthreads();
+            su = sw = 0.0;
+            for (int v = 0; v < W; ++v) {
+                su += sum_w[v][0];
+                sw += sum_w[v][1];
+            }
+        }
+        if (threadIdx.x == 0) {
             double p, t, w;
             if (!ok) {
                 p = t = w = __builtin_nan("");
@@ -205,10 +225,22 @@ __global__ __launch_bounds__(256) void k_neighbors(const DevBox* __restrict__ bo
 }
 
 // ---------------------------------------------------------- dispatch
-int launch_delta(const DevBox* d_box, bool mix, int64_t n_moves, const gcmc_move* moves, double* dp, double* dt,
+// Eight wavefronts a move where the stencil may hold 64 rows and the moves alone would not fill the chip.
+// Calls in us, four wavefronts each with a slot for every place (the mapping before k_delta) / one / eight:
+// 30,000 particles in 27 cells, 1 move 136 / 153 / 78, 256 moves 230 / 284 / 131, 1,024 moves 371 / 300 / 248;
+// 262,144 at a cutoff of 20, 256 moves 1,574 / 2,974 / 856; 4,000 in 27 cells, 64 moves 93 / 91 / 63.  Each
+// wavefront numbers the candidates of the whole stencil: with several groups of 64 cells that is worth it for
+// fewer moves (600 cells, 256 moves 73 / 66 / 64, 1,024 moves 84 / 72 / 93).
+int launch_delta(const DevBox& hb, const DevBox* d_box, int64_t n_moves, const gcmc_move* moves, double* dp, double* dt,
                  double* dw, hipStream_t s) {
     const unsigned g = (unsigned)(n_moves < 65536 ? n_moves : 65536);
-    auto f = mix ? k_delta<true> : k_delta<false>;
+    const bool mix = hb.ns > 1;
+    if (n_moves <= (hb.nstencil <= kWave ? 1024 : 256) && (int64_t)hb.nstencil * hb.cap >= 64 * kWave) {
+        auto f = mix ? k_delta<true, kDeltaWide> : k_delta<false, kDeltaWide>;
+        hipLaunchKernelGGL(f, dim3(g), dim3(kWave * kDeltaWide), 0, s, d_box, moves, n_moves, dp, dt, dw);
+        return 0;
+    }
+    auto f = mix ? k_delta<true, 1> : k_delta<false, 1>;
     hipLaunchKernelGGL(f, dim3(g), dim3(kWave), 0, s, d_box, moves, n_moves, dp, dt, dw);
     return 0;
 }
