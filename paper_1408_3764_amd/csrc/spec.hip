@@ -42,6 +42,13 @@
 // accepted move.  Per move, waves = 8: slab 1.36 -> 0.83 us, 4,000 particles 1.40 -> 0.87,
 // cutoff 4.25 on microcells 2.5 -> 1.7.
 //
+// An accepted move is a serial step of that one wavefront (an instruction every eight cycles, so every
+// instruction counts): N and the number of awaited moves are passed through readfirstlane, or
+// the compiler keeps the whole loop under execution masks with N in vector registers (24 of them
+// and 40 to 50 spills more), and the decision itself has no branch.  In a vapour, where three moves in
+// four are accepted, waves = 8 took 1.83 us a move without, 1.42 with (1.60 with eight moves a round
+// decided by the first evaluating wavefront); 4,000 particles 0.88 and 0.73.
+//
 // NG > 0: stencils of more than 32 cells (microcells, Sec. 3.3) go through
 // the evaluation's path with NG groups of 64 cells; the round and the commit
 // are the same.
@@ -49,12 +56,12 @@
 
 namespace gcmc {
 
-// Log acceptance ratio of a move (Eqs. 3-5) from its pair and tail energy changes and
-// its log prefactor.
-__device__ __forceinline__ double spec_arg_fin(const DevBox& B, int type, double dUp, double dUt, double lpref) {
-    const bool is_disp = type == GCMC_MOVE_DISPLACE, is_ins = type == GCMC_MOVE_INSERT;
-    const double dU = dUp + dUt;
-    return is_disp ? -(B.beta * dU) : (is_ins ? lpref + B.beta * (B.mu - dU) : lpref - B.beta * (B.mu + dU));
+// Log acceptance ratio of a move (Eqs. 3-5) from its energy change and its log prefactor (0 for a
+// displacement), without a branch on its type: sign holds the sign bit for an insertion, mu is 0 for a
+// displacement.
+__device__ __forceinline__ double spec_arg(double beta, double mu, uint64_t sign, double dU, double lpref) {
+    const double y = beta * (mu + __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, dU) ^ sign));
+    return lpref - __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, y) ^ sign);
 }
 
 // Log acceptance prefactors at N = base + t: insertion V / (Lambda^3 (N + 1)),
@@ -110,6 +117,9 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
                                                                const int32_t* __restrict__ order, int64_t n_moves,
                                                                uint64_t ctr0, gcmc_stats* stats, gcmc_log* trace) {
     constexpr int kOffs = NG ? NG * kWave / 2 : 64;    // stencil slots with a precomputed linear offset
+    // forms with more than 128 registers have room for what saves an accepted move latency (in the others it
+    // spills: 5 to 15 % slower there, 2 to 9 % faster here)
+    constexpr bool kRoomy = W == 2 || W == 11;
     constexpr int RING = W > 8 ? 32 : (W > 4 ? 16 : (W > 2 ? 8 : 4));   // a power of two, at least 2 W
     __shared__ uint32_t tab[kMaxStencil];
     __shared__ int32_t offs[kOffs];
@@ -139,8 +149,8 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
     BoxState* st = B.st;
 
     if (ctr0 == GCMC_COUNTER_CONTINUE) ctr0 = (uint64_t)st->counter;
-    int32_t N = (int32_t)st->n;   // below 2^31
-    int32_t err = st->error;
+    int32_t N = uni((int32_t)st->n);   // below 2^31
+    int32_t err = uni(st->error);
     const bool no_full = !(B.full[0] | B.full[1] | B.full[2]);
     for (int t = tid; t < B.nstencil; t += blockDim.x) {
         const uint32_t pk = gload(B.stab + t);
@@ -201,6 +211,10 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
     int32_t maxc = st->maxcount;
     const double tk = B.tailK[0];
     const int cap = B.cap;
+    // the arrays a commit stores to, in vector registers: as scalars they are spilled and read back word by word
+    double4 *cpos = B.pos, *cent = B.ent;
+    int32_t* ccount = B.count;
+    if constexpr (kRoomy) asm("" : "+v"(cpos), "+v"(cent), "+v"(ccount));
     const int32_t spin_cap = wait_bound(B.wait_limit);
     const double side[3] = {B.L[0] / (double)B.M[0], B.L[1] / (double)B.M[1], B.L[2] / (double)B.M[2]};
     double n_ins = 0.0, n_del = 0.0, y_ins = 0.0, y_del = 0.0;   // insertions and deletions, and those accepted
@@ -238,6 +252,7 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
                     break;
                 }
             }
+            kw = uni(kw);
             wave_lds_sync();
         };
         // the moves but for their sums; meanwhile what each would change in the later ones
@@ -299,14 +314,15 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
         const double p1x = R.p1[0], p1y = R.p1[1], p1z = R.p1[2];   // a displacement's new position
         const int32_t two = known_k ? R.two : 0;
         const int32_t loc = meta_low(R.rec.w);                       // slot of its particle's record
-        // the log prefactor and the tail energy change at the current N, of moves first .. W - 1
+        // the log prefactor (lp) and the tail energy change at the current N (none of a displacement)
         double lpref = 0.0, dUt = 0.0;
-        auto at_n = [&](int first) {
-            if (disp || lane < first) return;
-            lpref = ins ? lpi[N - lbase] : lpd[N - lbase];
-            dUt = tk * (ins ? (2.0 * (double)N + 1.0) : (1.0 - 2.0 * (double)N));
+        auto pref = [&](int32_t n) { return ins ? lpi[n - lbase] : lpd[n - lbase]; };
+        auto at_n = [&](double lp) {
+            const double n2 = 2.0 * (double)N;
+            lpref = kRoomy && disp ? 0.0 : lp;
+            dUt = kRoomy && disp ? 0.0 : tk * (ins ? n2 + 1.0 : 1.0 - n2);
         };
-        at_n(0);
+        if (kRoomy || !disp) at_n(pref(N));
         // the sums
         wait_for(&ready[lane < W ? lane : 0]);
         __builtin_amdgcn_s_setprio(3);
@@ -318,22 +334,20 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
         const int32_t n_round = N;
         bool stale = false;
         double arg = 0.0;
+        const double mu = disp ? 0.0 : B.mu;
+        const uint64_t sign = ins ? 1ull << 63 : 0ull;
         double aft_n = 0.0, aft_u = 0.0, aft_w = 0.0;
         uint64_t accbits = 0;
         int k = 0;
         while (k < kw) {
             const uint64_t todo = ((1ull << kw) - 1ull) & ~((1ull << k) - 1ull);
-            bool ok = false, bad = false;
-            if (mine && lane >= k) {
-                if (empty) {
-                    bad = N != 0;   // the empty-box rejection holds only while the box is still empty
-                } else {
-                    bad = stale || (!ins && ((pick >> (N - n_round + W - 1)) & 1u) == 0);
-                    arg = spec_arg_fin(B, type, dUp, dUt, lpref);
-                    const double dU = dUp + dUt;
-                    ok = dU == dU && lnA < arg;
-                }
-            }
+            // (branch-free: every lane's move, the others masked out below)
+            const double dU = dUp + dUt;
+            const double now = spec_arg(B.beta, mu, sign, dU, lpref);
+            const bool ok = dU == dU && lnA < now && !empty;
+            // the empty-box rejection holds only while the box is still empty
+            const bool bad = empty ? N != 0 : (stale | (!ins & (((pick >> (N - n_round + W - 1)) & 1u) == 0)));
+            arg = lane >= k ? now : arg;
             const uint64_t bads = __ballot(bad) & todo;
             const uint64_t stop = bads | (__ballot(ok) & todo);
             const int f = stop ? (int)__builtin_ctzll(stop) : kw;
@@ -349,6 +363,17 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
             const int32_t tf = of(type), fi = of(idx), ftwo = of(two), c0 = of(cl0), c1 = of(cl1);
             const bool fdisp = tf == GCMC_MOVE_DISPLACE, fins = tf == GCMC_MOVE_INSERT, fdel = tf == GCMC_MOVE_DELETE;
             const int32_t fcnt0 = of(cnt0), fcnt1 = of(cnt1), floc = of(loc);
+            // what it adds to the later moves, and their prefactors after it: requested before the commit
+            const int32_t n_next = N + (fins ? 1 : (fdel ? -1 : 0));
+            double add_u = 0.0, add_w = 0.0, lp = 0.0;
+            int32_t add_n = 0;
+            auto request = [&](int col) {
+                add_u = corr_u[f][col];
+                add_w = corr_w[f][col];
+                add_n = corr_n[f][col];
+                lp = pref(n_next);
+            };
+            if constexpr (kRoomy) request(lane < W ? lane : W - 1);
             int e = GCMC_OK;
             if (fins) {
                 if (N >= B.max_n) e = GCMC_ERR_CAPACITY;
@@ -376,20 +401,20 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
                 // every store to pos[j] for j in the round's window is mirrored in top[]
                 if (swap) {
                     const double4 el = R.elast;
-                    gstore(B.ent + loc, el);
+                    gstore(cent + loc, el);
                     const double w = pack_meta(meta_species(el.w), loc);
-                    gstore_w(B.pos + id_end, w);
+                    gstore_w(cpos + id_end, w);
                     const int32_t t = id_end - base;
                     if (t >= 0 && t < 2 * W) top[t].w = w;
                 }
-                if (removes) gstore(B.count + cl0, cnt0 - 1);
+                if (removes) gstore(ccount + cl0, cnt0 - 1);
                 double4 nr;
                 int32_t j = -1;
                 if (fdel) {
                     if (fi != N - 1) {
                         if (id_last == N - 1) rl.w = pack_meta(meta_species(rl.w), loc);
                         nr = rl;
-                        gstore_w(B.ent + meta_low(rl.w), pack_meta(meta_species(rl.w), fi));
+                        gstore_w(cent + meta_low(rl.w), pack_meta(meta_species(rl.w), fi));
                         j = fi;
                     }
                 } else {
@@ -399,12 +424,12 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
                     const int32_t slot = stay ? loc : cn * cap + nn;
                     j = fins ? N : fi;
                     const double x = fdisp ? p1x : p0x, y = fdisp ? p1y : p0y, z = fdisp ? p1z : p0z;
-                    gstore(B.ent + slot, make_double4(x, y, z, pack_meta(0, j)));
-                    if (!stay) gstore(B.count + cn, nn + 1);
+                    gstore(cent + slot, make_double4(x, y, z, pack_meta(0, j)));
+                    if (!stay) gstore(ccount + cn, nn + 1);
                     nr = make_double4(x, y, z, pack_meta(0, slot));
                 }
                 if (j >= 0) {
-                    gstore(B.pos + j, nr);
+                    gstore(cpos + j, nr);
                     const int32_t t = j - base;
                     if (t >= 0 && t < 2 * W) top[t] = nr;
                 }
@@ -418,13 +443,18 @@ __global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void 
                         cl0 == c0 || cl0 == c2 || (fdisp && ftwo && cl0 == c1) ||
                         (two && (cl1 == c0 || cl1 == c2 || (fdisp && ftwo && cl1 == c1)));
                 // its pairs with the position taken away and the one added
-                dUp += corr_u[f][lane];
-                dWp += corr_w[f][lane];
-                r_in += corr_n[f][lane];
-                stale = stale || corr_n[f][lane] == kSpecAgain;
+                if constexpr (!kRoomy) request(lane);
+                dUp += add_u;
+                dWp += add_w;
+                r_in += add_n;
+                stale = stale || add_n == kSpecAgain;
             }
-            N += fins ? 1 : (fdel ? -1 : 0);
-            at_n(f + 1);
+            N = n_next;
+            if (kRoomy) {
+                if (lane > f) at_n(lp);
+            } else if (!disp && lane > f) {
+                at_n(pref(N));
+            }
             U += read_lane(dUp, f);
             Wvir += read_lane(dWp, f);
             if (lane == f) {
