@@ -283,8 +283,8 @@ int gcmc_commit(gcmc_box* box, const gcmc_move* d_move, const double* d_dU_pair,
  * move at a time, `waves` wavefronts per workgroup and `rows` candidate slots
  * per lane per pass (1x8, 2x8, 4x2, 4x4, 4x8, 8x2, 8x4).  rows = 0:
  * speculative rounds, `waves` (2, 4, 8 or 16) choosing how many consecutive
- * moves are evaluated at once, one per wavefront (2, 7, 11 and 15 of them; 15 for
- * 8 too where the stencil has more than 32 cells; 2 and 4 let several boxes of a
+ * moves are evaluated at once, one per wavefront (3, 7, 11 and 15 of them; 2 and 15
+ * for 2 and 8 where the stencil has more than 32 cells; 2 and 4 let several boxes of a
  * batch share a compute unit), against
  * the round's starting state and decided in order by one more wavefront, each
  * corrected for the earlier accepted moves of its round or, where one of those

@@ -113,7 +113,7 @@ __device__ __attribute__((noinline)) void spec_draws(DrawRing<RING>* ring, uint6
 }
 // W evaluating wavefronts and one that decides.
 template <int W, int CR, int NG>
-__global__ __launch_bounds__(kWave*(W + 1), W <= 4 ? 3 : (W == 7 ? 4 : 1)) void k_chain_spec(const DevBox* __restrict__ boxes,
+__global__ __launch_bounds__(kWave*(W + 1), W == 2 ? 3 : (W == 3 || W == 7 ? 4 : 1)) void k_chain_spec(const DevBox* __restrict__ boxes,
                                                                const int32_t* __restrict__ order, int64_t n_moves,
                                                                uint64_t ctr0, gcmc_stats* stats, gcmc_log* trace) {
     constexpr int kOffs = NG ? NG * kWave / 2 : 64;    // stencil slots with a precomputed linear offset
@@ -581,7 +581,10 @@ struct SpecCfg {
 // What waves selects: how many moves are evaluated at once, the deciding wavefront
 // beside them.  More moves hide each other's latencies and share the decision, but
 // an accepted move makes more of them stale, and a wavefront has fewer registers.
-// 2: two.  4: seven in 128 registers, so that a compute unit holds two such boxes, or
+// 2: three in 128 registers, so that a compute unit holds four such boxes: 1,024 boxes of
+// 1,024 to 8,192 particles, 300 moves 1.16 ms, with two moves in 160 registers 2.07 (1.80 with two
+// wavefronts that did both); one box of 4,000 particles 1.76 and 2.42 us a move.  On microcells
+// two.  4: seven in 128 registers, so that a compute unit holds two such boxes, or
 // one and an LDS-held one: 64 boxes, 1,000 moves 2.35 ms with three moves (160
 // registers, three boxes), 1.38 with seven; 512 boxes 2.7 and 1.9; 1,024 boxes 3.7 and 3.1.
 // 8: eleven, the most that leave 160 registers: eight took 9.6 ms for the slab's
@@ -591,7 +594,7 @@ struct SpecCfg {
 // 15: 4,000 moves at a cutoff of 4.25 took 8.3 ms with eight, 7.8 with eleven, 7.1 with 13 and
 // 6.8 with 15.  16: 15, a workgroup having 16 wavefronts at most.
 static const SpecCfg kSpecCfgs[] = {
-    {2, 2, 0, k_chain_spec<2, 8, 0>},
+    {2, 3, 0, k_chain_spec<3, 4, 0>},
     {4, 7, 0, k_chain_spec<7, 4, 0>},
     {8, 11, 0, k_chain_spec<11, 8, 0>},
     {16, 15, 0, k_chain_spec<15, 4, 0>},
