@@ -525,11 +525,11 @@ __global__ __launch_bounds__(kWave*(W + 1), W == 2 ? 3 : (W == 3 || W == 7 ? 4 :
                 r.accepted = acc ? 1 : 0;
                 r.flags = empty ? 1 : 0;
                 r.dU_pair = dUp;
-                r.dU_tail = dUt;
+                r.dU_tail = empty ? 0.0 : dUt;
                 r.x = empty ? 0.0 : (disp ? p1x : p0x);
                 r.y = empty ? 0.0 : (disp ? p1y : p0y);
                 r.z = empty ? 0.0 : (disp ? p1z : p0z);
-                r.arg = arg;
+                r.arg = empty ? 0.0 : arg;
                 r.dW_pair = dWp;
                 trace[(size_t)bi * n_moves + m + lane] = r;
             }
