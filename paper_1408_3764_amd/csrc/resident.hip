@@ -1,9 +1,8 @@
 // The persistent chain of Algorithm 1 for a small box held in local memory.
 //
 // In a box of a few hundred to a couple of thousand particles the 27-cell
-// stencil covers most or all of the box, so the cell list prunes little, every
-// accepted move makes the rest of a speculative round of the global-memory
-// kernels stale, and a move costs a chain of dependent memory round trips of
+// stencil covers most or all of the box, so the cell list prunes little, and a move
+// of the global-memory kernels costs a chain of dependent memory round trips of
 // about a microsecond each.  Here one workgroup copies the box's coordinates
 // into LDS once per launch and runs every move against that copy.
 //
@@ -138,10 +137,10 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
     BoxState* st = B.st;
 
     if (ctr0 == GCMC_COUNTER_CONTINUE) ctr0 = (uint64_t)st->counter;
-    int32_t N = (int32_t)st->n;   // below 2^31
+    int32_t N = uni((int32_t)st->n);   // below 2^31
     double U = st->u_pair;      // running energy and virial: kept by wavefront 0
     double Wvir = st->w_pair;
-    int32_t err = st->error;
+    int32_t err = uni(st->error);
     int64_t err_move = st->error_move;
     const double tk = B.tailK[0];
     const double rc2 = B.rc2, eps4 = B.eps4[0], sig2 = B.sig2[0];
@@ -434,6 +433,7 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                         }
                     }
                 }
+                kw = uni(kw);
                 wave_lds_sync();
                 const bool mine = lane < kw;
                 const bool disp = type == GCMC_MOVE_DISPLACE, ins = type == GCMC_MOVE_INSERT;
@@ -475,20 +475,16 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                 int k = 0;
                 while (k < kw) {
                     const uint64_t todo = ((1ull << kw) - 1ull) & ~((1ull << k) - 1ull);
-                    bool ok = false, bad = false;
-                    if (mine && lane >= k) {
-                        if (empty) {
-                            bad = N != 0;   // the empty-box rejection holds only while the box is still empty
-                        } else {
-                            bad = !ins && (stale || ((pick >> (N - n_round + W - 1)) & 1u) == 0);
-                            dUt = disp ? 0.0 : tk * (ins ? (2.0 * (double)N + 1.0) : (1.0 - 2.0 * (double)N));
-                            const double dU = dUp + dUt;
-                            const double lpref = disp ? 0.0 : (ins ? lpi[N - lbase] : lpd[N - lbase]);
-                            arg = disp ? -(B.beta * dU)
-                                       : (ins ? lpref + B.beta * (B.mu - dU) : lpref - B.beta * (B.mu + dU));
-                            ok = dU == dU && lnA < arg;
-                        }
-                    }
+                    // (branch-free: every lane's move, the others masked out below)
+                    const double lp = ins ? lpi[N - lbase] : lpd[N - lbase], n2 = 2.0 * (double)N;
+                    const double t_now = disp ? 0.0 : tk * (ins ? n2 + 1.0 : 1.0 - n2);
+                    const double dU = dUp + t_now;
+                    const double now = spec_arg(B.beta, disp ? 0.0 : B.mu, ins ? 1ull << 63 : 0ull, dU, disp ? 0.0 : lp);
+                    const bool ok = !empty & (dU == dU) & (lnA < now);
+                    // the empty-box rejection holds only while the box is still empty
+                    const bool bad = empty ? N != 0 : !ins & (stale | (((pick >> (N - n_round + W - 1)) & 1u) == 0));
+                    arg = lane >= k ? now : arg;
+                    dUt = lane >= k ? t_now : dUt;
                     const uint64_t bads = __ballot(bad) & todo;
                     const uint64_t stop = bads | (__ballot(ok) & todo);
                     const int f = stop ? (int)__builtin_ctzll(stop) : kw;
@@ -572,12 +568,12 @@ __global__ __launch_bounds__(kWave* W* S, OCC) void k_chain_resident(const DevBo
                         r.accepted = acc ? 1 : 0;
                         r.flags = empty ? 1 : 0;
                         r.dU_pair = dUp;
-                        r.dU_tail = dUt;
+                        r.dU_tail = empty ? 0.0 : dUt;
                         const bool del = type == GCMC_MOVE_DELETE;
                         r.x = empty ? 0.0 : (del ? ax : bx);
                         r.y = empty ? 0.0 : (del ? ay : by);
                         r.z = empty ? 0.0 : (del ? az : bz);
-                        r.arg = arg;
+                        r.arg = empty ? 0.0 : arg;
                         r.dW_pair = dWp;
                         trace[(size_t)bi * n_moves + (m + lane)] = r;
                     }

@@ -56,14 +56,6 @@
 
 namespace gcmc {
 
-// Log acceptance ratio of a move (Eqs. 3-5) from its energy change and its log prefactor (0 for a
-// displacement), without a branch on its type: sign holds the sign bit for an insertion, mu is 0 for a
-// displacement.
-__device__ __forceinline__ double spec_arg(double beta, double mu, uint64_t sign, double dU, double lpref) {
-    const double y = beta * (mu + __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, dU) ^ sign));
-    return lpref - __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, y) ^ sign);
-}
-
 // Log acceptance prefactors at N = base + t: insertion V / (Lambda^3 (N + 1)),
 // deletion Lambda^3 N / V (entries at N < 0 are never read).  Filled by one wavefront.
 constexpr int kSpecPref = 128;

@@ -570,4 +570,12 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
     }
 }
 
+// Log acceptance ratio of a move (Eqs. 3-5) from its energy change and its log prefactor (0 for a
+// displacement), without a branch on its type: sign holds the sign bit for an insertion, mu is 0 for a
+// displacement.
+__device__ __forceinline__ double spec_arg(double beta, double mu, uint64_t sign, double dU, double lpref) {
+    const double y = beta * (mu + __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, dU) ^ sign));
+    return lpref - __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, y) ^ sign);
+}
+
 }  // namespace gcmc
