@@ -150,7 +150,14 @@ struct SpecSums {
 // one in seven, wait in LDS until 64 of them are evaluated, one per lane (the sign
 // bit marks a displacement's old position, whose terms are subtracted).  mid() runs
 // once while the counters are on their way.
-template <int CR, int NG, typename Mid>
+//
+// FEW: a block of at most two rows has its rows taken one by one.  In a gas a stencil
+// fills a part of one row, and in the pipelined chain, where a move evaluated again holds
+// up every later one, four rows' worth of distances per evaluation showed (waves = 4, 20,000
+// particles at density 0.02 2,610 -> 2,529 us per 1,000 moves, at 0.1 2,758 -> 2,647; at
+// 0.67 2,119 -> 2,106).  Rounds of moves wait for their slowest wavefront and keep the
+// shorter code.
+template <int CR, int NG, bool FEW, typename Mid>
 __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* tab, const int32_t* offs, SpecOwn<NG>& ownbuf,
                                               double* q, int type, int two, const double* p0, const double* p1,
                                               const int32_t* c0, const int32_t* c1, int32_t cl0, int32_t cl1,
@@ -194,9 +201,10 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
     };
     // rows base / 64 ... of the candidates e (x = 1e300: none); rows from flattened position
     // `second` on belong to the second stencil
-    auto consume = [&](const double3* e, int base, int end, int second, auto wrap_t, auto both_t) {
+    auto consume = [&](const double3* e, int base, int end, int second, auto wrap_t, auto both_t, auto few_t) {
         constexpr bool WRAP = decltype(wrap_t)::value, BOTH = decltype(both_t)::value;
-        constexpr int G = CR < (BOTH ? 2 : 4) ? CR : (BOTH ? 2 : 4);
+        constexpr int R = decltype(few_t)::value ? 2 : CR;
+        constexpr int G = decltype(few_t)::value ? 1 : (CR < (BOTH ? 2 : 4) ? CR : (BOTH ? 2 : 4));
         auto dist2 = [&](const double* p, const double3& c) {
             double dx = c.x - p[0], dy = c.y - p[1], dz = c.z - p[2];
             if (WRAP) {
@@ -207,7 +215,7 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
             return (dx * dx + dy * dy) + dz * dz;
         };
 #pragma unroll
-        for (int g = 0; g < CR; g += G) {
+        for (int g = 0; g < R; g += G) {
             if (base + g * kWave < end) {
                 double ra[G], rb[G];
                 bool neg[G];
@@ -235,13 +243,17 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
         }
     };
     auto dispatch = [&](const double3* e, int base, int end, int second) {
-        if (disp && !two) {
-            if (wrap) consume(e, base, end, second, std::true_type{}, std::true_type{});
-            else consume(e, base, end, second, std::false_type{}, std::true_type{});
-        } else {
-            if (wrap) consume(e, base, end, second, std::true_type{}, std::false_type{});
-            else consume(e, base, end, second, std::false_type{}, std::false_type{});
-        }
+        auto go = [&](auto few_t) {
+            if (disp && !two) {
+                if (wrap) consume(e, base, end, second, std::true_type{}, std::true_type{}, few_t);
+                else consume(e, base, end, second, std::false_type{}, std::true_type{}, few_t);
+            } else {
+                if (wrap) consume(e, base, end, second, std::true_type{}, std::false_type{}, few_t);
+                else consume(e, base, end, second, std::false_type{}, std::false_type{}, few_t);
+            }
+        };
+        if (FEW && end - base <= 2 * kWave) go(std::true_type{});
+        else go(std::false_type{});
     };
     int32_t first2 = INT32_MAX, gap_end = INT32_MAX;   // flattened end of the first stencil, start of the second
     int32_t n_all = 0, n_own = 0;                      // candidates, of those the moving particle itself
@@ -554,8 +566,8 @@ __device__ __forceinline__ void spec_eval(const DevBox& B, const uint32_t* tab, 
         }
         pub();
     };
-    const SpecSums S = spec_sums<CR, NG>(B, tab, offs, ownbuf, pq, type, two, p0, p1, c0, c1, cl0, cl1, excl_slot, no_full,
-                                         mid);
+    const SpecSums S = spec_sums<CR, NG, RING == 0>(B, tab, offs, ownbuf, pq, type, two, p0, p1, c0, c1, cl0, cl1,
+                                                    excl_slot, no_full, mid);
     const double dUp = type == GCMC_MOVE_DELETE ? -S.su : S.su;
     const double dWp = type == GCMC_MOVE_DELETE ? -S.sw : S.sw;
     if (lane == 0) {
