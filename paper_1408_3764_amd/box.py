@@ -191,14 +191,24 @@ class Box:
         ck = _lib.gcmc_export_state(self.handle, stream=self.stream)
         return checkpoint_dict(ck)
 
+    def _read_particles(self, read, count):
+        """(r, positions (N, 3), species (N,)) on the host: r = read(x, y, z, species, max_n) and N = count(r).
+        One copy brings both: two, and four arrays cleared first, were most of the time of a small box."""
+        cap = max(self.max_n, 1)
+        x, y, z = torch.empty((3, cap), dtype=torch.float64, device=self.device)
+        sp = torch.empty(cap, dtype=torch.int32, device=self.device)
+        r = read(x, y, z, sp, cap)
+        n = count(r)
+        if n == 0:
+            return r, np.zeros((0, 3)), np.zeros(0, dtype=np.int32)
+        out = torch.empty(28 * n, dtype=torch.uint8, device=self.device)
+        torch.stack([x[:n], y[:n], z[:n]], dim=1, out=out[:24 * n].view(torch.float64).view(n, 3))
+        out[24 * n:].view(torch.int32).copy_(sp[:n])
+        h = out.cpu().numpy()
+        return r, h[:24 * n].view(np.float64).reshape(n, 3), h[24 * n:].view(np.int32)
+
     def particles(self):
-        n = self.n
-        x = torch.zeros(max(n, 1), dtype=torch.float64, device=self.device)
-        y, z = torch.zeros_like(x), torch.zeros_like(x)
-        sp = torch.zeros(max(n, 1), dtype=torch.int32, device=self.device)
-        n = _lib.gcmc_get_particles(self.handle, x, y, z, sp, self.stream)
-        pos = torch.stack([x[:n], y[:n], z[:n]], dim=1).cpu().numpy()
-        return pos, sp[:n].cpu().numpy()
+        return self._read_particles(lambda *a: _lib.gcmc_get_particles(self.handle, *a[:4], self.stream), int)[1:]
 
     def cells(self):
         info = self.info()
@@ -224,14 +234,9 @@ class Box:
 
     def export_state(self):
         """A complete checkpoint: (positions (N, 3), species (N,), checkpoint dict)."""
-        cap = max(self.max_n, 1)
-        x = torch.zeros(cap, dtype=torch.float64, device=self.device)
-        y, z = torch.zeros_like(x), torch.zeros_like(x)
-        sp = torch.zeros(cap, dtype=torch.int32, device=self.device)
-        ck = _lib.gcmc_export_state(self.handle, x, y, z, sp, cap, self.stream)
-        n = int(ck.n)
-        pos = torch.stack([x[:n], y[:n], z[:n]], dim=1).cpu().numpy()
-        return pos, sp[:n].cpu().numpy(), checkpoint_dict(ck)
+        ck, pos, sp = self._read_particles(lambda *a: _lib.gcmc_export_state(self.handle, *a, self.stream),
+                                           lambda c: int(c.n))
+        return pos, sp, checkpoint_dict(ck)
 
     def import_state(self, pos, ck, species=None):
         """Restore a checkpoint taken by export_state (ck: its dict)."""
