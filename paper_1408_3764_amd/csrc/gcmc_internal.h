@@ -374,15 +374,6 @@ __device__ __forceinline__ int32_t wave_max_i32_uniform(int32_t v) {
     return ab > cd ? ab : cd;
 }
 
-__device__ __forceinline__ int32_t wave_max_i(int32_t v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        int32_t o = __shfl_xor(v, off, kWave);
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
 // ---------------------------------------------------------- acceptance
 // Log of the acceptance ratio (Eqs. 3-5; insertion with exponent
 // beta (mu - dU)), then accept iff arg >= 0 or A < exp(arg); NaN rejects.

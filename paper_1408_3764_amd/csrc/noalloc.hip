@@ -14,7 +14,7 @@ namespace gcmc {
 
 // 16 MiB; gcmc.h promises N + cells up to about 4.1 million and a refusal above
 // (a pass that also kept the particles in cell order needed N / 256 + (N + cells) / 2
-// doubles; this one needs at most 4,096).
+// doubles; this one needs at most 16,384, one for each workgroup).
 constexpr int64_t kNoAllocDoubles = (int64_t)1 << 21;
 constexpr int kNoAllocDevices = 64;
 

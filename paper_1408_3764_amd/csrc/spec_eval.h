@@ -91,18 +91,6 @@ struct SpecRec {
     int32_t cand, evals, incut, pad2;
 };
 
-// Inclusive prefix sum over the wavefront's lanes (DPP row shifts, then the
-// row broadcasts of gfx9 carry each row's total into the next rows).
-__device__ __forceinline__ int32_t wave_incl_scan(int32_t v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31
-    return v;
-}
-
 __device__ __forceinline__ int spec_type(const DevBox& B, const U8& u) {
     return (u.u[0] < B.p_disp) ? GCMC_MOVE_DISPLACE : ((u.u[1] < 0.5) ? GCMC_MOVE_DELETE : GCMC_MOVE_INSERT);
 }
@@ -271,7 +259,7 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
         }
         const int32_t cnt = cell_lane ? gload(B.count + cell) : 0;
         mid();
-        const int32_t incl = wave_incl_scan(cnt);
+        const int32_t incl = pass_scan(cnt);
         n_all = __builtin_amdgcn_readlane(incl, 63);
         int32_t pre = incl - cnt, total = n_all;
         if (two) {
@@ -355,7 +343,7 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
                 const int f = g * kWave + lane;
                 const bool on = f < ncs;
                 const int wh = f >= nst ? 1 : 0;
-                const int32_t incl = wave_incl_scan(cntg[g]);
+                const int32_t incl = pass_scan(cntg[g]);
                 preg[g] = n_all + incl - cntg[g];
                 if (two && (nst - 1) / kWave == g) first2 = n_all + __builtin_amdgcn_readlane(incl, (nst - 1) & (kWave - 1));
                 n_all += __builtin_amdgcn_readlane(incl, 63);
