@@ -11,11 +11,8 @@ namespace gcmc {
 // f(c, i0, i1) for the items of this workgroup (one wavefront): a home cell and the
 // share [i0, i1) of its nc particles, [part nc / parts, (part + 1) nc / parts).
 // Workgroups go to the 8 XCDs in turn (the grid is a multiple of 8); XCD x takes the
-// chunks x, x + 8, ... of `span` cells, sixteen of them, so that neighbouring home cells
-// find their stencils in the same L2 and particles that fill a part of the box only are
-// shared by all XCDs.  One range of cells for each XCD: a slab of 1.5 million, total energy
-// 510 us against 294, gradient 1,167 against 651; a drop of 200,000 in a box of 512,000 cells
-// 207 against 88; particles everywhere, level.  Four chunks: the drop 102.
+// chunks x, x + 8, ... of `span` cells, so that neighbouring home cells find their stencils in
+// the same L2 (how many chunks: pass_grid).
 // The counters of 64 items are read at once, so that empty cells cost little.
 template <typename F>
 __device__ __forceinline__ void pass_items(const PassBox& P, int32_t parts, int32_t span, const F& f) {
@@ -676,13 +673,25 @@ __global__ __launch_bounds__(kFinish) void k_pair_grad_finish(const DevBox* __re
 // 512 cells: 10.2 us with one part, 7.7 with two, 6.9 with three; 32,768
 // in 2,744 cells: 15.9, 14.6 with two, 16.4 with three; 262,144 in 15,625: 75 with one,
 // 81 with two.  At most 16,384 workgroups, each striding over its XCD's items.
-constexpr int kPassChunks = 8 * 16;   // chunks of cells dealt to the XCDs
+//
+// Chunks of cells: one range for each XCD where the particles are everywhere (the fullest cell holds at most
+// half as many again as the mean and 8), which reads the least into each L2: with sixteen, 48,000 particles of three
+// species in 2,744 cells 92 us for total energy and virial against 83, 65,000 of two in 4,096 131 against 122,
+// 4,000 to 262,144 of one level.  Sixteen where they fill a part of the box, which all XCDs share then: a slab of 1.5
+// million, total energy 294 us against 510, gradient 651 against 1,167; a drop of 200,000 in a box of 512,000
+// cells 88 against 207 (with four 102).
+constexpr int kPassChunks = 8 * 16;
 
 struct PassGrid {
     int32_t parts, span;
     unsigned blocks;
     bool sparse;
 };
+
+// The most items that an XCD has: with a wavefront for each, none comes round for a second item beside
+// others that had one (an eighth of all can be fewer; the passes of the 2,744 cells in sixteen chunks: 92 us
+// so, 89 with this).
+static int64_t xcd_items(int64_t items, int32_t span) { return ((items + span - 1) / span + 7) / 8 * span; }
 
 static PassGrid pass_grid(const DevBox& hb, int64_t n, int32_t maxcount) {
     const int64_t cells = hb.ncells > 0 ? hb.ncells : 1;
@@ -701,14 +710,15 @@ static PassGrid pass_grid(const DevBox& hb, int64_t n, int32_t maxcount) {
         const int64_t waves = std::min(groups, half <= 16384 ? half : n / kWave);
         g.parts = 1;
         g.span = (int32_t)((groups + kPassChunks - 1) / kPassChunks);
-        g.blocks = 8u * (unsigned)std::min<int64_t>((waves + 7) / 8, 2048);
+        g.blocks = 8u * (unsigned)std::min<int64_t>(waves == groups ? xcd_items(groups, g.span) : (waves + 7) / 8, 2048);
         return g;
     }
     int64_t parts = std::max<int64_t>((4096 + cells - 1) / cells, (mean + 23) / 24);
     parts = std::max<int64_t>(1, std::min(parts, mean / 2));
     g.parts = (int32_t)parts;
-    g.span = (int32_t)((cells + kPassChunks - 1) / kPassChunks);
-    g.blocks = 8u * (unsigned)std::min<int64_t>((cells + 7) / 8 * parts, 2048);
+    const int chunks = maxcount <= mean + mean / 2 + 8 ? 8 : kPassChunks;
+    g.span = (int32_t)((cells + chunks - 1) / chunks);
+    g.blocks = 8u * (unsigned)std::min<int64_t>(xcd_items(cells, g.span) * parts, 2048);
     return g;
 }
 
