@@ -139,12 +139,12 @@ struct SpecSums {
 // bit marks a displacement's old position, whose terms are subtracted).  mid() runs
 // once while the counters are on their way.
 //
-// FEW: a block of at most two rows has its rows taken one by one.  In a gas a stencil
-// fills a part of one row, and in the pipelined chain, where a move evaluated again holds
-// up every later one, four rows' worth of distances per evaluation showed (waves = 4, 20,000
-// particles at density 0.02 2,610 -> 2,529 us per 1,000 moves, at 0.1 2,758 -> 2,647; at
-// 0.67 2,119 -> 2,106).  Rounds of moves wait for their slowest wavefront and keep the
-// shorter code.
+// FEW: a block of at most two rows is taken by code of its own, one row after the other.
+// In a gas a stencil fills a part of one row, and in the pipelined chain, where a move
+// evaluated again holds up every later one, the instructions for CR rows showed (waves = 4, 20,000
+// particles at density 0.02 2,610 -> 2,360 us per 1,000 moves, at 0.1 2,758 -> 2,465; at
+// 0.67 2,125 -> 2,030; a cutoff of 4.25 4,110 -> 4,200).  Rounds of moves wait for their slowest
+// wavefront and keep the shorter code.
 template <int CR, int NG, bool FEW, typename Mid>
 __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* tab, const int32_t* offs, SpecOwn<NG>& ownbuf,
                                               double* q, int type, int two, const double* p0, const double* p1,
@@ -230,18 +230,14 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
             }
         }
     };
-    auto dispatch = [&](const double3* e, int base, int end, int second) {
-        auto go = [&](auto few_t) {
-            if (disp && !two) {
-                if (wrap) consume(e, base, end, second, std::true_type{}, std::true_type{}, few_t);
-                else consume(e, base, end, second, std::false_type{}, std::true_type{}, few_t);
-            } else {
-                if (wrap) consume(e, base, end, second, std::true_type{}, std::false_type{}, few_t);
-                else consume(e, base, end, second, std::false_type{}, std::false_type{}, few_t);
-            }
-        };
-        if (FEW && end - base <= 2 * kWave) go(std::true_type{});
-        else go(std::false_type{});
+    auto dispatch = [&](const double3* e, int base, int end, int second, auto few_t) {
+        if (disp && !two) {
+            if (wrap) consume(e, base, end, second, std::true_type{}, std::true_type{}, few_t);
+            else consume(e, base, end, second, std::false_type{}, std::true_type{}, few_t);
+        } else {
+            if (wrap) consume(e, base, end, second, std::true_type{}, std::false_type{}, few_t);
+            else consume(e, base, end, second, std::false_type{}, std::false_type{}, few_t);
+        }
     };
     int32_t first2 = INT32_MAX, gap_end = INT32_MAX;   // flattened end of the first stencil, start of the second
     int32_t n_all = 0, n_own = 0;                      // candidates, of those the moving particle itself
@@ -295,10 +291,11 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
         // last entry of the old centre cell (removal by swap-with-last)
         if (out.cnt0 > 0) out.elast = gload(B.ent + ((size_t)(uint32_t)cl0 * (uint32_t)B.cap + (out.cnt0 - 1)));
         // ---- candidates
-        for (int base = 0; base < total; base += kWave * CR) {
-            double3 e[CR];
+        auto block = [&](int base, auto few_t) {
+            constexpr int R = decltype(few_t)::value ? 2 : CR;
+            double3 e[R];
 #pragma unroll
-            for (int r = 0; r < CR; ++r) {
+            for (int r = 0; r < R; ++r) {
                 const int row = (base >> 6) + r;
                 e[r] = make_double3(1e300, 0.0, 0.0);
                 if (row < nrows) {
@@ -313,7 +310,11 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
                     if (in && !own) e[r] = gload_xyz(B.ent + (size_t)(uint32_t)ri);
                 }
             }
-            dispatch(e, base, total, two ? gap_end : INT32_MAX);
+            dispatch(e, base, total, two ? gap_end : INT32_MAX, few_t);
+        };
+        for (int base = 0; base < total; base += kWave * CR) {
+            if (FEW && total - base <= 2 * kWave) block(base, std::true_type{});
+            else block(base, std::false_type{});
         }
     } else {
         // ---- microcell stencils: groups of 64 cells, one lane per cell
@@ -394,7 +395,7 @@ __device__ __forceinline__ SpecSums spec_sums(const DevBox& B, const uint32_t* t
                         if (in && !own) e[r] = gload_xyz(B.ent + (size_t)(uint32_t)ri);
                     }
                 }
-                dispatch(e, base, w1, two ? gap_end : INT32_MAX);
+                dispatch(e, base, w1, two ? gap_end : INT32_MAX, std::false_type{});
             }
             wave_lds_sync();   // every lane has read this window before the next overwrites it
         }
