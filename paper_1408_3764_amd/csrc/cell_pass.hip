@@ -42,8 +42,8 @@ constexpr int kTotalQueue = kWave * kTotalRows + kWave;   // at most 63 left ove
 
 // partial[block] = the block's sum of pair energies (VIR: of pair virials), each
 // pair once.  Item = home cell x part: part p of `parts` takes the home
-// particles [p n / parts, (p + 1) n / parts).  64 VGPRs and 3.5 KB of LDS per
-// wavefront leave room for 8 wavefronts per SIMD.
+// particles [p n / parts, (p + 1) n / parts).  69 to 73 VGPRs and 3 to 3.6 KB of LDS
+// per wavefront leave room for 6 or 7 wavefronts per SIMD.
 template <bool MIX, bool VIR>
 __global__ __launch_bounds__(kWave) void k_pair_total(const DevBox* __restrict__ boxp, int32_t parts, int32_t span,
                                                       double* partial) {

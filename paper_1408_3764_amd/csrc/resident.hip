@@ -26,7 +26,7 @@
 // and only an accepted move (about one in eight) costs a serial step: N, the
 // running sums and the LDS copy change, and the later lanes add its corrections and
 // decide again.  Deciding move by move took 0.85 us each, two thirds of a round:
-// 512 particles 1.60 -> 0.84 us per move, 1,400 particles 2.3 -> 1.4 (waves = 8).  What bounds
+// 512 particles 1.63 -> 0.83 us per move, 1,536 particles 2.4 -> 1.3 (waves = 8).  What bounds
 // it now is the latency of one wavefront's evaluation (rows of 64 particles taken
 // two to four at a time) and about 1 us of decision per round.
 // Particles with an index of kResCap or more (a box that grows past it) are read
@@ -697,13 +697,13 @@ using resident_fn = void (*)(const DevBox*, const int32_t*, int64_t, uint64_t, g
 
 bool resident_cfg_exists(int waves) { return waves == 4 || waves == 8; }
 
-// waves = 4: four moves at a time by two wavefronts each, in 128 registers (three
+// waves = 4: four moves at a time by two wavefronts each, in 128 registers (one
 // spilled), so that a compute unit holds two boxes, or one beside a speculative one.
 // One wavefront a move left the SIMDs waiting (a wavefront issues an instruction every
 // eight cycles or so): 200 to 512 boxes of up to 1,024 particles 1.95 ms per 1,000 moves,
-// 1.75 with two; one box of 1,536 particles 2.20 and 1.83.  waves = 8: one wavefront a
-// move and as many registers as the kernel takes (512 particles, 1,000 moves: 0.91 ms,
-// 0.96 with two; from 1,000 particles on two would be 2 to 6 % faster).
+// 1.75 with two; one box of 1,536 particles 2.20 and 1.83 (1.67 since).  waves = 8: one wavefront
+// a move and as many registers as the kernel takes (512 particles, 1,000 moves: 0.91 ms,
+// 0.96 with two, 0.83 with one since; from 1,000 particles on two would be 2 to 6 % faster).
 int launch_chain_resident(const DevBox* d_boxes, const int32_t* d_order, int n_boxes, int waves, int64_t n_moves,
                           uint64_t ctr0, gcmc_stats* stats, gcmc_log* log, hipStream_t s) {
     if (!resident_cfg_exists(waves)) return -1;

@@ -34,13 +34,13 @@
 // state of the commit then takes no registers from the evaluation, whose scalar
 // values were spilled and reloaded inside the candidate loop (evaluation alone: 142
 // vector registers and 26 scalar spills; one kernel for both took 256 and 160).
-// With eight moves a round of the 1.5-million-particle slab took 7.6 us (12.5 with
-// the decisions in the first evaluating wavefront, 8.1 with the pair terms computed
-// after each accepted move): the slowest evaluation 6 (three dependent memory round
-// trips and the arithmetic; a wavefront issues an instruction every eight cycles or
-// so, so more of them side by side cost little), the decision 0.8 and 0.8 per
-// accepted move.  Per move, waves = 8: slab 1.36 -> 0.83 us, 4,000 particles 1.40 -> 0.87,
-// cutoff 4.25 on microcells 2.5 -> 1.7.
+// When eight moves a round were decided so first, a round of the 1.5-million-particle slab
+// took 7.6 us (12.5 with the decisions in the first evaluating wavefront, 8.1 with the pair
+// terms computed after each accepted move): the slowest evaluation 6 (three dependent
+// memory round trips and the arithmetic; a wavefront issues an instruction every eight
+// cycles or so, so more of them side by side cost little), the decision 0.8 and 0.8 per
+// accepted move.  Per move, waves = 8, with the decisions in an evaluating wavefront and
+// now: slab 1.35 -> 0.72 us, 4,000 particles 1.41 -> 0.73, cutoff 4.25 on microcells 2.5 -> 1.6.
 //
 // An accepted move is a serial step of that one wavefront (an instruction every eight cycles, so every
 // instruction counts): N and the number of awaited moves are passed through readfirstlane, or
@@ -574,17 +574,17 @@ struct SpecCfg {
 // beside them.  More moves hide each other's latencies and share the decision, but
 // an accepted move makes more of them stale, and a wavefront has fewer registers.
 // 2: three in 128 registers, so that a compute unit holds four such boxes: 1,024 boxes of
-// 1,024 to 8,192 particles, 300 moves 1.16 ms, with two moves in 160 registers 2.07 (1.80 with two
-// wavefronts that did both); one box of 4,000 particles 1.76 and 2.42 us a move.  On microcells
+// 1,024 to 8,192 particles, 300 moves 1.19 ms, with two moves in 160 registers 2.07 (1.74 with two
+// wavefronts that did both); one box of 4,000 particles 1.74 and 2.42 us a move.  On microcells
 // two.  4: seven in 128 registers, so that a compute unit holds two such boxes, or
-// one and an LDS-held one: 64 boxes, 1,000 moves 2.35 ms with three moves (160
-// registers, three boxes), 1.38 with seven; 512 boxes 2.7 and 1.9; 1,024 boxes 3.7 and 3.1.
-// 8: eleven, the most that leave 160 registers: eight took 9.6 ms for the slab's
-// 10,000 moves, eleven 8.3, and 15 (128 registers) 7.9, but at a density of 0.3, where
-// one move in four is accepted, 1.37 ms for 1,000 moves with eleven, 1.43 with 15, and in
-// a box of 128 particles 1.42 and 1.74.  On microcells, where the evaluation is longer,
-// 15: 4,000 moves at a cutoff of 4.25 took 8.3 ms with eight, 7.8 with eleven, 7.1 with 13 and
-// 6.8 with 15.  16: 15, a workgroup having 16 wavefronts at most.
+// one and an LDS-held one: 300 moves of 64 boxes of 128 to 1,024 particles 0.47 ms, with three moves
+// 0.78; of 512 boxes 0.68 and 0.99; of 1,024 boxes 1.12 and 1.02, of 1,024 to 8,192 particles 1.08 and
+// 1.19.  8: eleven, the most that leave 160 registers: the slab's 10,000 moves take 9.1 ms with
+// eight, 7.2 with eleven, 7.4 with 13 (128 registers) and 6.9 with 15, but at a density of 0.3, where
+// one move in four is accepted, 1,000 moves 1.06 ms with eleven and 1.19 with 15, and a box of 128
+// particles 1.37 and 1.76.  On microcells, where the evaluation is longer,
+// 15: 4,000 moves at a cutoff of 4.25 take 8.6 ms with eight, 7.0 with eleven, 6.9 with 13 and
+// 6.4 with 15.  16: 15, a workgroup having 16 wavefronts at most.
 static const SpecCfg kSpecCfgs[] = {
     {2, 3, 0, k_chain_spec<3, 4, 0>},
     {4, 7, 0, k_chain_spec<7, 4, 0>},
